@@ -5,8 +5,8 @@
 //   t_k = k/fs, terms kept iff |d - c t_k| <= trunc*sigma, e = f*M + m,
 //   x_e = R_f e_m + t_f (rigid array of Stage 4).
 //
-// GPU formulation (FP32 VALU, no matrix cores: the model is a windowed sum,
-// not a contraction).
+// GPU formulation (FP32 VALU; the model is a windowed sum, and only the expansion of the
+// forward's moments into samples is a contraction, done on the matrix cores).
 //   * Voxels are processed in regions: boxes of voxels around a common centre.
 //     One workgroup owns one region.  Its four wavefronts take 64-element
 //     chunks in turn, one element per lane, and walk the region's voxels in
@@ -24,13 +24,16 @@
 //     and Gamma_j = exp(-j^2 delta^2/2s^2) a per-call table.  So each sample
 //     costs one multiply of a running power of H plus one or two FMAs, with
 //     no transcendental; two or three exponentials are evaluated per pair.
-//   * Forward: every lane owns a private row of signal samples in LDS (layout
-//     [sample][lane], bank = lane, no conflicts) and updates it by
-//     read-modify-write; two z-neighbouring voxels share one pass over the rows
-//     (the Gaussian's rows about each voxel's centre sample are taken whole).
-//     At the end of each region the rows are added into the signals with
-//     global atomics (transposed, so each atomic instruction covers consecutive
-//     samples of one element): FP32 up to 4096 regions, FP64 sums beyond.
+//   * Forward with the Gaussian (single calls): every pair adds NM polynomial moments of its offset
+//     from its centre sample into fixed-point sums in LDS, which a region's workgroup expands into
+//     signal rows and adds to the signals with global atomics (k_forward_mom).
+//   * Forward otherwise (the batched step, other profiles, coarse sampling): every lane owns a private
+//     row of signal samples in LDS (layout [sample][lane], bank = lane, no conflicts) and updates it by
+//     read-modify-write; two z-neighbouring voxels share one pass over the rows (the Gaussian's rows
+//     about each voxel's centre sample are taken whole).  At the end of each region the rows are added
+//     into the signals with global atomics (transposed, so each atomic instruction covers consecutive
+//     samples of one element).
+//   * Sums of the regions' rows: FP32 up to 4096 row-form regions, FP64 sums beyond.
 //   * Adjoints with the Gaussian (single calls and the batched step): Taylor
 //     moments of dL/ds per sample (a table built once per call), two LDS
 //     reads and a Horner sum per pair, with its derivative for the element
@@ -94,6 +97,15 @@ constexpr double MOM_TOL = 1e-6;      // its largest admitted truncation error, 
 constexpr size_t LDS_MOM_BUDGET = 78 * 1024;   // moment-form adjoint: two region workgroups per CU
 constexpr int MOM_WAVES = 8;          // wavefronts of its region workgroup
 constexpr int MOM_PER = 5;            // its table rows staged per wavefront and chunk, at most
+constexpr int FM_WAVES = 8;           // wavefronts of the moment-form forward's region workgroup, two per CU
+constexpr int FM_WAVES_BIG = 16;      // and where its LDS leaves room for one per CU
+constexpr int FM_REFS = 2;            // element chunks whose references it computes at a time
+constexpr int FM_FIELDS = 13;         // floats of a reference
+constexpr int FM_RZ = 8;              // voxels of a column it unrolls
+constexpr int FM_SIDE = 16;           // its largest region side
+constexpr int FM_NM_MAX = 8;          // its largest number of moments
+constexpr double FM_TOL = 2e-7;       // its largest admitted expansion error, relative to the peak
+constexpr size_t LDS_FM_BUDGET = 80 * 1024;    // two of its workgroups per CU
 
 // ------------------------------------------------------------------------------------------
 // double-float arithmetic (value = h + l, |l| <= ulp(h)/2)
@@ -185,6 +197,11 @@ struct Geo {
     float kinv_w, kinv_w2;         // 1/w, 1/w^2
     float knu, k2nu;               // power law: K(x) = exp2(knu log2(1 + x^2/w^2)), knu = -nu; 2 nu
     double mom_dd, mom_sigma;      // moment forms: delta / sigma and sigma
+    // moment-form forward: lengths in units of delta / 2
+    int jt;                        // window half-width in samples
+    int nbin;                      // centre samples of a region, 2 jclamp + 1
+    float unit_h, unit_l;          // 2 / delta
+    float hs_u, hs_l;              // grid spacing in units (double-float)
 };
 
 // Workgroup -> region, so that each compute die (XCD) gets a contiguous run of
@@ -757,6 +774,423 @@ __global__ __launch_bounds__(BLOCK) void k_forward(Geo g, const float* __restric
 }
 
 // ------------------------------------------------------------------------------------------
+// forward in moment form (Gaussian profile)
+// ------------------------------------------------------------------------------------------
+// With lengths in units of delta / 2, a pair's distance is d = 2 kc + t with kc its nearest sample and
+// |t| <= 1.  The window row kc + j carries phi((t/2 - j) delta), which on |t| <= 1 is a polynomial
+// sum_n D_n(j) t^n of NM terms: its Chebyshev series, cut after NM terms on the host, which takes
+// the form only where the cut part is below FM_TOL of the pulse's peak.  So a pair needs only add
+// a t^n (a = p0/(2d), n < NM) to NM sums of its centre sample, and the region's signal rows follow
+// from all pairs' sums at once:
+//   s[kc + r] = sum_{|j| <= jt} sum_n D_n(j) M_n[r - j].
+//
+// The scatter.  A workgroup owns one region and one chunk of 64 elements at a time; its wavefronts share
+// one set of sums in LDS, [centre sample][n][lane = element], and take different columns of the region.
+// The adds are LDS atomics: ds_add_f32 takes 193 cycles a wavefront here (it serialises the lanes),
+// ds_add_u32 4.7, a private read-modify-write 5.7 (and then every wavefront would need its own set), so
+// the sums are 32-bit fixed point.  Their unit is chosen per region and element so that no sum can
+// overflow.  The voxels of one bin lie within one sample of each other, so of a line of voxels along an
+// axis the bin holds at most 1 + delta / (h c) of them, c the least |cosine| between the axis and the
+// direction to the element over the region; with B the sum over the lines of the largest |p0| in each,
+// the bin's sum is at most that count times B / d_low, d_low being the element's distance to the
+// region's box.  The best of the three axes, or sum |p0| / d_low, becomes 2^31 units: for 16^3 equal
+// voxels a term is rounded to 1.2e-7 of itself, as one FP32 addition would.  Regions whose p0 is not
+// finite, and elements inside or within half a voxel of the region's box, or not finite, take FP32 sums
+// by ds_add_f32 instead (slow, and the values then propagate as they would in FP32).
+//
+// The expansion into rows is a banded Toeplitz product, [rows x 64] = D [rows x (bins NM)] M: FP32
+// matrix instructions (16 rows x 16 elements x 4 bins each), whose result has consecutive samples
+// of an element in consecutive lanes, as the atomic adds into the signals want them.
+//
+// Distances.  A region is up to 1.3 mm in radius, 67 units, where FP32 rounds u = d - c t to 4e-6 units;
+// so each column of 8 voxels first takes its own distance and nearest sample, with D.o split into a
+// part that adds exactly and the rest, and its voxels count from there: rms error of t 0.9e-6 over
+// 16^3 voxels, against 1.4e-6 in the row form over 8x8x16.
+//
+// Bounds: 24 VALU instructions (one at a quarter of the rate) and NM ds_add_u32 (33 LDS cycles at NM = 7)
+// per pair and wavefront plus about 40 per column, against 104 VALU and 58 LDS cycles per pair in the
+// row form.  On the sweep (128x128x64 voxels of 0.1 mm, 8192 elements, sigma 0.08 mm) the adds take
+// about 8 ms of 9.9, the row form 26.9.  The FP32 matrix instructions share the VALU's time, so the
+// expansion adds to that: 5.7 ms with 8x8x8 regions, two workgroups to a CU; hence the largest regions
+// that the LDS holds, one workgroup of 16 wavefronts to a CU.
+struct MomCoef {
+    float d[FM_NM_MAX * (JMAX + 1)];   // D_n(j) / delta at n * (JMAX + 1) + j, j >= 0; D_n(-j) = (-1)^(n+1) D_n(j)
+};
+
+__device__ __forceinline__ float mom_coef(const MomCoef& m, int n, int j, int jt) {
+    const int a = j < 0 ? -j : j;
+    if (a > jt) return 0.0f;
+    const float v = m.d[n * (JMAX + 1) + a];
+    return (j < 0 && !(n & 1)) ? -v : v;
+}
+
+// Four floats as a native vector: copies of it are plain vector moves (no byte copies through
+// memory), so arrays of it stay in registers.
+typedef float vf4 __attribute__((ext_vector_type(4)));
+
+constexpr int FM_PAD = 20;                                   // zeros before D_n(-jt) in its LDS table
+constexpr int fm_stride(int nm) { return nm * WAVE + 16; }   // LDS words per bin: 4 bins read at once hit 32 banks
+constexpr int fm_dlen(int jt) { return 2 * jt + 1 + FM_PAD + 16; }
+// Its LDS in floats: sums and one zero bin, references, voxel offsets per axis, |p0| sums, D table.
+constexpr size_t fm_off_ref(int nm, int nbin) { return (size_t)(nbin + 1) * fm_stride(nm); }
+constexpr size_t fm_off_axis(int nm, int nbin) { return fm_off_ref(nm, nbin) + FM_REFS * FM_FIELDS * WAVE; }
+constexpr size_t fm_off_red(int nm, int nbin) { return fm_off_axis(nm, nbin) + 3 * FM_SIDE * 4; }
+constexpr size_t fm_off_dt(int nm, int nbin) { return fm_off_red(nm, nbin) + 4 * FM_WAVES_BIG; }
+constexpr size_t fm_lds(int nm, int nbin, int jt) { return (fm_off_dt(nm, nbin) + nm * fm_dlen(jt)) * sizeof(float); }
+
+// What bounds the sums of a region's bins: sum |p0|, and per axis the sum over the lines along it of the
+// largest |p0| in each (NaN if any p0 is not finite).
+struct FmBound {
+    float all, line[3];
+};
+
+// Reference of a (region, element) pair in units: D = centre - x_e in double-float, dh = |D| rounded,
+// uc0 = dh - 2 kc, n0 = (|D|^2 - dh^2) / 2, the unit of its sums, and the quantum of the column sums.
+struct FmRef {
+    float D[3], Dl[3], dh, uc0, n0, scale, inv, magic;
+    int kbase;                             // sample of row 0
+};
+
+__device__ __forceinline__ FmRef fm_make_ref(const Geo& g, const float* __restrict__ x, const Region& R,
+                                             const FmBound& bd) {
+#pragma clang fp contract(off)
+    const DF u{g.unit_h, g.unit_l};
+    const DF D[3] = {df_mul(df_add(R.cx, df_neg(DF{x[0], x[3]})), u), df_mul(df_add(R.cy, df_neg(DF{x[1], x[4]})), u),
+                     df_mul(df_add(R.cz, df_neg(DF{x[2], x[5]})), u)};
+    const DF d = df_sqrt(df_add(df_add(df_mul(D[0], D[0]), df_mul(D[1], D[1])), df_mul(D[2], D[2])));
+    const float kc = rintf(0.5f * d.h);
+    FmRef r;
+#pragma unroll
+    for (int a = 0; a < 3; ++a) {
+        r.D[a] = D[a].h;
+        r.Dl[a] = D[a].l;
+    }
+    r.dh = d.h;
+    r.uc0 = d.h - 2.0f * kc;
+    r.n0 = d.h * d.l;
+    r.kbase = (int)kc - g.jclamp - g.jt;
+    const float half[3] = {0.5f * (float)(g.rx - 1) * g.hs_u, 0.5f * (float)(g.ry - 1) * g.hs_u,
+                           0.5f * (float)(g.rz - 1) * g.hs_u};
+    const float rad = sqrtf(half[0] * half[0] + half[1] * half[1] + half[2] * half[2]) + 4.0f * g.hs_u;
+    const float far = d.h + rad;
+    // |D.o + o.o/2| < 2^e = rad far, so multiples of 2^(e - 22) below it add exactly
+    r.magic = 1.5f * __builtin_amdgcn_ldexpf(1.0f, __builtin_amdgcn_frexp_expf(rad * far) + 1);
+    float dl2 = 0.0f, most = bd.all;
+#pragma unroll
+    for (int a = 0; a < 3; ++a) {
+        const float out = fabsf(D[a].h) - half[a];           // distance past the box along the axis
+        if (!(out > 0.0f)) continue;
+        dl2 += out * out;
+        const float gap = g.hs_u * 0.999f * out / far;       // least difference in distance of two voxels of a line
+        const float cnt = floorf(2.0f / gap) + 1.0f;         // voxels of a line within one bin (2 units)
+        most = fminf(most, cnt * bd.line[a]);
+    }
+    most = bd.all - bd.all == 0.0f ? most * 1.001f : bd.all;  // fminf drops NaN
+    const float dlow = sqrtf(dl2) * 0.999f;
+    // 1/d <= 1/dlow for every term of the region; scale 0 (take FP32 sums) where that says nothing
+    const bool ok = dlow >= 0.5f * g.hs_u && d.h < 1e15f;
+    r.scale = ok ? 2.147e9f * dlow / most : 0.0f;
+    r.inv = most / (2.147e9f * dlow);
+    if (!(r.scale > 0.0f && r.scale < 1e37f && r.inv > 1e-37f && r.inv < 1e37f)) r.scale = r.inv = 0.0f;
+    return r;
+}
+
+// One axis' share of N = D.o + o.o/2 for the voxel offset o = t.x + t.y (t.z = o^2/2): hi, a multiple
+// of the quantum that `magic` rounds to, and what is left.
+__device__ __forceinline__ void fm_axis(float4 t, float D, float Dl, float magic, float& hi, float& lo) {
+#pragma clang fp contract(off)
+    const float p = t.x * D, e = fmaf(t.x, D, -p);
+    const float w = p + t.z;
+    hi = (w + magic) - magic;
+    lo = fmaf(t.y, D, fmaf(t.x, Dl, ((p - hi) + t.z) + e));
+}
+
+__device__ __forceinline__ int cvt_round_i32(float x) {      // floor(x + 1/2)
+    int v;
+    asm("v_cvt_rpi_i32_f32 %0, %1" : "=v"(v) : "v"(x));
+    return v;
+}
+
+constexpr float FM_MAGIC = 25165824.0f;    // 1.5 * 2^24: adding it rounds to a multiple of 2 (a sample)
+
+// A column of FM_RZ voxels: its centre's distance dc, that distance from the column's own nearest sample
+// (uc), and FM_MAGIC plus that sample's offset from kc.
+struct FmCol {
+    float dc, uc, magic;
+};
+
+// bh + bl = N at the column's centre; bh is exact.  One Newton step from y = sqrt(dh^2 + 2 bh), with
+// a = y - dh exact: d = y + (N - a dh - a^2/2) / y.
+__device__ __forceinline__ FmCol fm_col(float bh, float bl, float dh, float dh2, float uc0) {
+#pragma clang fp contract(off)
+    const float S = fmaf(2.0f, bh, dh2);
+    const float rs = __builtin_amdgcn_rsqf(S);
+    const float y = S * rs;
+    const float a = y - dh;
+    const float th = fmaf(-0.5f, a * a, fmaf(-a, dh, bh)) + bl;
+    const float corr = fmaf(th, rs, uc0);
+    FmCol c;
+    c.magic = (a + corr) + FM_MAGIC;
+    c.uc = (a - (c.magic - FM_MAGIC)) + corr;
+    c.dc = y;
+    return c;
+}
+
+// The adds of one column of FM_RZ voxels (p0 values pv, zero past the grid); ez: N of each voxel about
+// the column's centre.  INT: fixed-point sums.
+template <int NM, bool INT>
+__device__ __forceinline__ void fm_column(const float (&pv)[FM_RZ], const float (&ez)[FM_RZ], const FmCol& c, float scale,
+                                          float lo, float hi, unsigned off0, char* sums) {
+#pragma clang fp contract(off)                 // the distance's Newton step, as pair_dist
+    const float dc2 = c.dc * c.dc, hdc = 0.5f * c.dc;
+#pragma unroll
+    for (int k = 0; k < FM_RZ; ++k) {
+        const float S = fmaf(2.0f, ez[k], dc2);
+        const float rs = __builtin_amdgcn_rsqf(S);
+        const float y = S * rs;
+        const float a = y - c.dc;
+        const float bh = fmaf(0.5f, y, hdc);
+        const float th = fmaf(-a, bh, ez[k]);
+        const float uc = c.uc + fmaf(th, rs, a);
+        const float rm = __builtin_amdgcn_fmed3f(uc + c.magic, lo, hi);      // NaN lands in range too
+        const float t = uc - (rm - c.magic);
+        // the low 24 bits of rm are 0xC00000 + (centre sample offset)
+        const unsigned off = __umul24(__float_as_uint(rm), fm_stride(NM) * 4u) + off0;
+        float q = pv[k] * rs;
+        if (INT) q *= scale;
+#pragma unroll
+        for (int n = 0; n < NM; ++n) {
+            if (INT) {
+                int* dst = reinterpret_cast<int*>(sums + off) + n * WAVE;
+                __hip_atomic_fetch_add(dst, cvt_round_i32(q), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+            } else {
+                float* dst = reinterpret_cast<float*>(sums + off) + n * WAVE;
+                __hip_atomic_fetch_add(dst, q, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+            }
+            if (n + 1 < NM) q *= t;
+        }
+    }
+}
+
+// Sum |p0| and the line bounds of a region by the whole workgroup (`red`: LDS, 4 floats a wavefront).
+template <int NW>
+__device__ __forceinline__ FmBound fm_bound(const Geo& g, const Region& R, const float* __restrict__ pbase, float* red) {
+    const int tid = threadIdx.x, lane = tid & (WAVE - 1), wv = tid / WAVE;
+    const int n[3] = {R.ni, R.nj, R.nk};
+    const long long st[3] = {g.vsx, g.vsy, 1};
+    float b[4] = {0.0f, 0.0f, 0.0f, 0.0f};
+#pragma unroll
+    for (int a = 0; a < 3; ++a) {
+        const int p = a == 0 ? 1 : 0, q = a == 2 ? 1 : 2;    // the other two axes
+        for (int l = tid; l < n[p] * n[q]; l += NW * WAVE) {
+            const float* line = pbase + (size_t)(l / n[q]) * st[p] + (size_t)(l % n[q]) * st[q];
+            float top = 0.0f, sum = 0.0f;
+            for (int i = 0; i < n[a]; ++i) {
+                const float v = fabsf(line[(size_t)i * st[a]]);
+                top = fmaxf(top, v);
+                sum += v;
+            }
+            b[a] += top;
+            if (a == 2) b[3] += sum;
+        }
+    }
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+        b[i] = wave_sum_to_63(b[i]);
+        if (lane == WAVE - 1) red[4 * wv + i] = b[i];
+    }
+    __syncthreads();
+    FmBound r{0.0f, {0.0f, 0.0f, 0.0f}};
+    for (int w = 0; w < NW; ++w) {
+#pragma unroll
+        for (int i = 0; i < 3; ++i) r.line[i] += red[4 * w + i];
+        r.all += red[4 * w + 3];
+    }
+    return r;
+}
+
+// The forward work of one region for element chunks c0, c0 + cstep, ...  `lds` is the workgroup's LDS
+// (fm_lds bytes) with the D table in place.  Every thread of the workgroup must call it.
+template <int NM, int NW, typename SumT>
+__device__ __forceinline__ void fm_region(const Geo& g, int reg, int c0, int cstep, const float* __restrict__ p0,
+                                          const float* __restrict__ xe, SumT* __restrict__ s, float* lds) {
+    constexpr int STR = fm_stride(NM);
+    const int tid = threadIdx.x, lane = tid & (WAVE - 1);
+    const int wv = __builtin_amdgcn_readfirstlane(tid / WAVE);
+    const int nbin = g.nbin, jt = g.jt, K = g.K;
+    const int rows = nbin + 2 * jt;
+    float* refs = lds + fm_off_ref(NM, nbin);                // [slot][field][lane]
+    float4* axis = reinterpret_cast<float4*>(lds + fm_off_axis(NM, nbin));
+    const float* dt = lds + fm_off_dt(NM, nbin);
+    const Region R = region_info(g, reg);
+    const float* pbase = p0 + (size_t)R.i0 * g.vsx + (size_t)R.j0 * g.vsy + R.k0;
+    const int nchunk = (g.E + WAVE - 1) / WAVE;
+    const int ncol = R.ni * R.nj, mine = (ncol + NW - 1) / NW;
+    for (int i = tid; i < (nbin + 1) * STR / 4; i += NW * WAVE)
+        reinterpret_cast<float4*>(lds)[i] = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
+    if (tid < 3 * FM_SIDE) {                                 // voxel offsets from the region's centre; along z, of columns
+        const int a = tid / FM_SIDE, i = tid % FM_SIDE;
+        const float n = a == 0 ? (float)i - 0.5f * (float)(g.rx - 1)
+                               : a == 1 ? (float)i - 0.5f * (float)(g.ry - 1)
+                                        : (float)(i * FM_RZ) + 0.5f * (float)(FM_RZ - 1) - 0.5f * (float)(g.rz - 1);
+        const DF o = df_mul(DF{n, 0.0f}, DF{g.hs_u, g.hs_l});
+        axis[tid] = make_float4(o.h, o.l, 0.5f * o.h * o.h, 0.0f);
+    }
+    const FmBound bound = fm_bound<NW>(g, R, pbase, lds + fm_off_red(NM, nbin));
+    const float rlo = FM_MAGIC - 2.0f * g.jclampf, rhi = FM_MAGIC + 2.0f * g.jclampf;
+
+    int slot = FM_REFS;
+    for (int c = c0; c < nchunk; c += cstep, ++slot) {
+        if (slot == FM_REFS) {                               // references of the next FM_REFS chunks
+            slot = 0;
+            __syncthreads();
+            if (wv < FM_REFS) {
+                const int e = (c + wv * cstep) * WAVE + lane;
+                const FmRef r = fm_make_ref(g, xe + 6 * (size_t)min(e, g.E - 1), R, bound);
+                float* f = refs + wv * FM_FIELDS * WAVE + lane;
+                const float v[FM_FIELDS] = {r.D[0], r.D[1], r.D[2],  r.Dl[0], r.Dl[1], r.Dl[2], r.dh,
+                                            r.uc0,  r.n0,   r.scale, r.magic, r.inv,   __int_as_float(r.kbase)};
+#pragma unroll
+                for (int i = 0; i < FM_FIELDS; ++i) f[i * WAVE] = v[i];
+            }
+            __syncthreads();
+        }
+        const float* rf = refs + slot * FM_FIELDS * WAVE;
+        const float* rl = rf + lane;
+        const float dh = rl[6 * WAVE], scale = rl[9 * WAVE];
+        const int kb = __float_as_int(rl[12 * WAVE]);
+        const bool valid = c * WAVE + lane < g.E;
+        const bool finite = dh < 1e15f;
+        // nothing to add: every window of the chunk misses the record, or the region is all zero
+        const bool hit = valid && (!finite || (kb + rows > 0 && kb < K && bound.all != 0.0f));
+        if (!__any(hit)) continue;
+        const bool fixed = !__any(valid && scale == 0.0f);
+        const float Dx = rl[0], Dy = rl[WAVE], Dz = rl[2 * WAVE], Dxl = rl[3 * WAVE], Dyl = rl[4 * WAVE];
+        const float Dzl = rl[5 * WAVE], uc0 = rl[7 * WAVE], magic = rl[10 * WAVE], dh2 = dh * dh;
+        const unsigned off0 = (unsigned)lane * 4u + (unsigned)g.jclamp * (STR * 4u) - 0xC00000u * (STR * 4u);
+        for (int z0 = 0; z0 < R.nk; z0 += FM_RZ) {
+            const int nz = R.nk - z0;
+            const float4 tz = axis[2 * FM_SIDE + z0 / FM_RZ];
+            float zh, zl;
+            fm_axis(tz, Dz, Dzl, magic, zh, zl);
+            zl += rl[8 * WAVE];
+            const DF Dc = df_add(DF{Dz, Dzl}, DF{tz.x, tz.y});
+            float ez[FM_RZ];
+#pragma unroll
+            for (int k = 0; k < FM_RZ; ++k) {
+                const DF o = df_mul(DF{(float)k - 0.5f * (float)(FM_RZ - 1), 0.0f}, DF{g.hs_u, g.hs_l});
+                ez[k] = fmaf(o.h, Dc.l, fmaf(o.l, Dc.h, o.h * fmaf(0.5f, o.h, Dc.h)));
+            }
+            int ix = -1;
+            float xh = 0.0f, xl = 0.0f;
+            for (int col = wv * mine; col < min((wv + 1) * mine, ncol); ++col) {
+                const int i = col / R.nj, j = col - i * R.nj;
+                const float* pc = pbase + (size_t)i * g.vsx + (size_t)j * g.vsy + z0;
+                float pv[FM_RZ];
+                if (nz >= FM_RZ) {
+#pragma unroll
+                    for (int k = 0; k < FM_RZ; ++k) pv[k] = pc[k];
+                } else {
+#pragma unroll
+                    for (int k = 0; k < FM_RZ; ++k) pv[k] = k < nz ? pc[min(k, nz - 1)] : 0.0f;
+                }
+                if (i != ix) {                               // the wavefront's columns run along y
+                    ix = i;
+                    fm_axis(axis[i], Dx, Dxl, magic, xh, xl);
+                    xh += zh;
+                    xl += zl;
+                }
+                float yh, yl;
+                fm_axis(axis[FM_SIDE + j], Dy, Dyl, magic, yh, yl);
+                const FmCol cl = fm_col(xh + yh, xl + yl, dh, dh2, uc0);
+                if (fixed)
+                    fm_column<NM, true>(pv, ez, cl, scale, rlo, rhi, off0, reinterpret_cast<char*>(lds));
+                else
+                    fm_column<NM, false>(pv, ez, cl, 1.0f, rlo, rhi, off0, reinterpret_cast<char*>(lds));
+            }
+        }
+        __syncthreads();
+        if (fixed) {
+            // [16 rows x 16 elements] tiles: wavefront w takes elements 16 (w & 3).. and row tiles w / 4,
+            // w / 4 + NW / 4, .., two at a time (they share the D operand)
+            const int eg = wv & 3, li = lane & 15, lk = lane >> 4;
+            const int nq = (2 * jt + 16 + 3) / 4;
+            const int* acc = reinterpret_cast<const int*>(lds) + 16 * eg + li;
+            const float* db = dt + 2 * jt + FM_PAD + li - lk;          // D_n(jt + li - lk - 4 q)
+            const int dl = fm_dlen(jt);
+            const int e0 = 16 * eg + 4 * lk;
+            const vf4 inv = *reinterpret_cast<const vf4*>(rf + 11 * WAVE + e0);
+            const vf4 kbe = *reinterpret_cast<const vf4*>(rf + 12 * WAVE + e0);
+            auto add_rows = [&](vf4 v, int r0) {
+#pragma unroll
+                for (int i = 0; i < 4; ++i) {
+                    const int e = c * WAVE + e0 + i, k = __float_as_int(kbe[i]) + r0 + li;
+                    const float x = v[i] * inv[i];
+                    if (e < g.E && x != 0.0f && r0 + li < rows && k >= 0 && k < K)
+                        atomicAdd(s + (size_t)e * K + k, (SumT)x);
+                }
+            };
+            for (int r0 = 16 * (wv >> 2); r0 < rows; r0 += 8 * NW) {
+                const int r1 = r0 + 4 * NW;
+                vf4 s0 = {0.0f, 0.0f, 0.0f, 0.0f}, s1 = {0.0f, 0.0f, 0.0f, 0.0f};
+                const int b0 = r0 - 2 * jt + lk;
+                // bins that do not exist read the zero bin
+                auto bin = [&](int b) { return acc + (b >= 0 && b < nbin ? b : nbin) * STR; };
+                if (r1 < rows) {
+                    for (int q = 0; q < nq; ++q) {
+                        const int* a0 = bin(b0 + 4 * q);
+                        const int* a1 = bin(b0 + 4 * q + 4 * NW);
+#pragma unroll
+                        for (int n = 0; n < NM; ++n) {
+                            const float bv = db[n * dl - 4 * q];
+                            s0 = __builtin_amdgcn_mfma_f32_16x16x4f32((float)a0[n * WAVE], bv, s0, 0, 0, 0);
+                            s1 = __builtin_amdgcn_mfma_f32_16x16x4f32((float)a1[n * WAVE], bv, s1, 0, 0, 0);
+                        }
+                    }
+                    add_rows(s1, r1);
+                } else {
+                    for (int q = 0; q < nq; ++q) {
+                        const int* a0 = bin(b0 + 4 * q);
+#pragma unroll
+                        for (int n = 0; n < NM; ++n)
+                            s0 = __builtin_amdgcn_mfma_f32_16x16x4f32((float)a0[n * WAVE], db[n * dl - 4 * q], s0, 0, 0, 0);
+                    }
+                }
+                add_rows(s0, r0);
+            }
+        } else {
+            // FP32 sums: plain sums over the window rows, lane = element
+            const float* acc = lds + lane;
+            for (int r = wv; r < rows; r += NW) {
+                float v = 0.0f;
+                for (int b = max(r - 2 * jt, 0); b <= min(r, nbin - 1); ++b)
+#pragma unroll
+                    for (int n = 0; n < NM; ++n)
+                        v = fmaf(acc[b * STR + n * WAVE], dt[n * fm_dlen(jt) + FM_PAD + r - b], v);
+                const int k = kb + r;
+                if (valid && v != 0.0f && k >= 0 && k < K) atomicAdd(s + (size_t)(c * WAVE + lane) * K + k, (SumT)v);
+            }
+        }
+        __syncthreads();
+        for (int i = tid; i < nbin * STR / 4; i += NW * WAVE)
+            reinterpret_cast<float4*>(lds)[i] = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
+        __syncthreads();
+    }
+}
+
+template <int NM, int NW, typename SumT>
+__global__ __launch_bounds__(NW * WAVE) __attribute__((amdgpu_waves_per_eu(4))) void k_forward_mom(
+    Geo g, MomCoef mc, int nslice, const float* __restrict__ p0, const float* __restrict__ xe, SumT* __restrict__ s) {
+    extern __shared__ float lds[];
+    const int dl = fm_dlen(g.jt);
+    float* dt = lds + fm_off_dt(NM, g.nbin);
+    for (int i = threadIdx.x; i < NM * dl; i += NW * WAVE)
+        dt[i] = mom_coef(mc, i / dl, i % dl - FM_PAD - g.jt, g.jt);
+    const int b = region_of_block(blockIdx.x, gridDim.x);
+    fm_region<NM, NW, SumT>(g, b / nslice, b % nslice, nslice, p0, xe, s, lds);
+}
+
+// ------------------------------------------------------------------------------------------
 // adjoint: dL/dp0 and/or per-region element-gradient partials
 // ------------------------------------------------------------------------------------------
 // Moments of one (voxel, element) pair over its sample window, with r = dL/ds:
@@ -1207,10 +1641,6 @@ __device__ __forceinline__ void mom_load_x(const Geo& g, const float* __restrict
 #pragma unroll
     for (int i = 0; i < 6; ++i) xn[i] = xe[6 * e + i];
 }
-
-// Four floats as a native vector: copies of it are plain vector moves (no byte copies through
-// memory), so arrays of it stay in registers.
-typedef float vf4 __attribute__((ext_vector_type(4)));
 
 // Issue the loads of a wavefront's PER table rows (bins b0 .. b0 + nb - 1) of chunk c; rows that do
 // not exist or lie outside the table read the zero row after the table.
@@ -2293,6 +2723,10 @@ struct ra_ctx {
     char* arena = nullptr;                  // the context's scratch (grown by ensure_scratch)
     size_t arena_bytes = 0;
     char* static_scratch = nullptr;         // this device's static array (radiate_forward_static)
+    // series of the moment-form forward for the sampling of the last call (its key: profile, window, nu)
+    MomCoef series;
+    double series_key[4] = {0.0, 0.0, 0.0, 0.0};
+    double series_tail[FM_NM_MAX + 1];
     unsigned long long* h_count = nullptr;  // pinned
     double* h_f64 = nullptr;                // pinned, one value
     double* d_f64 = nullptr;                // device, one value
@@ -2365,6 +2799,10 @@ struct Plan {
     bool pose_moment;   // the adjoint with element gradients takes it too (k_adjoint_mom_pose) on regions g
     double mom_dd, mom_sigma;   // its delta / sigma and sigma
     bool f64_sums;      // the forward adds its partial rows into FP64 sums (else FP32, straight into s)
+    bool fm;            // the forward takes the moment form (k_forward_mom) on regions gm
+    Geo gm;
+    int fm_nm, fm_slices;   // its moments; workgroups that share a region's element chunks
+    size_t lds_fm;
     size_t lds_adj, lds_adj0, lds_fwd;
     // scratch layout (byte offsets)
     size_t off_xe, off_vtab, off_itab, off_vtab_a, off_itab_a, off_vtab_f, off_itab_f, off_part, off_ge, off_s,
@@ -2441,6 +2879,7 @@ void make_plan(const ra_grid* grid, int32_t M, int32_t F, const ra_sampling* sam
                bool allow_moment = true) {
     Geo& g = P.g;
     std::memset(&g, 0, sizeof(g));
+    P.fm = false;
     g.nx = grid->nx; g.ny = grid->ny; g.nz = grid->nz;
     g.vsx = (long long)grid->ny * grid->nz;
     g.vsy = grid->nz;
@@ -2598,6 +3037,128 @@ void make_plan(const ra_grid* grid, int32_t M, int32_t F, const ra_sampling* sam
     P.total = o;
 }
 
+// Series of phi((t/2 - j) delta) / delta in t, j = 0..jt: the Chebyshev coefficients from FM_NODES nodes,
+// the first FM_NM_MAX as a polynomial in each of its lengths would be; tail[n] bounds what is cut after
+// n terms, relative to the peak.
+constexpr int FM_NODES = 24;
+
+void mom_series(double dd, int jt, double cheb[FM_NM_MAX][JMAX + 1], double tail[FM_NM_MAX + 1]) {
+    const double pi = 3.14159265358979323846;
+    double cs[FM_NODES][FM_NODES];
+    for (int k = 0; k < FM_NODES; ++k)
+        for (int i = 0; i < FM_NODES; ++i) cs[k][i] = std::cos(pi * k * (i + 0.5) / FM_NODES);
+    const double peak = std::exp(-0.5) / dd;               // of x exp(-(x dd)^2 / 2)
+    for (int n = 0; n <= FM_NM_MAX; ++n) tail[n] = 0.0;
+    for (int j = 0; j <= jt; ++j) {
+        double f[FM_NODES];
+        for (int i = 0; i < FM_NODES; ++i) {
+            const double x = 0.5 * cs[1][i] - j;
+            f[i] = x * std::exp(-0.5 * x * x * dd * dd);
+        }
+        double rest = 0.0;
+        for (int k = FM_NODES - 1; k >= 0; --k) {
+            double c = 0.0;
+            for (int i = 0; i < FM_NODES; ++i) c += f[i] * cs[k][i];
+            c *= (k ? 2.0 : 1.0) / FM_NODES;
+            if (k < FM_NM_MAX) cheb[k][j] = c;
+            rest += std::fabs(c);
+            if (k <= FM_NM_MAX) tail[k] = std::max(tail[k], rest / peak);
+        }
+    }
+}
+
+// The sum of the first nm Chebyshev terms as a polynomial in t.
+void mom_monomials(const double cheb[FM_NM_MAX][JMAX + 1], int nm, int jt, MomCoef& out) {
+    double T[FM_NM_MAX][FM_NM_MAX] = {};                   // T[k][n]: coefficient of t^n in T_k
+    T[0][0] = 1.0;
+    T[1][1] = 1.0;
+    for (int k = 2; k < nm; ++k)
+        for (int n = 0; n < nm; ++n) T[k][n] = (n ? 2.0 * T[k - 1][n - 1] : 0.0) - T[k - 2][n];
+    std::memset(&out, 0, sizeof(out));
+    for (int j = 0; j <= jt; ++j)
+        for (int n = 0; n < nm; ++n) {
+            double v = 0.0;
+            for (int k = n; k < nm; ++k) v += cheb[k][j] * T[k][n];
+            out.d[n * (JMAX + 1) + j] = (float)v;
+        }
+}
+
+// The moment-form forward of a call: whether it is taken, with how many moments, on which regions.
+//   Window   the form takes the window's rows whole, as the Gaussian's other kernels do for the half-widths
+//            of RA_EXACT_LIST; for longer windows those test each term, so it is taken there only from
+//            6 sigma on, where the terms in question are below 1.5e-7 of the peak.
+//   Moments  the fewest (6, 7 or 8) whose cut series is within FM_TOL: 6 up to delta/sigma 0.41, 7 up to 0.64, 8 up
+//            to 1.05 (the row form's own rounding is about 4e-7); coarser sampling keeps the row form.
+//   Regions  those that make the estimated time least.  Per pair and wavefront a CU spends about 34 cycles on
+//            the adds; per region and chunk the expansion takes row tiles x quads x NM matrix instructions of 32
+//            cycles on each SIMD (measured: 1.45 times that, with the operand conversions and the atomics),
+//            and barriers and clearing about 2500 cycles where one workgroup has the CU, 800 where two share it.
+//            Large grids take 16x16x16; a box of 32^3 voxels seen by one chunk takes small ones, which fill the chip.
+void plan_forward_mom(ra_ctx* ctx, const ra_grid* grid, const ra_sampling* samp, Plan& P) {
+    P.fm = false;
+    const double delta = samp->c / samp->fs, dd = delta / samp->sigma;
+    const int jt = (int)std::floor(samp->trunc * samp->sigma / delta + 0.5);
+    if (samp->kernel != RA_KERNEL_GAUSSIAN || !(P.exact || samp->trunc >= 6.0) || jt < 1 || jt > JMAX) return;
+    const double key[4] = {(double)samp->kernel, dd, (double)jt, samp->nu};
+    if (std::memcmp(key, ctx->series_key, sizeof(key)) != 0) {
+        double cheb[FM_NM_MAX][JMAX + 1];
+        mom_series(dd, jt, cheb, ctx->series_tail);
+        int nm = 6;
+        while (nm < FM_NM_MAX && ctx->series_tail[nm] > FM_TOL) ++nm;
+        mom_monomials(cheb, nm, jt, ctx->series);
+        std::memcpy(ctx->series_key, key, sizeof(key));
+    }
+    int nm = 6;
+    while (nm < FM_NM_MAX && ctx->series_tail[nm] > FM_TOL) ++nm;
+    if (ctx->series_tail[nm] > FM_TOL) return;
+    static const int cand[][3] = {{16, 16, 16}, {16, 16, 8}, {8, 16, 8}, {8, 8, 16}, {8, 8, 8}, {4, 8, 8},
+                                  {4, 4, 8},    {2, 4, 8},   {2, 2, 8},  {1, 2, 8},  {1, 1, 8}};
+    const int nchunk = (P.g.E + WAVE - 1) / WAVE;
+    double best = 0.0;
+    for (const auto& cd : cand) {
+        Geo g = P.g;
+        // as many regions along x and y as the candidate's size gives, of even size
+        g.nrx = (g.nx + cd[0] - 1) / cd[0]; g.nry = (g.ny + cd[1] - 1) / cd[1]; g.nrz = (g.nz + cd[2] - 1) / cd[2];
+        g.rx = (g.nx + g.nrx - 1) / g.nrx; g.ry = (g.ny + g.nry - 1) / g.nry; g.rz = std::min(cd[2], g.nz);
+        const double rad = 0.5 * grid->spacing * std::sqrt((double)(g.rx - 1) * (g.rx - 1) + (double)(g.ry - 1) * (g.ry - 1) +
+                                                           (double)(g.rz - 1) * (g.rz - 1));
+        if (rad / delta > 1e4) continue;                   // never fits; keeps the bin count an int
+        g.jclamp = (int)std::ceil(rad / delta * (1.0 + 1e-6)) + 1;
+        g.jclampf = (float)g.jclamp;
+        g.jt = jt;
+        g.nbin = 2 * g.jclamp + 1;
+        const size_t lds = fm_lds(nm, g.nbin, jt);
+        if (lds > 160 * 1024) continue;
+        g.nrx = (g.nx + g.rx - 1) / g.rx; g.nry = (g.ny + g.ry - 1) / g.ry;
+        g.nreg = g.nrx * g.nry * g.nrz;
+        const int per_cu = lds <= LDS_FM_BUDGET ? 2 : 1;
+        const int slices = std::min(nchunk, std::max(1, (2048 + g.nreg - 1) / g.nreg));
+        const double expand = ((g.nbin + 2 * jt + 15) / 16) * ((2 * jt + 19) / 4) * nm * 32.0 * 1.45;
+        const int zl = g.nz - (g.nrz - 1) * g.rz;          // columns run in steps of FM_RZ voxels
+        const double zpad = (g.nrz - 1.0) * ((g.rz + FM_RZ - 1) / FM_RZ * FM_RZ) + (zl + FM_RZ - 1) / FM_RZ * FM_RZ;
+        const double pairs = (double)g.nx * g.ny * zpad / g.nreg * 34.0;
+        const double each = pairs + expand + (per_cu == 2 ? 800.0 : 2500.0);   // CU cycles per region and chunk
+        const double wgs = (double)g.nreg * slices, per_wg = (double)((nchunk + slices - 1) / slices);
+        // the last round of workgroups; a CU with one where two fit runs it about 1.6 times as fast
+        const double full = std::floor(wgs / (256.0 * per_cu)), left = wgs - full * 256.0 * per_cu;
+        const double last = left == 0.0 ? 0.0 : (left <= 256.0 && per_cu == 2 ? 0.62 : 1.0);
+        const double cost = (full + last) * per_cu * per_wg * each;
+        if (P.fm && cost >= best) continue;
+        best = cost;
+        P.fm = true;
+        P.gm = g;
+        P.fm_nm = nm;
+        P.fm_slices = slices;
+        P.lds_fm = lds;
+    }
+    if (!P.fm) return;
+    const double unit = 2.0 / delta;
+    P.gm.unit_h = (float)unit;
+    P.gm.unit_l = (float)(unit - (double)P.gm.unit_h);
+    P.gm.hs_u = (float)(grid->spacing * unit);
+    P.gm.hs_l = (float)(grid->spacing * unit - (double)P.gm.hs_u);
+}
+
 int ensure_scratch(ra_ctx* ctx, size_t bytes, hipStream_t stream) {
     if (bytes <= ctx->arena_bytes) return RA_OK;
     hipStreamCaptureStatus cs = hipStreamCaptureStatusNone;
@@ -2654,8 +3215,9 @@ int prologue(ra_ctx* ctx, char* base, const ra_grid* grid, const Plan& P, const 
         hipLaunchKernelGGL(k_voxel_table, dim3((P.ga.nvpad + 255) / 256), dim3(256), 0, stream, P.ga,
                            at<float4>(base, P.off_vtab_a), at<int4>(base, P.off_itab_a));
     }
-    hipLaunchKernelGGL(k_voxel_table, dim3((P.gf.nvpad + 255) / 256), dim3(256), 0, stream, P.gf,
-                       at<float4>(base, P.off_vtab_f), at<int4>(base, P.off_itab_f));
+    if (!P.fm)
+        hipLaunchKernelGGL(k_voxel_table, dim3((P.gf.nvpad + 255) / 256), dim3(256), 0, stream, P.gf,
+                           at<float4>(base, P.off_vtab_f), at<int4>(base, P.off_itab_f));
     RA_HIP(ctx, hipGetLastError());
     return RA_OK;
 }
@@ -2711,6 +3273,29 @@ int launch_forward_t(ra_ctx* ctx, char* base, const Plan& P, const float* p0, fl
     return RA_OK;
 }
 
+template <int NM, int NW>
+int launch_forward_mom(ra_ctx* ctx, char* base, const Plan& P, const float* p0, float* s, hipStream_t stream) {
+    const size_t n = (size_t)P.g.E * P.g.K;
+    const dim3 grid((unsigned)(P.gm.nreg * P.fm_slices)), block(NW * WAVE);
+    const float* xe = at<float>(base, P.off_xe);
+    if (!P.f64_sums) {
+        auto kern = k_forward_mom<NM, NW, float>;
+        RA_HIP(ctx, allow_full_lds(kern));
+        hipLaunchKernelGGL(k_fill, dim3(1024), dim3(256), 0, stream, s, n, 0.0f);
+        hipLaunchKernelGGL(kern, grid, block, P.lds_fm, stream, P.gm, ctx->series, P.fm_slices, p0, xe, s);
+        RA_HIP(ctx, hipGetLastError());
+        return RA_OK;
+    }
+    auto kern = k_forward_mom<NM, NW, double>;
+    RA_HIP(ctx, allow_full_lds(kern));
+    double* s64 = at<double>(base, P.off_s64);
+    hipLaunchKernelGGL(k_fill_f64, dim3(1024), dim3(256), 0, stream, s64, n);
+    hipLaunchKernelGGL(kern, grid, block, P.lds_fm, stream, P.gm, ctx->series, P.fm_slices, p0, xe, s64);
+    hipLaunchKernelGGL(k_to_f32, dim3(1024), dim3(256), 0, stream, s64, n, s);
+    RA_HIP(ctx, hipGetLastError());
+    return RA_OK;
+}
+
 // Kernels with a listed window bound JT test only their last GEN_STEP (Gaussian) or
 // EXP_STEP (exponential) steps, which needs every earlier step inside the window.
 bool generic_bound_ok(const Plan& P) {
@@ -2719,6 +3304,15 @@ bool generic_bound_ok(const Plan& P) {
 }
 
 int launch_forward(ra_ctx* ctx, char* base, const Plan& P, const float* p0, float* s, hipStream_t stream) {
+    if (P.fm) {
+        const bool big = P.lds_fm > LDS_FM_BUDGET;
+#define RA_CASE(n)                                                                    \
+    if (P.fm_nm == n)                                                                 \
+        return big ? launch_forward_mom<n, FM_WAVES_BIG>(ctx, base, P, p0, s, stream) \
+                   : launch_forward_mom<n, FM_WAVES>(ctx, base, P, p0, s, stream);
+        RA_CASE(6) RA_CASE(7) RA_CASE(8)
+#undef RA_CASE
+    }
     if (!generic_bound_ok(P)) return fail(ctx, RA_ENOTSUP, "window half-width not supported");
     // other profiles; the per-sample kernels index from the centre row kmargin (JT = 0)
     switch (P.g.ktype) {
@@ -2944,8 +3538,9 @@ int radiate_forward(ra_ctx* ctx, const ra_grid* grid, const float* p0, int32_t M
     RA_HIP(ctx, hipSetDevice(ctx->device));
     Plan P;
     make_plan(grid, M, F, samp, P, ctx->sums_mode);
+    plan_forward_mom(ctx, grid, samp, P);
     if ((rc = ensure_scratch(ctx, P.total, st)) != RA_OK) return rc;
-    if ((rc = prologue(ctx, ctx->arena, grid, P, elem, poses, st)) != RA_OK) return rc;
+    if ((rc = prologue(ctx, ctx->arena, grid, P, elem, poses, st, true)) != RA_OK) return rc;
     return launch_forward(ctx, ctx->arena, P, p0, s, st);
 }
 
@@ -2960,6 +3555,7 @@ int radiate_forward_static(ra_ctx* ctx, const ra_grid* grid, const float* p0, in
     RA_HIP(ctx, hipSetDevice(ctx->device));
     Plan P;
     make_plan(grid, M, F, samp, P, ctx->sums_mode);
+    plan_forward_mom(ctx, grid, samp, P);
     const size_t need = forward_layout(P);
     if (need > STATIC_SCRATCH_BYTES)
         return fail(ctx, RA_ENOMEM, "radiate_forward_static needs " + std::to_string(need) +
@@ -3003,6 +3599,7 @@ int loss_and_grad(ra_ctx* ctx, const ra_grid* grid, const float* p0, int32_t M, 
     RA_HIP(ctx, hipSetDevice(ctx->device));
     Plan P;
     make_plan(grid, M, F, samp, P, ctx->sums_mode);
+    plan_forward_mom(ctx, grid, samp, P);
     if ((rc = ensure_scratch(ctx, P.total, st)) != RA_OK) return rc;
     if ((rc = prologue(ctx, ctx->arena, grid, P, elem, poses, st)) != RA_OK) return rc;
     float* s = at<float>(ctx, P.off_s);
@@ -3046,6 +3643,7 @@ int nc_loss_and_grad(ra_ctx* ctx, const ra_grid* grid, const float* p0, int32_t 
     RA_HIP(ctx, hipSetDevice(ctx->device));
     Plan P;
     make_plan(grid, M, F, samp, P, ctx->sums_mode);
+    plan_forward_mom(ctx, grid, samp, P);
     if ((rc = ensure_scratch(ctx, P.total, st)) != RA_OK) return rc;
     if ((rc = prologue(ctx, ctx->arena, grid, P, elem, poses, st)) != RA_OK) return rc;
     float* s = at<float>(ctx, P.off_s);
