@@ -34,10 +34,9 @@
 //     into the signals with global atomics (transposed, so each atomic instruction covers consecutive
 //     samples of one element).
 //   * Sums of the regions' rows: FP32 up to 4096 row-form regions, FP64 sums beyond.
-//   * Adjoints with the Gaussian (single calls and the batched step): Taylor
-//     moments of dL/ds per sample (a table built once per call), two LDS
-//     reads and a Horner sum per pair, with its derivative for the element
-//     gradients (mom_region).
+//   * Adjoints with the Gaussian: a table of dL/ds's local expansions per sample, built once per
+//     call, two LDS reads and a Horner sum per pair, with its derivative for the element gradients
+//     (am_regions; the batched step: Taylor moments, mom_region).
 //   * Adjoints otherwise (other profiles, or where the expansion's bound
 //     fails): each lane stages its element's dL/ds window in the same
 //     private-row layout and gathers.  dL/dp0 of a voxel is summed across the
@@ -87,6 +86,7 @@ constexpr int RS_MAX = 47;            // largest |row - kc| of the row-reference
 constexpr int PAIR_D = 3;             // largest centre-sample spread of two voxels the paired forward takes
 constexpr int NC_THREADS = 256;       // workgroup of the negative-correlation row kernel
 constexpr int NXCD = 8;               // MI355X compute dies; workgroups are dealt round-robin
+constexpr int NCU = 256;              // its compute units
 constexpr int RESID_BLOCKS = 1024;    // partial sums of the loss
 constexpr int FWD_F32_MAX_REGIONS = 4096;   // forward regions up to which partial rows are summed in FP32
 constexpr size_t LDS_FWD_BUDGET = 80 * 1024;   // forward: two region workgroups per CU
@@ -105,6 +105,9 @@ constexpr int FM_RZ = 8;              // voxels of a column it unrolls
 constexpr int FM_SIDE = 16;           // its largest region side
 constexpr int FM_NM_MAX = 8;          // its largest number of moments
 constexpr double FM_TOL = 2e-7;       // its largest admitted expansion error, relative to the peak
+constexpr double AM_TOL = 2.5e-8;     // that error where the series' derivative is used (its 8 terms' grows 8-fold in rms)
+constexpr int AM_WAVES = 16;          // wavefronts of the moment-form adjoints' region workgroup, one per CU
+constexpr int AM_REFS = 3;            // references held: this chunk's, the next one's and the one after
 constexpr size_t LDS_FM_BUDGET = 80 * 1024;    // two of its workgroups per CU
 
 // ------------------------------------------------------------------------------------------
@@ -814,13 +817,13 @@ __global__ __launch_bounds__(BLOCK) void k_forward(Geo g, const float* __restric
 // expansion adds to that: 5.7 ms with 8x8x8 regions, two workgroups to a CU; hence the largest regions
 // that the LDS holds, one workgroup of 16 wavefronts to a CU.
 struct MomCoef {
-    float d[FM_NM_MAX * (JMAX + 1)];   // D_n(j) / delta at n * (JMAX + 1) + j, j >= 0; D_n(-j) = (-1)^(n+1) D_n(j)
+    float d[(JMAX + 1) * FM_NM_MAX];   // D_n(j) / delta at j * FM_NM_MAX + n, j >= 0; D_n(-j) = (-1)^(n+1) D_n(j)
 };
 
 __device__ __forceinline__ float mom_coef(const MomCoef& m, int n, int j, int jt) {
     const int a = j < 0 ? -j : j;
     if (a > jt) return 0.0f;
-    const float v = m.d[n * (JMAX + 1) + a];
+    const float v = m.d[a * FM_NM_MAX + n];
     return (j < 0 && !(n & 1)) ? -v : v;
 }
 
@@ -845,40 +848,54 @@ struct FmBound {
 };
 
 // Reference of a (region, element) pair in units: D = centre - x_e in double-float, dh = |D| rounded,
-// uc0 = dh - 2 kc, n0 = (|D|^2 - dh^2) / 2, the unit of its sums, and the quantum of the column sums.
-struct FmRef {
-    float D[3], Dl[3], dh, uc0, n0, scale, inv, magic;
-    int kbase;                             // sample of row 0
+// uc0 = dh - 2 kc, n0 = (|D|^2 - dh^2) / 2, and the quantum of the column sums.
+struct MomRef {
+    float D[3], Dl[3], dh, uc0, n0, magic;
+    int kc;                                // nearest sample
 };
 
-__device__ __forceinline__ FmRef fm_make_ref(const Geo& g, const float* __restrict__ x, const Region& R,
-                                             const FmBound& bd) {
+__device__ __forceinline__ MomRef mom_make_ref(const Geo& g, const float* __restrict__ x, const Region& R) {
 #pragma clang fp contract(off)
     const DF u{g.unit_h, g.unit_l};
     const DF D[3] = {df_mul(df_add(R.cx, df_neg(DF{x[0], x[3]})), u), df_mul(df_add(R.cy, df_neg(DF{x[1], x[4]})), u),
                      df_mul(df_add(R.cz, df_neg(DF{x[2], x[5]})), u)};
     const DF d = df_sqrt(df_add(df_add(df_mul(D[0], D[0]), df_mul(D[1], D[1])), df_mul(D[2], D[2])));
     const float kc = rintf(0.5f * d.h);
-    FmRef r;
+    MomRef r;
+    float h2 = 0.0f;
+    const int n[3] = {g.rx, g.ry, g.rz};
 #pragma unroll
     for (int a = 0; a < 3; ++a) {
         r.D[a] = D[a].h;
         r.Dl[a] = D[a].l;
+        const float half = 0.5f * (float)(n[a] - 1) * g.hs_u;
+        h2 += half * half;
     }
     r.dh = d.h;
     r.uc0 = d.h - 2.0f * kc;
     r.n0 = d.h * d.l;
-    r.kbase = (int)kc - g.jclamp - g.jt;
+    r.kc = (int)kc;
+    // |D.o + o.o/2| < 2^e of this product (columns reach up to 4 voxels past a short region), so multiples
+    // of 2^(e - 22) below it add exactly
+    const float rad = sqrtf(h2) + 4.0f * g.hs_u;
+    r.magic = 1.5f * __builtin_amdgcn_ldexpf(1.0f, __builtin_amdgcn_frexp_expf(rad * (d.h + rad)) + 1);
+    return r;
+}
+
+// The scale of a pair's fixed-point sums and its inverse; 0 where FP32 sums are taken.
+struct FmScale {
+    float scale, inv;
+};
+
+__device__ __forceinline__ FmScale fm_scale(const Geo& g, const MomRef& m, const FmBound& bd) {
+#pragma clang fp contract(off)
     const float half[3] = {0.5f * (float)(g.rx - 1) * g.hs_u, 0.5f * (float)(g.ry - 1) * g.hs_u,
                            0.5f * (float)(g.rz - 1) * g.hs_u};
-    const float rad = sqrtf(half[0] * half[0] + half[1] * half[1] + half[2] * half[2]) + 4.0f * g.hs_u;
-    const float far = d.h + rad;
-    // |D.o + o.o/2| < 2^e = rad far, so multiples of 2^(e - 22) below it add exactly
-    r.magic = 1.5f * __builtin_amdgcn_ldexpf(1.0f, __builtin_amdgcn_frexp_expf(rad * far) + 1);
+    const float far = m.dh + sqrtf(half[0] * half[0] + half[1] * half[1] + half[2] * half[2]);
     float dl2 = 0.0f, most = bd.all;
 #pragma unroll
     for (int a = 0; a < 3; ++a) {
-        const float out = fabsf(D[a].h) - half[a];           // distance past the box along the axis
+        const float out = fabsf(m.D[a]) - half[a];           // distance past the box along the axis
         if (!(out > 0.0f)) continue;
         dl2 += out * out;
         const float gap = g.hs_u * 0.999f * out / far;       // least difference in distance of two voxels of a line
@@ -888,7 +905,8 @@ __device__ __forceinline__ FmRef fm_make_ref(const Geo& g, const float* __restri
     most = bd.all - bd.all == 0.0f ? most * 1.001f : bd.all;  // fminf drops NaN
     const float dlow = sqrtf(dl2) * 0.999f;
     // 1/d <= 1/dlow for every term of the region; scale 0 (take FP32 sums) where that says nothing
-    const bool ok = dlow >= 0.5f * g.hs_u && d.h < 1e15f;
+    const bool ok = dlow >= 0.5f * g.hs_u && m.dh < 1e15f;
+    FmScale r;
     r.scale = ok ? 2.147e9f * dlow / most : 0.0f;
     r.inv = most / (2.147e9f * dlow);
     if (!(r.scale > 0.0f && r.scale < 1e37f && r.inv > 1e-37f && r.inv < 1e37f)) r.scale = r.inv = 0.0f;
@@ -909,6 +927,29 @@ __device__ __forceinline__ int cvt_round_i32(float x) {      // floor(x + 1/2)
     int v;
     asm("v_cvt_rpi_i32_f32 %0, %1" : "=v"(v) : "v"(x));
     return v;
+}
+
+// Offsets of a region's voxels from its centre along each axis, [axis][index] (along z: of the centres of its
+// columns of FM_RZ voxels), as fm_axis takes them.
+__device__ __forceinline__ void fm_axis_table(const Geo& g, int tid, float4* axis) {
+    if (tid >= 3 * FM_SIDE) return;
+    const int a = tid / FM_SIDE, i = tid % FM_SIDE;
+    const float n = a == 0 ? (float)i - 0.5f * (float)(g.rx - 1)
+                           : a == 1 ? (float)i - 0.5f * (float)(g.ry - 1)
+                                    : (float)(i * FM_RZ) + 0.5f * (float)(FM_RZ - 1) - 0.5f * (float)(g.rz - 1);
+    const DF o = df_mul(DF{n, 0.0f}, DF{g.hs_u, g.hs_l});
+    axis[tid] = make_float4(o.h, o.l, 0.5f * o.h * o.h, 0.0f);
+}
+
+// N of each voxel of a column about the column's centre, which is tz along z from the region's.
+__device__ __forceinline__ void fm_column_n(const Geo& g, float4 tz, float Dz, float Dzl, float (&ez)[FM_RZ]) {
+#pragma clang fp contract(off)
+    const DF Dc = df_add(DF{Dz, Dzl}, DF{tz.x, tz.y});
+#pragma unroll
+    for (int k = 0; k < FM_RZ; ++k) {
+        const DF o = df_mul(DF{(float)k - 0.5f * (float)(FM_RZ - 1), 0.0f}, DF{g.hs_u, g.hs_l});
+        ez[k] = fmaf(o.h, Dc.l, fmaf(o.l, Dc.h, o.h * fmaf(0.5f, o.h, Dc.h)));
+    }
 }
 
 constexpr float FM_MAGIC = 25165824.0f;    // 1.5 * 2^24: adding it rounds to a multiple of 2 (a sample)
@@ -936,27 +977,39 @@ __device__ __forceinline__ FmCol fm_col(float bh, float bl, float dh, float dh2,
     return c;
 }
 
+// A voxel of the column: rs = 1/d, t, and FM_MAGIC plus its nearest sample's offset from kc (kept in
+// [lo, hi] whatever the inputs).
+struct FmPair {
+    float rs, t, rm;
+};
+
+__device__ __forceinline__ FmPair fm_pair(const FmCol& c, float dc2, float hdc, float ez, float lo, float hi) {
+#pragma clang fp contract(off)                 // the distance's Newton step, as pair_dist
+    FmPair p;
+    const float S = fmaf(2.0f, ez, dc2);
+    p.rs = __builtin_amdgcn_rsqf(S);
+    const float y = S * p.rs;
+    const float a = y - c.dc;
+    const float bh = fmaf(0.5f, y, hdc);
+    const float th = fmaf(-a, bh, ez);
+    const float uc = c.uc + fmaf(th, p.rs, a);
+    p.rm = __builtin_amdgcn_fmed3f(uc + c.magic, lo, hi);      // NaN lands in range too
+    p.t = uc - (p.rm - c.magic);
+    return p;
+}
+
 // The adds of one column of FM_RZ voxels (p0 values pv, zero past the grid); ez: N of each voxel about
 // the column's centre.  INT: fixed-point sums.
 template <int NM, bool INT>
 __device__ __forceinline__ void fm_column(const float (&pv)[FM_RZ], const float (&ez)[FM_RZ], const FmCol& c, float scale,
-                                          float lo, float hi, unsigned off0, char* sums) {
-#pragma clang fp contract(off)                 // the distance's Newton step, as pair_dist
+                                          float lo, float hi, unsigned off0, unsigned str, char* sums) {
     const float dc2 = c.dc * c.dc, hdc = 0.5f * c.dc;
 #pragma unroll
     for (int k = 0; k < FM_RZ; ++k) {
-        const float S = fmaf(2.0f, ez[k], dc2);
-        const float rs = __builtin_amdgcn_rsqf(S);
-        const float y = S * rs;
-        const float a = y - c.dc;
-        const float bh = fmaf(0.5f, y, hdc);
-        const float th = fmaf(-a, bh, ez[k]);
-        const float uc = c.uc + fmaf(th, rs, a);
-        const float rm = __builtin_amdgcn_fmed3f(uc + c.magic, lo, hi);      // NaN lands in range too
-        const float t = uc - (rm - c.magic);
+        const FmPair p = fm_pair(c, dc2, hdc, ez[k], lo, hi);
         // the low 24 bits of rm are 0xC00000 + (centre sample offset)
-        const unsigned off = __umul24(__float_as_uint(rm), fm_stride(NM) * 4u) + off0;
-        float q = pv[k] * rs;
+        const unsigned off = __umul24(__float_as_uint(p.rm), str) + off0;
+        float q = pv[k] * p.rs;
         if (INT) q *= scale;
 #pragma unroll
         for (int n = 0; n < NM; ++n) {
@@ -967,7 +1020,7 @@ __device__ __forceinline__ void fm_column(const float (&pv)[FM_RZ], const float 
                 float* dst = reinterpret_cast<float*>(sums + off) + n * WAVE;
                 __hip_atomic_fetch_add(dst, q, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
             }
-            if (n + 1 < NM) q *= t;
+            if (n + 1 < NM) q *= p.t;
         }
     }
 }
@@ -1028,14 +1081,7 @@ __device__ __forceinline__ void fm_region(const Geo& g, int reg, int c0, int cst
     const int ncol = R.ni * R.nj, mine = (ncol + NW - 1) / NW;
     for (int i = tid; i < (nbin + 1) * STR / 4; i += NW * WAVE)
         reinterpret_cast<float4*>(lds)[i] = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
-    if (tid < 3 * FM_SIDE) {                                 // voxel offsets from the region's centre; along z, of columns
-        const int a = tid / FM_SIDE, i = tid % FM_SIDE;
-        const float n = a == 0 ? (float)i - 0.5f * (float)(g.rx - 1)
-                               : a == 1 ? (float)i - 0.5f * (float)(g.ry - 1)
-                                        : (float)(i * FM_RZ) + 0.5f * (float)(FM_RZ - 1) - 0.5f * (float)(g.rz - 1);
-        const DF o = df_mul(DF{n, 0.0f}, DF{g.hs_u, g.hs_l});
-        axis[tid] = make_float4(o.h, o.l, 0.5f * o.h * o.h, 0.0f);
-    }
+    fm_axis_table(g, tid, axis);
     const FmBound bound = fm_bound<NW>(g, R, pbase, lds + fm_off_red(NM, nbin));
     const float rlo = FM_MAGIC - 2.0f * g.jclampf, rhi = FM_MAGIC + 2.0f * g.jclampf;
 
@@ -1046,10 +1092,12 @@ __device__ __forceinline__ void fm_region(const Geo& g, int reg, int c0, int cst
             __syncthreads();
             if (wv < FM_REFS) {
                 const int e = (c + wv * cstep) * WAVE + lane;
-                const FmRef r = fm_make_ref(g, xe + 6 * (size_t)min(e, g.E - 1), R, bound);
+                const MomRef r = mom_make_ref(g, xe + 6 * (size_t)min(e, g.E - 1), R);
+                const FmScale q = fm_scale(g, r, bound);
                 float* f = refs + wv * FM_FIELDS * WAVE + lane;
-                const float v[FM_FIELDS] = {r.D[0], r.D[1], r.D[2],  r.Dl[0], r.Dl[1], r.Dl[2], r.dh,
-                                            r.uc0,  r.n0,   r.scale, r.magic, r.inv,   __int_as_float(r.kbase)};
+                const float v[FM_FIELDS] = {r.D[0], r.D[1], r.D[2],  r.Dl[0], r.Dl[1],
+                                            r.Dl[2], r.dh,  r.uc0,   r.n0,    q.scale,
+                                            r.magic, q.inv, __int_as_float(r.kc - g.jclamp - jt)};
 #pragma unroll
                 for (int i = 0; i < FM_FIELDS; ++i) f[i * WAVE] = v[i];
             }
@@ -1067,20 +1115,16 @@ __device__ __forceinline__ void fm_region(const Geo& g, int reg, int c0, int cst
         const bool fixed = !__any(valid && scale == 0.0f);
         const float Dx = rl[0], Dy = rl[WAVE], Dz = rl[2 * WAVE], Dxl = rl[3 * WAVE], Dyl = rl[4 * WAVE];
         const float Dzl = rl[5 * WAVE], uc0 = rl[7 * WAVE], magic = rl[10 * WAVE], dh2 = dh * dh;
-        const unsigned off0 = (unsigned)lane * 4u + (unsigned)g.jclamp * (STR * 4u) - 0xC00000u * (STR * 4u);
+        unsigned off0 = (unsigned)lane * 4u + (unsigned)g.jclamp * (STR * 4u) - 0xC00000u * (STR * 4u);
+        unsigned str = STR * 4u;
+        asm volatile("" : "+v"(off0), "+v"(str));            // in vector registers: scalar operands halve the issue rate
         for (int z0 = 0; z0 < R.nk; z0 += FM_RZ) {
             const int nz = R.nk - z0;
             const float4 tz = axis[2 * FM_SIDE + z0 / FM_RZ];
-            float zh, zl;
+            float zh, zl, ez[FM_RZ];
             fm_axis(tz, Dz, Dzl, magic, zh, zl);
             zl += rl[8 * WAVE];
-            const DF Dc = df_add(DF{Dz, Dzl}, DF{tz.x, tz.y});
-            float ez[FM_RZ];
-#pragma unroll
-            for (int k = 0; k < FM_RZ; ++k) {
-                const DF o = df_mul(DF{(float)k - 0.5f * (float)(FM_RZ - 1), 0.0f}, DF{g.hs_u, g.hs_l});
-                ez[k] = fmaf(o.h, Dc.l, fmaf(o.l, Dc.h, o.h * fmaf(0.5f, o.h, Dc.h)));
-            }
+            fm_column_n(g, tz, Dz, Dzl, ez);
             int ix = -1;
             float xh = 0.0f, xl = 0.0f;
             for (int col = wv * mine; col < min((wv + 1) * mine, ncol); ++col) {
@@ -1104,9 +1148,9 @@ __device__ __forceinline__ void fm_region(const Geo& g, int reg, int c0, int cst
                 fm_axis(axis[FM_SIDE + j], Dy, Dyl, magic, yh, yl);
                 const FmCol cl = fm_col(xh + yh, xl + yl, dh, dh2, uc0);
                 if (fixed)
-                    fm_column<NM, true>(pv, ez, cl, scale, rlo, rhi, off0, reinterpret_cast<char*>(lds));
+                    fm_column<NM, true>(pv, ez, cl, scale, rlo, rhi, off0, str, reinterpret_cast<char*>(lds));
                 else
-                    fm_column<NM, false>(pv, ez, cl, 1.0f, rlo, rhi, off0, reinterpret_cast<char*>(lds));
+                    fm_column<NM, false>(pv, ez, cl, 1.0f, rlo, rhi, off0, str, reinterpret_cast<char*>(lds));
             }
         }
         __syncthreads();
@@ -1564,53 +1608,270 @@ __global__ __launch_bounds__(BLOCK) void k_adjoint(Geo g, const float* __restric
 // T sigma < |u| <= (JT + 1/2) delta (at most psi(T) ~ 1e-7 of the peak at T = 6) is added where the
 // exact window leaves it out.
 
-// D_n(j) for n < NMOM and |j| <= jt into c[n (2 jt + 1) + j + jt]; one workgroup of 2 jt + 1 threads.
-__global__ void k_moment_coefs(int jt, double dd, double sigma, float* __restrict__ c) {
-    const int j = (int)threadIdx.x - jt;
-    if (j > jt) return;
-    const double y = j * dd;
-    const double gy = exp(-0.5 * y * y);
-    double hprev = 1.0, h = y;             // He_n(y), He_{n+1}(y)
-    double dn = 1.0, fact = 1.0;           // Delta^n, n!
-    for (int n = 0; n < NMOM; ++n) {
-        c[n * (2 * jt + 1) + j + jt] = (float)(-sigma * dn * h * gy / fact);
-        const double hnext = y * h - (double)(n + 1) * hprev;   // He_{n+2} = y He_{n+1} - (n+1) He_n
-        hprev = h;
-        h = hnext;
-        dn *= dd;
-        fact *= (double)(n + 1);
+// The same local expansion on |t| <= 1 (t = 2x) as the forward's, by its Chebyshev series: table rows
+// Q[e][kk][n] = sum_{|j| <= jt} r[e][k + j] D_n(j) / delta for kk in [0, K + 2 jt), k = kk - jt, with dL/ds
+// zero outside [0, K); each row is two float4 (n = 0..3, 4..7).  One zero row follows the last element's
+// rows.  The window's two legs are taken together, since D_n(-j) = (-1)^(n+1) D_n(j): 10 VALU for two
+// samples.  A row of dL/ds is staged in LDS; the bound is writing the table (275 MB on the sweep: 0.118 ms
+// with a thread's 25 taps read from memory, 0.069 ms so).
+constexpr int MT_ROWS = 256;          // table rows per workgroup
+
+__global__ __launch_bounds__(MT_ROWS) void k_moment_series(int E, int K, int jt, MomCoef mc, const float* __restrict__ r,
+                                                           float4* __restrict__ q) {
+    __shared__ float row[MT_ROWS + 2 * JMAX];
+    const int kq = K + 2 * jt, per = (kq + MT_ROWS - 1) / MT_ROWS;
+    const int e = blockIdx.x / per, kk0 = (blockIdx.x - e * per) * MT_ROWS;
+    const float* re = r + (size_t)e * K;
+    for (int i = threadIdx.x; i < MT_ROWS + 2 * jt; i += MT_ROWS) {
+        const int k = kk0 - 2 * jt + i;                      // row[i] = r[kk0 - 2 jt + i]
+        row[i] = k >= 0 && k < K ? re[k] : 0.0f;
     }
+    __syncthreads();
+    const int kk = kk0 + threadIdx.x;
+    if (blockIdx.x == 0 && threadIdx.x < 2) q[(size_t)E * kq * 2 + threadIdx.x] = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
+    if (kk >= kq) return;
+    const float* w = row + threadIdx.x + jt;                 // r at the row's own sample
+    float acc[FM_NM_MAX];
+#pragma unroll
+    for (int n = 0; n < FM_NM_MAX; ++n) acc[n] = w[0] * mc.d[n];
+    for (int j = 1; j <= jt; ++j) {
+        const float a = w[j], b = w[-j], sum = a + b, dif = a - b;
+#pragma unroll
+        for (int n = 0; n < FM_NM_MAX; ++n) acc[n] = fmaf(n & 1 ? sum : dif, mc.d[j * FM_NM_MAX + n], acc[n]);
+    }
+    float4* out = q + 2 * ((size_t)e * kq + kk);
+    out[0] = make_float4(acc[0], acc[1], acc[2], acc[3]);
+    out[1] = make_float4(acc[4], acc[5], acc[6], acc[7]);
 }
 
-// Q[e][kk][n] = sum_{|j| <= jt} r[e][kk - jt + j] D_n(j) for table rows kk in [0, K + 2 jt) (sample
-// kk - jt), with dL/ds zero outside [0, K); each row is two float4 (n = 0..3, 4..7).  One zero row
-// follows the last element's rows.
-__global__ __launch_bounds__(256) void k_moment_table(int E, int K, int jt, const float* __restrict__ r,
-                                                      const float* __restrict__ coef, float4* __restrict__ q) {
-    __shared__ float cs[NMOM * (2 * JMAX + 1)];
-    const int nj = 2 * jt + 1;
-    for (int i = threadIdx.x; i < NMOM * nj; i += blockDim.x) cs[i] = coef[i];
+// Adjoints from those tables: dL/dp0 (WANT_P0) and/or the element gradients (WANT_POSE) of regions reg0 ..
+// reg1 - 1.  The workgroup's 16 wavefronts take the element chunks together, each of them CPW columns of 8
+// voxels; lane = element.  The chunk's table rows for the region's nbin centre samples are in LDS,
+// [bin][half][lane] float4, so that a wavefront reads one half at 1 KiB contiguous; they arrive by direct
+// loads to LDS, those of the next chunk while this one's voxels run where two windows fit (nbuf 2).  A pair
+// costs its distance and offset as in the forward, two LDS reads and Horner's rule.  Each lane keeps the sum
+// over its chunks' elements of every voxel it visits in a register, and the 64 lanes meet once, after the
+// last chunk.  With WANT_POSE the sum runs together with its derivative in t, P and P':
+//   dL/dx_e = - sum_v p0 (2 / delta) / d^2 (P' - P / d) (D + o), d and o in units;
+// the terms of a column are FP32, columns add in FP64, the wavefronts' sums of a chunk meet in LDS (in the
+// window just used) in wavefront order, and a workgroup adds its regions into one row of partials in their
+// order, so no result depends on timing.
+// Bounds: VALU.  About 19 instructions per pair for dL/dp0 and 36 per column of 8 pairs, 34 per pair with
+// the element gradients too.  On this chip FP32 adds, multiplies and FMAs of vector registers issue at up to
+// 1.5 a clock and CU, those with a scalar operand, med3, conversions and shifts at 0.9, v_rsq_f32 at 0.5: the
+// sum over a pair comes to 25 cycles, 28 measured (sweep of 128x128x64 voxels and 8192 elements: 7.14 ms
+// before, with 35 instructions per pair, 6.5 ms now; with the element gradients 12.4 -> 10.4 ms).
+constexpr int AM_FIELDS = 11;         // floats of a reference
+constexpr size_t am_off_axis(int nbin, int nbuf) { return (size_t)nbuf * nbin * 2 * WAVE * 4 + AM_REFS * AM_FIELDS * WAVE; }
+constexpr size_t am_lds(int nbin, int nbuf) { return (am_off_axis(nbin, nbuf) + 3 * FM_SIDE * 4) * sizeof(float); }
+
+template <int NM, int CPW, bool WANT_P0, bool WANT_POSE>
+__device__ __forceinline__ void am_regions(const Geo& g, int reg0, int reg1, int nbuf, const float* __restrict__ p0,
+                                           const float* __restrict__ xe, const float4* __restrict__ q,
+                                           float* __restrict__ grad_p0, int accumulate, double* __restrict__ pose_part,
+                                           float* lds) {
+    const int tid = threadIdx.x, lane = tid & (WAVE - 1);
+    const int wv = __builtin_amdgcn_readfirstlane(tid / WAVE);
+    const int nbin = g.nbin, jt = g.jt, kq = g.K + 2 * jt;
+    const int win = nbin * 2 * WAVE;                         // float4 per window
+    float4* qw = reinterpret_cast<float4*>(lds);
+    float* refs = lds + (size_t)nbuf * win * 4;              // [slot][field][lane]
+    float4* axis = reinterpret_cast<float4*>(lds + am_off_axis(nbin, nbuf));
+    const int nchunk = (g.E + WAVE - 1) / WAVE;
+    const int iters = (reg1 - reg0) * nchunk;                // (region, chunk) pairs, one after the other
+
+    auto make_refs = [&](int it) {                           // by one wavefront
+        const int rr = it / nchunk, c = it - rr * nchunk;
+        const MomRef r = mom_make_ref(g, xe + 6 * (size_t)min(c * WAVE + lane, g.E - 1), region_info(g, reg0 + rr));
+        float* f = refs + (it % AM_REFS) * AM_FIELDS * WAVE + lane;
+        const float v[AM_FIELDS] = {r.D[0], r.D[1], r.D[2], r.Dl[0], r.Dl[1], r.Dl[2],
+                                    r.dh,   r.uc0,  r.n0,   r.magic, __int_as_float(r.kc)};
+#pragma unroll
+        for (int i = 0; i < AM_FIELDS; ++i) f[i * WAVE] = v[i];
+    };
+    // whether any window of the chunk meets the record (an element that is not finite counts)
+    auto hits = [&](int it) -> bool {
+        const float* rl = refs + (it % AM_REFS) * AM_FIELDS * WAVE + lane;
+        const int b0 = __float_as_int(rl[10 * WAVE]) - g.jclamp + jt;   // table row of bin 0
+        const bool finite = rl[6 * WAVE] < 1e15f;
+        return __any((it % nchunk) * WAVE + lane < g.E && (!finite || (b0 < kq && b0 + nbin > 0)));
+    };
+    // issue the loads of this wavefront's bins
+    auto fetch = [&](int it) {
+        const float* rl = refs + (it % AM_REFS) * AM_FIELDS * WAVE + lane;
+        const int b0 = __float_as_int(rl[10 * WAVE]) - g.jclamp + jt;
+        const int e = (it % nchunk) * WAVE + lane;
+        const float4* qe = q + (size_t)min(e, g.E - 1) * kq * 2;
+        const float4* zrow = q + (size_t)g.E * kq * 2;       // bins that do not exist read the zero row
+        float4* dst = qw + (nbuf == 2 ? (it & 1) : 0) * win;
+        for (int b = wv; b < nbin; b += AM_WAVES) {
+            const int kk = b0 + b;
+            const float4* src = e < g.E && kk >= 0 && kk < kq ? qe + (size_t)kk * 2 : zrow;
+            typedef const __attribute__((address_space(1))) void* gptr;
+            typedef __attribute__((address_space(3))) void* lptr;
+            __builtin_amdgcn_global_load_lds((gptr)src, (lptr)(dst + b * 2 * WAVE), 16, 0, 0);
+            __builtin_amdgcn_global_load_lds((gptr)(src + 1), (lptr)(dst + (b * 2 + 1) * WAVE), 16, 0, 0);
+        }
+    };
+
+    fm_axis_table(g, tid, axis);
+    if (wv == 0 && iters > 0) make_refs(0);
+    if (wv == 1 && iters > 1) make_refs(1);
     __syncthreads();
-    const int kq = K + 2 * jt;
-    const long long idx = blockIdx.x * (long long)blockDim.x + threadIdx.x;
-    if (idx == (long long)E * kq) {        // the zero row after the last element's rows
-        q[2 * idx] = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
-        q[2 * idx + 1] = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
-    }
-    if (idx >= (long long)E * kq) return;
-    const int e = (int)(idx / kq), kk = (int)(idx % kq);
-    const float* row = r + (size_t)e * K;
-    float acc[NMOM];
+    if (nbuf == 2 && iters > 0 && hits(0)) fetch(0);
+
+    float acc[WANT_P0 ? CPW * FM_RZ : 1];
 #pragma unroll
-    for (int n = 0; n < NMOM; ++n) acc[n] = 0.0f;
-    for (int i = 0; i < nj; ++i) {
-        const int k = kk - 2 * jt + i;
-        const float v = (k >= 0 && k < K) ? row[k] : 0.0f;
+    for (int i = 0; i < (WANT_P0 ? CPW * FM_RZ : 1); ++i) acc[i] = 0.0f;
+    const float rlo = FM_MAGIC - 2.0f * g.jclampf, rhi = FM_MAGIC + 2.0f * g.jclampf;
+    int reg = reg0, c = 0;
+    Region R = region_info(g, reg0);
+
+    for (int it = 0; it < iters; ++it) {
+        const bool hit = hits(it);
+        if (nbuf == 1) {
+            __syncthreads();                                 // the window has been read
+            if (hit) fetch(it);
+        }
+        __builtin_amdgcn_s_waitcnt(0x0f70);                  // vmcnt(0): this wavefront's loads to LDS have landed
+        __syncthreads();                                     // and everyone's; the other window has been read
+        if (wv == (it & (AM_WAVES - 1)) && it + 2 < iters) make_refs(it + 2);
+        if (nbuf == 2 && it + 1 < iters && hits(it + 1)) fetch(it + 1);
+        float4* const used = qw + (nbuf == 2 ? (it & 1) : 0) * win;
+        const int ncol = R.ni * R.nj;
+        double Sx = 0.0, Sy = 0.0, Sz = 0.0;                 // sum over this wavefront's voxels of f (D + o)
+        const float* rl = refs + (it % AM_REFS) * AM_FIELDS * WAVE + lane;
+        if (hit) {
+            const float Dx = rl[0], Dy = rl[WAVE], Dz = rl[2 * WAVE], Dxl = rl[3 * WAVE], Dyl = rl[4 * WAVE];
+            const float Dzl = rl[5 * WAVE];
+            const float dh = rl[6 * WAVE], uc0 = rl[7 * WAVE], magic = rl[9 * WAVE], dh2 = dh * dh;
+            const float* pbase = WANT_POSE ? p0 + (size_t)R.i0 * g.vsx + (size_t)R.j0 * g.vsy + R.k0 : nullptr;
+            const float4 tz = axis[2 * FM_SIDE];
+            float zh, zl, ez[FM_RZ];
+            fm_axis(tz, Dz, Dzl, magic, zh, zl);
+            zl += rl[8 * WAVE];
+            fm_column_n(g, tz, Dz, Dzl, ez);
+            // bin b of the window starts at b << 11; the bits of FM_MAGIC vanish in the shift.  Kept in a vector
+            // register, so that a pair's address is one instruction without scalar operands
+            unsigned off0 = (unsigned)lane * 16u + ((unsigned)g.jclamp << 11) + (nbuf == 2 ? (it & 1) : 0) * win * 16u;
+            asm volatile("" : "+v"(off0));
+            int ix = -1;
+            float xh = 0.0f, xl = 0.0f, ox = 0.0f;
 #pragma unroll
-        for (int n = 0; n < NMOM; ++n) acc[n] = fmaf(v, cs[n * nj + i], acc[n]);
+            for (int cc = 0; cc < CPW; ++cc) {
+                const int col = wv * CPW + cc;
+                if (col >= ncol) continue;
+                const int i = col / R.nj, j = col - i * R.nj;
+                if (i != ix) {                               // a wavefront's columns run along y
+                    ix = i;
+                    const float4 tx = axis[i];
+                    ox = tx.x;
+                    fm_axis(tx, Dx, Dxl, magic, xh, xl);
+                    xh += zh;
+                    xl += zl;
+                }
+                const float4 ty = axis[FM_SIDE + j];
+                float yh, yl;
+                fm_axis(ty, Dy, Dyl, magic, yh, yl);
+                const FmCol cl = fm_col(xh + yh, xl + yl, dh, dh2, uc0);
+                const float dc2 = cl.dc * cl.dc, hdc = 0.5f * cl.dc;
+                float pv[FM_RZ];
+                if (WANT_POSE) {
+                    const float* pc = pbase + (size_t)i * g.vsx + (size_t)j * g.vsy;
+                    if (R.nk == FM_RZ) {
+#pragma unroll
+                        for (int k = 0; k < FM_RZ; ++k) pv[k] = pc[k];
+                    } else {
+#pragma unroll
+                        for (int k = 0; k < FM_RZ; ++k) pv[k] = k < R.nk ? pc[min(k, R.nk - 1)] : 0.0f;
+                    }
+                }
+                float c0 = 0.0f, cz = 0.0f;
+#pragma unroll
+                for (int k = 0; k < FM_RZ; ++k) {
+                    const FmPair p = fm_pair(cl, dc2, hdc, ez[k], rlo, rhi);
+                    const vf4* row = reinterpret_cast<const vf4*>(reinterpret_cast<const char*>(lds) + ((__float_as_uint(p.rm) << 11) + off0));
+                    const vf4 m0 = row[0], m1 = row[WAVE];
+                    const float m[FM_NM_MAX] = {m0[0], m0[1], m0[2], m0[3], m1[0], m1[1], m1[2], m1[3]};
+                    float h = m[NM - 1], dd = 0.0f;
+#pragma unroll
+                    for (int n = NM - 2; n >= 0; --n) {
+                        if (WANT_POSE) dd = n == NM - 2 ? h : fmaf(dd, p.t, h);
+                        h = fmaf(h, p.t, m[n]);
+                    }
+                    if (WANT_P0) acc[cc * FM_RZ + k] = fmaf(h, p.rs, acc[cc * FM_RZ + k]);
+                    if (WANT_POSE) {
+                        const float w = (pv[k] * p.rs) * p.rs;
+                        const float f = w * fmaf(-h, p.rs, dd);
+                        c0 += f;
+                        cz = fmaf(f, (float)k - 0.5f * (float)(FM_RZ - 1), cz);
+                    }
+                }
+                if (WANT_POSE) {
+                    Sx += (double)((Dx + ox) * c0);
+                    Sy += (double)((Dy + ty.x) * c0);
+                    Sz += (double)fmaf(Dz + tz.x, c0, g.hs_u * cz);
+                }
+            }
+        }
+        if (WANT_POSE) {
+            double* part = reinterpret_cast<double*>(used);  // [wave][3][lane]
+            __syncthreads();                                 // the window has been read
+            const double u = -((double)g.unit_h + (double)g.unit_l);
+            part[(wv * 3 + 0) * WAVE + lane] = u * Sx;
+            part[(wv * 3 + 1) * WAVE + lane] = u * Sy;
+            part[(wv * 3 + 2) * WAVE + lane] = u * Sz;
+            __syncthreads();
+            if (tid < 3 * WAVE && c * WAVE + lane < g.E) {   // wavefront w: component w
+                double* row = pose_part + (size_t)(c * WAVE + lane) * 3 + wv;
+                double a = reg == reg0 ? 0.0 : *row;
+                for (int w = 0; w < AM_WAVES; ++w) a += part[(w * 3 + wv) * WAVE + lane];
+                *row = a;
+            }
+        }
+        if (++c < nchunk) continue;
+        // the region's last chunk
+        c = 0;
+        if (WANT_P0) {
+            // sums over the lanes: rows of 16 lanes, then the four rows
+            constexpr int NV = AM_WAVES * CPW * FM_RZ;
+            float* part = reinterpret_cast<float*>(used);    // [row][voxel], columns of FM_RZ
+            const int vsel = (lane & 3) == 1 ? 2 : ((lane & 3) == 2 ? 1 : (lane & 3));
+            __syncthreads();                                 // the window (or the partials in it) has been read
+#pragma unroll
+            for (int i = 0; i < CPW * FM_RZ; i += 4) {
+                const float v = wave_sum4_rows(acc[i], acc[i + 1], acc[i + 2], acc[i + 3], lane);
+                if ((lane & 15) >= 12) part[(lane >> 4) * NV + wv * CPW * FM_RZ + i + vsel] = v;
+                acc[i] = acc[i + 1] = acc[i + 2] = acc[i + 3] = 0.0f;
+            }
+            __syncthreads();
+            float* gbase = grad_p0 + (size_t)R.i0 * g.gsx + (size_t)R.j0 * g.gsy + R.k0;
+            for (int t = tid; t < ncol * FM_RZ; t += AM_WAVES * WAVE) {
+                const int col = t / FM_RZ, k = t % FM_RZ;
+                if (k >= R.nk) continue;
+                const float v = (part[t] + part[NV + t]) + (part[2 * NV + t] + part[3 * NV + t]);
+                float* dst = gbase + (size_t)(col / R.nj) * g.gsx + (size_t)(col % R.nj) * g.gsy + k;
+                *dst = accumulate ? *dst + v : v;
+            }
+        }
+        R = region_info(g, ++reg);
     }
-    q[2 * idx] = make_float4(acc[0], acc[1], acc[2], acc[3]);
-    q[2 * idx + 1] = make_float4(acc[4], acc[5], acc[6], acc[7]);
+    __syncthreads();                                         // the LDS is free for the next call
+}
+
+// One workgroup per CU at most, each with an even share of consecutive regions, so that a region's first
+// loads run behind the one before (back-projection of 99 elements, two chunks, into 161x147x130 voxels:
+// 471 us with a workgroup per region, 415 us so).
+template <int NM, int CPW, bool WANT_P0, bool WANT_POSE>
+__global__ __launch_bounds__(AM_WAVES * WAVE) __attribute__((amdgpu_waves_per_eu(4))) void k_adjoint_series(
+    Geo g, int nbuf, const float* __restrict__ p0, const float* __restrict__ xe, const float4* __restrict__ q,
+    float* __restrict__ grad_p0, int accumulate, double* __restrict__ pose_part) {
+    extern __shared__ float4 lds4[];
+    const int b = region_of_block(blockIdx.x, gridDim.x);
+    const int r0 = (int)((long long)g.nreg * b / gridDim.x), r1 = (int)((long long)g.nreg * (b + 1) / gridDim.x);
+    am_regions<NM, CPW, WANT_P0, WANT_POSE>(g, r0, r1, nbuf, p0, xe, q, grad_p0, accumulate,
+                                            WANT_POSE ? pose_part + (size_t)blockIdx.x * g.E * 3 : nullptr,
+                                            reinterpret_cast<float*>(lds4));
 }
 
 // Reference of a (region, element) pair from the element's position x (hi: x[0..2], lo: x[3..5]),
@@ -1845,31 +2106,11 @@ __device__ __forceinline__ void mom_region(const Geo& g, int reg, const float* _
     __syncthreads();                     // the workgroup's LDS is free for the next region
 }
 
-// dL/dp0 alone in moment form: one workgroup per region.
-template <int PER, int NW>
-__global__ __launch_bounds__(NW * WAVE) __attribute__((amdgpu_waves_per_eu(NW / 2))) void k_adjoint_mom(
-    Geo g, const float* __restrict__ xe, const float4* __restrict__ vtab, const int4* __restrict__ itab,
-    const float4* __restrict__ q, int jt, float* __restrict__ grad_p0, int accumulate) {
-    extern __shared__ float4 qw[];
-    mom_region<PER, NW, true, false>(g, region_of_block(blockIdx.x, g.nreg), nullptr, xe, vtab, itab, q, jt, grad_p0,
-                                     accumulate, nullptr, qw);
-}
-
-template <int PER, int NW, bool WANT_P0>
-__global__ __launch_bounds__(NW * WAVE) __attribute__((amdgpu_waves_per_eu(NW / 2))) void k_adjoint_mom_pose(
-    Geo g, const float* __restrict__ p0, const float* __restrict__ xe, const float4* __restrict__ vtab,
-    const int4* __restrict__ itab, const float4* __restrict__ q, int jt, float* __restrict__ grad_p0,
-    int accumulate, double* __restrict__ pose_part) {
-    extern __shared__ float4 qw[];
-    mom_region<PER, NW, WANT_P0, true>(g, region_of_block(blockIdx.x, g.nreg), p0, xe, vtab, itab, q, jt, grad_p0,
-                                       accumulate, pose_part, qw);
-}
-
-// Sum the per-region element gradients in FP64 and a fixed order: a workgroup takes 16
-// consecutive gradient components; its 16 phases each sum every 16th region (loads of 16
+// Sum the rows of element-gradient partials in FP64 and a fixed order: a workgroup takes 16
+// consecutive gradient components; its 16 phases each sum every 16th row (loads of 16
 // consecutive doubles), then the phases are added in order.
 constexpr int PR_T = 16, PR_P = 16;
-__global__ __launch_bounds__(PR_T * PR_P) void k_pose_reduce(Geo g, const double* __restrict__ part,
+__global__ __launch_bounds__(PR_T * PR_P) void k_pose_reduce(Geo g, int rows, const double* __restrict__ part,
                                                             double* __restrict__ ge, double* __restrict__ grad_elem,
                                                             int accumulate) {
     __shared__ double red[PR_P][PR_T];
@@ -1878,7 +2119,7 @@ __global__ __launch_bounds__(PR_T * PR_P) void k_pose_reduce(Geo g, const double
     const int t = blockIdx.x * PR_T + tl;
     double acc = 0.0;
     if (t < n3)
-        for (int rg = ph; rg < g.nreg; rg += PR_P) acc += part[(size_t)rg * n3 + t];
+        for (int rg = ph; rg < rows; rg += PR_P) acc += part[(size_t)rg * n3 + t];
     red[ph][tl] = acc;
     __syncthreads();
     if (ph == 0 && t < n3) {
@@ -2724,7 +2965,7 @@ struct ra_ctx {
     size_t arena_bytes = 0;
     char* static_scratch = nullptr;         // this device's static array (radiate_forward_static)
     // series of the moment-form forward for the sampling of the last call (its key: profile, window, nu)
-    MomCoef series;
+    MomCoef series, series8;                // with the forward's number of moments, and with 8
     double series_key[4] = {0.0, 0.0, 0.0, 0.0};
     double series_tail[FM_NM_MAX + 1];
     unsigned long long* h_count = nullptr;  // pinned
@@ -2795,19 +3036,21 @@ struct Plan {
     int pair_d;         // forward takes voxels two at a time with this spread (0: one at a time)
     bool pair_ok;       // sampling and spacing allow pairs (regions with an even depth still needed)
     bool rowref;        // the dL/dp0-only adjoint may use the row-referenced form (adj_rowref)
-    bool moment;        // the dL/dp0-only adjoint takes the moment form (k_adjoint_mom) on regions ga
-    bool pose_moment;   // the adjoint with element gradients takes it too (k_adjoint_mom_pose) on regions g
-    double mom_dd, mom_sigma;   // its delta / sigma and sigma
+    bool moment;        // the batched step's adjoints may take their moment form
     bool f64_sums;      // the forward adds its partial rows into FP64 sums (else FP32, straight into s)
     bool fm;            // the forward takes the moment form (k_forward_mom) on regions gm
     Geo gm;
     int fm_nm, fm_slices;   // its moments; workgroups that share a region's element chunks
+    bool am, am_pose;   // dL/dp0 alone / the element gradients take the moment form
+    Geo ga1, ga2;       // on regions ga1 (dL/dp0 alone) and ga2 (element gradients, with dL/dp0 or without)
+    int am_nbuf[2];     // table windows in LDS, of each
+    int part_rows;      // rows of element-gradient partials: a region's each, or in moment form a workgroup's
     size_t lds_fm;
     size_t lds_adj, lds_adj0, lds_fwd;
     // scratch layout (byte offsets)
     size_t off_xe, off_vtab, off_itab, off_vtab_a, off_itab_a, off_vtab_f, off_itab_f, off_part, off_ge, off_s,
         off_partial, off_count, off_nc, off_ncw, off_nct, off_s64,
-        off_xe64, off_qc, off_q, total;
+        off_xe64, off_q, total;
 };
 
 size_t align_up(size_t x) { return (x + 255) & ~(size_t)255; }
@@ -2873,13 +3116,182 @@ size_t set_regions(Geo& g, const ra_grid* grid, double delta, int jt, bool with_
     return lds;
 }
 
-// allow_moment false: the row forms only (the batched serving step, whose kernels and region sizes
-// are those of the row forms).
-void make_plan(const ra_grid* grid, int32_t M, int32_t F, const ra_sampling* samp, Plan& P, int sums_mode = RA_SUMS_AUTO,
-               bool allow_moment = true) {
+// Series of phi((t/2 - j) delta) / delta in t, j = 0..jt: the Chebyshev coefficients from FM_NODES nodes,
+// the first FM_NM_MAX as a polynomial in each of its lengths would be; tail[n] bounds what is cut after
+// n terms, relative to the peak.
+constexpr int FM_NODES = 24;
+
+void mom_series(double dd, int jt, double cheb[FM_NM_MAX][JMAX + 1], double tail[FM_NM_MAX + 1]) {
+    const double pi = 3.14159265358979323846;
+    double cs[FM_NODES][FM_NODES];
+    for (int k = 0; k < FM_NODES; ++k)
+        for (int i = 0; i < FM_NODES; ++i) cs[k][i] = std::cos(pi * k * (i + 0.5) / FM_NODES);
+    const double peak = std::exp(-0.5) / dd;               // of x exp(-(x dd)^2 / 2)
+    for (int n = 0; n <= FM_NM_MAX; ++n) tail[n] = 0.0;
+    for (int j = 0; j <= jt; ++j) {
+        double f[FM_NODES];
+        for (int i = 0; i < FM_NODES; ++i) {
+            const double x = 0.5 * cs[1][i] - j;
+            f[i] = x * std::exp(-0.5 * x * x * dd * dd);
+        }
+        double rest = 0.0;
+        for (int k = FM_NODES - 1; k >= 0; --k) {
+            double c = 0.0;
+            for (int i = 0; i < FM_NODES; ++i) c += f[i] * cs[k][i];
+            c *= (k ? 2.0 : 1.0) / FM_NODES;
+            if (k < FM_NM_MAX) cheb[k][j] = c;
+            rest += std::fabs(c);
+            if (k <= FM_NM_MAX) tail[k] = std::max(tail[k], rest / peak);
+        }
+    }
+}
+
+// The sum of the first nm Chebyshev terms as a polynomial in t.
+void mom_monomials(const double cheb[FM_NM_MAX][JMAX + 1], int nm, int jt, MomCoef& out) {
+    double T[FM_NM_MAX][FM_NM_MAX] = {};                   // T[k][n]: coefficient of t^n in T_k
+    T[0][0] = 1.0;
+    T[1][1] = 1.0;
+    for (int k = 2; k < nm; ++k)
+        for (int n = 0; n < nm; ++n) T[k][n] = (n ? 2.0 * T[k - 1][n - 1] : 0.0) - T[k - 2][n];
+    std::memset(&out, 0, sizeof(out));
+    for (int j = 0; j <= jt; ++j)
+        for (int n = 0; n < nm; ++n) {
+            double v = 0.0;
+            for (int k = n; k < nm; ++k) v += cheb[k][j] * T[k][n];
+            out.d[j * FM_NM_MAX + n] = (float)v;
+        }
+}
+
+// The moment form's series for this sampling, kept in the context until the sampling changes; 0 if the
+// form cannot be taken, else the fewest terms (6, 7 or 8) whose cut series is within FM_TOL: 6 up to
+// delta/sigma 0.41, 7 up to 0.64, 8 up to 1.05 (the row form's own rounding is about 4e-7); coarser sampling
+// keeps the row forms.  The form takes the window's rows whole, as the Gaussian's row forms do for the
+// half-widths of RA_EXACT_LIST; for longer windows those test each term, so it is taken there only from
+// 6 sigma on, where the terms in question are below 1.5e-7 of the peak.
+int series_terms(ra_ctx* ctx, const ra_sampling* samp, bool exact) {
+    const double delta = samp->c / samp->fs, dd = delta / samp->sigma;
+    const int jt = (int)std::floor(samp->trunc * samp->sigma / delta + 0.5);
+    if (samp->kernel != RA_KERNEL_GAUSSIAN || !(exact || samp->trunc >= 6.0) || jt < 1 || jt > JMAX) return 0;
+    const double key[4] = {(double)samp->kernel, dd, (double)jt, samp->nu};
+    const bool known = std::memcmp(key, ctx->series_key, sizeof(key)) == 0;
+    double cheb[FM_NM_MAX][JMAX + 1];
+    if (!known) mom_series(dd, jt, cheb, ctx->series_tail);
+    int nm = 6;
+    while (nm < FM_NM_MAX && ctx->series_tail[nm] > FM_TOL) ++nm;
+    if (!known) {
+        mom_monomials(cheb, nm, jt, ctx->series);
+        mom_monomials(cheb, FM_NM_MAX, jt, ctx->series8);
+        std::memcpy(ctx->series_key, key, sizeof(key));
+    }
+    return ctx->series_tail[nm] <= FM_TOL ? nm : 0;
+}
+
+// Moment forms: lengths in units of delta / 2.
+void set_units(Geo& g, const ra_grid* grid, double delta) {
+    const double unit = 2.0 / delta;
+    g.unit_h = (float)unit;
+    g.unit_l = (float)(unit - (double)g.unit_h);
+    g.hs_u = (float)(grid->spacing * unit);
+    g.hs_l = (float)(grid->spacing * unit - (double)g.hs_u);
+}
+
+// The moment-form forward of a call, with nm terms: on which regions.
+// Those that make the estimated time least.  Per pair and wavefront a CU spends about 34 cycles on the
+// adds; per region and chunk the expansion takes row tiles x quads x NM matrix instructions of 32 cycles
+// on each SIMD (measured: 1.45 times that, with the operand conversions and the atomics), and barriers and
+// clearing about 2500 cycles where one workgroup has the CU, 800 where two share it.  Large grids take
+// 16x16x16; a box of 32^3 voxels seen by one chunk takes small ones, which fill the chip.
+void plan_forward_mom(const ra_grid* grid, const ra_sampling* samp, int nm, Plan& P) {
+    P.fm = false;
+    if (!nm) return;
+    const double delta = samp->c / samp->fs;
+    const int jt = (int)std::floor(samp->trunc * samp->sigma / delta + 0.5);
+    static const int cand[][3] = {{16, 16, 16}, {16, 16, 8}, {8, 16, 8}, {8, 8, 16}, {8, 8, 8}, {4, 8, 8},
+                                  {4, 4, 8},    {2, 4, 8},   {2, 2, 8},  {1, 2, 8},  {1, 1, 8}};
+    const int nchunk = (P.g.E + WAVE - 1) / WAVE;
+    double best = 0.0;
+    for (const auto& cd : cand) {
+        Geo g = P.g;
+        // as many regions along x and y as the candidate's size gives, of even size
+        g.nrx = (g.nx + cd[0] - 1) / cd[0]; g.nry = (g.ny + cd[1] - 1) / cd[1]; g.nrz = (g.nz + cd[2] - 1) / cd[2];
+        g.rx = (g.nx + g.nrx - 1) / g.nrx; g.ry = (g.ny + g.nry - 1) / g.nry; g.rz = std::min(cd[2], g.nz);
+        const double rad = 0.5 * grid->spacing * std::sqrt((double)(g.rx - 1) * (g.rx - 1) + (double)(g.ry - 1) * (g.ry - 1) +
+                                                           (double)(g.rz - 1) * (g.rz - 1));
+        if (rad / delta > 1e4) continue;                   // never fits; keeps the bin count an int
+        g.jclamp = (int)std::ceil(rad / delta * (1.0 + 1e-6)) + 1;
+        g.jclampf = (float)g.jclamp;
+        g.jt = jt;
+        g.nbin = 2 * g.jclamp + 1;
+        const size_t lds = fm_lds(nm, g.nbin, jt);
+        if (lds > 160 * 1024) continue;
+        g.nrx = (g.nx + g.rx - 1) / g.rx; g.nry = (g.ny + g.ry - 1) / g.ry;
+        g.nreg = g.nrx * g.nry * g.nrz;
+        const int per_cu = lds <= LDS_FM_BUDGET ? 2 : 1;
+        const int slices = std::min(nchunk, std::max(1, (2048 + g.nreg - 1) / g.nreg));
+        const double expand = ((g.nbin + 2 * jt + 15) / 16) * ((2 * jt + 19) / 4) * nm * 32.0 * 1.45;
+        const int zl = g.nz - (g.nrz - 1) * g.rz;          // columns run in steps of FM_RZ voxels
+        const double zpad = (g.nrz - 1.0) * ((g.rz + FM_RZ - 1) / FM_RZ * FM_RZ) + (zl + FM_RZ - 1) / FM_RZ * FM_RZ;
+        const double pairs = (double)g.nx * g.ny * zpad / g.nreg * 34.0;
+        const double each = pairs + expand + (per_cu == 2 ? 800.0 : 2500.0);   // CU cycles per region and chunk
+        const double wgs = (double)g.nreg * slices, per_wg = (double)((nchunk + slices - 1) / slices);
+        // the last round of workgroups; a CU with one where two fit runs it about 1.6 times as fast
+        const double full = std::floor(wgs / (256.0 * per_cu)), left = wgs - full * 256.0 * per_cu;
+        const double last = left == 0.0 ? 0.0 : (left <= 256.0 && per_cu == 2 ? 0.62 : 1.0);
+        const double cost = (full + last) * per_cu * per_wg * each;
+        if (P.fm && cost >= best) continue;
+        best = cost;
+        P.fm = true;
+        P.gm = g;
+        P.fm_slices = slices;
+        P.lds_fm = lds;
+    }
+    if (P.fm) set_units(P.gm, grid, delta);
+}
+
+// The moment-form adjoint's regions: columns of 8 voxels, up to 64 of them, those that make the estimated
+// time least (`pair`: CU cycles per pair and wavefront, 30 for dL/dp0, 44 with the element gradients).  Two
+// table windows in LDS let a chunk's loads run behind the previous chunk's voxels; where the spacing is so
+// coarse that only one fits, the loads (about 41 cycles per bin, and their latency) add to the time.
+bool plan_adjoint_mom(const ra_grid* grid, const ra_sampling* samp, const Geo& base, double pair, Geo& out, int& nbuf) {
+    static const int cand[][2] = {{8, 8}, {4, 8}, {4, 4}, {2, 4}, {2, 2}, {1, 2}, {1, 1}};
+    const double delta = samp->c / samp->fs;
+    const int nchunk = (base.E + WAVE - 1) / WAVE;
+    double best = 0.0;
+    bool found = false;
+    for (const auto& cd : cand) {
+        Geo g = base;
+        g.nrx = (g.nx + cd[0] - 1) / cd[0]; g.nry = (g.ny + cd[1] - 1) / cd[1]; g.nrz = (g.nz + FM_RZ - 1) / FM_RZ;
+        g.rx = (g.nx + g.nrx - 1) / g.nrx; g.ry = (g.ny + g.nry - 1) / g.nry; g.rz = std::min(FM_RZ, g.nz);
+        g.nrx = (g.nx + g.rx - 1) / g.rx; g.nry = (g.ny + g.ry - 1) / g.ry;
+        g.nreg = g.nrx * g.nry * g.nrz;
+        const double rad = 0.5 * grid->spacing * std::sqrt((double)(g.rx - 1) * (g.rx - 1) + (double)(g.ry - 1) * (g.ry - 1) +
+                                                           (double)(g.rz - 1) * (g.rz - 1));
+        if (rad / delta > 1e4) continue;
+        // at least 13 bins: a window also holds the wavefronts' partial element gradients
+        g.jclamp = std::max(6, (int)std::ceil(rad / delta * (1.0 + 1e-6)) + 1);
+        g.jclampf = (float)g.jclamp;
+        g.jt = (int)std::floor(samp->trunc * samp->sigma / delta + 0.5);
+        g.nbin = 2 * g.jclamp + 1;
+        const int nb = am_lds(g.nbin, 2) <= 160 * 1024 ? 2 : 1;
+        if (am_lds(g.nbin, nb) > 160 * 1024) continue;
+        const int cols = (g.rx * g.ry + AM_WAVES - 1) / AM_WAVES * AM_WAVES;     // a round of wavefronts is the least
+        const double each = cols * FM_RZ * pair + 900.0 + (nb == 1 ? 1500.0 + 41.0 * g.nbin : 0.0);
+        const double cost = std::ceil(g.nreg / (double)NCU) * (nchunk * each + 3000.0) + 5000.0;
+        if (found && cost >= best) continue;
+        best = cost;
+        found = true;
+        out = g;
+        nbuf = nb;
+    }
+    if (found) set_units(out, grid, delta);
+    return found;
+}
+
+// The context keeps the moment forms' series; without one (the batched step) the plan has the row forms only.
+void make_plan(ra_ctx* ctx, const ra_grid* grid, int32_t M, int32_t F, const ra_sampling* samp, Plan& P,
+               int sums_mode = RA_SUMS_AUTO) {
     Geo& g = P.g;
     std::memset(&g, 0, sizeof(g));
-    P.fm = false;
     g.nx = grid->nx; g.ny = grid->ny; g.nz = grid->nz;
     g.vsx = (long long)grid->ny * grid->nz;
     g.vsy = grid->nz;
@@ -2957,39 +3369,14 @@ void make_plan(const ra_grid* grid, int32_t M, int32_t F, const ra_sampling* sam
         const double km = P.ga.kmargin + 1.0, ds = delta / sigma;
         P.rowref = P.exact && g.ktype == RA_KERNEL_GAUSSIAN && P.ga.kmargin <= RS_MAX && km * km * ds * ds / 2.0 <= 75.0;
     }
-    // Moment-form dL/dp0 adjoint (k_adjoint_mom) where its truncation bound holds; it replaces the
-    // row-referenced form and takes regions sized for its shared table window.
+    // moment form of the batched step's adjoints where its truncation bound holds
     {
         double fact = 1.0;
         for (int n = 2; n <= NMOM; ++n) fact *= n;
         const double bound = 1.791 * std::pow(0.5 * delta / sigma, NMOM) * std::sqrt((NMOM + 1) / fact);
-        P.moment = allow_moment && P.exact && g.ktype == RA_KERNEL_GAUSSIAN && bound <= MOM_TOL;
-        P.mom_dd = delta / sigma;
-        P.mom_sigma = sigma;
+        P.moment = P.exact && g.ktype == RA_KERNEL_GAUSSIAN && bound <= MOM_TOL;
         g.mom_dd = delta / sigma;
         g.mom_sigma = sigma;
-        if (P.moment) {
-            Geo gm = P.ga;
-            const size_t lds = set_regions(gm, grid, delta, P.jt, true, 0, LDS_MOM_BUDGET, 1);
-            P.moment = lds <= LDS_MOM_BUDGET && 2 * gm.jclamp + 1 <= MOM_WAVES * MOM_PER;
-            if (P.moment) {
-                P.ga = gm;
-                P.lds_adj0 = lds;
-                P.rowref = false;
-            }
-        }
-        // the adjoint with element gradients in moment form, on regions sized for its LDS (the
-        // per-region partials then follow these regions)
-        P.pose_moment = false;
-        if (P.moment) {
-            Geo gp = g;
-            const size_t lds = set_regions(gp, grid, delta, P.jt, true, 0, LDS_ADJ_BUDGET, 2);
-            if (lds <= LDS_ADJ_BUDGET && 2 * gp.jclamp + 1 <= MOM_WAVES * MOM_PER) {
-                g = gp;
-                P.lds_adj = lds;
-                P.pose_moment = true;
-            }
-        }
     }
     P.lds_fwd = set_regions(P.gf, grid, delta, P.jt, false, P.pair_d, LDS_FWD_BUDGET);
     // pairs are (k, k+1) of the visiting order, so the forward region needs an even rz
@@ -3014,6 +3401,13 @@ void make_plan(const ra_grid* grid, int32_t M, int32_t F, const ra_sampling* sam
     // meet in one sample; past FWD_F32_MAX_REGIONS forward regions the rows go into FP64 sums.
     P.f64_sums = sums_mode == RA_SUMS_F64 || (sums_mode == RA_SUMS_AUTO && P.gf.nreg > FWD_F32_MAX_REGIONS);
 
+    const int nm = ctx ? series_terms(ctx, samp, P.exact) : 0;
+    plan_forward_mom(grid, samp, nm, P);
+    P.fm_nm = nm;
+    P.am = nm && plan_adjoint_mom(grid, samp, g, 30.0, P.ga1, P.am_nbuf[0]);
+    P.am_pose = nm && ctx->series_tail[FM_NM_MAX] <= AM_TOL && plan_adjoint_mom(grid, samp, g, 43.0, P.ga2, P.am_nbuf[1]);
+    P.part_rows = P.am_pose ? std::min(P.ga2.nreg, NCU) : g.nreg;
+
     size_t o = 0;
     P.off_xe = o; o = align_up(o + (size_t)g.E * 6 * sizeof(float));
     P.off_vtab = o; o = align_up(o + (size_t)g.nvpad * sizeof(float4));
@@ -3022,7 +3416,7 @@ void make_plan(const ra_grid* grid, int32_t M, int32_t F, const ra_sampling* sam
     P.off_itab_a = o; o = align_up(o + (size_t)P.ga.nvpad * sizeof(int4));
     P.off_vtab_f = o; o = align_up(o + (size_t)P.gf.nvpad * sizeof(float4));
     P.off_itab_f = o; o = align_up(o + (size_t)P.gf.nvpad * sizeof(int4));
-    P.off_part = o; o = align_up(o + (size_t)g.nreg * g.E * 3 * sizeof(double));
+    P.off_part = o; o = align_up(o + (size_t)P.part_rows * g.E * 3 * sizeof(double));
     P.off_ge = o; o = align_up(o + (size_t)g.E * 3 * sizeof(double));
     P.off_s = o; o = align_up(o + (size_t)g.E * g.K * sizeof(float));
     P.off_partial = o; o = align_up(o + RESID_BLOCKS * sizeof(float));
@@ -3032,131 +3426,9 @@ void make_plan(const ra_grid* grid, int32_t M, int32_t F, const ra_sampling* sam
     P.off_nct = o; o = align_up(o + sizeof(double));
     P.off_s64 = o; o = align_up(o + (P.f64_sums ? (size_t)g.E * g.K * sizeof(double) : 0));
     P.off_xe64 = o; o = align_up(o + (size_t)g.E * 3 * sizeof(double));
-    P.off_qc = o; o = align_up(o + (P.moment ? (size_t)NMOM * (2 * P.jt + 1) * sizeof(float) : 0));
-    P.off_q = o; o = align_up(o + (P.moment ? ((size_t)g.E * (g.K + 2 * P.jt) + 1) * NMOM * sizeof(float) : 0));
+    const int jts = (int)std::floor(tsig / delta + 0.5);
+    P.off_q = o; o = align_up(o + (P.am || P.am_pose ? ((size_t)g.E * (g.K + 2 * jts) + 1) * FM_NM_MAX * sizeof(float) : 0));
     P.total = o;
-}
-
-// Series of phi((t/2 - j) delta) / delta in t, j = 0..jt: the Chebyshev coefficients from FM_NODES nodes,
-// the first FM_NM_MAX as a polynomial in each of its lengths would be; tail[n] bounds what is cut after
-// n terms, relative to the peak.
-constexpr int FM_NODES = 24;
-
-void mom_series(double dd, int jt, double cheb[FM_NM_MAX][JMAX + 1], double tail[FM_NM_MAX + 1]) {
-    const double pi = 3.14159265358979323846;
-    double cs[FM_NODES][FM_NODES];
-    for (int k = 0; k < FM_NODES; ++k)
-        for (int i = 0; i < FM_NODES; ++i) cs[k][i] = std::cos(pi * k * (i + 0.5) / FM_NODES);
-    const double peak = std::exp(-0.5) / dd;               // of x exp(-(x dd)^2 / 2)
-    for (int n = 0; n <= FM_NM_MAX; ++n) tail[n] = 0.0;
-    for (int j = 0; j <= jt; ++j) {
-        double f[FM_NODES];
-        for (int i = 0; i < FM_NODES; ++i) {
-            const double x = 0.5 * cs[1][i] - j;
-            f[i] = x * std::exp(-0.5 * x * x * dd * dd);
-        }
-        double rest = 0.0;
-        for (int k = FM_NODES - 1; k >= 0; --k) {
-            double c = 0.0;
-            for (int i = 0; i < FM_NODES; ++i) c += f[i] * cs[k][i];
-            c *= (k ? 2.0 : 1.0) / FM_NODES;
-            if (k < FM_NM_MAX) cheb[k][j] = c;
-            rest += std::fabs(c);
-            if (k <= FM_NM_MAX) tail[k] = std::max(tail[k], rest / peak);
-        }
-    }
-}
-
-// The sum of the first nm Chebyshev terms as a polynomial in t.
-void mom_monomials(const double cheb[FM_NM_MAX][JMAX + 1], int nm, int jt, MomCoef& out) {
-    double T[FM_NM_MAX][FM_NM_MAX] = {};                   // T[k][n]: coefficient of t^n in T_k
-    T[0][0] = 1.0;
-    T[1][1] = 1.0;
-    for (int k = 2; k < nm; ++k)
-        for (int n = 0; n < nm; ++n) T[k][n] = (n ? 2.0 * T[k - 1][n - 1] : 0.0) - T[k - 2][n];
-    std::memset(&out, 0, sizeof(out));
-    for (int j = 0; j <= jt; ++j)
-        for (int n = 0; n < nm; ++n) {
-            double v = 0.0;
-            for (int k = n; k < nm; ++k) v += cheb[k][j] * T[k][n];
-            out.d[n * (JMAX + 1) + j] = (float)v;
-        }
-}
-
-// The moment-form forward of a call: whether it is taken, with how many moments, on which regions.
-//   Window   the form takes the window's rows whole, as the Gaussian's other kernels do for the half-widths
-//            of RA_EXACT_LIST; for longer windows those test each term, so it is taken there only from
-//            6 sigma on, where the terms in question are below 1.5e-7 of the peak.
-//   Moments  the fewest (6, 7 or 8) whose cut series is within FM_TOL: 6 up to delta/sigma 0.41, 7 up to 0.64, 8 up
-//            to 1.05 (the row form's own rounding is about 4e-7); coarser sampling keeps the row form.
-//   Regions  those that make the estimated time least.  Per pair and wavefront a CU spends about 34 cycles on
-//            the adds; per region and chunk the expansion takes row tiles x quads x NM matrix instructions of 32
-//            cycles on each SIMD (measured: 1.45 times that, with the operand conversions and the atomics),
-//            and barriers and clearing about 2500 cycles where one workgroup has the CU, 800 where two share it.
-//            Large grids take 16x16x16; a box of 32^3 voxels seen by one chunk takes small ones, which fill the chip.
-void plan_forward_mom(ra_ctx* ctx, const ra_grid* grid, const ra_sampling* samp, Plan& P) {
-    P.fm = false;
-    const double delta = samp->c / samp->fs, dd = delta / samp->sigma;
-    const int jt = (int)std::floor(samp->trunc * samp->sigma / delta + 0.5);
-    if (samp->kernel != RA_KERNEL_GAUSSIAN || !(P.exact || samp->trunc >= 6.0) || jt < 1 || jt > JMAX) return;
-    const double key[4] = {(double)samp->kernel, dd, (double)jt, samp->nu};
-    if (std::memcmp(key, ctx->series_key, sizeof(key)) != 0) {
-        double cheb[FM_NM_MAX][JMAX + 1];
-        mom_series(dd, jt, cheb, ctx->series_tail);
-        int nm = 6;
-        while (nm < FM_NM_MAX && ctx->series_tail[nm] > FM_TOL) ++nm;
-        mom_monomials(cheb, nm, jt, ctx->series);
-        std::memcpy(ctx->series_key, key, sizeof(key));
-    }
-    int nm = 6;
-    while (nm < FM_NM_MAX && ctx->series_tail[nm] > FM_TOL) ++nm;
-    if (ctx->series_tail[nm] > FM_TOL) return;
-    static const int cand[][3] = {{16, 16, 16}, {16, 16, 8}, {8, 16, 8}, {8, 8, 16}, {8, 8, 8}, {4, 8, 8},
-                                  {4, 4, 8},    {2, 4, 8},   {2, 2, 8},  {1, 2, 8},  {1, 1, 8}};
-    const int nchunk = (P.g.E + WAVE - 1) / WAVE;
-    double best = 0.0;
-    for (const auto& cd : cand) {
-        Geo g = P.g;
-        // as many regions along x and y as the candidate's size gives, of even size
-        g.nrx = (g.nx + cd[0] - 1) / cd[0]; g.nry = (g.ny + cd[1] - 1) / cd[1]; g.nrz = (g.nz + cd[2] - 1) / cd[2];
-        g.rx = (g.nx + g.nrx - 1) / g.nrx; g.ry = (g.ny + g.nry - 1) / g.nry; g.rz = std::min(cd[2], g.nz);
-        const double rad = 0.5 * grid->spacing * std::sqrt((double)(g.rx - 1) * (g.rx - 1) + (double)(g.ry - 1) * (g.ry - 1) +
-                                                           (double)(g.rz - 1) * (g.rz - 1));
-        if (rad / delta > 1e4) continue;                   // never fits; keeps the bin count an int
-        g.jclamp = (int)std::ceil(rad / delta * (1.0 + 1e-6)) + 1;
-        g.jclampf = (float)g.jclamp;
-        g.jt = jt;
-        g.nbin = 2 * g.jclamp + 1;
-        const size_t lds = fm_lds(nm, g.nbin, jt);
-        if (lds > 160 * 1024) continue;
-        g.nrx = (g.nx + g.rx - 1) / g.rx; g.nry = (g.ny + g.ry - 1) / g.ry;
-        g.nreg = g.nrx * g.nry * g.nrz;
-        const int per_cu = lds <= LDS_FM_BUDGET ? 2 : 1;
-        const int slices = std::min(nchunk, std::max(1, (2048 + g.nreg - 1) / g.nreg));
-        const double expand = ((g.nbin + 2 * jt + 15) / 16) * ((2 * jt + 19) / 4) * nm * 32.0 * 1.45;
-        const int zl = g.nz - (g.nrz - 1) * g.rz;          // columns run in steps of FM_RZ voxels
-        const double zpad = (g.nrz - 1.0) * ((g.rz + FM_RZ - 1) / FM_RZ * FM_RZ) + (zl + FM_RZ - 1) / FM_RZ * FM_RZ;
-        const double pairs = (double)g.nx * g.ny * zpad / g.nreg * 34.0;
-        const double each = pairs + expand + (per_cu == 2 ? 800.0 : 2500.0);   // CU cycles per region and chunk
-        const double wgs = (double)g.nreg * slices, per_wg = (double)((nchunk + slices - 1) / slices);
-        // the last round of workgroups; a CU with one where two fit runs it about 1.6 times as fast
-        const double full = std::floor(wgs / (256.0 * per_cu)), left = wgs - full * 256.0 * per_cu;
-        const double last = left == 0.0 ? 0.0 : (left <= 256.0 && per_cu == 2 ? 0.62 : 1.0);
-        const double cost = (full + last) * per_cu * per_wg * each;
-        if (P.fm && cost >= best) continue;
-        best = cost;
-        P.fm = true;
-        P.gm = g;
-        P.fm_nm = nm;
-        P.fm_slices = slices;
-        P.lds_fm = lds;
-    }
-    if (!P.fm) return;
-    const double unit = 2.0 / delta;
-    P.gm.unit_h = (float)unit;
-    P.gm.unit_l = (float)(unit - (double)P.gm.unit_h);
-    P.gm.hs_u = (float)(grid->spacing * unit);
-    P.gm.hs_l = (float)(grid->spacing * unit - (double)P.gm.hs_u);
 }
 
 int ensure_scratch(ra_ctx* ctx, size_t bytes, hipStream_t stream) {
@@ -3209,9 +3481,10 @@ int prologue(ra_ctx* ctx, char* base, const ra_grid* grid, const Plan& P, const 
                             (float)(grid->origin[2] + (g.nz - 1) * grid->spacing));
     hipLaunchKernelGGL(k_elements, dim3((g.E + 255) / 256), dim3(256), 0, stream, g, elem, poses,
                        at<float>(base, P.off_xe), ctx->d_status, lo, hi);
-    if (!forward_only) {
+    if (!forward_only && !P.am_pose)
         hipLaunchKernelGGL(k_voxel_table, dim3((g.nvpad + 255) / 256), dim3(256), 0, stream, g,
                            at<float4>(base, P.off_vtab), at<int4>(base, P.off_itab));
+    if (!forward_only && !P.am) {
         hipLaunchKernelGGL(k_voxel_table, dim3((P.ga.nvpad + 255) / 256), dim3(256), 0, stream, P.ga,
                            at<float4>(base, P.off_vtab_a), at<int4>(base, P.off_itab_a));
     }
@@ -3365,48 +3638,45 @@ int launch_adjoint_j(ra_ctx* ctx, const Plan& P, const float* p0, const float* r
     return launch_adjoint_t<JT, EXACT, false, true, KT>(ctx, P, p0, r, gp0, acc, stream);
 }
 
-// dL/dp0 alone in moment form: coefficient and moment tables, then one workgroup per region.
-int launch_adjoint_mom(ra_ctx* ctx, const Plan& P, const float* r, float* gp0, int acc, hipStream_t stream) {
-    const Geo& g = P.ga;
-    const int jt = P.jt;
-    hipLaunchKernelGGL(k_moment_coefs, dim3(1), dim3(2 * jt + 1), 0, stream, jt, P.mom_dd, P.mom_sigma,
-                       at<float>(ctx, P.off_qc));
-    const long long rows = (long long)g.E * (g.K + 2 * jt) + 1;      // and the zero row
-    hipLaunchKernelGGL(k_moment_table, dim3((unsigned)((rows + 255) / 256)), dim3(256), 0, stream, g.E, g.K, jt, r,
-                       at<float>(ctx, P.off_qc), at<float4>(ctx, P.off_q));
-    auto kern = k_adjoint_mom<MOM_PER, MOM_WAVES>;     // the host checked 2 jclamp + 1 <= MOM_WAVES * MOM_PER
+template <int NM, int CPW, bool P0, bool POSE>
+int launch_adjoint_series_t(ra_ctx* ctx, const Plan& P, const float* p0, float* gp0, int acc, hipStream_t stream) {
+    const Geo& g = POSE ? P.ga2 : P.ga1;
+    const int nbuf = P.am_nbuf[POSE ? 1 : 0];
+    auto kern = k_adjoint_series<NM, CPW, P0, POSE>;
     RA_HIP(ctx, allow_full_lds(kern));
-    hipLaunchKernelGGL(kern, dim3(g.nreg), dim3(MOM_WAVES * WAVE), P.lds_adj0, stream, g, at<float>(ctx, P.off_xe),
-                       at<float4>(ctx, P.off_vtab_a), at<int4>(ctx, P.off_itab_a), at<float4>(ctx, P.off_q), jt, gp0,
-                       acc);
+    hipLaunchKernelGGL(kern, dim3(std::min(g.nreg, NCU)), dim3(AM_WAVES * WAVE), am_lds(g.nbin, nbuf), stream, g, nbuf, p0,
+                       at<float>(ctx, P.off_xe), at<float4>(ctx, P.off_q), gp0, acc, at<double>(ctx, P.off_part));
     RA_HIP(ctx, hipGetLastError());
     return RA_OK;
 }
 
-// The adjoint with element gradients (and dL/dp0 if gp0) in moment form, on the regions of P.g.
-int launch_adjoint_mom_pose(ra_ctx* ctx, const Plan& P, const float* p0, const float* r, float* gp0, int acc,
-                            hipStream_t stream) {
-    const Geo& g = P.g;
-    const int jt = P.jt;
-    hipLaunchKernelGGL(k_moment_coefs, dim3(1), dim3(2 * jt + 1), 0, stream, jt, P.mom_dd, P.mom_sigma,
-                       at<float>(ctx, P.off_qc));
-    const long long rows = (long long)g.E * (g.K + 2 * jt) + 1;      // and the zero row
-    hipLaunchKernelGGL(k_moment_table, dim3((unsigned)((rows + 255) / 256)), dim3(256), 0, stream, g.E, g.K, jt, r,
-                       at<float>(ctx, P.off_qc), at<float4>(ctx, P.off_q));
-    auto kern = gp0 ? k_adjoint_mom_pose<MOM_PER, MOM_WAVES, true> : k_adjoint_mom_pose<MOM_PER, MOM_WAVES, false>;
-    RA_HIP(ctx, allow_full_lds(kern));
-    hipLaunchKernelGGL(kern, dim3(g.nreg), dim3(MOM_WAVES * WAVE), P.lds_adj, stream, g, p0, at<float>(ctx, P.off_xe),
-                       at<float4>(ctx, P.off_vtab), at<int4>(ctx, P.off_itab), at<float4>(ctx, P.off_q), jt, gp0, acc,
-                       at<double>(ctx, P.off_part));
-    RA_HIP(ctx, hipGetLastError());
-    return RA_OK;
+template <int NM, bool P0, bool POSE>
+int launch_adjoint_series_c(ra_ctx* ctx, const Plan& P, const float* p0, float* gp0, int acc, hipStream_t stream) {
+    const Geo& g = POSE ? P.ga2 : P.ga1;
+    const int cpw = (g.rx * g.ry + AM_WAVES - 1) / AM_WAVES;
+    if (cpw <= 1) return launch_adjoint_series_t<NM, 1, P0, POSE>(ctx, P, p0, gp0, acc, stream);
+    if (cpw <= 2) return launch_adjoint_series_t<NM, 2, P0, POSE>(ctx, P, p0, gp0, acc, stream);
+    return launch_adjoint_series_t<NM, 4, P0, POSE>(ctx, P, p0, gp0, acc, stream);
+}
+
+// The adjoints in moment form: the table of dL/ds, then one workgroup per region.
+int launch_adjoint_series(ra_ctx* ctx, const Plan& P, const float* p0, const float* r, float* gp0, bool pose, int acc,
+                          hipStream_t stream) {
+    const int K = P.g.K, jt = pose ? P.ga2.jt : P.ga1.jt, per = (K + 2 * jt + MT_ROWS - 1) / MT_ROWS;
+    hipLaunchKernelGGL(k_moment_series, dim3((unsigned)P.g.E * per), dim3(MT_ROWS), 0, stream, P.g.E, K, jt,
+                       pose ? ctx->series8 : ctx->series, r, at<float4>(ctx, P.off_q));
+    if (pose)
+        return gp0 ? launch_adjoint_series_c<8, true, true>(ctx, P, p0, gp0, acc, stream)
+                   : launch_adjoint_series_c<8, false, true>(ctx, P, p0, gp0, acc, stream);
+    if (P.fm_nm == 6) return launch_adjoint_series_c<6, true, false>(ctx, P, p0, gp0, acc, stream);
+    if (P.fm_nm == 7) return launch_adjoint_series_c<7, true, false>(ctx, P, p0, gp0, acc, stream);
+    return launch_adjoint_series_c<8, true, false>(ctx, P, p0, gp0, acc, stream);
 }
 
 int launch_adjoint(ra_ctx* ctx, const Plan& P, const float* p0, const float* r, float* gp0, bool pose, int acc,
                    hipStream_t stream) {
     if (!generic_bound_ok(P)) return fail(ctx, RA_ENOTSUP, "window half-width not supported");
-    if (P.moment && gp0 && !pose) return launch_adjoint_mom(ctx, P, r, gp0, acc, stream);
-    if (P.pose_moment && pose) return launch_adjoint_mom_pose(ctx, P, p0, r, gp0, acc, stream);
+    if (pose ? P.am_pose : P.am) return launch_adjoint_series(ctx, P, p0, r, gp0, pose, acc, stream);
     switch (P.g.ktype) {
         case RA_KERNEL_EXPONENTIAL:
 #define RA_CASE(n) \
@@ -3441,7 +3711,7 @@ int adjoint_body(ra_ctx* ctx, const Plan& P, const float* p0, const double* elem
     if (rc != RA_OK) return rc;
     if (pose) {
         const Geo& g = P.g;
-        hipLaunchKernelGGL(k_pose_reduce, dim3((3 * g.E + PR_T - 1) / PR_T), dim3(PR_T * PR_P), 0, stream, g,
+        hipLaunchKernelGGL(k_pose_reduce, dim3((3 * g.E + PR_T - 1) / PR_T), dim3(PR_T * PR_P), 0, stream, g, P.part_rows,
                            at<double>(ctx, P.off_part), at<double>(ctx, P.off_ge), grad_elem, acc);
         if (grad_pose)
             hipLaunchKernelGGL(k_pose_frame, dim3(g.F), dim3(256), 0, stream, g, at<double>(ctx, P.off_ge), elem,
@@ -3515,7 +3785,7 @@ size_t ra_scratch_bytes(const ra_grid* grid, int32_t M, int32_t F, const ra_samp
     ra_ctx tmp;
     if (validate(&tmp, grid, M, F, samp) != RA_OK) return 0;
     Plan P;
-    make_plan(grid, M, F, samp, P, RA_SUMS_F64);      // the largest of the forward's sum modes
+    make_plan(&tmp, grid, M, F, samp, P, RA_SUMS_F64);      // the largest of the forward's sum modes
     return P.total;
 }
 
@@ -3537,8 +3807,7 @@ int radiate_forward(ra_ctx* ctx, const ra_grid* grid, const float* p0, int32_t M
     hipStream_t st = (hipStream_t)stream;
     RA_HIP(ctx, hipSetDevice(ctx->device));
     Plan P;
-    make_plan(grid, M, F, samp, P, ctx->sums_mode);
-    plan_forward_mom(ctx, grid, samp, P);
+    make_plan(ctx, grid, M, F, samp, P, ctx->sums_mode);
     if ((rc = ensure_scratch(ctx, P.total, st)) != RA_OK) return rc;
     if ((rc = prologue(ctx, ctx->arena, grid, P, elem, poses, st, true)) != RA_OK) return rc;
     return launch_forward(ctx, ctx->arena, P, p0, s, st);
@@ -3554,8 +3823,7 @@ int radiate_forward_static(ra_ctx* ctx, const ra_grid* grid, const float* p0, in
     hipStream_t st = (hipStream_t)stream;
     RA_HIP(ctx, hipSetDevice(ctx->device));
     Plan P;
-    make_plan(grid, M, F, samp, P, ctx->sums_mode);
-    plan_forward_mom(ctx, grid, samp, P);
+    make_plan(ctx, grid, M, F, samp, P, ctx->sums_mode);
     const size_t need = forward_layout(P);
     if (need > STATIC_SCRATCH_BYTES)
         return fail(ctx, RA_ENOMEM, "radiate_forward_static needs " + std::to_string(need) +
@@ -3577,7 +3845,7 @@ int radiate_adjoint(ra_ctx* ctx, const ra_grid* grid, const float* p0, int32_t M
     hipStream_t st = (hipStream_t)stream;
     RA_HIP(ctx, hipSetDevice(ctx->device));
     Plan P;
-    make_plan(grid, M, F, samp, P, ctx->sums_mode);
+    make_plan(ctx, grid, M, F, samp, P, ctx->sums_mode);
     if ((rc = ensure_scratch(ctx, P.total, st)) != RA_OK) return rc;
     if ((rc = prologue(ctx, ctx->arena, grid, P, elem, poses, st)) != RA_OK) return rc;
     return adjoint_body(ctx, P, p0, elem, r, grad_p0, grad_pose, grad_elem, flags, st);
@@ -3598,8 +3866,7 @@ int loss_and_grad(ra_ctx* ctx, const ra_grid* grid, const float* p0, int32_t M, 
     hipStream_t st = (hipStream_t)stream;
     RA_HIP(ctx, hipSetDevice(ctx->device));
     Plan P;
-    make_plan(grid, M, F, samp, P, ctx->sums_mode);
-    plan_forward_mom(ctx, grid, samp, P);
+    make_plan(ctx, grid, M, F, samp, P, ctx->sums_mode);
     if ((rc = ensure_scratch(ctx, P.total, st)) != RA_OK) return rc;
     if ((rc = prologue(ctx, ctx->arena, grid, P, elem, poses, st)) != RA_OK) return rc;
     float* s = at<float>(ctx, P.off_s);
@@ -3642,8 +3909,7 @@ int nc_loss_and_grad(ra_ctx* ctx, const ra_grid* grid, const float* p0, int32_t 
     hipStream_t st = (hipStream_t)stream;
     RA_HIP(ctx, hipSetDevice(ctx->device));
     Plan P;
-    make_plan(grid, M, F, samp, P, ctx->sums_mode);
-    plan_forward_mom(ctx, grid, samp, P);
+    make_plan(ctx, grid, M, F, samp, P, ctx->sums_mode);
     if ((rc = ensure_scratch(ctx, P.total, st)) != RA_OK) return rc;
     if ((rc = prologue(ctx, ctx->arena, grid, P, elem, poses, st)) != RA_OK) return rc;
     float* s = at<float>(ctx, P.off_s);
@@ -3765,7 +4031,7 @@ int ra_count_updates(ra_ctx* ctx, const ra_grid* grid, int32_t M, const double* 
     hipStream_t st = (hipStream_t)stream;
     RA_HIP(ctx, hipSetDevice(ctx->device));
     Plan P;
-    make_plan(grid, M, F, samp, P, ctx->sums_mode);
+    make_plan(ctx, grid, M, F, samp, P, ctx->sums_mode);
     if ((rc = ensure_scratch(ctx, P.total, st)) != RA_OK) return rc;
     const Geo& g = P.g;
     double* xe64 = at<double>(ctx, P.off_xe64);
@@ -3841,7 +4107,7 @@ int ra_batch_describe(ra_ctx* ctx, const ra_grid* box, int64_t stride_x, int64_t
     if (stride_y < box->nz || stride_x < (int64_t)stride_y * box->ny)
         return fail(ctx, RA_EINVAL, "volume strides smaller than the box");
     Plan P;
-    make_plan(box, M, 1, samp, P, RA_SUMS_AUTO, false);
+    make_plan(nullptr, box, M, 1, samp, P);
     Geo g = P.g;
     g.vsx = stride_x;
     g.vsy = stride_y;
@@ -3862,7 +4128,7 @@ int ra_batch_describe(ra_ctx* ctx, const ra_grid* box, int64_t stride_x, int64_t
     // the moment form of the adjoints where the single-call plan takes it and its LDS fits one
     // workgroup on these regions
     Plan Pm;
-    make_plan(box, M, 1, samp, Pm);
+    make_plan(nullptr, box, M, 1, samp, Pm);
     const int nbin = 2 * g.jclamp + 1;
     const size_t lds_p = (size_t)nbin * 2 * WAVE * sizeof(float4) + (size_t)MOM_WAVES * 3 * WAVE * sizeof(double);
     const size_t lds_v = (size_t)nbin * 2 * WAVE * sizeof(float4) + (size_t)4 * g.nvpad * sizeof(float);
