@@ -8,13 +8,13 @@
  *   phi(u)   = u * exp(-u^2 / (2 sigma^2)),            t_k = k / fs,
  *
  * keeping only the terms with |d - c t_k| <= trunc * sigma (the other source profiles
- * of Appendix A replace the Gaussian, see ra_sampling).  For the Gaussian the forward and
- * the dL/dp0-only adjoint take the samples within floor(trunc*sigma*fs/c + 1/2) of each
- * term's nearest sample whole: every kept term is among them, and each term they add
- * beyond the window is below psi(trunc) of the kernel's peak (psi(y) = y exp(-y^2/2);
- * 1.5e-7 at trunc = 6), and that adjoint evaluates each voxel-element pair's window sum
- * by an 8-term Taylor expansion whose error is below 1e-6 of the peak (the library takes
- * it only where that bound holds).  Main text Eq. (1)
+ * of Appendix A replace the Gaussian, see ra_sampling).  The Gaussian's calls take the
+ * samples within floor(trunc*sigma*fs/c + 1/2) of each term's nearest sample whole: every
+ * kept term is among them, and each term they add beyond the window is below psi(trunc) of
+ * the kernel's peak (psi(y) = y exp(-y^2/2); 1.5e-7 at trunc = 6).  Each voxel-element pair's
+ * window is evaluated as a polynomial of 6 to 8 terms in the pair's offset from its nearest
+ * sample, whose error is below 2e-7 of the peak (the library takes it only where that bound
+ * holds, and otherwise evaluates the window sample by sample).  Main text Eq. (1)
  * sums the source intensity against a kernel of the source-sensor distance;
  * Appendix A, Eq. (A13) (the discretised far-field model with the Gaussian
  * kernel K_G) fixes the kernel used here.  Element positions follow the rigid
@@ -322,8 +322,8 @@ typedef struct {
     const double* elem;     /* double[M][3] array template                                    */
     float* xe;              /* float[M][6] scratch                                             */
     float* loss;            /* float[1]: sum (s - y)^2 at the start of the step               */
-    float* q;               /* ra_batch_info.q_bytes scratch: moment table of dL/ds (batches
-                               with ra_batch.moment; unused otherwise)                        */
+    float* q;               /* ra_batch_info.q_bytes scratch: moment table of dL/ds and the elements'
+                               losses (batches with ra_batch.moment; unused otherwise)        */
     int32_t kind;           /* RA_REQ_POSE or RA_REQ_VOLUME                                   */
     int32_t nreg;           /* regions of the box (ra_batch_info.nreg)                        */
     double lr_w;            /* pose: Adam step on w; volume: step size on p0                  */
@@ -336,13 +336,12 @@ typedef struct {
     int32_t jt, exact;      /* window code: equal for requests that may share a batch        */
     int32_t pair_d;         /* forward pairs z-neighbour voxels with this spread (0: no):
                                equal for requests that may share a batch                     */
-    int32_t lmax;           /* LDS sample rows needed                                         */
+    int32_t lmax;           /* LDS rows of 1 KiB the forward needs                           */
     int32_t nvpad;          /* voxels per region (padded)                                     */
     int32_t rx, ry, rz;     /* region size                                                    */
-    int32_t moment;         /* 1: the batch may take the moment form of the adjoints (the
-                               Gaussian's window sums from 8 Taylor moments of dL/ds per
-                               sample, as the single calls do); equal for requests that may
-                               share a batch                                                  */
+    int32_t moment;         /* 1: the batch may take the moment forms (a pair's window as a
+                               polynomial in its offset from its nearest sample, as the
+                               single calls do); equal for requests that may share a batch    */
     int32_t nbin;           /* centre samples per region and element (moment form)           */
     int64_t q_bytes;        /* bytes of the request's moment table (0 without the form)      */
 } ra_batch_info;
@@ -364,10 +363,10 @@ typedef struct {
     int32_t pair_d;               /* from ra_batch_describe (equal for all requests)        */
     int32_t lmax, nvpad;          /* maxima over the batch                                  */
     int32_t grid_blocks;          /* workgroups per launch; 0 = 1024                        */
-    int32_t moment;               /* 1: adjoints in moment form (every request has ra_batch_info
-                                     .moment set and a q buffer); 0: row form.  RA_EINVAL
-                                     for the moment form without coef, without the exact
-                                     window, or with nbin outside 1..40 or beyond the LDS  */
+    int32_t moment;               /* 1: forward and adjoints in moment form (every request has
+                                     ra_batch_info.moment set and a q buffer); 0: row form.
+                                     RA_EINVAL for the moment form without coef, without the
+                                     exact window, or with nbin outside 1..40 or beyond the LDS */
     int32_t nbin;                 /* ra_batch_info.nbin (moment form; equal for all requests:
                                      a request whose window needs more bins is skipped)     */
     float* coef;                  /* moment form: float[8 (2 jt + 1)] device scratch (jt <= 40,

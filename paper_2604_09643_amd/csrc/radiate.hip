@@ -24,10 +24,10 @@
 //     and Gamma_j = exp(-j^2 delta^2/2s^2) a per-call table.  So each sample
 //     costs one multiply of a running power of H plus one or two FMAs, with
 //     no transcendental; two or three exponentials are evaluated per pair.
-//   * Forward with the Gaussian (single calls): every pair adds NM polynomial moments of its offset
+//   * Forward with the Gaussian: every pair adds NM polynomial moments of its offset
 //     from its centre sample into fixed-point sums in LDS, which a region's workgroup expands into
 //     signal rows and adds to the signals with global atomics (k_forward_mom).
-//   * Forward otherwise (the batched step, other profiles, coarse sampling): every lane owns a private
+//   * Forward otherwise (other profiles, coarse sampling): every lane owns a private
 //     row of signal samples in LDS (layout [sample][lane], bank = lane, no conflicts) and updates it by
 //     read-modify-write; two z-neighbouring voxels share one pass over the rows (the Gaussian's rows
 //     about each voxel's centre sample are taken whole).  At the end of each region the rows are added
@@ -36,7 +36,7 @@
 //   * Sums of the regions' rows: FP32 up to 4096 row-form regions, FP64 sums beyond.
 //   * Adjoints with the Gaussian: a table of dL/ds's local expansions per sample, built once per
 //     call, two LDS reads and a Horner sum per pair, with its derivative for the element gradients
-//     (am_regions; the batched step: Taylor moments, mom_region).
+//     (am_regions).
 //   * Adjoints otherwise (other profiles, or where the expansion's bound
 //     fails): each lane stages its element's dL/ds window in the same
 //     private-row layout and gathers.  dL/dp0 of a voxel is summed across the
@@ -92,11 +92,7 @@ constexpr int FWD_F32_MAX_REGIONS = 4096;   // forward regions up to which parti
 constexpr size_t LDS_FWD_BUDGET = 80 * 1024;   // forward: two region workgroups per CU
 constexpr size_t LDS_ADJ_BUDGET = 80 * 1024;   // adjoint with element gradients: two per CU
 constexpr size_t LDS_ADJ0_BUDGET = 53 * 1024;  // adjoint for dL/dp0 only: three per CU
-constexpr int NMOM = 8;               // Taylor moments per sample of the moment-form dL/dp0 adjoint
-constexpr double MOM_TOL = 1e-6;      // its largest admitted truncation error, relative to the peak
-constexpr size_t LDS_MOM_BUDGET = 78 * 1024;   // moment-form adjoint: two region workgroups per CU
-constexpr int MOM_WAVES = 8;          // wavefronts of its region workgroup
-constexpr int MOM_PER = 5;            // its table rows staged per wavefront and chunk, at most
+constexpr int BATCH_BINS_MAX = 40;    // centre samples of a region the batched step's moment form takes
 constexpr int FM_WAVES = 8;           // wavefronts of the moment-form forward's region workgroup, two per CU
 constexpr int FM_WAVES_BIG = 16;      // and where its LDS leaves room for one per CU
 constexpr int FM_REFS = 2;            // element chunks whose references it computes at a time
@@ -199,8 +195,7 @@ struct Geo {
     float kexp;                    // exponential: K(x) = exp2(kexp x)
     float kinv_w, kinv_w2;         // 1/w, 1/w^2
     float knu, k2nu;               // power law: K(x) = exp2(knu log2(1 + x^2/w^2)), knu = -nu; 2 nu
-    double mom_dd, mom_sigma;      // moment forms: delta / sigma and sigma
-    // moment-form forward: lengths in units of delta / 2
+    // moment forms: lengths in units of delta / 2
     int jt;                        // window half-width in samples
     int nbin;                      // centre samples of a region, 2 jclamp + 1
     float unit_h, unit_l;          // 2 / delta
@@ -1591,24 +1586,15 @@ __global__ __launch_bounds__(BLOCK) void k_adjoint(Geo g, const float* __restric
 }
 
 // ------------------------------------------------------------------------------------------
-// dL/dp0 adjoint in moment form (Gaussian profile)
+// adjoints in moment form (Gaussian profile)
 // ------------------------------------------------------------------------------------------
-// Write a pair's distance as d = (kc + x) delta with kc its nearest sample and |x| <= 1/2.  The
-// window row kc + j carries phi((x - j) delta) = sigma psi((x - j) Delta), psi(y) = y exp(-y^2/2),
-// Delta = delta / sigma.  A Taylor expansion in x about the sample (the local expansion of the fast
-// Gauss transform of Greengard and Strain), with psi^(n)(-y) = -He_{n+1}(y) exp(-y^2/2) in the
-// probabilists' Hermite polynomials, gives
-//   sum_j r[kc + j] phi((x - j) delta) = sum_{n < NMOM} x^n Q_n[kc],
-//   Q_n[k] = sum_{|j| <= JT} r[k + j] D_n(j),  D_n(j) = -sigma Delta^n He_{n+1}(j Delta) e^{-(j Delta)^2/2} / n!.
-// The tables Q are built once per call from dL/ds; a pair then costs its distance, two LDS reads
-// and NMOM - 1 FMAs of Horner's rule instead of a pass over its 2 JT + 1 window rows.  Cramer's
-// bound on Hermite functions, |He_m(y)| e^{-y^2/2} <= 1.0865 sqrt(m!), bounds the truncation error
-// by 1.791 (Delta/2)^NMOM sqrt((NMOM + 1) / NMOM!) of the kernel's peak; the host takes this form
-// only where that is at most MOM_TOL.  Rows are taken whole about kc, so a term with
-// T sigma < |u| <= (JT + 1/2) delta (at most psi(T) ~ 1e-7 of the peak at T = 6) is added where the
-// exact window leaves it out.
-
-// The same local expansion on |t| <= 1 (t = 2x) as the forward's, by its Chebyshev series: table rows
+// The transpose of the forward's moment form: the window sum of a pair with nearest sample kc and offset t is
+//   sum_j r[kc + j] phi((t/2 - j) delta) = delta sum_n t^n Q_n[kc],  Q_n[k] = sum_j r[k + j] D_n(j) / delta,
+// so a pair costs its distance, two LDS reads and Horner's rule instead of a pass over its 2 JT + 1 window
+// rows.  Rows are taken whole about kc, so a term with T sigma < |u| <= (JT + 1/2) delta (at most psi(T) ~ 1e-7
+// of the peak at T = 6) is added where the exact window leaves it out.
+//
+// The table built once per call from dL/ds: rows
 // Q[e][kk][n] = sum_{|j| <= jt} r[e][k + j] D_n(j) / delta for kk in [0, K + 2 jt), k = kk - jt, with dL/ds
 // zero outside [0, K); each row is two float4 (n = 0..3, 4..7).  One zero row follows the last element's
 // rows.  The window's two legs are taken together, since D_n(-j) = (-1)^(n+1) D_n(j): 10 VALU for two
@@ -1655,25 +1641,27 @@ __global__ __launch_bounds__(MT_ROWS) void k_moment_series(int E, int K, int jt,
 //   dL/dx_e = - sum_v p0 (2 / delta) / d^2 (P' - P / d) (D + o), d and o in units;
 // the terms of a column are FP32, columns add in FP64, the wavefronts' sums of a chunk meet in LDS (in the
 // window just used) in wavefront order, and a workgroup adds its regions into one row of partials in their
-// order, so no result depends on timing.
+// order (or each into its own row, row_step apart), so no result depends on timing.
 // Bounds: VALU.  About 19 instructions per pair for dL/dp0 and 36 per column of 8 pairs, 34 per pair with
 // the element gradients too.  On this chip FP32 adds, multiplies and FMAs of vector registers issue at up to
 // 1.5 a clock and CU, those with a scalar operand, med3, conversions and shifts at 0.9, v_rsq_f32 at 0.5: the
 // sum over a pair comes to 25 cycles, 28 measured (sweep of 128x128x64 voxels and 8192 elements: 7.14 ms
 // before, with 35 instructions per pair, 6.5 ms now; with the element gradients 12.4 -> 10.4 ms).
 constexpr int AM_FIELDS = 11;         // floats of a reference
-constexpr size_t am_off_axis(int nbin, int nbuf) { return (size_t)nbuf * nbin * 2 * WAVE * 4 + AM_REFS * AM_FIELDS * WAVE; }
+constexpr int AM_BINS_MIN = 13;       // bins a window's LDS holds at least: it also takes the wavefronts' partials
+constexpr int am_win(int nbin) { return (nbin > AM_BINS_MIN ? nbin : AM_BINS_MIN) * 2 * WAVE; }      // float4 per window
+constexpr size_t am_off_axis(int nbin, int nbuf) { return (size_t)nbuf * am_win(nbin) * 4 + AM_REFS * AM_FIELDS * WAVE; }
 constexpr size_t am_lds(int nbin, int nbuf) { return (am_off_axis(nbin, nbuf) + 3 * FM_SIDE * 4) * sizeof(float); }
 
 template <int NM, int CPW, bool WANT_P0, bool WANT_POSE>
 __device__ __forceinline__ void am_regions(const Geo& g, int reg0, int reg1, int nbuf, const float* __restrict__ p0,
                                            const float* __restrict__ xe, const float4* __restrict__ q,
                                            float* __restrict__ grad_p0, int accumulate, double* __restrict__ pose_part,
-                                           float* lds) {
+                                           size_t row_step, float* lds) {
     const int tid = threadIdx.x, lane = tid & (WAVE - 1);
     const int wv = __builtin_amdgcn_readfirstlane(tid / WAVE);
     const int nbin = g.nbin, jt = g.jt, kq = g.K + 2 * jt;
-    const int win = nbin * 2 * WAVE;                         // float4 per window
+    const int win = am_win(nbin);
     float4* qw = reinterpret_cast<float4*>(lds);
     float* refs = lds + (size_t)nbuf * win * 4;              // [slot][field][lane]
     float4* axis = reinterpret_cast<float4*>(lds + am_off_axis(nbin, nbuf));
@@ -1823,8 +1811,8 @@ __device__ __forceinline__ void am_regions(const Geo& g, int reg0, int reg1, int
             part[(wv * 3 + 2) * WAVE + lane] = u * Sz;
             __syncthreads();
             if (tid < 3 * WAVE && c * WAVE + lane < g.E) {   // wavefront w: component w
-                double* row = pose_part + (size_t)(c * WAVE + lane) * 3 + wv;
-                double a = reg == reg0 ? 0.0 : *row;
+                double* row = pose_part + (reg - reg0) * row_step + (size_t)(c * WAVE + lane) * 3 + wv;
+                double a = reg == reg0 || row_step ? 0.0 : *row;
                 for (int w = 0; w < AM_WAVES; ++w) a += part[(w * 3 + wv) * WAVE + lane];
                 *row = a;
             }
@@ -1870,240 +1858,8 @@ __global__ __launch_bounds__(AM_WAVES * WAVE) __attribute__((amdgpu_waves_per_eu
     const int b = region_of_block(blockIdx.x, gridDim.x);
     const int r0 = (int)((long long)g.nreg * b / gridDim.x), r1 = (int)((long long)g.nreg * (b + 1) / gridDim.x);
     am_regions<NM, CPW, WANT_P0, WANT_POSE>(g, r0, r1, nbuf, p0, xe, q, grad_p0, accumulate,
-                                            WANT_POSE ? pose_part + (size_t)blockIdx.x * g.E * 3 : nullptr,
+                                            WANT_POSE ? pose_part + (size_t)blockIdx.x * g.E * 3 : nullptr, 0,
                                             reinterpret_cast<float*>(lds4));
-}
-
-// Reference of a (region, element) pair from the element's position x (hi: x[0..2], lo: x[3..5]),
-// as make_ref.
-__device__ __forceinline__ Ref make_ref_x(const Geo& g, const float* x, const Region& R) {
-#pragma clang fp contract(off)
-    DF Dx = df_add(R.cx, df_neg(DF{x[0], x[3]}));
-    DF Dy = df_add(R.cy, df_neg(DF{x[1], x[4]}));
-    DF Dz = df_add(R.cz, df_neg(DF{x[2], x[5]}));
-    DF d2 = df_add(df_add(df_mul(Dx, Dx), df_mul(Dy, Dy)), df_mul(Dz, Dz));
-    DF d = df_sqrt(d2);
-    float kc = rintf(d.h * g.inv_dlt);
-    DF kd = df_add(two_prod(kc, g.dlt_h), DF{kc * g.dlt_l, 0.f});
-    DF u = df_add(d, df_neg(kd));
-    Ref r;
-    r.Dx = Dx.h; r.Dy = Dy.h; r.Dz = Dz.h;
-    r.dh = d.h;
-    r.dh2 = d.h * d.h;
-    r.uc0 = u.h;
-    r.hdh = 0.5f * d.h;
-    r.kbase = (int)kc - g.kmargin;
-    return r;
-}
-
-// Position of this lane's element in chunk c (the last element past the end).
-__device__ __forceinline__ void mom_load_x(const Geo& g, const float* __restrict__ xe, int c, int lane, float* xn) {
-    const int e = min(c * WAVE + lane, g.E - 1);
-#pragma unroll
-    for (int i = 0; i < 6; ++i) xn[i] = xe[6 * e + i];
-}
-
-// Issue the loads of a wavefront's PER table rows (bins b0 .. b0 + nb - 1) of chunk c; rows that do
-// not exist or lie outside the table read the zero row after the table.
-template <int PER>
-__device__ __forceinline__ void mom_fetch(const Geo& g, const vf4* __restrict__ q, int c, int lane,
-                                          const Ref& ref, int jt, int b0, int nb, vf4 (&plo)[PER],
-                                          vf4 (&phi)[PER]) {
-    const int e = c * WAVE + lane;
-    const bool valid = e < g.E;
-    const int kq = g.K + 2 * jt;
-    // table row of bin 0: sample kc - jclamp, with kc = kbase + kmargin
-    const int kk0 = ref.kbase + g.kmargin - g.jclamp + jt + b0;
-    const vf4* qe = q + (size_t)(valid ? e : 0) * kq * 2;
-    const vf4* zrow = q + (size_t)g.E * kq * 2;
-#pragma unroll
-    for (int i = 0; i < PER; ++i) {
-        const int kk = kk0 + i;
-        const bool in = valid && i < nb && kk >= 0 && kk < kq;
-        const vf4* src = in ? qe + (size_t)kk * 2 : zrow;
-        plo[i] = src[0];
-        phi[i] = src[1];
-    }
-}
-
-// dL/dp0 (with WANT_P0) and/or the per-region element gradients (with WANT_POSE) of one region
-// from the moment tables; `qw` is the workgroup's LDS.  The workgroup's NW wavefronts take the
-// element chunks together: they stage the chunk's table rows for the region's 2 jclamp + 1 centre
-// samples in LDS ([bin][half][lane] float4, so a wavefront's reads of one half are 1 KiB
-// contiguous), then each sums its own share of the region's voxels (groups of four, dealt
-// round-robin) over the 64 elements of the chunk (eight wavefronts measured 27% faster than four:
-// more waves to hide the LDS reads and the staging, which each wavefront then does less of).
-// Per-voxel sums (one partial per row of 16 lanes) stay in LDS across chunks; no atomics.  Loads
-// run ahead of use: a wavefront's PER table rows of the next chunk are fetched into registers while
-// the current chunk's voxels run (the voxel loop issues no other vector memory loads; voxel offsets
-// come in through scalar loads) and the element positions two chunks ahead.  With WANT_POSE the
-// Horner sum runs together with its derivative, A = sum_n x^n Q_n = sum_k r phi(u) and
-// A' = dA/dx, so B = sum_k r phi'(u) = A' / delta; the pair adds p0 (B/(2d) - A/(2d^2)) (x_e - x_v)/d
-// to its element's gradient (FP32 over four voxels, then FP64 per lane).  At the end of a chunk the
-// wavefronts' FP64 partials meet in LDS and are added in wavefront order into the region's partial
-// of each element, so the result does not depend on timing.  The derivative of the 8-term
-// expansion is a 7-term expansion of phi', within about 1.8 (Delta/2)^7 sqrt(8/7!) of its peak
-// (3e-6 on the sweep).
-template <int PER, int NW, bool WANT_P0, bool WANT_POSE>
-__device__ __forceinline__ void mom_region(const Geo& g, int reg, const float* __restrict__ p0,
-                                           const float* __restrict__ xe, const float4* __restrict__ vtab,
-                                           const int4* __restrict__ itab, const float4* __restrict__ q, int jt,
-                                           float* __restrict__ grad_p0, int accumulate,
-                                           double* __restrict__ pose_part, float4* qw) {
-    const int lane = threadIdx.x & (WAVE - 1);
-    const int wv = __builtin_amdgcn_readfirstlane((int)(threadIdx.x / WAVE));
-    const int nbin = 2 * g.jclamp + 1;
-    float* gsum = reinterpret_cast<float*>(qw + (size_t)nbin * 2 * WAVE);   // [row of 16 lanes][voxel]
-    double* pbuf = reinterpret_cast<double*>(gsum + (WANT_P0 ? 4 * g.nvpad : 0));  // [wave][3][lane]
-    const Region R = region_info(g, reg);
-    const float* pbase = p0 ? p0 + (size_t)R.i0 * g.vsx + (size_t)R.j0 * g.vsy + R.k0 : nullptr;
-    const bool interior = R.ni == g.rx && R.nj == g.ry && R.nk == g.rz && (g.rz & 3) == 0;
-    if (WANT_P0)
-        for (int t = threadIdx.x; t < 4 * g.nvpad; t += NW * WAVE) gsum[t] = 0.0f;
-    const bool adder = (lane & 15) >= 12;
-    const int vsel = (lane & 3) == 1 ? 2 : ((lane & 3) == 2 ? 1 : (lane & 3));
-    float* gsum_row = gsum + (size_t)(lane >> 4) * g.nvpad + vsel;
-    const int nchunk = (g.E + WAVE - 1) / WAVE;
-    const float jcl = g.jclampf, njcl = -g.jclampf;
-    const int b0 = wv * PER, nb = max(0, min(nbin - b0, PER));
-
-    const vf4* qv = reinterpret_cast<const vf4*>(q);
-    vf4* qwv = reinterpret_cast<vf4*>(qw);
-    vf4 plo[PER], phi[PER];
-    float xn[6];
-    mom_load_x(g, xe, 0, lane, xn);
-    Ref ref = make_ref_x(g, xn, R);
-    mom_fetch<PER>(g, qv, 0, lane, ref, jt, b0, nb, plo, phi);
-    mom_load_x(g, xe, 1, lane, xn);
-
-    for (int c = 0; c < nchunk; ++c) {
-        __syncthreads();                 // the previous chunk's rows and partials have been read
-        if (WANT_POSE && c > 0 && wv == 0) {   // the previous chunk's element partials, in wavefront order
-            const int e = (c - 1) * WAVE + lane;
-            double a[3] = {0.0, 0.0, 0.0};
-            for (int w = 0; w < NW; ++w)
-#pragma unroll
-                for (int i = 0; i < 3; ++i) a[i] += pbuf[((size_t)w * 3 + i) * WAVE + lane];
-            if (e < g.E) {
-                double* out = pose_part + ((size_t)reg * g.E + e) * 3;
-                out[0] = a[0]; out[1] = a[1]; out[2] = a[2];
-            }
-        }
-        if (nb > 0) {
-            // every row slot is written, in descending order: slots past this wavefront's last bin
-            // write zeros to that bin first, which its own row then overwrites
-#pragma unroll
-            for (int i = PER - 1; i >= 0; --i) {
-                const int row = b0 + min(i, nb - 1);
-                qwv[(row * 2) * WAVE + lane] = plo[i];
-                qwv[(row * 2 + 1) * WAVE + lane] = phi[i];
-            }
-        }
-        __syncthreads();
-        const Ref cur = ref;
-        if (c + 1 < nchunk) {
-            ref = make_ref_x(g, xn, R);
-            mom_fetch<PER>(g, qv, c + 1, lane, ref, jt, b0, nb, plo, phi);
-            mom_load_x(g, xe, c + 2, lane, xn);
-        }
-        double gx = 0.0, gy = 0.0, gz = 0.0;
-        for (int t = 4 * wv; t < g.nvpad; t += 4 * NW) {
-            float pv4[4] = {0.0f, 0.0f, 0.0f, 0.0f};
-            if (WANT_POSE) {
-                if (interior) {                      // four consecutive voxels along z
-                    const int off = itab[t].w;
-#pragma unroll
-                    for (int v = 0; v < 4; ++v) pv4[v] = pbase[off + v];
-                } else {
-#pragma unroll
-                    for (int v = 0; v < 4; ++v) {
-                        const int4 ix = itab[t + v];
-                        const bool inside = ix.x < R.ni && ix.y < R.nj && ix.z < R.nk;
-                        const float val = pbase[inside ? ix.w : 0];
-                        pv4[v] = inside ? val : 0.0f;
-                    }
-                }
-            }
-            float G[4];
-            float fx = 0.0f, fy = 0.0f, fz = 0.0f;
-#pragma unroll
-            for (int v = 0; v < 4; ++v) {
-                const float4 o = vtab[t + v];
-                const Dist d = pair_dist(cur, o);
-                const float tt = d.uc * g.inv_dlt;                           // d / delta - kc
-                const float jf = __builtin_amdgcn_fmed3f(rintf(tt), njcl, jcl);
-                const float x = tt - jf;
-                const int b = (int)jf + g.jclamp;
-                const float4 m0 = qw[(b * 2) * WAVE + lane], m1 = qw[(b * 2 + 1) * WAVE + lane];
-                float h = m1.w, dh = 0.0f;
-                if (WANT_POSE) {                     // A and dA/dx together by Horner's rule
-                    dh = fmaf(dh, x, h); h = fmaf(h, x, m1.z);
-                    dh = fmaf(dh, x, h); h = fmaf(h, x, m1.y);
-                    dh = fmaf(dh, x, h); h = fmaf(h, x, m1.x);
-                    dh = fmaf(dh, x, h); h = fmaf(h, x, m0.w);
-                    dh = fmaf(dh, x, h); h = fmaf(h, x, m0.z);
-                    dh = fmaf(dh, x, h); h = fmaf(h, x, m0.y);
-                    dh = fmaf(dh, x, h); h = fmaf(h, x, m0.x);
-                } else {
-                    h = fmaf(h, x, m1.z);
-                    h = fmaf(h, x, m1.y);
-                    h = fmaf(h, x, m1.x);
-                    h = fmaf(h, x, m0.w);
-                    h = fmaf(h, x, m0.z);
-                    h = fmaf(h, x, m0.y);
-                    h = fmaf(h, x, m0.x);
-                }
-                const float A = h;                                           // sum r phi
-                G[v] = A * d.hr;
-                if (WANT_POSE) {
-                    const float B = dh * g.inv_dlt;                          // sum r phi'
-                    const float twohr = 2.0f * d.hr;                         // 1/d
-                    // p0 (B/(2d) - A/(2d^2)) / d times (x_e - x_v) = -(D + o)
-                    const float coef = -pv4[v] * d.hr * twohr * fmaf(-twohr, A, B);
-                    fx = fmaf(coef, cur.Dx + o.x, fx);
-                    fy = fmaf(coef, cur.Dy + o.y, fy);
-                    fz = fmaf(coef, cur.Dz + o.z, fz);
-                }
-            }
-            if (WANT_POSE) {
-                gx += (double)fx;
-                gy += (double)fy;
-                gz += (double)fz;
-            }
-            if (WANT_P0) {
-                const float part = wave_sum4_rows(G[0], G[1], G[2], G[3], lane);
-                if (adder) gsum_row[t] += part;
-            }
-        }
-        if (WANT_POSE) {
-            pbuf[((size_t)wv * 3 + 0) * WAVE + lane] = gx;
-            pbuf[((size_t)wv * 3 + 1) * WAVE + lane] = gy;
-            pbuf[((size_t)wv * 3 + 2) * WAVE + lane] = gz;
-        }
-    }
-    __syncthreads();
-    if (WANT_POSE && wv == 0) {          // the last chunk's element partials
-        const int e = (nchunk - 1) * WAVE + lane;
-        double a[3] = {0.0, 0.0, 0.0};
-        for (int w = 0; w < NW; ++w)
-#pragma unroll
-            for (int i = 0; i < 3; ++i) a[i] += pbuf[((size_t)w * 3 + i) * WAVE + lane];
-        if (e < g.E) {
-            double* out = pose_part + ((size_t)reg * g.E + e) * 3;
-            out[0] = a[0]; out[1] = a[1]; out[2] = a[2];
-        }
-    }
-    if (WANT_P0) {
-        float* gbase = grad_p0 + (size_t)R.i0 * g.gsx + (size_t)R.j0 * g.gsy + R.k0;
-        for (int t = threadIdx.x; t < g.nvpad; t += NW * WAVE) {
-            const int4 ix = itab[t];
-            if (!(ix.x < R.ni && ix.y < R.nj && ix.z < R.nk)) continue;
-            const float v = (gsum[t] + gsum[g.nvpad + t]) + (gsum[2 * g.nvpad + t] + gsum[3 * g.nvpad + t]);
-            float* dst = gbase + ix.x * g.gsx + ix.y * g.gsy + ix.z;
-            *dst = accumulate ? *dst + v : v;
-        }
-    }
-    __syncthreads();                     // the workgroup's LDS is free for the next region
 }
 
 // Sum the rows of element-gradient partials in FP64 and a fixed order: a workgroup takes 16
@@ -2660,10 +2416,17 @@ __global__ __launch_bounds__(256) void k_probe_exp(float* __restrict__ out, int 
 // ==========================================================================================
 constexpr int BATCH_THREADS = 256;
 
-__global__ void k_batch_elements(const Geo* __restrict__ geos, const ra_batch_request* __restrict__ reqs,
-                                 const int2* __restrict__ items, const int* __restrict__ counts) {
-    const int n = counts[3];
-    for (int it = blockIdx.x * blockDim.x + threadIdx.x; it < n; it += gridDim.x * blockDim.x) {
+// A request's descriptor: its geometry and the moment forms' series (nm terms for the forward, 8 for the adjoints).
+struct BatchGeo {
+    Geo g;
+    int nm;
+    MomCoef series, series8;
+};
+
+// Element positions of every request, by threads t0, t0 + stride, ..
+__device__ __forceinline__ void batch_elements(const ra_batch_request* __restrict__ reqs, const int2* __restrict__ items,
+                                               int n, int t0, int stride) {
+    for (int it = t0; it < n; it += stride) {
         const int2 w = items[it];
         const ra_batch_request& q = reqs[w.x];
         double R[9];
@@ -2680,13 +2443,18 @@ __global__ void k_batch_elements(const Geo* __restrict__ geos, const ra_batch_re
     }
 }
 
+__global__ void k_batch_elements(const ra_batch_request* __restrict__ reqs, const int2* __restrict__ items,
+                                 const int* __restrict__ counts) {
+    batch_elements(reqs, items, counts[3], blockIdx.x * blockDim.x + threadIdx.x, gridDim.x * blockDim.x);
+}
+
 // zero the signal buffer of every request (slot-major, one workgroup per slot at a time)
-__global__ void k_batch_zero(const Geo* __restrict__ geos, const ra_batch_request* __restrict__ reqs,
+__global__ void k_batch_zero(const BatchGeo* __restrict__ geos, const ra_batch_request* __restrict__ reqs,
                              const int* __restrict__ counts) {
     const int ns = counts[4];
     for (int slot = blockIdx.x; slot < ns; slot += gridDim.x) {
         if (reqs[slot].kind < 0) continue;      // slot not in this batch
-        const Geo& g = geos[slot];
+        const Geo& g = geos[slot].g;
         float* s = reqs[slot].s;
         const int n = g.E * g.K;
         for (int i = threadIdx.x; i < n; i += blockDim.x) s[i] = 0.0f;
@@ -2694,7 +2462,7 @@ __global__ void k_batch_zero(const Geo* __restrict__ geos, const ra_batch_reques
 }
 
 // r = 2 (s - y) in place and the loss sum (s - y)^2 of every request
-__global__ __launch_bounds__(BATCH_THREADS) void k_batch_residual(const Geo* __restrict__ geos,
+__global__ __launch_bounds__(BATCH_THREADS) void k_batch_residual(const BatchGeo* __restrict__ geos,
                                                                   const ra_batch_request* __restrict__ reqs,
                                                                   const int* __restrict__ counts) {
     __shared__ float red[BATCH_THREADS];
@@ -2702,7 +2470,7 @@ __global__ __launch_bounds__(BATCH_THREADS) void k_batch_residual(const Geo* __r
     for (int slot = blockIdx.x; slot < ns; slot += gridDim.x) {
         const ra_batch_request& q = reqs[slot];
         if (q.kind < 0) continue;               // slot not in this batch (uniform per block)
-        const Geo& g = geos[slot];
+        const Geo& g = geos[slot].g;
         const int n = g.E * g.K;
         float acc = 0.0f;
         for (int i = threadIdx.x; i < n; i += blockDim.x) {
@@ -2722,7 +2490,7 @@ __global__ __launch_bounds__(BATCH_THREADS) void k_batch_residual(const Geo* __r
 }
 
 template <int JT, bool EXACT, int D>
-__global__ __launch_bounds__(BLOCK) void k_forward_batch(const Geo* __restrict__ geos,
+__global__ __launch_bounds__(BLOCK) void k_forward_batch(const BatchGeo* __restrict__ geos,
                                                          const ra_batch_request* __restrict__ reqs,
                                                          const float4* __restrict__ vtab,
                                                          const int4* __restrict__ itab,
@@ -2736,12 +2504,12 @@ __global__ __launch_bounds__(BLOCK) void k_forward_batch(const Geo* __restrict__
     for (int it = blockIdx.x; it < n; it += gridDim.x) {
         const int2 w = items[it];
         const ra_batch_request& q = reqs[w.x];
-        forward_region<JT, EXACT, D, float>(geos[w.x], w.y, q.p0, q.xe, vtab, itab, q.s, rows, lane, wave);
+        forward_region<JT, EXACT, D, float>(geos[w.x].g, w.y, q.p0, q.xe, vtab, itab, q.s, rows, lane, wave);
     }
 }
 
 template <int JT, bool EXACT, bool WANT_P0, bool WANT_POSE>
-__global__ __launch_bounds__(BLOCK) void k_adjoint_batch(const Geo* __restrict__ geos,
+__global__ __launch_bounds__(BLOCK) void k_adjoint_batch(const BatchGeo* __restrict__ geos,
                                                          const ra_batch_request* __restrict__ reqs,
                                                          const float4* __restrict__ vtab,
                                                          const int4* __restrict__ itab,
@@ -2755,138 +2523,220 @@ __global__ __launch_bounds__(BLOCK) void k_adjoint_batch(const Geo* __restrict__
     for (int it = blockIdx.x; it < n; it += gridDim.x) {
         const int2 w = items[it];
         const ra_batch_request& q = reqs[w.x];
-        adjoint_region<JT, EXACT, WANT_P0, WANT_POSE>(geos[w.x], w.y, q.p0, q.xe, vtab, itab, q.s, q.grad_p0, 0,
+        adjoint_region<JT, EXACT, WANT_P0, WANT_POSE>(geos[w.x].g, w.y, q.p0, q.xe, vtab, itab, q.s, q.grad_p0, 0,
                                                        q.pose_part, rows, gsum, lane, wave);
     }
 }
 
-// Moment form of the batched adjoints (requests sharing the window code, region size and
-// moment coefficients).  The coefficients come from the first active slot's descriptor; each
-// request's table is built from its own dL/ds into its `q` buffer.
-__global__ void k_batch_moment_coefs(const Geo* __restrict__ geos, const ra_batch_request* __restrict__ reqs,
-                                     const int* __restrict__ counts, int jt, float* __restrict__ c) {
-    const int ns = counts[4];
-    int first = -1;
-    for (int slot = 0; slot < ns && first < 0; ++slot)
-        if (reqs[slot].kind >= 0) first = slot;
-    if (first < 0) return;
-    const Geo& g = geos[first];
-    const int j = (int)threadIdx.x - jt;
-    if (j > jt) return;
-    const double y = j * g.mom_dd;
-    const double gy = exp(-0.5 * y * y);
-    double hprev = 1.0, h = y, dn = 1.0, fact = 1.0;
-    for (int n = 0; n < NMOM; ++n) {
-        c[n * (2 * jt + 1) + j + jt] = (float)(-g.mom_sigma * dn * h * gy / fact);
-        const double hnext = y * h - (double)(n + 1) * hprev;
-        hprev = h;
-        h = hnext;
-        dn *= g.mom_dd;
-        fact *= (double)(n + 1);
-    }
-}
-
-__global__ __launch_bounds__(256) void k_batch_moment_table(const Geo* __restrict__ geos,
-                                                            const ra_batch_request* __restrict__ reqs,
-                                                            const int* __restrict__ counts, int jt,
-                                                            const float* __restrict__ coef) {
-    __shared__ float cs[NMOM * (2 * JMAX + 1)];
-    const int nj = 2 * jt + 1;
-    for (int i = threadIdx.x; i < NMOM * nj; i += blockDim.x) cs[i] = coef[i];
-    __syncthreads();
-    const int ns = counts[4];
+// Moment form of the batched step.  Element positions of every request, and cleared signals.
+__global__ __launch_bounds__(BATCH_THREADS) void k_batch_begin(const BatchGeo* __restrict__ geos,
+                                                               const ra_batch_request* __restrict__ reqs,
+                                                               const int2* __restrict__ items,
+                                                               const int* __restrict__ counts) {
+    const int ns = counts[4], stride = gridDim.x * BATCH_THREADS, t0 = blockIdx.x * BATCH_THREADS + threadIdx.x;
+    batch_elements(reqs, items, counts[3], t0, stride);
     for (int slot = 0; slot < ns; ++slot) {
-        const ra_batch_request& rq = reqs[slot];
-        if (rq.kind < 0) continue;                         // uniform per block
-        const Geo& g = geos[slot];
-        const int kq = g.K + 2 * jt;
-        const long long nrow = (long long)g.E * kq;
-        float4* q = reinterpret_cast<float4*>(rq.q);
-        for (long long idx = blockIdx.x * (long long)blockDim.x + threadIdx.x; idx <= nrow;
-             idx += (long long)gridDim.x * blockDim.x) {
-            if (idx == nrow) {                             // the zero row after the table
-                q[2 * idx] = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
-                q[2 * idx + 1] = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
-                continue;
-            }
-            const int e = (int)(idx / kq), kk = (int)(idx % kq);
-            const float* row = rq.s + (size_t)e * g.K;     // dL/ds after k_batch_residual
-            float acc[NMOM];
-#pragma unroll
-            for (int n = 0; n < NMOM; ++n) acc[n] = 0.0f;
-            for (int i = 0; i < nj; ++i) {
-                const int k = kk - 2 * jt + i;
-                const float v = (k >= 0 && k < g.K) ? row[k] : 0.0f;
-#pragma unroll
-                for (int n = 0; n < NMOM; ++n) acc[n] = fmaf(v, cs[n * nj + i], acc[n]);
-            }
-            q[2 * idx] = make_float4(acc[0], acc[1], acc[2], acc[3]);
-            q[2 * idx + 1] = make_float4(acc[4], acc[5], acc[6], acc[7]);
-        }
+        if (reqs[slot].kind < 0) continue;
+        const long long n = (long long)geos[slot].g.E * geos[slot].g.K;
+        float* s = reqs[slot].s;
+        for (long long i = t0; i < n; i += stride) s[i] = 0.0f;
     }
 }
 
-// which: 1 = pose requests (element gradients), 2 = volume requests (dL/dp0).  The LDS window was
-// sized for nbin bins; a request whose window needs more (a descriptor from another batch layout)
-// is skipped rather than overrun it.
-template <bool WANT_P0, bool WANT_POSE>
-__global__ __launch_bounds__(MOM_WAVES * WAVE) __attribute__((amdgpu_waves_per_eu(MOM_WAVES / 2)))
-void k_adjoint_mom_batch(const Geo* __restrict__ geos, const ra_batch_request* __restrict__ reqs,
-                         const float4* __restrict__ vtab, const int4* __restrict__ itab,
-                         const int2* __restrict__ items, const int* __restrict__ counts, int which, int jt,
-                         int nbin) {
-    extern __shared__ float4 qw[];
-    const int n = counts[which];
+// lds_bytes: this launch's LDS; a request that needs more (a descriptor from another batch layout) is skipped.
+template <int NM>
+__device__ __forceinline__ void batch_forward_item(const BatchGeo& bg, const ra_batch_request& rq, int reg, float* lds) {
+    const int dl = fm_dlen(bg.g.jt);
+    float* dt = lds + fm_off_dt(NM, bg.g.nbin);
+    for (int i = threadIdx.x; i < NM * dl; i += FM_WAVES * WAVE)
+        dt[i] = mom_coef(bg.series, i / dl, i % dl - FM_PAD - bg.g.jt, bg.g.jt);
+    fm_region<NM, FM_WAVES, float>(bg.g, reg, 0, 1, rq.p0, rq.xe, rq.s, lds);
+    __syncthreads();                                         // the LDS is free for the next item
+}
+
+__global__ __launch_bounds__(FM_WAVES * WAVE) __attribute__((amdgpu_waves_per_eu(4))) void k_forward_mom_batch(
+    const BatchGeo* __restrict__ geos, const ra_batch_request* __restrict__ reqs, const int2* __restrict__ items,
+    const int* __restrict__ counts, int lds_bytes) {
+    extern __shared__ float lds[];
+    const int n = counts[0];
     for (int it = blockIdx.x; it < n; it += gridDim.x) {
         const int2 w = items[it];
-        if (2 * geos[w.x].jclamp + 1 > nbin) continue;     // uniform per workgroup
+        const BatchGeo& bg = geos[w.x];
+        if ((int)fm_lds(bg.nm, bg.g.nbin, bg.g.jt) > lds_bytes) continue;      // uniform per workgroup
+        if (bg.nm == 6) batch_forward_item<6>(bg, reqs[w.x], w.y, lds);
+        else if (bg.nm == 7) batch_forward_item<7>(bg, reqs[w.x], w.y, lds);
+        else batch_forward_item<8>(bg, reqs[w.x], w.y, lds);
+    }
+}
+
+// dL/ds = 2 (s - y) in place, each element's loss, and the table of dL/ds, as k_moment_series: a workgroup takes an
+// element's row from its start, and the window of table row kk ends at r[kk], so each segment needs only the tail of
+// the one before.  The loss of element e goes behind the table (the batch's residual and table kernels took
+// 0.204 and 0.013 ms a step, one workgroup a request; 0.018 ms so).
+__global__ __launch_bounds__(MT_ROWS) void k_batch_series(const BatchGeo* __restrict__ geos,
+                                                          const ra_batch_request* __restrict__ reqs,
+                                                          const int2* __restrict__ items, const int* __restrict__ counts) {
+    __shared__ float row[MT_ROWS + 2 * JMAX];
+    __shared__ float red[MT_ROWS / WAVE];
+    const int n = counts[3], tid = threadIdx.x;
+    for (int it = blockIdx.x; it < n; it += gridDim.x) {
+        const int2 w = items[it];
+        const BatchGeo& bg = geos[w.x];
         const ra_batch_request& rq = reqs[w.x];
-        mom_region<MOM_PER, MOM_WAVES, WANT_P0, WANT_POSE>(geos[w.x], w.y, rq.p0, rq.xe, vtab, itab,
-                                                           reinterpret_cast<const float4*>(rq.q), jt, rq.grad_p0, 0,
-                                                           rq.pose_part, qw);
+        const int E = bg.g.E, K = bg.g.K, jt = bg.g.jt, kq = K + 2 * jt, e = w.y;
+        float* s = rq.s + (size_t)e * K;
+        const float* y = rq.y + (size_t)e * K;
+        float4* q = reinterpret_cast<float4*>(rq.q);
+        float loss = 0.0f;
+        __syncthreads();                                     // the last item's row has been read
+        if (tid < 2 * jt) row[tid] = 0.0f;
+        for (int kk0 = 0; kk0 < kq; kk0 += MT_ROWS) {
+            const int kk = kk0 + tid;
+            float r = 0.0f;
+            if (kk < K) {
+                const float d = s[kk] - y[kk];
+                loss = fmaf(d, d, loss);
+                r = 2.0f * d;
+                s[kk] = r;
+            }
+            row[2 * jt + tid] = r;                           // row[2 jt + i] = r[kk0 + i]
+            __syncthreads();
+            const float* c = row + tid + jt;                 // r at the row's own sample kk - jt
+            float acc[FM_NM_MAX];
+#pragma unroll
+            for (int m = 0; m < FM_NM_MAX; ++m) acc[m] = c[0] * bg.series8.d[m];
+            for (int j = 1; j <= jt; ++j) {
+                const float a = c[j], b = c[-j], sum = a + b, dif = a - b;
+#pragma unroll
+                for (int m = 0; m < FM_NM_MAX; ++m) acc[m] = fmaf(m & 1 ? sum : dif, bg.series8.d[j * FM_NM_MAX + m], acc[m]);
+            }
+            if (kk < kq) {
+                float4* out = q + 2 * ((size_t)e * kq + kk);
+                out[0] = make_float4(acc[0], acc[1], acc[2], acc[3]);
+                out[1] = make_float4(acc[4], acc[5], acc[6], acc[7]);
+            }
+            float tail = 0.0f;
+            if (tid < 2 * jt) tail = row[MT_ROWS + tid];
+            __syncthreads();
+            if (tid < 2 * jt) row[tid] = tail;
+        }
+        loss = wave_sum_to_63(loss);
+        if ((tid & (WAVE - 1)) == WAVE - 1) red[tid / WAVE] = loss;
+        __syncthreads();
+        if (tid == 0) {
+            float t = 0.0f;
+            for (int i = 0; i < MT_ROWS / WAVE; ++i) t += red[i];
+            rq.q[((size_t)E * kq + 1) * FM_NM_MAX + e] = t;
+        }
+        if (e == 0 && tid < 2) q[(size_t)E * kq * 2 + tid] = make_float4(0.0f, 0.0f, 0.0f, 0.0f);     // the zero row
+    }
+}
+
+// The moment-form adjoints of every request: the pose items, then the volume items.  A workgroup takes units of
+// BATCH_UNIT consecutive items, far apart in the list, and in each the runs of consecutive regions of a request
+// together: items differ in cost by their element count and by the windows that miss the record (six requests of 61 to
+// 127 voxels a side, 64 to 256 elements: 1.50 ms with an even share of consecutive items per workgroup, 1.10 ms so).
+constexpr int BATCH_UNIT = 8;
+
+template <int CPW, bool WANT_P0, bool WANT_POSE>
+__device__ __forceinline__ void batch_adjoint_run(const BatchGeo& bg, const ra_batch_request& rq, int reg, int cnt, int nbuf,
+                                                  float* lds) {
+    const size_t row = (size_t)bg.g.E * 3;
+    am_regions<FM_NM_MAX, CPW, WANT_P0, WANT_POSE>(bg.g, reg, reg + cnt, nbuf, rq.p0, rq.xe,
+                                                   reinterpret_cast<const float4*>(rq.q), rq.grad_p0, 0,
+                                                   WANT_POSE ? rq.pose_part + reg * row : nullptr, row, lds);
+}
+
+__global__ __launch_bounds__(AM_WAVES * WAVE) __attribute__((amdgpu_waves_per_eu(4))) void k_adjoint_series_batch(
+    const BatchGeo* __restrict__ geos, const ra_batch_request* __restrict__ reqs, const int2* __restrict__ ipose,
+    const int2* __restrict__ ivol, const int* __restrict__ counts, int nbin, int nbuf) {
+    extern __shared__ float4 lds4[];
+    float* lds = reinterpret_cast<float*>(lds4);
+    const int lane = threadIdx.x & (WAVE - 1);
+    const int np = counts[1], n = np + counts[2];
+    int i = 0, end = 0;
+    for (int unit = blockIdx.x;;) {
+        if (i >= end) {
+            if ((long long)unit * BATCH_UNIT >= n) break;
+            i = unit * BATCH_UNIT;
+            end = min(i + BATCH_UNIT, n);
+            unit += gridDim.x;
+        }
+        const bool pose = i < np;
+        const int2* list = pose ? ipose : ivol - np;         // indexed by i
+        const int stop = pose ? min(end, np) : end;
+        const int2 w = list[i];
+        const int j = i + lane;
+        const int2 v = list[min(j, stop - 1)];
+        const unsigned long long other = __ballot(j >= stop || v.x != w.x || v.y != w.y + lane);
+        const int cnt = __builtin_amdgcn_readfirstlane(other ? __builtin_ctzll(other) : WAVE);
+        const int x = __builtin_amdgcn_readfirstlane(w.x), reg = __builtin_amdgcn_readfirstlane(w.y);
+        const BatchGeo& bg = geos[x];
+        i += cnt;
+        if (bg.g.nbin > nbin) continue;                      // the LDS windows hold nbin bins
+        const bool wide = bg.g.rx * bg.g.ry > 2 * AM_WAVES;
+        if (pose) {
+            if (wide) batch_adjoint_run<4, false, true>(bg, reqs[x], reg, cnt, nbuf, lds);
+            else batch_adjoint_run<2, false, true>(bg, reqs[x], reg, cnt, nbuf, lds);
+        } else {
+            if (wide) batch_adjoint_run<4, true, false>(bg, reqs[x], reg, cnt, nbuf, lds);
+            else batch_adjoint_run<2, true, false>(bg, reqs[x], reg, cnt, nbuf, lds);
+        }
     }
 }
 
 // Pose requests: element gradients summed over regions (FP64, fixed order), chained to
 // (dL/dR, dL/dt), then to (dL/dw, dL/dt), followed by one Adam step on the pose.
 // First stage of the pose update: the per-region element gradients of a pose request are
-// summed in POSE_CHUNKS fixed chunks of regions, each over the chunk's first row (FP64, in
+// summed in POSE_CHUNKS fixed chunks of regions, each into the chunk's first row (FP64, in
 // region order), so that the per-request stage below adds POSE_CHUNKS rows instead of
-// nreg.  Work items run over (chunk, element) with the element fastest (coalesced rows).
+// nreg.  A workgroup's threads take consecutive components of one chunk (coalesced rows).
 constexpr int POSE_CHUNKS = 32;
-__global__ void k_batch_pose_chunks(const Geo* __restrict__ geos, const ra_batch_request* __restrict__ reqs,
-                                    const int2* __restrict__ items, const int* __restrict__ counts) {
-    const int ne = counts[3];
-    const long long n = (long long)ne * POSE_CHUNKS;
-    for (long long it = blockIdx.x * (long long)blockDim.x + threadIdx.x; it < n;
-         it += (long long)gridDim.x * blockDim.x) {
-        const int2 w = items[it % ne];
-        const int c = (int)(it / ne);
-        const ra_batch_request& q = reqs[w.x];
+__global__ __launch_bounds__(BATCH_THREADS) void k_batch_pose_chunks(const BatchGeo* __restrict__ geos,
+                                                                     const ra_batch_request* __restrict__ reqs,
+                                                                     const int* __restrict__ counts) {
+    const int ns = counts[4];
+    for (int it = blockIdx.x; it < ns * POSE_CHUNKS; it += gridDim.x) {
+        const int slot = it / POSE_CHUNKS, c = it % POSE_CHUNKS;
+        const ra_batch_request& q = reqs[slot];
         if (q.kind != RA_REQ_POSE) continue;
-        const Geo& g = geos[w.x];
+        const int n3 = 3 * geos[slot].g.E;
         const int cs = (q.nreg + POSE_CHUNKS - 1) / POSE_CHUNKS;
         const int r0 = c * cs, r1 = min(r0 + cs, q.nreg);
         if (r0 >= r1) continue;
-        double a0 = 0.0, a1 = 0.0, a2 = 0.0;
-        for (int rg = r0; rg < r1; ++rg) {
-            const double* pp = q.pose_part + ((size_t)rg * g.E + w.y) * 3;
-            a0 += pp[0]; a1 += pp[1]; a2 += pp[2];
+        for (int t = threadIdx.x; t < n3; t += BATCH_THREADS) {
+            double* col = q.pose_part + t;
+            double a = 0.0;
+#pragma unroll 4
+            for (int rg = r0; rg < r1; ++rg) a += col[(size_t)rg * n3];
+            col[(size_t)r0 * n3] = a;
         }
-        double* out = q.pose_part + ((size_t)r0 * g.E + w.y) * 3;
-        out[0] = a0; out[1] = a1; out[2] = a2;
     }
 }
 
-__global__ __launch_bounds__(BATCH_THREADS) void k_batch_pose_update(const Geo* __restrict__ geos,
+__global__ __launch_bounds__(BATCH_THREADS) void k_batch_pose_update(const BatchGeo* __restrict__ geos,
                                                                      const ra_batch_request* __restrict__ reqs,
-                                                                     const int* __restrict__ counts) {
+                                                                     const int* __restrict__ counts, int moment) {
     __shared__ double red[12][BATCH_THREADS];
     const int ns = counts[4];
     for (int slot = blockIdx.x; slot < ns; slot += gridDim.x) {
         const ra_batch_request& q = reqs[slot];
+        if (moment && q.kind >= 0) {             // the loss: the elements' sums behind the moment table, in FP64
+            const Geo& gl = geos[slot].g;
+            const float* le = q.q + ((size_t)gl.E * (gl.K + 2 * gl.jt) + 1) * FM_NM_MAX;
+            double a = 0.0;
+            for (int e = threadIdx.x; e < gl.E; e += BATCH_THREADS) a += (double)le[e];
+            red[0][threadIdx.x] = a;
+            __syncthreads();
+            for (int w = BATCH_THREADS / 2; w > 0; w >>= 1) {
+                if ((int)threadIdx.x < w) red[0][threadIdx.x] += red[0][threadIdx.x + w];
+                __syncthreads();
+            }
+            if (threadIdx.x == 0) q.loss[0] = (float)red[0][0];
+            __syncthreads();
+        }
         if (q.kind != RA_REQ_POSE) continue;
-        const Geo& g = geos[slot];
+        const Geo& g = geos[slot].g;
         double acc[12];
         for (int i = 0; i < 12; ++i) acc[i] = 0.0;
         const int cs = (q.nreg + POSE_CHUNKS - 1) / POSE_CHUNKS;      // chunk sums from k_batch_pose_chunks
@@ -2931,7 +2781,7 @@ __global__ __launch_bounds__(BATCH_THREADS) void k_batch_pose_update(const Geo* 
 }
 
 // Volume requests: p0 -= lr * dL/dp0 over the request's box (atomic: boxes may overlap).
-__global__ __launch_bounds__(BLOCK) void k_batch_volume_apply(const Geo* __restrict__ geos,
+__global__ __launch_bounds__(BLOCK) void k_batch_volume_apply(const BatchGeo* __restrict__ geos,
                                                               const ra_batch_request* __restrict__ reqs,
                                                               const int4* __restrict__ itab,
                                                               const int2* __restrict__ items,
@@ -2939,7 +2789,7 @@ __global__ __launch_bounds__(BLOCK) void k_batch_volume_apply(const Geo* __restr
     const int n = counts[2];
     for (int it = blockIdx.x; it < n; it += gridDim.x) {
         const int2 w = items[it];
-        const Geo& g = geos[w.x];
+        const Geo& g = geos[w.x].g;
         const ra_batch_request& q = reqs[w.x];
         const Region R = region_info(g, w.y);
         float* pbase = q.p0 + (size_t)R.i0 * g.vsx + (size_t)R.j0 * g.vsy + R.k0;
@@ -3036,7 +2886,6 @@ struct Plan {
     int pair_d;         // forward takes voxels two at a time with this spread (0: one at a time)
     bool pair_ok;       // sampling and spacing allow pairs (regions with an even depth still needed)
     bool rowref;        // the dL/dp0-only adjoint may use the row-referenced form (adj_rowref)
-    bool moment;        // the batched step's adjoints may take their moment form
     bool f64_sums;      // the forward adds its partial rows into FP64 sums (else FP32, straight into s)
     bool fm;            // the forward takes the moment form (k_forward_mom) on regions gm
     Geo gm;
@@ -3085,7 +2934,7 @@ int validate(ra_ctx* ctx, const ra_grid* grid, int32_t M, int32_t F, const ra_sa
 // Region size: the largest candidate box whose LDS footprint (sample rows of every
 // wavefront, plus per-voxel sums for the adjoint) fits the byte budget per workgroup.
 size_t set_regions(Geo& g, const ra_grid* grid, double delta, int jt, bool with_gsum, int extra_rows,
-                   size_t budget, int moments = 0) {
+                   size_t budget) {
     static const int cand[][3] = {{8, 8, 16}, {8, 8, 8}, {4, 8, 8}, {4, 4, 8}, {4, 4, 4},
                                   {2, 4, 4},  {2, 2, 4}, {2, 2, 2}, {1, 1, 2}, {1, 1, 1}};
     size_t lds = 0;
@@ -3097,10 +2946,6 @@ size_t set_regions(Geo& g, const ra_grid* grid, double delta, int jt, bool with_
         int L = 2 * (jclamp + jt) + 1 + extra_rows;
         int nvpad = (rx * ry * rz + 3) & ~3;
         lds = (size_t)WAVES * L * WAVE * sizeof(float) + (with_gsum ? (size_t)WAVES * nvpad * sizeof(float) : 0);
-        if (moments)     // moment-form adjoint: one shared window of 2 jclamp + 1 table rows, four sums per voxel
-            lds = (size_t)(2 * jclamp + 1) * 2 * WAVE * sizeof(float4) + (size_t)4 * nvpad * sizeof(float);
-        if (moments == 2)   // and with element gradients: the wavefronts' FP64 partials of a chunk
-            lds += (size_t)MOM_WAVES * 3 * WAVE * sizeof(double);
         g.rx = rx; g.ry = ry; g.rz = rz;
         g.nvpad = nvpad;
         g.jclamp = jclamp;
@@ -3267,8 +3112,7 @@ bool plan_adjoint_mom(const ra_grid* grid, const ra_sampling* samp, const Geo& b
         const double rad = 0.5 * grid->spacing * std::sqrt((double)(g.rx - 1) * (g.rx - 1) + (double)(g.ry - 1) * (g.ry - 1) +
                                                            (double)(g.rz - 1) * (g.rz - 1));
         if (rad / delta > 1e4) continue;
-        // at least 13 bins: a window also holds the wavefronts' partial element gradients
-        g.jclamp = std::max(6, (int)std::ceil(rad / delta * (1.0 + 1e-6)) + 1);
+        g.jclamp = (int)std::ceil(rad / delta * (1.0 + 1e-6)) + 1;
         g.jclampf = (float)g.jclamp;
         g.jt = (int)std::floor(samp->trunc * samp->sigma / delta + 0.5);
         g.nbin = 2 * g.jclamp + 1;
@@ -3368,15 +3212,6 @@ void make_plan(ra_ctx* ctx, const ra_grid* grid, int32_t M, int32_t F, const ra_
     {
         const double km = P.ga.kmargin + 1.0, ds = delta / sigma;
         P.rowref = P.exact && g.ktype == RA_KERNEL_GAUSSIAN && P.ga.kmargin <= RS_MAX && km * km * ds * ds / 2.0 <= 75.0;
-    }
-    // moment form of the batched step's adjoints where its truncation bound holds
-    {
-        double fact = 1.0;
-        for (int n = 2; n <= NMOM; ++n) fact *= n;
-        const double bound = 1.791 * std::pow(0.5 * delta / sigma, NMOM) * std::sqrt((NMOM + 1) / fact);
-        P.moment = P.exact && g.ktype == RA_KERNEL_GAUSSIAN && bound <= MOM_TOL;
-        g.mom_dd = delta / sigma;
-        g.mom_sigma = sigma;
     }
     P.lds_fwd = set_regions(P.gf, grid, delta, P.jt, false, P.pair_d, LDS_FWD_BUDGET);
     // pairs are (k, k+1) of the visiting order, so the forward region needs an even rz
@@ -4094,7 +3929,7 @@ int ra_probe_rates(ra_ctx* ctx, double* fma_per_s, double* exp_per_s, void* stre
 
 extern "C" {
 
-size_t ra_batch_geo_bytes(void) { return sizeof(Geo); }
+size_t ra_batch_geo_bytes(void) { return sizeof(BatchGeo); }
 
 int ra_batch_describe(ra_ctx* ctx, const ra_grid* box, int64_t stride_x, int64_t stride_y, int32_t M,
                       const ra_sampling* samp, void* geo, ra_batch_info* info) {
@@ -4108,33 +3943,43 @@ int ra_batch_describe(ra_ctx* ctx, const ra_grid* box, int64_t stride_x, int64_t
         return fail(ctx, RA_EINVAL, "volume strides smaller than the box");
     Plan P;
     make_plan(nullptr, box, M, 1, samp, P);
-    Geo g = P.g;
+    BatchGeo bg;
+    std::memset(&bg, 0, sizeof(bg));
+    Geo& g = bg.g;
+    g = P.g;
     g.vsx = stride_x;
     g.vsy = stride_y;
     g.gsx = (long long)box->ny * box->nz;
     g.gsy = box->nz;
-    // the batched forward pairs z-neighbours when it can: D more rows (the adjoint stages
+    // the batched row-form forward pairs z-neighbours when it can: D more rows (the adjoint stages
     // them too, and never reads them)
     const int pd = (P.pair_ok && !(g.rz & 1)) ? PAIR_D : 0;
     g.L += pd;
-    std::memcpy(geo, &g, sizeof(Geo));
+    // the moment forms on the same regions, where their series and LDS allow it
+    const double delta = samp->c / samp->fs;
+    g.jt = P.jt;
+    g.nbin = 2 * g.jclamp + 1;
+    set_units(g, box, delta);
+    bg.nm = P.exact ? series_terms(ctx, samp, true) : 0;
+    const bool moment = bg.nm && ctx->series_tail[FM_NM_MAX] <= AM_TOL && g.rz <= FM_RZ && g.nbin <= BATCH_BINS_MAX &&
+                        fm_lds(bg.nm, g.nbin, g.jt) <= 160 * 1024 && am_lds(g.nbin, 1) <= 160 * 1024;
+    if (moment) {
+        bg.series = ctx->series;
+        bg.series8 = ctx->series8;
+    }
+    std::memcpy(geo, &bg, sizeof(BatchGeo));
     info->nreg = g.nreg;
     info->jt = P.jt;
     info->exact = P.exact ? 1 : 0;
     info->pair_d = pd;
-    info->lmax = g.L;
+    // rows of LDS of 1 KiB: the row form's samples, or what the moment-form forward needs
+    info->lmax = moment ? std::max(g.L, (int)((fm_lds(bg.nm, g.nbin, g.jt) + 1023) / 1024)) : g.L;
     info->nvpad = g.nvpad;
     info->rx = g.rx; info->ry = g.ry; info->rz = g.rz;
-    // the moment form of the adjoints where the single-call plan takes it and its LDS fits one
-    // workgroup on these regions
-    Plan Pm;
-    make_plan(nullptr, box, M, 1, samp, Pm);
-    const int nbin = 2 * g.jclamp + 1;
-    const size_t lds_p = (size_t)nbin * 2 * WAVE * sizeof(float4) + (size_t)MOM_WAVES * 3 * WAVE * sizeof(double);
-    const size_t lds_v = (size_t)nbin * 2 * WAVE * sizeof(float4) + (size_t)4 * g.nvpad * sizeof(float);
-    info->moment = (Pm.moment && nbin <= MOM_WAVES * MOM_PER && std::max(lds_p, lds_v) <= 160 * 1024) ? 1 : 0;
-    info->nbin = nbin;
-    info->q_bytes = info->moment ? ((int64_t)M * (samp->K + 2 * P.jt) + 1) * NMOM * (int64_t)sizeof(float) : 0;
+    info->moment = moment ? 1 : 0;
+    info->nbin = g.nbin;
+    // the table with its zero row, then one loss per element
+    info->q_bytes = moment ? (((int64_t)M * (samp->K + 2 * P.jt) + 1) * FM_NM_MAX + M) * (int64_t)sizeof(float) : 0;
     return RA_OK;
 }
 
@@ -4155,9 +4000,22 @@ int ra_batch_tables(ra_ctx* ctx, const void* geo, void* vtab, void* itab, void* 
 
 namespace {
 
+// Pose updates, losses of the moment form, and volume updates.
+int batch_finish(ra_ctx* ctx, const ra_batch* b, uint32_t flags, hipStream_t st) {
+    const BatchGeo* geos = (const BatchGeo*)b->geos;
+    const int grid = b->grid_blocks > 0 ? b->grid_blocks : 1024;
+    hipLaunchKernelGGL(k_batch_pose_chunks, dim3(grid), dim3(BATCH_THREADS), 0, st, geos, b->reqs, b->counts);
+    hipLaunchKernelGGL(k_batch_pose_update, dim3(grid), dim3(BATCH_THREADS), 0, st, geos, b->reqs, b->counts, b->moment);
+    if (flags & RA_BATCH_APPLY_UPDATES)
+        hipLaunchKernelGGL(k_batch_volume_apply, dim3(grid), dim3(BLOCK), 0, st, geos, b->reqs, (const int4*)b->itab,
+                           (const int2*)b->items_vol, b->counts);
+    RA_HIP(ctx, hipGetLastError());
+    return RA_OK;
+}
+
 template <int JT, bool EXACT, int D>
 int batch_step_t(ra_ctx* ctx, const ra_batch* b, uint32_t flags, hipStream_t st) {
-    const Geo* geos = (const Geo*)b->geos;
+    const BatchGeo* geos = (const BatchGeo*)b->geos;
     const float4* vtab = (const float4*)b->vtab;
     const int4* itab = (const int4*)b->itab;
     const int2* ifwd = (const int2*)b->items_fwd;
@@ -4173,39 +4031,34 @@ int batch_step_t(ra_ctx* ctx, const ra_batch* b, uint32_t flags, hipStream_t st)
     RA_HIP(ctx, allow_full_lds(kf));
     RA_HIP(ctx, allow_full_lds(kp));
     RA_HIP(ctx, allow_full_lds(kv));
-    hipLaunchKernelGGL(k_batch_elements, dim3(64), dim3(256), 0, st, geos, b->reqs, ielem, b->counts);
+    hipLaunchKernelGGL(k_batch_elements, dim3(64), dim3(256), 0, st, b->reqs, ielem, b->counts);
     hipLaunchKernelGGL(k_batch_zero, dim3(grid), dim3(256), 0, st, geos, b->reqs, b->counts);
     hipLaunchKernelGGL(kf, dim3(grid), dim3(BLOCK), lds_f, st, geos, b->reqs, vtab, itab, ifwd, b->counts, b->lmax);
     hipLaunchKernelGGL(k_batch_residual, dim3(grid), dim3(BATCH_THREADS), 0, st, geos, b->reqs, b->counts);
-    if (b->moment) {
-        // moment form: coefficients, each request's table from its dL/ds, then the adjoints
-        const size_t lds_v = (size_t)b->nbin * 2 * WAVE * sizeof(float4) + (size_t)4 * b->nvpad * sizeof(float);
-        const size_t lds_p = (size_t)b->nbin * 2 * WAVE * sizeof(float4) + (size_t)MOM_WAVES * 3 * WAVE * sizeof(double);
-        auto mp = k_adjoint_mom_batch<false, true>;
-        auto mv = k_adjoint_mom_batch<true, false>;
-        RA_HIP(ctx, allow_full_lds(mp));
-        RA_HIP(ctx, allow_full_lds(mv));
-        hipLaunchKernelGGL(k_batch_moment_coefs, dim3(1), dim3(2 * b->jt + 1), 0, st, geos, b->reqs, b->counts, b->jt,
-                           b->coef);
-        hipLaunchKernelGGL(k_batch_moment_table, dim3(grid), dim3(256), 0, st, geos, b->reqs, b->counts, b->jt,
-                           b->coef);
-        hipLaunchKernelGGL(mp, dim3(grid), dim3(MOM_WAVES * WAVE), lds_p, st, geos, b->reqs, vtab, itab, ipose,
-                           b->counts, 1, b->jt, b->nbin);
-        hipLaunchKernelGGL(mv, dim3(grid), dim3(MOM_WAVES * WAVE), lds_v, st, geos, b->reqs, vtab, itab, ivol,
-                           b->counts, 2, b->jt, b->nbin);
-    } else {
-        hipLaunchKernelGGL(kp, dim3(grid), dim3(BLOCK), lds_a, st, geos, b->reqs, vtab, itab, ipose, b->counts, 1,
-                           b->lmax);
-        hipLaunchKernelGGL(kv, dim3(grid), dim3(BLOCK), lds_a, st, geos, b->reqs, vtab, itab, ivol, b->counts, 2,
-                           b->lmax);
-    }
-    hipLaunchKernelGGL(k_batch_pose_chunks, dim3(grid), dim3(256), 0, st, geos, b->reqs, ielem, b->counts);
-    hipLaunchKernelGGL(k_batch_pose_update, dim3(grid), dim3(BATCH_THREADS), 0, st, geos, b->reqs, b->counts);
-    if (flags & RA_BATCH_APPLY_UPDATES)
-        hipLaunchKernelGGL(k_batch_volume_apply, dim3(grid), dim3(BLOCK), 0, st, geos, b->reqs, itab, ivol,
-                           b->counts);
-    RA_HIP(ctx, hipGetLastError());
-    return RA_OK;
+    hipLaunchKernelGGL(kp, dim3(grid), dim3(BLOCK), lds_a, st, geos, b->reqs, vtab, itab, ipose, b->counts, 1,
+                       b->lmax);
+    hipLaunchKernelGGL(kv, dim3(grid), dim3(BLOCK), lds_a, st, geos, b->reqs, vtab, itab, ivol, b->counts, 2,
+                       b->lmax);
+    return batch_finish(ctx, b, flags, st);
+}
+
+// The moment form: positions and cleared signals, the forward, residuals with losses and tables, both kinds of
+// adjoint in one launch.
+int batch_step_mom(ra_ctx* ctx, const ra_batch* b, uint32_t flags, hipStream_t st) {
+    const BatchGeo* geos = (const BatchGeo*)b->geos;
+    const int2* ielem = (const int2*)b->items_elem;
+    const int grid = b->grid_blocks > 0 ? b->grid_blocks : 1024;
+    const size_t lds_f = (size_t)b->lmax * 1024;
+    const int nbuf = am_lds(b->nbin, 2) <= 160 * 1024 ? 2 : 1;
+    RA_HIP(ctx, allow_full_lds(k_forward_mom_batch));
+    RA_HIP(ctx, allow_full_lds(k_adjoint_series_batch));
+    hipLaunchKernelGGL(k_batch_begin, dim3(grid), dim3(BATCH_THREADS), 0, st, geos, b->reqs, ielem, b->counts);
+    hipLaunchKernelGGL(k_forward_mom_batch, dim3(grid), dim3(FM_WAVES * WAVE), lds_f, st, geos, b->reqs,
+                       (const int2*)b->items_fwd, b->counts, (int)lds_f);
+    hipLaunchKernelGGL(k_batch_series, dim3(grid), dim3(MT_ROWS), 0, st, geos, b->reqs, ielem, b->counts);
+    hipLaunchKernelGGL(k_adjoint_series_batch, dim3(std::min(grid, NCU)), dim3(AM_WAVES * WAVE), am_lds(b->nbin, nbuf), st,
+                       geos, b->reqs, (const int2*)b->items_pose, (const int2*)b->items_vol, b->counts, b->nbin, nbuf);
+    return batch_finish(ctx, b, flags, st);
 }
 
 }  // namespace
@@ -4222,21 +4075,18 @@ extern "C" int ra_batch_step(ra_ctx* ctx, const ra_batch* b, uint32_t flags, voi
         return fail(ctx, RA_EINVAL, "lmax / nvpad exceed the LDS of a workgroup");
     const bool ex = b->exact != 0;
     if (b->moment) {
-        // the moment form exists for the exact Gaussian window only; its LDS window holds nbin bins
-        // of 2 x 64 float4 plus the dL/dp0 sums or the wavefronts' FP64 pose partials
+        // the moment form exists for the exact Gaussian window only; its LDS windows hold nbin bins
         if (!b->coef) return fail(ctx, RA_EINVAL, "the moment form needs the coefficient scratch (coef)");
         if (!ex || b->jt < 1 || b->jt > JMAX) return fail(ctx, RA_EINVAL, "moment form with a window it does not cover");
-        if (b->nbin < 1 || b->nbin > MOM_WAVES * MOM_PER)
+        if (b->nbin < 1 || b->nbin > BATCH_BINS_MAX)
             return fail(ctx, RA_EINVAL, "nbin must be the value ra_batch_describe reported");
-        const size_t win = (size_t)b->nbin * 2 * WAVE * sizeof(float4);
-        if (win + std::max((size_t)4 * b->nvpad * sizeof(float), (size_t)MOM_WAVES * 3 * WAVE * sizeof(double)) >
-            160 * 1024)
-            return fail(ctx, RA_EINVAL, "nbin / nvpad exceed the LDS of a workgroup");
+        if (am_lds(b->nbin, 1) > 160 * 1024) return fail(ctx, RA_EINVAL, "nbin exceeds the LDS of a workgroup");
     }
     RA_HIP(ctx, hipSetDevice(ctx->device));
     hipStream_t st = (hipStream_t)stream;
     if (b->pair_d != 0 && (b->pair_d != PAIR_D || !ex))
         return fail(ctx, RA_EINVAL, "pair_d must be the value ra_batch_describe reported");
+    if (b->moment) return batch_step_mom(ctx, b, flags, st);
 #define RA_CASE(n)                                                                                      \
     if (ex && b->jt == n)                                                                               \
         return b->pair_d ? batch_step_t<n, true, PAIR_D>(ctx, b, flags, st)                             \

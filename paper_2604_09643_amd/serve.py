@@ -341,7 +341,7 @@ class GpuExecutor:
         self.h_reqs = torch.zeros_like(self.d_reqs, device="cpu").pin_memory()
         self.h_items = torch.zeros((4, max_items, 2), dtype=torch.int32).pin_memory()
         self.h_counts = torch.zeros(8, dtype=torch.int32).pin_memory()
-        # moment-form coefficients of the batched adjoints (8 per window step, at most 81 steps)
+        # coefficient scratch of the batched moment form (8 per window step, at most 81 steps)
         self.d_coef = torch.zeros(8 * 81, dtype=torch.float32, device=dev)
         # one loss per slot, read back with one copy per tick
         self.d_loss = torch.zeros(slots, dtype=torch.float32, device=dev)
