@@ -99,8 +99,10 @@ constexpr int FM_REFS = 2;            // element chunks whose references it comp
 constexpr int FM_FIELDS = 13;         // floats of a reference
 constexpr int FM_RZ = 8;              // voxels of a column it unrolls
 constexpr int FM_SIDE = 16;           // its largest region side
-constexpr int FM_NM_MAX = 8;          // its largest number of moments
+constexpr int MOM_MAX = 12;           // largest number of moments
+constexpr int MOM_G = 8;              // and the Gaussian's
 constexpr double FM_TOL = 2e-7;       // its largest admitted expansion error, relative to the peak
+constexpr double FM_EDGE = 0.004;     // its largest phi at the window's edge (other profiles), relative to the peak
 constexpr double AM_TOL = 2.5e-8;     // that error where the series' derivative is used (its 8 terms' grows 8-fold in rms)
 constexpr int AM_WAVES = 16;          // wavefronts of the moment-form adjoints' region workgroup, one per CU
 constexpr int AM_REFS = 3;            // references held: this chunk's, the next one's and the one after
@@ -200,6 +202,12 @@ struct Geo {
     int nbin;                      // centre samples of a region, 2 jclamp + 1
     float unit_h, unit_l;          // 2 / delta
     float hs_u, hs_l;              // grid spacing in units (double-float)
+    // terms of the other profiles that no polynomial in t holds: of the window's outermost samples kc +- jt, in the
+    // window for some offsets only, and of the exponential's kink at kc (see edge_phi)
+    int xkind;                     // 0 none, 1 an outermost sample, 2 that and the centre
+    float thr, ev[4], es;
+    unsigned flip;                 // 0: the outermost sample on t's side; sign bit: the one on the other side
+    float kx;                      // centre: t/2 exp2(kx |t|)
 };
 
 // Workgroup -> region, so that each compute die (XCD) gets a contiguous run of
@@ -772,7 +780,7 @@ __global__ __launch_bounds__(BLOCK) void k_forward(Geo g, const float* __restric
 }
 
 // ------------------------------------------------------------------------------------------
-// forward in moment form (Gaussian profile)
+// forward in moment form (Gaussian, exponential and power-law profiles)
 // ------------------------------------------------------------------------------------------
 // With lengths in units of delta / 2, a pair's distance is d = 2 kc + t with kc its nearest sample and
 // |t| <= 1.  The window row kc + j carries phi((t/2 - j) delta), which on |t| <= 1 is a polynomial
@@ -812,13 +820,13 @@ __global__ __launch_bounds__(BLOCK) void k_forward(Geo g, const float* __restric
 // expansion adds to that: 5.7 ms with 8x8x8 regions, two workgroups to a CU; hence the largest regions
 // that the LDS holds, one workgroup of 16 wavefronts to a CU.
 struct MomCoef {
-    float d[(JMAX + 1) * FM_NM_MAX];   // D_n(j) / delta at j * FM_NM_MAX + n, j >= 0; D_n(-j) = (-1)^(n+1) D_n(j)
+    float d[(JMAX + 1) * MOM_MAX];     // D_n(j) / delta at j * MOM_MAX + n, j >= 0; D_n(-j) = (-1)^(n+1) D_n(j)
 };
 
 __device__ __forceinline__ float mom_coef(const MomCoef& m, int n, int j, int jt) {
     const int a = j < 0 ? -j : j;
     if (a > jt) return 0.0f;
-    const float v = m.d[a * FM_NM_MAX + n];
+    const float v = m.d[a * MOM_MAX + n];
     return (j < 0 && !(n & 1)) ? -v : v;
 }
 
@@ -834,7 +842,10 @@ constexpr size_t fm_off_ref(int nm, int nbin) { return (size_t)(nbin + 1) * fm_s
 constexpr size_t fm_off_axis(int nm, int nbin) { return fm_off_ref(nm, nbin) + FM_REFS * FM_FIELDS * WAVE; }
 constexpr size_t fm_off_red(int nm, int nbin) { return fm_off_axis(nm, nbin) + 3 * FM_SIDE * 4; }
 constexpr size_t fm_off_dt(int nm, int nbin) { return fm_off_red(nm, nbin) + 4 * FM_WAVES_BIG; }
-constexpr size_t fm_lds(int nm, int nbin, int jt) { return (fm_off_dt(nm, nbin) + nm * fm_dlen(jt)) * sizeof(float); }
+constexpr size_t fm_off_edge(int nm, int nbin, int jt) { return fm_off_dt(nm, nbin) + (nm * fm_dlen(jt) + 63) / 64 * 64; }
+constexpr size_t fm_lds(int nm, int nbin, int jt, bool edge) {       // with edge sums, [row][lane]
+    return (fm_off_edge(nm, nbin, jt) + (edge ? (size_t)(nbin + 2 * jt) * WAVE : 0)) * sizeof(float);
+}
 
 // What bounds the sums of a region's bins: sum |p0|, and per axis the sum over the lines along it of the
 // largest |p0| in each (NaN if any p0 is not finite).
@@ -995,8 +1006,41 @@ __device__ __forceinline__ FmPair fm_pair(const FmCol& c, float dc2, float hdc, 
 
 // The adds of one column of FM_RZ voxels (p0 values pv, zero past the grid); ez: N of each voxel about
 // the column's centre.  INT: fixed-point sums.
-template <int NM, bool INT>
-__device__ __forceinline__ void fm_column(const float (&pv)[FM_RZ], const float (&ez)[FM_RZ], const FmCol& c, float scale,
+// What a pair adds beyond its polynomial, at one of the window's outermost samples kc +- jt, each of which is in
+// the window for |u| <= T w only.  If the window reaches less than half a sample past kc + jt - 1/2 .. (thr > 0, the
+// polynomial holds |j| < jt), that is the sample on t's side, for |t| >= thr; otherwise the polynomial holds |j| <= jt and
+// the sample on the other side is taken back for |t| > thr.  phi is odd, so both are sgn(t) F(|t|); F: four terms.
+struct Edge {
+    float v, d;                            // value and its derivative in t (0 inside thr)
+    unsigned row;                          // 0: kc - jt, or the byte offset of kc + jt
+};
+
+struct EdgeCoef {
+    float thr, e0, e1, e2, e3;
+    unsigned flip, far;
+};
+
+__device__ __forceinline__ EdgeCoef edge_coef(const Geo& g, float scale) {     // in vector registers
+    EdgeCoef c{g.thr, g.ev[0] * scale, g.ev[1] * scale, g.ev[2] * scale, g.ev[3] * scale, g.flip,
+               (unsigned)g.jt * 2u * WAVE * 4u};
+    asm volatile("" : "+v"(c.thr), "+v"(c.e0), "+v"(c.e1), "+v"(c.e2), "+v"(c.e3), "+v"(c.flip), "+v"(c.far));
+    return c;
+}
+
+__device__ __forceinline__ Edge edge_phi(const EdgeCoef& c, float t) {
+    const float a = fabsf(t);
+    const bool in = a >= c.thr;
+    const float f = fmaf(a, fmaf(a, fmaf(a, c.e3, c.e2), c.e1), c.e0);
+    const float d = fmaf(a, fmaf(3.0f * a, c.e3, 2.0f * c.e2), c.e1);
+    Edge e;
+    e.v = in ? copysignf(1.0f, t) * f : 0.0f;
+    e.d = in ? d : 0.0f;
+    e.row = ~(unsigned)((int)(__float_as_uint(t) ^ c.flip) >> 31) & c.far;
+    return e;
+}
+
+template <int NM, bool INT, int X>
+__device__ __forceinline__ void fm_column(const Geo& g, const EdgeCoef& xc, unsigned eoff, const float (&pv)[FM_RZ], const float (&ez)[FM_RZ], const FmCol& c, float scale,
                                           float lo, float hi, unsigned off0, unsigned str, char* sums) {
     const float dc2 = c.dc * c.dc, hdc = 0.5f * c.dc;
 #pragma unroll
@@ -1016,6 +1060,22 @@ __device__ __forceinline__ void fm_column(const float (&pv)[FM_RZ], const float 
                 __hip_atomic_fetch_add(dst, q, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
             }
             if (n + 1 < NM) q *= p.t;
+        }
+        if (X) {                               // sums of single rows: of kc - jt at er
+            const float a = INT ? pv[k] * p.rs * scale : pv[k] * p.rs;
+            const unsigned er = (__float_as_uint(p.rm) << 8) + eoff;
+            const Edge e = edge_phi(xc, p.t);
+            auto add = [&](unsigned at, float v) {
+                if (INT)
+                    __hip_atomic_fetch_add(reinterpret_cast<int*>(sums + at), cvt_round_i32(v), __ATOMIC_RELAXED,
+                                           __HIP_MEMORY_SCOPE_WORKGROUP);
+                else if (v != 0.0f)
+                    __hip_atomic_fetch_add(reinterpret_cast<float*>(sums + at), v, __ATOMIC_RELAXED,
+                                           __HIP_MEMORY_SCOPE_WORKGROUP);
+            };
+            add(er + e.row, INT || e.v != 0.0f ? a * e.v : 0.0f);
+            if (X == 2)
+                add(er + xc.far / 2u, (a * 0.5f * g.es) * (p.t * __builtin_amdgcn_exp2f(g.kx * fabsf(p.t))));
         }
     }
 }
@@ -1059,7 +1119,7 @@ __device__ __forceinline__ FmBound fm_bound(const Geo& g, const Region& R, const
 
 // The forward work of one region for element chunks c0, c0 + cstep, ...  `lds` is the workgroup's LDS
 // (fm_lds bytes) with the D table in place.  Every thread of the workgroup must call it.
-template <int NM, int NW, typename SumT>
+template <int NM, int NW, int X, typename SumT>
 __device__ __forceinline__ void fm_region(const Geo& g, int reg, int c0, int cstep, const float* __restrict__ p0,
                                           const float* __restrict__ xe, SumT* __restrict__ s, float* lds) {
     constexpr int STR = fm_stride(NM);
@@ -1070,15 +1130,19 @@ __device__ __forceinline__ void fm_region(const Geo& g, int reg, int c0, int cst
     float* refs = lds + fm_off_ref(NM, nbin);                // [slot][field][lane]
     float4* axis = reinterpret_cast<float4*>(lds + fm_off_axis(NM, nbin));
     const float* dt = lds + fm_off_dt(NM, nbin);
+    float* edge = lds + fm_off_edge(NM, nbin, jt);           // sums of single rows, [row][lane]
     const Region R = region_info(g, reg);
     const float* pbase = p0 + (size_t)R.i0 * g.vsx + (size_t)R.j0 * g.vsy + R.k0;
     const int nchunk = (g.E + WAVE - 1) / WAVE;
     const int ncol = R.ni * R.nj, mine = (ncol + NW - 1) / NW;
     for (int i = tid; i < (nbin + 1) * STR / 4; i += NW * WAVE)
         reinterpret_cast<float4*>(lds)[i] = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
+    if (X)
+        for (int i = tid; i < rows * WAVE; i += NW * WAVE) edge[i] = 0.0f;
     fm_axis_table(g, tid, axis);
     const FmBound bound = fm_bound<NW>(g, R, pbase, lds + fm_off_red(NM, nbin));
     const float rlo = FM_MAGIC - 2.0f * g.jclampf, rhi = FM_MAGIC + 2.0f * g.jclampf;
+    const float ies = X ? 1.0f / g.es : 0.0f;
 
     int slot = FM_REFS;
     for (int c = c0; c < nchunk; c += cstep, ++slot) {
@@ -1113,6 +1177,10 @@ __device__ __forceinline__ void fm_region(const Geo& g, int reg, int c0, int cst
         unsigned off0 = (unsigned)lane * 4u + (unsigned)g.jclamp * (STR * 4u) - 0xC00000u * (STR * 4u);
         unsigned str = STR * 4u;
         asm volatile("" : "+v"(off0), "+v"(str));            // in vector registers: scalar operands halve the issue rate
+        // row of a bin's sample kc - jt; FM_MAGIC << 8 is 0xC0000000
+        unsigned eoff = (unsigned)(fm_off_edge(NM, nbin, jt) + lane + g.jclamp * WAVE) * 4u - 0xC0000000u;
+        asm volatile("" : "+v"(eoff));
+        const EdgeCoef xc = edge_coef(g, g.es);
         for (int z0 = 0; z0 < R.nk; z0 += FM_RZ) {
             const int nz = R.nk - z0;
             const float4 tz = axis[2 * FM_SIDE + z0 / FM_RZ];
@@ -1143,9 +1211,9 @@ __device__ __forceinline__ void fm_region(const Geo& g, int reg, int c0, int cst
                 fm_axis(axis[FM_SIDE + j], Dy, Dyl, magic, yh, yl);
                 const FmCol cl = fm_col(xh + yh, xl + yl, dh, dh2, uc0);
                 if (fixed)
-                    fm_column<NM, true>(pv, ez, cl, scale, rlo, rhi, off0, str, reinterpret_cast<char*>(lds));
+                    fm_column<NM, true, X>(g, xc, eoff, pv, ez, cl, scale, rlo, rhi, off0, str, reinterpret_cast<char*>(lds));
                 else
-                    fm_column<NM, false>(pv, ez, cl, 1.0f, rlo, rhi, off0, str, reinterpret_cast<char*>(lds));
+                    fm_column<NM, false, X>(g, xc, eoff, pv, ez, cl, 1.0f, rlo, rhi, off0, str, reinterpret_cast<char*>(lds));
             }
         }
         __syncthreads();
@@ -1164,7 +1232,9 @@ __device__ __forceinline__ void fm_region(const Geo& g, int reg, int c0, int cst
 #pragma unroll
                 for (int i = 0; i < 4; ++i) {
                     const int e = c * WAVE + e0 + i, k = __float_as_int(kbe[i]) + r0 + li;
-                    const float x = v[i] * inv[i];
+                    float x = v[i] * inv[i];
+                    if (X && r0 + li < rows)
+                        x = fmaf((float)reinterpret_cast<const int*>(edge)[(r0 + li) * WAVE + e0 + i], inv[i] * ies, x);
                     if (e < g.E && x != 0.0f && r0 + li < rows && k >= 0 && k < K)
                         atomicAdd(s + (size_t)e * K + k, (SumT)x);
                 }
@@ -1201,7 +1271,7 @@ __device__ __forceinline__ void fm_region(const Geo& g, int reg, int c0, int cst
             // FP32 sums: plain sums over the window rows, lane = element
             const float* acc = lds + lane;
             for (int r = wv; r < rows; r += NW) {
-                float v = 0.0f;
+                float v = X ? edge[r * WAVE + lane] * ies : 0.0f;
                 for (int b = max(r - 2 * jt, 0); b <= min(r, nbin - 1); ++b)
 #pragma unroll
                     for (int n = 0; n < NM; ++n)
@@ -1213,11 +1283,13 @@ __device__ __forceinline__ void fm_region(const Geo& g, int reg, int c0, int cst
         __syncthreads();
         for (int i = tid; i < nbin * STR / 4; i += NW * WAVE)
             reinterpret_cast<float4*>(lds)[i] = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
+        if (X)
+            for (int i = tid; i < rows * WAVE; i += NW * WAVE) edge[i] = 0.0f;
         __syncthreads();
     }
 }
 
-template <int NM, int NW, typename SumT>
+template <int NM, int NW, int X, typename SumT>
 __global__ __launch_bounds__(NW * WAVE) __attribute__((amdgpu_waves_per_eu(4))) void k_forward_mom(
     Geo g, MomCoef mc, int nslice, const float* __restrict__ p0, const float* __restrict__ xe, SumT* __restrict__ s) {
     extern __shared__ float lds[];
@@ -1226,7 +1298,7 @@ __global__ __launch_bounds__(NW * WAVE) __attribute__((amdgpu_waves_per_eu(4))) 
     for (int i = threadIdx.x; i < NM * dl; i += NW * WAVE)
         dt[i] = mom_coef(mc, i / dl, i % dl - FM_PAD - g.jt, g.jt);
     const int b = region_of_block(blockIdx.x, gridDim.x);
-    fm_region<NM, NW, SumT>(g, b / nslice, b % nslice, nslice, p0, xe, s, lds);
+    fm_region<NM, NW, X, SumT>(g, b / nslice, b % nslice, nslice, p0, xe, s, lds);
 }
 
 // ------------------------------------------------------------------------------------------
@@ -1586,7 +1658,7 @@ __global__ __launch_bounds__(BLOCK) void k_adjoint(Geo g, const float* __restric
 }
 
 // ------------------------------------------------------------------------------------------
-// adjoints in moment form (Gaussian profile)
+// adjoints in moment form (Gaussian, exponential and power-law profiles)
 // ------------------------------------------------------------------------------------------
 // The transpose of the forward's moment form: the window sum of a pair with nearest sample kc and offset t is
 //   sum_j r[kc + j] phi((t/2 - j) delta) = delta sum_n t^n Q_n[kc],  Q_n[k] = sum_j r[k + j] D_n(j) / delta,
@@ -1596,12 +1668,13 @@ __global__ __launch_bounds__(BLOCK) void k_adjoint(Geo g, const float* __restric
 //
 // The table built once per call from dL/ds: rows
 // Q[e][kk][n] = sum_{|j| <= jt} r[e][k + j] D_n(j) / delta for kk in [0, K + 2 jt), k = kk - jt, with dL/ds
-// zero outside [0, K); each row is two float4 (n = 0..3, 4..7).  One zero row follows the last element's
+// zero outside [0, K); each row is NQ float4 (4 terms each).  One zero row follows the last element's
 // rows.  The window's two legs are taken together, since D_n(-j) = (-1)^(n+1) D_n(j): 10 VALU for two
 // samples.  A row of dL/ds is staged in LDS; the bound is writing the table (275 MB on the sweep: 0.118 ms
 // with a thread's 25 taps read from memory, 0.069 ms so).
 constexpr int MT_ROWS = 256;          // table rows per workgroup
 
+template <int NQ>
 __global__ __launch_bounds__(MT_ROWS) void k_moment_series(int E, int K, int jt, MomCoef mc, const float* __restrict__ r,
                                                            float4* __restrict__ q) {
     __shared__ float row[MT_ROWS + 2 * JMAX];
@@ -1614,20 +1687,20 @@ __global__ __launch_bounds__(MT_ROWS) void k_moment_series(int E, int K, int jt,
     }
     __syncthreads();
     const int kk = kk0 + threadIdx.x;
-    if (blockIdx.x == 0 && threadIdx.x < 2) q[(size_t)E * kq * 2 + threadIdx.x] = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
+    if (blockIdx.x == 0 && threadIdx.x < NQ) q[(size_t)E * kq * NQ + threadIdx.x] = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
     if (kk >= kq) return;
     const float* w = row + threadIdx.x + jt;                 // r at the row's own sample
-    float acc[FM_NM_MAX];
+    float acc[4 * NQ];
 #pragma unroll
-    for (int n = 0; n < FM_NM_MAX; ++n) acc[n] = w[0] * mc.d[n];
+    for (int n = 0; n < 4 * NQ; ++n) acc[n] = w[0] * mc.d[n];
     for (int j = 1; j <= jt; ++j) {
         const float a = w[j], b = w[-j], sum = a + b, dif = a - b;
 #pragma unroll
-        for (int n = 0; n < FM_NM_MAX; ++n) acc[n] = fmaf(n & 1 ? sum : dif, mc.d[j * FM_NM_MAX + n], acc[n]);
+        for (int n = 0; n < 4 * NQ; ++n) acc[n] = fmaf(n & 1 ? sum : dif, mc.d[j * MOM_MAX + n], acc[n]);
     }
-    float4* out = q + 2 * ((size_t)e * kq + kk);
-    out[0] = make_float4(acc[0], acc[1], acc[2], acc[3]);
-    out[1] = make_float4(acc[4], acc[5], acc[6], acc[7]);
+    float4* out = q + NQ * ((size_t)e * kq + kk);
+#pragma unroll
+    for (int i = 0; i < NQ; ++i) out[i] = make_float4(acc[4 * i], acc[4 * i + 1], acc[4 * i + 2], acc[4 * i + 3]);
 }
 
 // Adjoints from those tables: dL/dp0 (WANT_P0) and/or the element gradients (WANT_POSE) of regions reg0 ..
@@ -1648,23 +1721,32 @@ __global__ __launch_bounds__(MT_ROWS) void k_moment_series(int E, int K, int jt,
 // sum over a pair comes to 25 cycles, 28 measured (sweep of 128x128x64 voxels and 8192 elements: 7.14 ms
 // before, with 35 instructions per pair, 6.5 ms now; with the element gradients 12.4 -> 10.4 ms).
 constexpr int AM_FIELDS = 11;         // floats of a reference
-constexpr int AM_BINS_MIN = 13;       // bins a window's LDS holds at least: it also takes the wavefronts' partials
-constexpr int am_win(int nbin) { return (nbin > AM_BINS_MIN ? nbin : AM_BINS_MIN) * 2 * WAVE; }      // float4 per window
-constexpr size_t am_off_axis(int nbin, int nbuf) { return (size_t)nbuf * am_win(nbin) * 4 + AM_REFS * AM_FIELDS * WAVE; }
-constexpr size_t am_lds(int nbin, int nbuf) { return (am_off_axis(nbin, nbuf) + 3 * FM_SIDE * 4) * sizeof(float); }
+constexpr int am_nq(int nm) { return (nm + 3) / 4; }         // float4 per table row
+// float4 per window: the table rows (at least what the wavefronts' partials need), then the samples of dL/ds that
+// the profiles with edge terms read, [row][lane] (xrows of them, 0 for the Gaussian)
+constexpr int am_rows(int nbin, int nq) { return nbin * nq * WAVE > 1536 ? nbin * nq * WAVE : 1536; }
+constexpr int am_win(int nbin, int nq, int xrows) { return am_rows(nbin, nq) + xrows * WAVE / 4; }
+constexpr size_t am_off_axis(int nbin, int nq, int xrows, int nbuf) {
+    return (size_t)nbuf * am_win(nbin, nq, xrows) * 4 + AM_REFS * AM_FIELDS * WAVE;
+}
+constexpr size_t am_lds(int nbin, int nq, int xrows, int nbuf) {
+    return (am_off_axis(nbin, nq, xrows, nbuf) + 3 * FM_SIDE * 4) * sizeof(float);
+}
 
-template <int NM, int CPW, bool WANT_P0, bool WANT_POSE>
+template <int NM, int CPW, bool WANT_P0, bool WANT_POSE, int X>
 __device__ __forceinline__ void am_regions(const Geo& g, int reg0, int reg1, int nbuf, const float* __restrict__ p0,
                                            const float* __restrict__ xe, const float4* __restrict__ q,
-                                           float* __restrict__ grad_p0, int accumulate, double* __restrict__ pose_part,
-                                           size_t row_step, float* lds) {
+                                           const float* __restrict__ r, float* __restrict__ grad_p0, int accumulate,
+                                           double* __restrict__ pose_part, size_t row_step, float* lds) {
+    constexpr int NQ = am_nq(NM);
     const int tid = threadIdx.x, lane = tid & (WAVE - 1);
     const int wv = __builtin_amdgcn_readfirstlane(tid / WAVE);
     const int nbin = g.nbin, jt = g.jt, kq = g.K + 2 * jt;
-    const int win = am_win(nbin);
+    const int xrows = X ? nbin + 2 * jt : 0;
+    const int win = am_win(nbin, NQ, xrows);
     float4* qw = reinterpret_cast<float4*>(lds);
     float* refs = lds + (size_t)nbuf * win * 4;              // [slot][field][lane]
-    float4* axis = reinterpret_cast<float4*>(lds + am_off_axis(nbin, nbuf));
+    float4* axis = reinterpret_cast<float4*>(lds + am_off_axis(nbin, NQ, xrows, nbuf));
     const int nchunk = (g.E + WAVE - 1) / WAVE;
     const int iters = (reg1 - reg0) * nchunk;                // (region, chunk) pairs, one after the other
 
@@ -1689,16 +1771,26 @@ __device__ __forceinline__ void am_regions(const Geo& g, int reg0, int reg1, int
         const float* rl = refs + (it % AM_REFS) * AM_FIELDS * WAVE + lane;
         const int b0 = __float_as_int(rl[10 * WAVE]) - g.jclamp + jt;
         const int e = (it % nchunk) * WAVE + lane;
-        const float4* qe = q + (size_t)min(e, g.E - 1) * kq * 2;
-        const float4* zrow = q + (size_t)g.E * kq * 2;       // bins that do not exist read the zero row
+        const float4* qe = q + (size_t)min(e, g.E - 1) * kq * NQ;
+        const float4* zrow = q + (size_t)g.E * kq * NQ;      // what does not exist reads the zero row
         float4* dst = qw + (nbuf == 2 ? (it & 1) : 0) * win;
+        typedef const __attribute__((address_space(1))) void* gptr;
+        typedef __attribute__((address_space(3))) void* lptr;
         for (int b = wv; b < nbin; b += AM_WAVES) {
             const int kk = b0 + b;
-            const float4* src = e < g.E && kk >= 0 && kk < kq ? qe + (size_t)kk * 2 : zrow;
-            typedef const __attribute__((address_space(1))) void* gptr;
-            typedef __attribute__((address_space(3))) void* lptr;
-            __builtin_amdgcn_global_load_lds((gptr)src, (lptr)(dst + b * 2 * WAVE), 16, 0, 0);
-            __builtin_amdgcn_global_load_lds((gptr)(src + 1), (lptr)(dst + (b * 2 + 1) * WAVE), 16, 0, 0);
+            const float4* src = e < g.E && kk >= 0 && kk < kq ? qe + (size_t)kk * NQ : zrow;
+#pragma unroll
+            for (int i = 0; i < NQ; ++i)
+                __builtin_amdgcn_global_load_lds((gptr)(src + i), (lptr)(dst + (b * NQ + i) * WAVE), 16, 0, 0);
+        }
+        if (X) {                                             // row x of the samples is kc - jclamp - jt + x
+            const float* re = r + (size_t)min(e, g.E - 1) * g.K;
+            float* rdst = reinterpret_cast<float*>(dst + am_rows(nbin, NQ));
+            for (int x = wv; x < xrows; x += AM_WAVES) {
+                const int k = b0 - 2 * jt + x;
+                const float* src = e < g.E && k >= 0 && k < g.K ? re + k : reinterpret_cast<const float*>(zrow);
+                __builtin_amdgcn_global_load_lds((gptr)src, (lptr)(rdst + x * WAVE), 4, 0, 0);
+            }
         }
     };
 
@@ -1739,10 +1831,15 @@ __device__ __forceinline__ void am_regions(const Geo& g, int reg0, int reg1, int
             fm_axis(tz, Dz, Dzl, magic, zh, zl);
             zl += rl[8 * WAVE];
             fm_column_n(g, tz, Dz, Dzl, ez);
-            // bin b of the window starts at b << 11; the bits of FM_MAGIC vanish in the shift.  Kept in a vector
-            // register, so that a pair's address is one instruction without scalar operands
-            unsigned off0 = (unsigned)lane * 16u + ((unsigned)g.jclamp << 11) + (nbuf == 2 ? (it & 1) : 0) * win * 16u;
-            asm volatile("" : "+v"(off0));
+            // a bin's table row, from the low 24 bits of rm, 0xC00000 + (centre sample offset).  Kept in vector
+            // registers, so that a pair's address is one instruction without scalar operands
+            constexpr unsigned STEP = NQ * WAVE * 16u;
+            const unsigned wbase = (nbuf == 2 ? (it & 1) : 0) * win * 16u;
+            unsigned off0 = (unsigned)lane * 16u + (NQ == 2 ? (unsigned)g.jclamp : (unsigned)g.jclamp - 0xC00000u) * STEP + wbase, step = STEP;
+            // row of a bin's sample kc - jt among the samples of dL/ds; FM_MAGIC << 8 is 0xC0000000
+            unsigned xoff = wbase + (unsigned)am_rows(nbin, NQ) * 16u + (unsigned)(lane + g.jclamp * WAVE) * 4u - 0xC0000000u;
+            asm volatile("" : "+v"(off0), "+v"(step), "+v"(xoff));
+            const EdgeCoef xc = edge_coef(g, 1.0f);
             int ix = -1;
             float xh = 0.0f, xl = 0.0f, ox = 0.0f;
 #pragma unroll
@@ -1778,14 +1875,31 @@ __device__ __forceinline__ void am_regions(const Geo& g, int reg0, int reg1, int
 #pragma unroll
                 for (int k = 0; k < FM_RZ; ++k) {
                     const FmPair p = fm_pair(cl, dc2, hdc, ez[k], rlo, rhi);
-                    const vf4* row = reinterpret_cast<const vf4*>(reinterpret_cast<const char*>(lds) + ((__float_as_uint(p.rm) << 11) + off0));
-                    const vf4 m0 = row[0], m1 = row[WAVE];
-                    const float m[FM_NM_MAX] = {m0[0], m0[1], m0[2], m0[3], m1[0], m1[1], m1[2], m1[3]};
-                    float h = m[NM - 1], dd = 0.0f;
+                    const unsigned off = NQ == 2 ? (__float_as_uint(p.rm) << 11) + off0
+                                                 : __umul24(__float_as_uint(p.rm), step) + off0;
+                    const vf4* row = reinterpret_cast<const vf4*>(reinterpret_cast<const char*>(lds) + off);
+                    vf4 m4[NQ];
+#pragma unroll
+                    for (int i = 0; i < NQ; ++i) m4[i] = row[i * WAVE];
+                    float h = m4[(NM - 1) / 4][(NM - 1) % 4], dd = 0.0f;
 #pragma unroll
                     for (int n = NM - 2; n >= 0; --n) {
                         if (WANT_POSE) dd = n == NM - 2 ? h : fmaf(dd, p.t, h);
-                        h = fmaf(h, p.t, m[n]);
+                        h = fmaf(h, p.t, m4[n / 4][n % 4]);
+                    }
+                    if (X) {                                 // an outermost sample and the centre
+                        const char* rx = reinterpret_cast<const char*>(lds) + ((__float_as_uint(p.rm) << 8) + xoff);
+                        const Edge e = edge_phi(xc, p.t);
+                        float rv = *reinterpret_cast<const float*>(rx + e.row);
+                        rv = e.v != 0.0f ? rv : 0.0f;        // dL/ds outside the window may be anything
+                        h = fmaf(rv, e.v, h);
+                        if (WANT_POSE) dd = fmaf(rv, e.d, dd);
+                        if (X == 2) {                        // exp2(kx |t|) = exp(-|t| delta / 2w)
+                            const float r0 = 0.5f * *reinterpret_cast<const float*>(rx + xc.far / 2u), ta = fabsf(p.t);
+                            const float x0 = r0 * __builtin_amdgcn_exp2f(g.kx * ta);
+                            h = fmaf(x0, p.t, h);
+                            if (WANT_POSE) dd = fmaf(x0, fmaf(0.6931471805599453f * g.kx, ta, 1.0f), dd);
+                        }
                     }
                     if (WANT_P0) acc[cc * FM_RZ + k] = fmaf(h, p.rs, acc[cc * FM_RZ + k]);
                     if (WANT_POSE) {
@@ -1850,14 +1964,14 @@ __device__ __forceinline__ void am_regions(const Geo& g, int reg0, int reg1, int
 // One workgroup per CU at most, each with an even share of consecutive regions, so that a region's first
 // loads run behind the one before (back-projection of 99 elements, two chunks, into 161x147x130 voxels:
 // 471 us with a workgroup per region, 415 us so).
-template <int NM, int CPW, bool WANT_P0, bool WANT_POSE>
+template <int NM, int CPW, bool WANT_P0, bool WANT_POSE, int X>
 __global__ __launch_bounds__(AM_WAVES * WAVE) __attribute__((amdgpu_waves_per_eu(4))) void k_adjoint_series(
     Geo g, int nbuf, const float* __restrict__ p0, const float* __restrict__ xe, const float4* __restrict__ q,
-    float* __restrict__ grad_p0, int accumulate, double* __restrict__ pose_part) {
+    const float* __restrict__ r, float* __restrict__ grad_p0, int accumulate, double* __restrict__ pose_part) {
     extern __shared__ float4 lds4[];
     const int b = region_of_block(blockIdx.x, gridDim.x);
     const int r0 = (int)((long long)g.nreg * b / gridDim.x), r1 = (int)((long long)g.nreg * (b + 1) / gridDim.x);
-    am_regions<NM, CPW, WANT_P0, WANT_POSE>(g, r0, r1, nbuf, p0, xe, q, grad_p0, accumulate,
+    am_regions<NM, CPW, WANT_P0, WANT_POSE, X>(g, r0, r1, nbuf, p0, xe, q, r, grad_p0, accumulate,
                                             WANT_POSE ? pose_part + (size_t)blockIdx.x * g.E * 3 : nullptr, 0,
                                             reinterpret_cast<float*>(lds4));
 }
@@ -2550,7 +2664,7 @@ __device__ __forceinline__ void batch_forward_item(const BatchGeo& bg, const ra_
     float* dt = lds + fm_off_dt(NM, bg.g.nbin);
     for (int i = threadIdx.x; i < NM * dl; i += FM_WAVES * WAVE)
         dt[i] = mom_coef(bg.series, i / dl, i % dl - FM_PAD - bg.g.jt, bg.g.jt);
-    fm_region<NM, FM_WAVES, float>(bg.g, reg, 0, 1, rq.p0, rq.xe, rq.s, lds);
+    fm_region<NM, FM_WAVES, 0, float>(bg.g, reg, 0, 1, rq.p0, rq.xe, rq.s, lds);
     __syncthreads();                                         // the LDS is free for the next item
 }
 
@@ -2562,7 +2676,7 @@ __global__ __launch_bounds__(FM_WAVES * WAVE) __attribute__((amdgpu_waves_per_eu
     for (int it = blockIdx.x; it < n; it += gridDim.x) {
         const int2 w = items[it];
         const BatchGeo& bg = geos[w.x];
-        if ((int)fm_lds(bg.nm, bg.g.nbin, bg.g.jt) > lds_bytes) continue;      // uniform per workgroup
+        if ((int)fm_lds(bg.nm, bg.g.nbin, bg.g.jt, false) > lds_bytes) continue;      // uniform per workgroup
         if (bg.nm == 6) batch_forward_item<6>(bg, reqs[w.x], w.y, lds);
         else if (bg.nm == 7) batch_forward_item<7>(bg, reqs[w.x], w.y, lds);
         else batch_forward_item<8>(bg, reqs[w.x], w.y, lds);
@@ -2602,13 +2716,13 @@ __global__ __launch_bounds__(MT_ROWS) void k_batch_series(const BatchGeo* __rest
             row[2 * jt + tid] = r;                           // row[2 jt + i] = r[kk0 + i]
             __syncthreads();
             const float* c = row + tid + jt;                 // r at the row's own sample kk - jt
-            float acc[FM_NM_MAX];
+            float acc[MOM_G];
 #pragma unroll
-            for (int m = 0; m < FM_NM_MAX; ++m) acc[m] = c[0] * bg.series8.d[m];
+            for (int m = 0; m < MOM_G; ++m) acc[m] = c[0] * bg.series8.d[m];
             for (int j = 1; j <= jt; ++j) {
                 const float a = c[j], b = c[-j], sum = a + b, dif = a - b;
 #pragma unroll
-                for (int m = 0; m < FM_NM_MAX; ++m) acc[m] = fmaf(m & 1 ? sum : dif, bg.series8.d[j * FM_NM_MAX + m], acc[m]);
+                for (int m = 0; m < MOM_G; ++m) acc[m] = fmaf(m & 1 ? sum : dif, bg.series8.d[j * MOM_MAX + m], acc[m]);
             }
             if (kk < kq) {
                 float4* out = q + 2 * ((size_t)e * kq + kk);
@@ -2626,7 +2740,7 @@ __global__ __launch_bounds__(MT_ROWS) void k_batch_series(const BatchGeo* __rest
         if (tid == 0) {
             float t = 0.0f;
             for (int i = 0; i < MT_ROWS / WAVE; ++i) t += red[i];
-            rq.q[((size_t)E * kq + 1) * FM_NM_MAX + e] = t;
+            rq.q[((size_t)E * kq + 1) * MOM_G + e] = t;
         }
         if (e == 0 && tid < 2) q[(size_t)E * kq * 2 + tid] = make_float4(0.0f, 0.0f, 0.0f, 0.0f);     // the zero row
     }
@@ -2642,8 +2756,8 @@ template <int CPW, bool WANT_P0, bool WANT_POSE>
 __device__ __forceinline__ void batch_adjoint_run(const BatchGeo& bg, const ra_batch_request& rq, int reg, int cnt, int nbuf,
                                                   float* lds) {
     const size_t row = (size_t)bg.g.E * 3;
-    am_regions<FM_NM_MAX, CPW, WANT_P0, WANT_POSE>(bg.g, reg, reg + cnt, nbuf, rq.p0, rq.xe,
-                                                   reinterpret_cast<const float4*>(rq.q), rq.grad_p0, 0,
+    am_regions<MOM_G, CPW, WANT_P0, WANT_POSE, 0>(bg.g, reg, reg + cnt, nbuf, rq.p0, rq.xe,
+                                                   reinterpret_cast<const float4*>(rq.q), nullptr, rq.grad_p0, 0,
                                                    WANT_POSE ? rq.pose_part + reg * row : nullptr, row, lds);
 }
 
@@ -2723,7 +2837,7 @@ __global__ __launch_bounds__(BATCH_THREADS) void k_batch_pose_update(const Batch
         const ra_batch_request& q = reqs[slot];
         if (moment && q.kind >= 0) {             // the loss: the elements' sums behind the moment table, in FP64
             const Geo& gl = geos[slot].g;
-            const float* le = q.q + ((size_t)gl.E * (gl.K + 2 * gl.jt) + 1) * FM_NM_MAX;
+            const float* le = q.q + ((size_t)gl.E * (gl.K + 2 * gl.jt) + 1) * MOM_G;
             double a = 0.0;
             for (int e = threadIdx.x; e < gl.E; e += BATCH_THREADS) a += (double)le[e];
             red[0][threadIdx.x] = a;
@@ -2808,6 +2922,14 @@ __global__ __launch_bounds__(BLOCK) void k_batch_volume_apply(const BatchGeo* __
 // ==============================================================================================
 // host side
 // ==============================================================================================
+// Terms of the moment forms' series (0: the form cannot be taken).
+struct MomTerms {
+    int fwd, vol, pose;
+    float thr, ev[4], es, kx;      // Geo's of the same names
+    unsigned flip;
+    int xkind;
+};
+
 struct ra_ctx {
     int device = 0;
     int* d_status = nullptr;
@@ -2815,9 +2937,10 @@ struct ra_ctx {
     size_t arena_bytes = 0;
     char* static_scratch = nullptr;         // this device's static array (radiate_forward_static)
     // series of the moment-form forward for the sampling of the last call (its key: profile, window, nu)
-    MomCoef series, series8;                // with the forward's number of moments, and with 8
+    MomCoef series, seriesv, seriesp;       // with the terms of the forward, of dL/dp0 alone and of the element gradients
     double series_key[4] = {0.0, 0.0, 0.0, 0.0};
-    double series_tail[FM_NM_MAX + 1];
+    double series_tail[MOM_MAX + 1];
+    MomTerms terms;
     unsigned long long* h_count = nullptr;  // pinned
     double* h_f64 = nullptr;                // pinned, one value
     double* d_f64 = nullptr;                // device, one value
@@ -2889,7 +3012,8 @@ struct Plan {
     bool f64_sums;      // the forward adds its partial rows into FP64 sums (else FP32, straight into s)
     bool fm;            // the forward takes the moment form (k_forward_mom) on regions gm
     Geo gm;
-    int fm_nm, fm_slices;   // its moments; workgroups that share a region's element chunks
+    int fm_slices;      // workgroups that share a region's element chunks
+    MomTerms terms;     // terms of the moment forms' series
     bool am, am_pose;   // dL/dp0 alone / the element gradients take the moment form
     Geo ga1, ga2;       // on regions ga1 (dL/dp0 alone) and ga2 (element gradients, with dL/dp0 or without)
     int am_nbuf[2];     // table windows in LDS, of each
@@ -2961,74 +3085,121 @@ size_t set_regions(Geo& g, const ra_grid* grid, double delta, int jt, bool with_
     return lds;
 }
 
-// Series of phi((t/2 - j) delta) / delta in t, j = 0..jt: the Chebyshev coefficients from FM_NODES nodes,
-// the first FM_NM_MAX as a polynomial in each of its lengths would be; tail[n] bounds what is cut after
-// n terms, relative to the peak.
-constexpr int FM_NODES = 24;
+// phi(x delta) / delta of a source profile, x in samples, dd = delta / w.
+double profile(const ra_sampling* samp, double dd, double x) {
+    const double y = std::fabs(x) * dd;
+    switch (samp->kernel) {
+        case RA_KERNEL_EXPONENTIAL: return x * std::exp(-y);
+        case RA_KERNEL_POWER: return x * std::pow(1.0 + y * y, -samp->nu);
+        case RA_KERNEL_UNIFORM: return x;
+        default: return x * std::exp(-0.5 * y * y);
+    }
+}
 
-void mom_series(double dd, int jt, double cheb[FM_NM_MAX][JMAX + 1], double tail[FM_NM_MAX + 1]) {
+// Chebyshev coefficients in t of phi((t/2 - j) delta) / delta for j = j0..j1, from MOM_NODES nodes; tail[n] bounds
+// what is cut after n terms, relative to `peak`.
+constexpr int MOM_NODES = 24;
+
+void mom_series(const ra_sampling* samp, double dd, int j0, int j1, double peak, double cheb[MOM_MAX][JMAX + 1],
+                double tail[MOM_MAX + 1]) {
     const double pi = 3.14159265358979323846;
-    double cs[FM_NODES][FM_NODES];
-    for (int k = 0; k < FM_NODES; ++k)
-        for (int i = 0; i < FM_NODES; ++i) cs[k][i] = std::cos(pi * k * (i + 0.5) / FM_NODES);
-    const double peak = std::exp(-0.5) / dd;               // of x exp(-(x dd)^2 / 2)
-    for (int n = 0; n <= FM_NM_MAX; ++n) tail[n] = 0.0;
-    for (int j = 0; j <= jt; ++j) {
-        double f[FM_NODES];
-        for (int i = 0; i < FM_NODES; ++i) {
-            const double x = 0.5 * cs[1][i] - j;
-            f[i] = x * std::exp(-0.5 * x * x * dd * dd);
-        }
+    double cs[MOM_NODES][MOM_NODES];
+    for (int k = 0; k < MOM_NODES; ++k)
+        for (int i = 0; i < MOM_NODES; ++i) cs[k][i] = std::cos(pi * k * (i + 0.5) / MOM_NODES);
+    for (int n = 0; n <= MOM_MAX; ++n) tail[n] = 0.0;
+    for (int j = j0; j <= j1; ++j) {
+        double f[MOM_NODES];
+        for (int i = 0; i < MOM_NODES; ++i) f[i] = profile(samp, dd, 0.5 * cs[1][i] - j);
         double rest = 0.0;
-        for (int k = FM_NODES - 1; k >= 0; --k) {
+        for (int k = MOM_NODES - 1; k >= 0; --k) {
             double c = 0.0;
-            for (int i = 0; i < FM_NODES; ++i) c += f[i] * cs[k][i];
-            c *= (k ? 2.0 : 1.0) / FM_NODES;
-            if (k < FM_NM_MAX) cheb[k][j] = c;
+            for (int i = 0; i < MOM_NODES; ++i) c += f[i] * cs[k][i];
+            c *= (k ? 2.0 : 1.0) / MOM_NODES;
+            if (k < MOM_MAX) cheb[k][j] = c;
             rest += std::fabs(c);
-            if (k <= FM_NM_MAX) tail[k] = std::max(tail[k], rest / peak);
+            if (k <= MOM_MAX) tail[k] = std::max(tail[k], rest / peak);
         }
     }
 }
 
-// The sum of the first nm Chebyshev terms as a polynomial in t.
-void mom_monomials(const double cheb[FM_NM_MAX][JMAX + 1], int nm, int jt, MomCoef& out) {
-    double T[FM_NM_MAX][FM_NM_MAX] = {};                   // T[k][n]: coefficient of t^n in T_k
+// The sum of the first nm Chebyshev terms of sample j as a polynomial in t.
+void mom_monomials(const double cheb[MOM_MAX][JMAX + 1], int nm, int j, float* out) {
+    double T[MOM_MAX][MOM_MAX] = {};                       // T[k][n]: coefficient of t^n in T_k
     T[0][0] = 1.0;
     T[1][1] = 1.0;
     for (int k = 2; k < nm; ++k)
         for (int n = 0; n < nm; ++n) T[k][n] = (n ? 2.0 * T[k - 1][n - 1] : 0.0) - T[k - 2][n];
-    std::memset(&out, 0, sizeof(out));
-    for (int j = 0; j <= jt; ++j)
-        for (int n = 0; n < nm; ++n) {
-            double v = 0.0;
-            for (int k = n; k < nm; ++k) v += cheb[k][j] * T[k][n];
-            out.d[j * FM_NM_MAX + n] = (float)v;
-        }
+    for (int n = 0; n < nm; ++n) {
+        double v = 0.0;
+        for (int k = n; k < nm; ++k) v += cheb[k][j] * T[k][n];
+        out[n] = (float)v;
+    }
 }
 
-// The moment form's series for this sampling, kept in the context until the sampling changes; 0 if the
-// form cannot be taken, else the fewest terms (6, 7 or 8) whose cut series is within FM_TOL: 6 up to
-// delta/sigma 0.41, 7 up to 0.64, 8 up to 1.05 (the row form's own rounding is about 4e-7); coarser sampling
-// keeps the row forms.  The form takes the window's rows whole, as the Gaussian's row forms do for the
-// half-widths of RA_EXACT_LIST; for longer windows those test each term, so it is taken there only from
-// 6 sigma on, where the terms in question are below 1.5e-7 of the peak.
-int series_terms(ra_ctx* ctx, const ra_sampling* samp, bool exact) {
-    const double delta = samp->c / samp->fs, dd = delta / samp->sigma;
-    const int jt = (int)std::floor(samp->trunc * samp->sigma / delta + 0.5);
-    if (samp->kernel != RA_KERNEL_GAUSSIAN || !(exact || samp->trunc >= 6.0) || jt < 1 || jt > JMAX) return 0;
-    const double key[4] = {(double)samp->kernel, dd, (double)jt, samp->nu};
-    const bool known = std::memcmp(key, ctx->series_key, sizeof(key)) == 0;
-    double cheb[FM_NM_MAX][JMAX + 1];
-    if (!known) mom_series(dd, jt, cheb, ctx->series_tail);
-    int nm = 6;
-    while (nm < FM_NM_MAX && ctx->series_tail[nm] > FM_TOL) ++nm;
-    if (!known) {
-        mom_monomials(cheb, nm, jt, ctx->series);
-        mom_monomials(cheb, FM_NM_MAX, jt, ctx->series8);
-        std::memcpy(ctx->series_key, key, sizeof(key));
+// The moment forms' series for this sampling, kept in the context until the sampling changes.  Their numbers of
+// terms are the fewest of those compiled whose cut series is within FM_TOL (AM_TOL where the derivative is used too):
+//   Gaussian     6 up to delta/sigma 0.41, 7 up to 0.64, 8 up to 1.05 (the row form's own rounding is about 4e-7); 8 with
+//                derivatives, up to 0.75.  The window's rows are taken whole, as the Gaussian's row forms do for
+//                the half-widths of RA_EXACT_LIST; for longer windows those test each term, so the form is taken
+//                there only from 6 sigma on, where the terms in question are below 1.5e-7 of the peak.
+//   the others   6 or 8 for the exponential (without the centre sample, which is added by itself), 8 to 12 for the
+//                power law.  A sample that is in the window for some offsets only is added by itself too, by its
+//                first four terms.  Only where phi has fallen to FM_EDGE of its peak at the window's edge: the
+//                forward and the adjoint take different regions, so that their rounding of a pair's offset can
+//                put an edge sample in on one side and out on the other, which the row forms, on shared
+//                regions, avoid (single results then moved by 1.4e-3 at an edge value of 0.0135).  The uniform
+//                sphere keeps those always; a power law with nu = 2 passes from 9.1 widths on, the exponential from 8.7.
+const MomTerms& series_terms(ra_ctx* ctx, const ra_sampling* samp, bool exact) {
+    const double delta = samp->c / samp->fs, dd = delta / samp->sigma, jw = samp->trunc * samp->sigma / delta;
+    const double key[4] = {(double)samp->kernel + (exact ? 0.5 : 0.0), dd, samp->trunc, samp->nu};
+    if (std::memcmp(key, ctx->series_key, sizeof(key)) == 0) return ctx->terms;
+    std::memcpy(ctx->series_key, key, sizeof(key));
+    MomTerms& t = ctx->terms;
+    t = MomTerms{};
+    const int jo = (int)std::floor(jw + 0.5), kt = samp->kernel;
+    if (jo < 1 || jo > JMAX || kt == RA_KERNEL_UNIFORM || (kt == RA_KERNEL_GAUSSIAN && !(exact || samp->trunc >= 6.0))) return t;
+    double peak = 0.0;
+    for (int i = 1; i <= 1024; ++i) peak = std::max(peak, profile(samp, dd, jw * i / 1024.0));
+    double cheb[MOM_MAX][JMAX + 1] = {}, ce[MOM_MAX][JMAX + 1] = {}, te[MOM_MAX + 1];
+    const double edge = 2.0 * (jo - jw);                   // kc + jo is in the window for t >= edge
+    const int j0 = kt == RA_KERNEL_EXPONENTIAL ? 1 : 0, j1 = kt == RA_KERNEL_GAUSSIAN || edge <= 0.0 ? jo : jo - 1;
+    double* tail = ctx->series_tail;
+    mom_series(samp, dd, j0, j1, peak, cheb, tail);
+    if (kt != RA_KERNEL_GAUSSIAN) {
+        mom_series(samp, dd, jo, jo, peak, ce, te);
+        if (!(te[4] <= FM_TOL) || profile(samp, dd, jw) > FM_EDGE * peak) return t;
+        t.xkind = kt == RA_KERNEL_EXPONENTIAL ? 2 : 1;
+        mom_monomials(ce, 4, jo, t.ev);
+        t.thr = (float)edge;
+        if (edge <= 0.0) {                                 // take back phi at kc - jo for t > -edge: F(|t|) = E(-|t|)
+            t.thr = std::nextafterf((float)-edge, 2.0f);
+            t.flip = 0x80000000u;
+            t.ev[1] = -t.ev[1];
+            t.ev[3] = -t.ev[3];
+        }
+        // |phi| / delta of the single samples: three of them meet in a row at most (centre, kc + jt, kc - jt)
+        double top = 0.0;
+        for (int i = -1; i <= 1; ++i) top = std::max(top, std::fabs(profile(samp, dd, 0.5 * i - jo)));
+        t.es = (float)(1.0 / (0.5 + 2.0 * std::max(top, peak)));
+        t.kx = (float)(-0.5 * dd * 1.4426950408889634);
     }
-    return ctx->series_tail[nm] <= FM_TOL ? nm : 0;
+    static const int terms[3][3] = {{6, 7, 8}, {6, 8, 8}, {8, 10, 12}};      // by profile
+    auto fewest = [&](double tol, int from) {
+        for (int i = from; i < 3; ++i)
+            if (tail[terms[kt][i]] <= tol) return terms[kt][i];
+        return 0;
+    };
+    t.fwd = fewest(FM_TOL, 0);
+    if (!t.fwd) return t;
+    t.vol = kt == RA_KERNEL_GAUSSIAN ? t.fwd : kt == RA_KERNEL_POWER && t.fwd > 8 ? 12 : terms[kt][1] == 10 ? 8 : terms[kt][1];
+    t.pose = kt == RA_KERNEL_POWER ? (tail[8] <= AM_TOL ? 8 : fewest(AM_TOL, 2)) : fewest(AM_TOL, 2);
+    const int nm[3] = {t.fwd, t.vol, t.pose};
+    MomCoef* const out[3] = {&ctx->series, &ctx->seriesv, &ctx->seriesp};
+    for (int i = 0; i < 3; ++i) {
+        std::memset(out[i], 0, sizeof(MomCoef));
+        for (int j = j0; nm[i] && j <= j1; ++j) mom_monomials(cheb, nm[i], j, out[i]->d + j * MOM_MAX);
+    }
+    return t;
 }
 
 // Moment forms: lengths in units of delta / 2.
@@ -3040,14 +3211,24 @@ void set_units(Geo& g, const ra_grid* grid, double delta) {
     g.hs_l = (float)(grid->spacing * unit - (double)g.hs_u);
 }
 
+void set_terms(Geo& g, const MomTerms& t) {
+    g.xkind = t.xkind;
+    g.thr = t.thr;
+    g.flip = t.flip;
+    for (int i = 0; i < 4; ++i) g.ev[i] = t.ev[i];
+    g.es = t.es;
+    g.kx = t.kx;
+}
+
 // The moment-form forward of a call, with nm terms: on which regions.
 // Those that make the estimated time least.  Per pair and wavefront a CU spends about 34 cycles on the
 // adds; per region and chunk the expansion takes row tiles x quads x NM matrix instructions of 32 cycles
 // on each SIMD (measured: 1.45 times that, with the operand conversions and the atomics), and barriers and
 // clearing about 2500 cycles where one workgroup has the CU, 800 where two share it.  Large grids take
 // 16x16x16; a box of 32^3 voxels seen by one chunk takes small ones, which fill the chip.
-void plan_forward_mom(const ra_grid* grid, const ra_sampling* samp, int nm, Plan& P) {
+void plan_forward_mom(const ra_grid* grid, const ra_sampling* samp, const MomTerms& mt, Plan& P) {
     P.fm = false;
+    const int nm = mt.fwd;
     if (!nm) return;
     const double delta = samp->c / samp->fs;
     const int jt = (int)std::floor(samp->trunc * samp->sigma / delta + 0.5);
@@ -3067,7 +3248,7 @@ void plan_forward_mom(const ra_grid* grid, const ra_sampling* samp, int nm, Plan
         g.jclampf = (float)g.jclamp;
         g.jt = jt;
         g.nbin = 2 * g.jclamp + 1;
-        const size_t lds = fm_lds(nm, g.nbin, jt);
+        const size_t lds = fm_lds(nm, g.nbin, jt, mt.xkind != 0);
         if (lds > 160 * 1024) continue;
         g.nrx = (g.nx + g.rx - 1) / g.rx; g.nry = (g.ny + g.ry - 1) / g.ry;
         g.nreg = g.nrx * g.nry * g.nrz;
@@ -3090,14 +3271,17 @@ void plan_forward_mom(const ra_grid* grid, const ra_sampling* samp, int nm, Plan
         P.fm_slices = slices;
         P.lds_fm = lds;
     }
-    if (P.fm) set_units(P.gm, grid, delta);
+    if (!P.fm) return;
+    set_units(P.gm, grid, delta);
+    set_terms(P.gm, mt);
 }
 
 // The moment-form adjoint's regions: columns of 8 voxels, up to 64 of them, those that make the estimated
 // time least (`pair`: CU cycles per pair and wavefront, 30 for dL/dp0, 44 with the element gradients).  Two
 // table windows in LDS let a chunk's loads run behind the previous chunk's voxels; where the spacing is so
 // coarse that only one fits, the loads (about 41 cycles per bin, and their latency) add to the time.
-bool plan_adjoint_mom(const ra_grid* grid, const ra_sampling* samp, const Geo& base, double pair, Geo& out, int& nbuf) {
+bool plan_adjoint_mom(const ra_grid* grid, const ra_sampling* samp, const Geo& base, double pair, int nq, bool edge, Geo& out,
+                      int& nbuf) {
     static const int cand[][2] = {{8, 8}, {4, 8}, {4, 4}, {2, 4}, {2, 2}, {1, 2}, {1, 1}};
     const double delta = samp->c / samp->fs;
     const int nchunk = (base.E + WAVE - 1) / WAVE;
@@ -3116,8 +3300,9 @@ bool plan_adjoint_mom(const ra_grid* grid, const ra_sampling* samp, const Geo& b
         g.jclampf = (float)g.jclamp;
         g.jt = (int)std::floor(samp->trunc * samp->sigma / delta + 0.5);
         g.nbin = 2 * g.jclamp + 1;
-        const int nb = am_lds(g.nbin, 2) <= 160 * 1024 ? 2 : 1;
-        if (am_lds(g.nbin, nb) > 160 * 1024) continue;
+        const int xrows = edge ? g.nbin + 2 * g.jt : 0;
+        const int nb = am_lds(g.nbin, nq, xrows, 2) <= 160 * 1024 ? 2 : 1;
+        if (am_lds(g.nbin, nq, xrows, nb) > 160 * 1024) continue;
         const int cols = (g.rx * g.ry + AM_WAVES - 1) / AM_WAVES * AM_WAVES;     // a round of wavefronts is the least
         const double each = cols * FM_RZ * pair + 900.0 + (nb == 1 ? 1500.0 + 41.0 * g.nbin : 0.0);
         const double cost = std::ceil(g.nreg / (double)NCU) * (nchunk * each + 3000.0) + 5000.0;
@@ -3236,11 +3421,18 @@ void make_plan(ra_ctx* ctx, const ra_grid* grid, int32_t M, int32_t F, const ra_
     // meet in one sample; past FWD_F32_MAX_REGIONS forward regions the rows go into FP64 sums.
     P.f64_sums = sums_mode == RA_SUMS_F64 || (sums_mode == RA_SUMS_AUTO && P.gf.nreg > FWD_F32_MAX_REGIONS);
 
-    const int nm = ctx ? series_terms(ctx, samp, P.exact) : 0;
-    plan_forward_mom(grid, samp, nm, P);
-    P.fm_nm = nm;
-    P.am = nm && plan_adjoint_mom(grid, samp, g, 30.0, P.ga1, P.am_nbuf[0]);
-    P.am_pose = nm && ctx->series_tail[FM_NM_MAX] <= AM_TOL && plan_adjoint_mom(grid, samp, g, 43.0, P.ga2, P.am_nbuf[1]);
+    static const MomTerms none{};
+    const MomTerms& mt = ctx ? series_terms(ctx, samp, P.exact) : none;
+    P.terms = mt;
+    P.fm = P.am = P.am_pose = false;
+    if (mt.fwd) {
+        const bool x = mt.xkind != 0;
+        plan_forward_mom(grid, samp, mt, P);
+        P.am = plan_adjoint_mom(grid, samp, g, x ? 45.0 : 30.0, am_nq(mt.vol), x, P.ga1, P.am_nbuf[0]);
+        P.am_pose = mt.pose && plan_adjoint_mom(grid, samp, g, x ? 60.0 : 43.0, am_nq(mt.pose), x, P.ga2, P.am_nbuf[1]);
+        set_terms(P.ga1, mt);
+        set_terms(P.ga2, mt);
+    }
     P.part_rows = P.am_pose ? std::min(P.ga2.nreg, NCU) : g.nreg;
 
     size_t o = 0;
@@ -3261,8 +3453,8 @@ void make_plan(ra_ctx* ctx, const ra_grid* grid, int32_t M, int32_t F, const ra_
     P.off_nct = o; o = align_up(o + sizeof(double));
     P.off_s64 = o; o = align_up(o + (P.f64_sums ? (size_t)g.E * g.K * sizeof(double) : 0));
     P.off_xe64 = o; o = align_up(o + (size_t)g.E * 3 * sizeof(double));
-    const int jts = (int)std::floor(tsig / delta + 0.5);
-    P.off_q = o; o = align_up(o + (P.am || P.am_pose ? ((size_t)g.E * (g.K + 2 * jts) + 1) * FM_NM_MAX * sizeof(float) : 0));
+    const int nq = std::max(P.am ? am_nq(mt.vol) : 0, P.am_pose ? am_nq(mt.pose) : 0);
+    P.off_q = o; o = align_up(o + ((size_t)g.E * (g.K + 2 * jout) + 1) * nq * sizeof(float4));
     P.total = o;
 }
 
@@ -3381,20 +3573,20 @@ int launch_forward_t(ra_ctx* ctx, char* base, const Plan& P, const float* p0, fl
     return RA_OK;
 }
 
-template <int NM, int NW>
+template <int NM, int NW, int X>
 int launch_forward_mom(ra_ctx* ctx, char* base, const Plan& P, const float* p0, float* s, hipStream_t stream) {
     const size_t n = (size_t)P.g.E * P.g.K;
     const dim3 grid((unsigned)(P.gm.nreg * P.fm_slices)), block(NW * WAVE);
     const float* xe = at<float>(base, P.off_xe);
     if (!P.f64_sums) {
-        auto kern = k_forward_mom<NM, NW, float>;
+        auto kern = k_forward_mom<NM, NW, X, float>;
         RA_HIP(ctx, allow_full_lds(kern));
         hipLaunchKernelGGL(k_fill, dim3(1024), dim3(256), 0, stream, s, n, 0.0f);
         hipLaunchKernelGGL(kern, grid, block, P.lds_fm, stream, P.gm, ctx->series, P.fm_slices, p0, xe, s);
         RA_HIP(ctx, hipGetLastError());
         return RA_OK;
     }
-    auto kern = k_forward_mom<NM, NW, double>;
+    auto kern = k_forward_mom<NM, NW, X, double>;
     RA_HIP(ctx, allow_full_lds(kern));
     double* s64 = at<double>(base, P.off_s64);
     hipLaunchKernelGGL(k_fill_f64, dim3(1024), dim3(256), 0, stream, s64, n);
@@ -3414,11 +3606,12 @@ bool generic_bound_ok(const Plan& P) {
 int launch_forward(ra_ctx* ctx, char* base, const Plan& P, const float* p0, float* s, hipStream_t stream) {
     if (P.fm) {
         const bool big = P.lds_fm > LDS_FM_BUDGET;
-#define RA_CASE(n)                                                                    \
-    if (P.fm_nm == n)                                                                 \
-        return big ? launch_forward_mom<n, FM_WAVES_BIG>(ctx, base, P, p0, s, stream) \
-                   : launch_forward_mom<n, FM_WAVES>(ctx, base, P, p0, s, stream);
-        RA_CASE(6) RA_CASE(7) RA_CASE(8)
+#define RA_CASE(n, x)                                                                    \
+    if (P.terms.fwd == n && P.terms.xkind == x)                                          \
+        return big ? launch_forward_mom<n, FM_WAVES_BIG, x>(ctx, base, P, p0, s, stream) \
+                   : launch_forward_mom<n, FM_WAVES, x>(ctx, base, P, p0, s, stream);
+        RA_CASE(6, 0) RA_CASE(7, 0) RA_CASE(8, 0)
+        RA_CASE(8, 1) RA_CASE(10, 1) RA_CASE(12, 1) RA_CASE(6, 2) RA_CASE(8, 2)
 #undef RA_CASE
     }
     if (!generic_bound_ok(P)) return fail(ctx, RA_ENOTSUP, "window half-width not supported");
@@ -3473,45 +3666,58 @@ int launch_adjoint_j(ra_ctx* ctx, const Plan& P, const float* p0, const float* r
     return launch_adjoint_t<JT, EXACT, false, true, KT>(ctx, P, p0, r, gp0, acc, stream);
 }
 
-template <int NM, int CPW, bool P0, bool POSE>
-int launch_adjoint_series_t(ra_ctx* ctx, const Plan& P, const float* p0, float* gp0, int acc, hipStream_t stream) {
+template <int NM, int CPW, bool P0, bool POSE, int X>
+int launch_adjoint_series_t(ra_ctx* ctx, const Plan& P, const float* p0, const float* r, float* gp0, int acc,
+                            hipStream_t stream) {
     const Geo& g = POSE ? P.ga2 : P.ga1;
-    const int nbuf = P.am_nbuf[POSE ? 1 : 0];
-    auto kern = k_adjoint_series<NM, CPW, P0, POSE>;
+    const int nbuf = P.am_nbuf[POSE ? 1 : 0], xrows = X ? g.nbin + 2 * g.jt : 0;
+    auto kern = k_adjoint_series<NM, CPW, P0, POSE, X>;
     RA_HIP(ctx, allow_full_lds(kern));
-    hipLaunchKernelGGL(kern, dim3(std::min(g.nreg, NCU)), dim3(AM_WAVES * WAVE), am_lds(g.nbin, nbuf), stream, g, nbuf, p0,
-                       at<float>(ctx, P.off_xe), at<float4>(ctx, P.off_q), gp0, acc, at<double>(ctx, P.off_part));
+    hipLaunchKernelGGL(kern, dim3(std::min(g.nreg, NCU)), dim3(AM_WAVES * WAVE), am_lds(g.nbin, am_nq(NM), xrows, nbuf),
+                       stream, g, nbuf, p0, at<float>(ctx, P.off_xe), at<float4>(ctx, P.off_q), r, gp0, acc,
+                       at<double>(ctx, P.off_part));
     RA_HIP(ctx, hipGetLastError());
     return RA_OK;
 }
 
-template <int NM, bool P0, bool POSE>
-int launch_adjoint_series_c(ra_ctx* ctx, const Plan& P, const float* p0, float* gp0, int acc, hipStream_t stream) {
+template <int NM, bool P0, bool POSE, int X>
+int launch_adjoint_series_c(ra_ctx* ctx, const Plan& P, const float* p0, const float* r, float* gp0, int acc,
+                            hipStream_t stream) {
     const Geo& g = POSE ? P.ga2 : P.ga1;
     const int cpw = (g.rx * g.ry + AM_WAVES - 1) / AM_WAVES;
-    if (cpw <= 1) return launch_adjoint_series_t<NM, 1, P0, POSE>(ctx, P, p0, gp0, acc, stream);
-    if (cpw <= 2) return launch_adjoint_series_t<NM, 2, P0, POSE>(ctx, P, p0, gp0, acc, stream);
-    return launch_adjoint_series_t<NM, 4, P0, POSE>(ctx, P, p0, gp0, acc, stream);
+    if constexpr (X == 0) {
+        if (cpw <= 1) return launch_adjoint_series_t<NM, 1, P0, POSE, X>(ctx, P, p0, r, gp0, acc, stream);
+        if (cpw <= 2) return launch_adjoint_series_t<NM, 2, P0, POSE, X>(ctx, P, p0, r, gp0, acc, stream);
+    }
+    return launch_adjoint_series_t<NM, 4, P0, POSE, X>(ctx, P, p0, r, gp0, acc, stream);
 }
 
-// The adjoints in moment form: the table of dL/ds, then one workgroup per region.
+// The adjoints in moment form: the table of dL/ds, then the regions.
 int launch_adjoint_series(ra_ctx* ctx, const Plan& P, const float* p0, const float* r, float* gp0, bool pose, int acc,
                           hipStream_t stream) {
     const int K = P.g.K, jt = pose ? P.ga2.jt : P.ga1.jt, per = (K + 2 * jt + MT_ROWS - 1) / MT_ROWS;
-    hipLaunchKernelGGL(k_moment_series, dim3((unsigned)P.g.E * per), dim3(MT_ROWS), 0, stream, P.g.E, K, jt,
-                       pose ? ctx->series8 : ctx->series, r, at<float4>(ctx, P.off_q));
-    if (pose)
-        return gp0 ? launch_adjoint_series_c<8, true, true>(ctx, P, p0, gp0, acc, stream)
-                   : launch_adjoint_series_c<8, false, true>(ctx, P, p0, gp0, acc, stream);
-    if (P.fm_nm == 6) return launch_adjoint_series_c<6, true, false>(ctx, P, p0, gp0, acc, stream);
-    if (P.fm_nm == 7) return launch_adjoint_series_c<7, true, false>(ctx, P, p0, gp0, acc, stream);
-    return launch_adjoint_series_c<8, true, false>(ctx, P, p0, gp0, acc, stream);
+    const int nm = pose ? P.terms.pose : P.terms.vol;
+    auto table = am_nq(nm) == 2 ? k_moment_series<2> : k_moment_series<3>;
+    hipLaunchKernelGGL(table, dim3((unsigned)P.g.E * per), dim3(MT_ROWS), 0, stream, P.g.E, K, jt,
+                       pose ? ctx->seriesp : ctx->seriesv, r, at<float4>(ctx, P.off_q));
+#define RA_CASE(n, x)                                                                                    \
+    if (nm == n && P.terms.xkind == x && pose)                                                           \
+        return gp0 ? launch_adjoint_series_c<n, true, true, x>(ctx, P, p0, r, gp0, acc, stream)          \
+                   : launch_adjoint_series_c<n, false, true, x>(ctx, P, p0, r, gp0, acc, stream);
+    RA_CASE(8, 0) RA_CASE(8, 1) RA_CASE(12, 1) RA_CASE(8, 2)
+#undef RA_CASE
+#define RA_CASE(n, x) \
+    if (nm == n && P.terms.xkind == x && !pose)  \
+        return launch_adjoint_series_c<n, true, false, x>(ctx, P, p0, r, gp0, acc, stream);
+    RA_CASE(6, 0) RA_CASE(7, 0) RA_CASE(8, 0) RA_CASE(8, 1) RA_CASE(12, 1) RA_CASE(8, 2)
+#undef RA_CASE
+    return fail(ctx, RA_ENOTSUP, "moment form without a kernel for its terms");
 }
 
 int launch_adjoint(ra_ctx* ctx, const Plan& P, const float* p0, const float* r, float* gp0, bool pose, int acc,
                    hipStream_t stream) {
-    if (!generic_bound_ok(P)) return fail(ctx, RA_ENOTSUP, "window half-width not supported");
     if (pose ? P.am_pose : P.am) return launch_adjoint_series(ctx, P, p0, r, gp0, pose, acc, stream);
+    if (!generic_bound_ok(P)) return fail(ctx, RA_ENOTSUP, "window half-width not supported");
     switch (P.g.ktype) {
         case RA_KERNEL_EXPONENTIAL:
 #define RA_CASE(n) \
@@ -3960,12 +4166,13 @@ int ra_batch_describe(ra_ctx* ctx, const ra_grid* box, int64_t stride_x, int64_t
     g.jt = P.jt;
     g.nbin = 2 * g.jclamp + 1;
     set_units(g, box, delta);
-    bg.nm = P.exact ? series_terms(ctx, samp, true) : 0;
-    const bool moment = bg.nm && ctx->series_tail[FM_NM_MAX] <= AM_TOL && g.rz <= FM_RZ && g.nbin <= BATCH_BINS_MAX &&
-                        fm_lds(bg.nm, g.nbin, g.jt) <= 160 * 1024 && am_lds(g.nbin, 1) <= 160 * 1024;
+    const MomTerms mt = P.exact ? series_terms(ctx, samp, true) : MomTerms{};
+    bg.nm = mt.fwd;
+    const bool moment = mt.fwd && mt.pose && g.rz <= FM_RZ && g.nbin <= BATCH_BINS_MAX &&
+                        fm_lds(bg.nm, g.nbin, g.jt, false) <= 160 * 1024 && am_lds(g.nbin, 2, 0, 1) <= 160 * 1024;
     if (moment) {
         bg.series = ctx->series;
-        bg.series8 = ctx->series8;
+        bg.series8 = ctx->seriesp;
     }
     std::memcpy(geo, &bg, sizeof(BatchGeo));
     info->nreg = g.nreg;
@@ -3973,13 +4180,13 @@ int ra_batch_describe(ra_ctx* ctx, const ra_grid* box, int64_t stride_x, int64_t
     info->exact = P.exact ? 1 : 0;
     info->pair_d = pd;
     // rows of LDS of 1 KiB: the row form's samples, or what the moment-form forward needs
-    info->lmax = moment ? std::max(g.L, (int)((fm_lds(bg.nm, g.nbin, g.jt) + 1023) / 1024)) : g.L;
+    info->lmax = moment ? std::max(g.L, (int)((fm_lds(bg.nm, g.nbin, g.jt, false) + 1023) / 1024)) : g.L;
     info->nvpad = g.nvpad;
     info->rx = g.rx; info->ry = g.ry; info->rz = g.rz;
     info->moment = moment ? 1 : 0;
     info->nbin = g.nbin;
     // the table with its zero row, then one loss per element
-    info->q_bytes = moment ? (((int64_t)M * (samp->K + 2 * P.jt) + 1) * FM_NM_MAX + M) * (int64_t)sizeof(float) : 0;
+    info->q_bytes = moment ? (((int64_t)M * (samp->K + 2 * P.jt) + 1) * MOM_G + M) * (int64_t)sizeof(float) : 0;
     return RA_OK;
 }
 
@@ -4049,14 +4256,14 @@ int batch_step_mom(ra_ctx* ctx, const ra_batch* b, uint32_t flags, hipStream_t s
     const int2* ielem = (const int2*)b->items_elem;
     const int grid = b->grid_blocks > 0 ? b->grid_blocks : 1024;
     const size_t lds_f = (size_t)b->lmax * 1024;
-    const int nbuf = am_lds(b->nbin, 2) <= 160 * 1024 ? 2 : 1;
+    const int nbuf = am_lds(b->nbin, 2, 0, 2) <= 160 * 1024 ? 2 : 1;
     RA_HIP(ctx, allow_full_lds(k_forward_mom_batch));
     RA_HIP(ctx, allow_full_lds(k_adjoint_series_batch));
     hipLaunchKernelGGL(k_batch_begin, dim3(grid), dim3(BATCH_THREADS), 0, st, geos, b->reqs, ielem, b->counts);
     hipLaunchKernelGGL(k_forward_mom_batch, dim3(grid), dim3(FM_WAVES * WAVE), lds_f, st, geos, b->reqs,
                        (const int2*)b->items_fwd, b->counts, (int)lds_f);
     hipLaunchKernelGGL(k_batch_series, dim3(grid), dim3(MT_ROWS), 0, st, geos, b->reqs, ielem, b->counts);
-    hipLaunchKernelGGL(k_adjoint_series_batch, dim3(std::min(grid, NCU)), dim3(AM_WAVES * WAVE), am_lds(b->nbin, nbuf), st,
+    hipLaunchKernelGGL(k_adjoint_series_batch, dim3(std::min(grid, NCU)), dim3(AM_WAVES * WAVE), am_lds(b->nbin, 2, 0, nbuf), st,
                        geos, b->reqs, (const int2*)b->items_pose, (const int2*)b->items_vol, b->counts, b->nbin, nbuf);
     return batch_finish(ctx, b, flags, st);
 }
@@ -4080,7 +4287,7 @@ extern "C" int ra_batch_step(ra_ctx* ctx, const ra_batch* b, uint32_t flags, voi
         if (!ex || b->jt < 1 || b->jt > JMAX) return fail(ctx, RA_EINVAL, "moment form with a window it does not cover");
         if (b->nbin < 1 || b->nbin > BATCH_BINS_MAX)
             return fail(ctx, RA_EINVAL, "nbin must be the value ra_batch_describe reported");
-        if (am_lds(b->nbin, 1) > 160 * 1024) return fail(ctx, RA_EINVAL, "nbin exceeds the LDS of a workgroup");
+        if (am_lds(b->nbin, 2, 0, 1) > 160 * 1024) return fail(ctx, RA_EINVAL, "nbin exceeds the LDS of a workgroup");
     }
     RA_HIP(ctx, hipSetDevice(ctx->device));
     hipStream_t st = (hipStream_t)stream;
