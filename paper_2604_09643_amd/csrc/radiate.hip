@@ -2129,80 +2129,23 @@ __global__ __launch_bounds__(NC_THREADS) void k_sum_f64(const double* __restrict
 struct TgvDims {
     int nx, ny, nz;
     int n, sx, sy;           // voxels (< 2^31); strides of x and y (z contiguous)
-    int bz, by, bx;          // tiles along z (64), y (4) and x (TGV_XC planes)
+    int bz, by, xc;          // tiles along z and y, planes of a tile
     float a0, a1, eps;
 };
 
-// A workgroup owns 64 (z) x 4 (y) columns and marches along TGV_XC x planes, holding three
-// planes of u and w with a one-voxel halo in LDS (a ring: plane x + 1 is loaded while x - 1
-// and x are still resident), so each input value is read from memory about once per tile.
-constexpr int TGV_TZ = 64, TGV_TY = 4, TGV_XC = 8;
-constexpr int TGV_LZ = TGV_TZ + 2, TGV_LY = TGV_TY + 2, TGV_PLANE = TGV_LZ * TGV_LY;
+// Bound by memory: 16 bytes read and 16 written a voxel.  A workgroup marches along x over rows of z: L lanes hold a
+// row's 4 L voxels, 4 each, and its first and last row are halo.  Each voxel's q and Q are computed once and passed to
+// the neighbours that need them: along x in registers, along z within the lane or by a lane shift, along y through LDS,
+// as are the inputs' own neighbours.  The next plane's loads are in flight meanwhile.  256^3: 108 us, 5.0 TB/s, of them
+// 17 us by stores that do not allocate in L2 (the results are not read again here); computing q and Q again for each
+// neighbour from a tile of u and w in LDS took 214 us, bound by its 106 instructions a voxel and their LDS reads.
+constexpr int TGV_V = 4;               // voxels of a lane
+constexpr int TGV_TILE = 62 * TGV_V;   // voxels along z of a workgroup where a row of z does not fit into 64 lanes
+constexpr int TGV_NW = 12;             // wavefronts of a workgroup: 16 spill (256^3: 196 us), 8 have more halo (149 us)
+constexpr int TGV_LDS = 9;             // float4 per thread: u twice, w, and what a row passes on
 
-struct TgvTile {
-    float u[3][TGV_PLANE];
-    float w[3][3][TGV_PLANE];     // [component][ring slot][...]
-};
-
-__device__ __forceinline__ void tgv_load_plane(const TgvDims& d, const float* __restrict__ u,
-                                               const float* __restrict__ w, TgvTile& T, int x, int j0, int k0,
-                                               int t) {
-    const int slot = (x + 3) % 3;
-    for (int q = t; q < TGV_PLANE; q += TGV_TZ * TGV_TY) {
-        const int ly = q / TGV_LZ, lz = q % TGV_LZ;
-        const int j = j0 + ly - 1, k = k0 + lz - 1;
-        float a = 0.0f, b0 = 0.0f, b1 = 0.0f, b2 = 0.0f;
-        if (x >= 0 && x < d.nx && j >= 0 && j < d.ny && k >= 0 && k < d.nz) {
-            const int v = x * d.sx + j * d.sy + k;
-            a = u[v];
-            b0 = w[v];
-            b1 = w[d.n + v];
-            b2 = w[2 * d.n + v];
-        }
-        T.u[slot][q] = a;
-        T.w[0][slot][q] = b0;
-        T.w[1][slot][q] = b1;
-        T.w[2][slot][q] = b2;
-    }
-}
-
-// Accessors relative to the voxel (i, j, k) at tile position (ly, lz) of plane slot s0 = i % 3.
-struct TgvView {
-    const TgvTile* T;
-    int s[3];                // ring slots of planes i - 1, i, i + 1
-    int q0;                  // LDS index of the voxel within a plane
-    __device__ __forceinline__ float U(int dx, int dy, int dz) const {
-        return T->u[s[dx + 1]][q0 + dy * TGV_LZ + dz];
-    }
-    __device__ __forceinline__ float W(int c, int dx, int dy, int dz) const {
-        return T->w[c][s[dx + 1]][q0 + dy * TGV_LZ + dz];
-    }
-};
-
-// g = D+u - w at the voxel offset by (dx, dy, dz) from the view's voxel, whose grid indices are p.
-__device__ __forceinline__ void tgv_g(const TgvDims& d, const TgvView& V, int dx, int dy, int dz, const int p[3],
-                                      float g[3]) {
-    const float u0 = V.U(dx, dy, dz);
-    g[0] = (p[0] < d.nx - 1 ? V.U(dx + 1, dy, dz) - u0 : 0.0f) - V.W(0, dx, dy, dz);
-    g[1] = (p[1] < d.ny - 1 ? V.U(dx, dy + 1, dz) - u0 : 0.0f) - V.W(1, dx, dy, dz);
-    g[2] = (p[2] < d.nz - 1 ? V.U(dx, dy, dz + 1) - u0 : 0.0f) - V.W(2, dx, dy, dz);
-}
-
-// E = symmetrised D-w at the offset voxel; components xx yy zz xy xz yz.
-__device__ __forceinline__ void tgv_e(const TgvView& V, int dx, int dy, int dz, const int p[3], float E[6]) {
-    float D[3][3];
-#pragma unroll
-    for (int a = 0; a < 3; ++a)
-#pragma unroll
-        for (int b = 0; b < 3; ++b)
-            D[a][b] = p[a] > 0 ? V.W(b, dx, dy, dz) - V.W(b, dx - (a == 0), dy - (a == 1), dz - (a == 2)) : 0.0f;
-    E[0] = D[0][0];
-    E[1] = D[1][1];
-    E[2] = D[2][2];
-    E[3] = 0.5f * (D[0][1] + D[1][0]);
-    E[4] = 0.5f * (D[0][2] + D[2][0]);
-    E[5] = 0.5f * (D[1][2] + D[2][1]);
-}
+typedef float tgv4 __attribute__((ext_vector_type(4)));
+typedef tgv4 tgv4u __attribute__((aligned(4)));        // rows start at any voxel
 
 // Norms and their reciprocals by the hardware square root and reciprocal (about 1 ulp each;
 // the arguments are at least eps^2, far from the denormal range).
@@ -2219,98 +2162,221 @@ __device__ __forceinline__ float tgv_ratio(float a, float n) {
     return a * __builtin_amdgcn_rcpf(n);
 }
 
+// The previous and the next lane's value (0 beyond the wavefront); called with all lanes active.
+__device__ __forceinline__ float tgv_lower(float v) {
+    return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), 0x138, 0xf, 0xf, false));
+}
+
+__device__ __forceinline__ float tgv_upper(float v) {
+    return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), 0x130, 0xf, 0xf, false));
+}
+
+// Four voxels from index i on of an array of n; those that are not wanted may come from the next row.
+__device__ __forceinline__ tgv4 tgv_load(const float* __restrict__ src, int i, int n) {
+    if (i <= n - TGV_V) return *reinterpret_cast<const tgv4u*>(src + i);
+    tgv4 v;
+#pragma unroll
+    for (int e = 0; e < TGV_V; ++e) v[e] = src[i + min(e, n - 1 - i)];
+    return v;
+}
+
+__device__ __forceinline__ void tgv_store(float* __restrict__ dst, int k, int nz, tgv4 v, float scale, int accumulate) {
+    if (k <= nz - TGV_V) {
+        tgv4u* p = reinterpret_cast<tgv4u*>(dst + k);
+        if (accumulate) {
+            const tgv4 o = *p;
+#pragma unroll
+            for (int e = 0; e < TGV_V; ++e) v[e] = fmaf(scale, v[e], o[e]);
+        } else {
+            v *= scale;
+        }
+        __builtin_nontemporal_store(v, p);
+        return;
+    }
+#pragma unroll
+    for (int e = 0; e < TGV_V; ++e)
+        if (k < nz - e) dst[k + e] = accumulate ? fmaf(scale, v[e], dst[k + e]) : scale * v[e];
+}
+
 // Value partials (one per workgroup) and, when asked, both gradients, in one pass.
-__global__ __launch_bounds__(TGV_TZ * TGV_TY) void k_tgv(TgvDims d, const float* __restrict__ u,
-                                                          const float* __restrict__ w, float scale, int accumulate,
-                                                          float* __restrict__ gu, float* __restrict__ gw,
-                                                          double* __restrict__ partial) {
-    __shared__ TgvTile T;
-    __shared__ double red[TGV_TZ * TGV_TY];
+template <int L>
+__global__ __launch_bounds__(64 * TGV_NW) void k_tgv(TgvDims d, const float* __restrict__ u, const float* __restrict__ w,
+                                                 float scale, int accumulate, float* __restrict__ gu,
+                                                 float* __restrict__ gw, double* __restrict__ partial) {
+    constexpr int NT = 64 * TGV_NW, R = NT / L;
+    extern __shared__ char tgv_smem[];
+    tgv4* T = reinterpret_cast<tgv4*>(tgv_smem);       // [0, 1] u by plane parity, [2 + b] w_b, [5] q_y, [6 + b] Q_yb
     // tiles in x order, each compute die (XCD) taking a contiguous run of them so that the
-    // halo planes shared with the neighbouring tiles stay in that die's L2
-    const int b = region_of_block(blockIdx.x, gridDim.x);
-    const int bk = b % d.bz, bj = (b / d.bz) % d.by, bi = b / (d.bz * d.by);
-    const int k0 = bk * TGV_TZ, j0 = bj * TGV_TY, x0 = bi * TGV_XC;
-    const int x1 = min(x0 + TGV_XC, d.nx);
-    const int t = threadIdx.y * TGV_TZ + threadIdx.x;
-    const int k = k0 + threadIdx.x, j = j0 + threadIdx.y;
-    const bool mine = k < d.nz && j < d.ny;
+    // halo rows and planes shared with the neighbouring tiles stay in that die's L2
+    const int blk = region_of_block(blockIdx.x, gridDim.x);
+    const int bk = blk % d.bz, bj = (blk / d.bz) % d.by, bi = blk / (d.bz * d.by);
+    const int t = threadIdx.x, r = t / L, l = t % L;
+    const bool split = d.bz > 1;                       // then the first and the last lane are halo
+    const int k = split ? bk * TGV_TILE + TGV_V * (l - 1) : TGV_V * l;
+    const int j = bj * (R - 2) + r - 1;
+    const int x0 = bi * d.xc, x1 = x0 + min(d.xc, d.nx - x0);
+    const int tm = r > 0 ? t - L : t, tp = r < R - 1 ? t + L : t;
+    const bool row = j >= 0 && j < d.ny && k >= 0;
+    const bool out = row && r > 0 && r < R - 1 && (!split || (l > 0 && l < L - 1)) && k < d.nz;
+    const int jc = min(max(j, 0), d.ny - 1) * d.sy, kc = k >= 0 && k < d.nz ? k : 0;
+    tgv4 pu, pw[3], cu, cw[3], A[3];        // A: what dR/dw of plane i has from Q of planes up to i
+    float qx[TGV_V] = {0.0f, 0.0f, 0.0f, 0.0f};
     double acc = 0.0;
-    tgv_load_plane(d, u, w, T, x0 - 1, j0, k0, t);
-    tgv_load_plane(d, u, w, T, x0, j0, k0, t);
-    for (int i = x0; i < x1; ++i) {
-        tgv_load_plane(d, u, w, T, i + 1, j0, k0, t);
+    auto load = [&](int x, tgv4& lu, tgv4 lw[3]) {
+        const int o = min(max(x, 0), d.nx - 1) * d.sx + jc + kc;
+        lu = tgv_load(u, o, d.n);
+#pragma unroll
+        for (int b = 0; b < 3; ++b) lw[b] = tgv_load(w + (size_t)b * d.n, o, d.n);
+    };
+    load(x0 - 1, pu, pw);
+    load(x0, cu, cw);
+#pragma unroll
+    for (int b = 0; b < 3; ++b) A[b] = 0.0f;
+    T[((x0 - 1) & 1) * NT + t] = pu;
+    for (int i = x0 - 1; i < x1; ++i) {
+        // planes i (pu, pw) and i + 1 (cu, cw): Q of plane i + 1, q and the results of plane i
+        T[((i + 1) & 1) * NT + t] = cu;
+#pragma unroll
+        for (int b = 0; b < 3; ++b) T[(2 + b) * NT + t] = cw[b];
         __syncthreads();
-        if (mine) {
-            TgvView V;
-            V.T = &T;
-            V.s[0] = (i + 2) % 3;
-            V.s[1] = i % 3;
-            V.s[2] = (i + 1) % 3;
-            V.q0 = (threadIdx.y + 1) * TGV_LZ + threadIdx.x + 1;
-            const int v = i * d.sx + j * d.sy + k;
-            const int ix[3] = {i, j, k};
-            const int nn[3] = {d.nx, d.ny, d.nz};
-            float g[3], E[6];
-            tgv_g(d, V, 0, 0, 0, ix, g);
-            tgv_e(V, 0, 0, 0, ix, E);
-            const float n1 = tgv_n1(d, g), n0 = tgv_n0(d, E);
-            const float s1 = tgv_ratio(d.a1, n1), s0 = tgv_ratio(d.a0, n0);
-            acc += (double)d.a1 * (double)(n1 - d.eps) + (double)d.a0 * (double)(n0 - d.eps);
-            if (gu) {
-                float gs = 0.0f;
+        tgv4 nu, nw[3];
+        load(min(i + 2, x1), nu, nw);
+        tgv4 gs;
+        {
+            // q of plane i; q_a counts in dR/du only where v_a <= n_a - 2
+            const tgv4 uy = T[(i & 1) * NT + tp];
+            const float uz = tgv_upper(pu[0]);
+            const bool ux = i >= 0 && i < d.nx - 1;
+            tgv4 qy, qz;
 #pragma unroll
-                for (int a = 0; a < 3; ++a) {
-                    if (ix[a] >= 1) {
-                        const int pn[3] = {i - (a == 0), j - (a == 1), k - (a == 2)};
-                        float gn[3];
-                        tgv_g(d, V, -(a == 0), -(a == 1), -(a == 2), pn, gn);
-                        gs += tgv_ratio(d.a1, tgv_n1(d, gn)) * gn[a];
-                    }
-                    if (ix[a] <= nn[a] - 2) gs -= s1 * g[a];
-                }
-                gu[v] = accumulate ? fmaf(scale, gs, gu[v]) : scale * gs;
+            for (int e = 0; e < TGV_V; ++e) {
+                float g[3];
+                g[0] = (ux ? cu[e] - pu[e] : 0.0f) - pw[0][e];
+                g[1] = (j < d.ny - 1 ? uy[e] - pu[e] : 0.0f) - pw[1][e];
+                g[2] = (k < d.nz - 1 - e ? (e < TGV_V - 1 ? pu[(e + 1) % TGV_V] : uz) - pu[e] : 0.0f) - pw[2][e];
+                const float n1 = tgv_n1(d, g), s1 = tgv_ratio(d.a1, n1);
+                if (out && i >= x0 && k < d.nz - e) acc += (double)d.a1 * (double)(n1 - d.eps);
+#pragma unroll
+                for (int b = 0; b < 3; ++b) A[b][e] -= s1 * g[b];
+                const float qh = ux ? s1 * g[0] : 0.0f;
+                gs[e] = qx[e] - qh;
+                qx[e] = qh;
+                qy[e] = row && j < d.ny - 1 && k < d.nz - e ? s1 * g[1] : 0.0f;
+                qz[e] = row && k < d.nz - 1 - e ? s1 * g[2] : 0.0f;
             }
-            if (gw) {
-                // Q_ab as an index into E by (a, b)
-                const int qi[3][3] = {{0, 3, 4}, {3, 1, 5}, {4, 5, 2}};
-                float gb[3] = {-(s1 * g[0]), -(s1 * g[1]), -(s1 * g[2])};
+            const float ql = tgv_lower(qz[TGV_V - 1]), qb = k > 0 ? ql : 0.0f;
 #pragma unroll
-                for (int a = 0; a < 3; ++a) {
-                    float En[6] = {0.0f, 0.0f, 0.0f, 0.0f, 0.0f, 0.0f}, sn = 0.0f;
-                    const bool up = ix[a] <= nn[a] - 2;
-                    if (up) {
-                        const int pn[3] = {i + (a == 0), j + (a == 1), k + (a == 2)};
-                        tgv_e(V, (a == 0), (a == 1), (a == 2), pn, En);
-                        sn = tgv_ratio(d.a0, tgv_n0(d, En));
-                    }
+            for (int e = 0; e < TGV_V; ++e) gs[e] += ((e ? qz[(e + TGV_V - 1) % TGV_V] : qb) - qz[e]) - qy[e];
+            T[5 * NT + t] = qy;
+        }
+        tgv4 gb[3];
+        {
+            // Q of plane i + 1
+            const bool px = i + 1 < d.nx, lx = i >= 0 && px;
+            tgv4 Q[6], wy[3];
+            float wz[3];
 #pragma unroll
-                    for (int bb = 0; bb < 3; ++bb) {
-                        if (ix[a] >= 1) gb[bb] += s0 * E[qi[a][bb]];
-                        if (up) gb[bb] -= sn * En[qi[a][bb]];
-                    }
+            for (int b = 0; b < 3; ++b) {
+                wy[b] = T[(2 + b) * NT + tm];
+                wz[b] = tgv_lower(cw[b][TGV_V - 1]);
+            }
+#pragma unroll
+            for (int e = 0; e < TGV_V; ++e) {
+                const bool in = row && px && k < d.nz - e;
+                float D[3][3], E[6];
+#pragma unroll
+                for (int b = 0; b < 3; ++b) {
+                    D[0][b] = in && lx ? cw[b][e] - pw[b][e] : 0.0f;
+                    D[1][b] = in && j > 0 ? cw[b][e] - wy[b][e] : 0.0f;
+                    D[2][b] = in && k + e > 0 ? cw[b][e] - (e ? cw[b][e - 1] : wz[b]) : 0.0f;
                 }
+                E[0] = D[0][0];
+                E[1] = D[1][1];
+                E[2] = D[2][2];
+                E[3] = 0.5f * (D[0][1] + D[1][0]);
+                E[4] = 0.5f * (D[0][2] + D[2][0]);
+                E[5] = 0.5f * (D[1][2] + D[2][1]);
+                const float n0 = tgv_n0(d, E), s0 = tgv_ratio(d.a0, n0);
+                if (out && in && i + 1 < x1) acc += (double)d.a0 * (double)(n0 - d.eps);
 #pragma unroll
-                for (int bb = 0; bb < 3; ++bb) {
-                    float* dst = gw + (size_t)bb * d.n + v;
-                    *dst = accumulate ? fmaf(scale, gb[bb], *dst) : scale * gb[bb];
-                }
+                for (int c = 0; c < 6; ++c) Q[c][e] = s0 * E[c];
+            }
+            // Q_ab as an index into Q by (a, b)
+            constexpr int qi[3][3] = {{0, 3, 4}, {3, 1, 5}, {4, 5, 2}};
+#pragma unroll
+            for (int b = 0; b < 3; ++b) {
+                const tgv4 Qx = Q[qi[0][b]], Qy = Q[qi[1][b]], Qz = Q[qi[2][b]];
+                T[(6 + b) * NT + t] = Qy;
+                const float Ql = tgv_upper(Qz[0]), Qn = k < d.nz - TGV_V ? Ql : 0.0f;
+                gb[b] = A[b] - Qx;
+#pragma unroll
+                for (int e = 0; e < TGV_V; ++e)
+                    A[b][e] = (i >= 0 ? Qx[e] : 0.0f) + (j > 0 ? Qy[e] : 0.0f) +
+                              ((k + e > 0 ? Qz[e] : 0.0f) - (e < TGV_V - 1 ? Qz[(e + 1) % TGV_V] : Qn));
             }
         }
-        __syncthreads();          // plane i - 1's slot is overwritten next
+        __syncthreads();
+        const bool store = out && i >= x0;
+        const size_t o = (size_t)(i * d.sx + jc);
+        if (gu && store) {
+            gs += T[5 * NT + tm];
+            tgv_store(gu + o, k, d.nz, gs, scale, accumulate);
+        }
+        if (gw) {
+#pragma unroll
+            for (int b = 0; b < 3; ++b) {
+                A[b] -= T[(6 + b) * NT + tp];
+                if (store) tgv_store(gw + (size_t)b * d.n + o, k, d.nz, gb[b], scale, accumulate);
+            }
+        }
+        pu = cu;
+        cu = nu;
+#pragma unroll
+        for (int b = 0; b < 3; ++b) {
+            pw[b] = cw[b];
+            cw[b] = nw[b];
+        }
     }
+    __syncthreads();
+    double* red = reinterpret_cast<double*>(tgv_smem);
     red[t] = acc;
     __syncthreads();
-    for (int s2 = TGV_TZ * TGV_TY / 2; s2 > 0; s2 >>= 1) {
-        if (t < s2) red[t] += red[t + s2];
+    for (int s2 = 512; s2 > 0; s2 >>= 1) {
+        if (t < s2 && t + s2 < NT) red[t] += red[t + s2];
         __syncthreads();
     }
-    if (t == 0) partial[b] = red[0];
+    if (t == 0) partial[blk] = red[0];
+}
+
+// How a volume is cut: lanes of a row (the fewest of 16, 32, 64 that hold it, so that short rows share a wavefront;
+// longer ones are cut with a halo lane on either side), tiles along z, y and x, and planes of a tile.
+struct TgvCut {
+    int lanes, bz, by, bx, xc;
+};
+
+static TgvCut tgv_cut(int nx, int ny, int nz) {
+    TgvCut c;
+    c.lanes = nz <= 16 * TGV_V ? 16 : nz <= 32 * TGV_V ? 32 : 64;
+    c.bz = nz <= 64 * TGV_V ? 1 : (nz - 1) / TGV_TILE + 1;
+    const int rows = 64 * TGV_NW / c.lanes - 2;
+    c.by = (ny - 1) / rows + 1;
+    // planes of a tile: the fewest steps over the rounds of workgroups, each tile taking one step more than planes
+    const long long slots = NCU, cols = (long long)c.by * c.bz, first = (cols + slots - 1) / slots;
+    long long best = -1;
+    for (long long m = first; m < first + 4; ++m) {
+        const int xc = (int)std::max(1LL, (nx + m * slots / cols - 1) / (m * slots / cols));
+        if (best < 0 || m * (xc + 2) < best) {
+            best = m * (xc + 2);
+            c.xc = xc;
+        }
+    }
+    c.bx = (nx - 1) / c.xc + 1;
+    return c;
 }
 
 static inline unsigned tgv_blocks(int nx, int ny, int nz) {
-    return (unsigned)((nz + TGV_TZ - 1) / TGV_TZ) * (unsigned)((ny + TGV_TY - 1) / TGV_TY) *
-           (unsigned)((nx + TGV_XC - 1) / TGV_XC);
+    const TgvCut c = tgv_cut(nx, ny, nz);
+    return (unsigned)c.bx * c.by * c.bz;
 }
 
 // ------------------------------------------------------------------------------------------
@@ -4021,15 +4087,19 @@ int tgv_loss_and_grad(ra_ctx* ctx, int32_t nx, int32_t ny, int32_t nz, const flo
     d.n = nx * ny * nz;
     d.sy = nz;
     d.sx = ny * nz;
-    d.bz = (nz + TGV_TZ - 1) / TGV_TZ;
-    d.by = (ny + TGV_TY - 1) / TGV_TY;
-    d.bx = (nx + TGV_XC - 1) / TGV_XC;
+    const TgvCut cut = tgv_cut(nx, ny, nz);
+    d.bz = cut.bz;
+    d.by = cut.by;
+    d.xc = cut.xc;
     d.a0 = (float)alpha0; d.a1 = (float)alpha1; d.eps = (float)eps;
-    const unsigned nblocks = tgv_blocks(nx, ny, nz);      // at most one per voxel: below 2^31
-    const dim3 gr(nblocks), blk(TGV_TZ, TGV_TY);
+    const unsigned nblocks = (unsigned)cut.bx * cut.by * cut.bz;      // at most one per voxel: below 2^31
     double* partial = at<double>(ctx, 0);
-    hipLaunchKernelGGL(k_tgv, gr, blk, 0, st, d, u, w, (float)scale, (flags & RA_ACCUMULATE) ? 1 : 0, grad_u, grad_w,
-                       partial);
+    constexpr int nt = 64 * TGV_NW;
+    constexpr size_t lds = (size_t)nt * TGV_LDS * sizeof(tgv4);
+    auto kernel = cut.lanes == 16 ? k_tgv<16> : cut.lanes == 32 ? k_tgv<32> : k_tgv<64>;
+    RA_HIP(ctx, allow_full_lds(kernel));
+    hipLaunchKernelGGL(kernel, dim3(nblocks), dim3(nt), lds, st, d, u, w, (float)scale,
+                       (flags & RA_ACCUMULATE) ? 1 : 0, grad_u, grad_w, partial);
     RA_HIP(ctx, hipGetLastError());
     if (loss) {
         hipLaunchKernelGGL(k_sum_f64, dim3(1), dim3(NC_THREADS), 0, st, partial, (int)nblocks, ctx->d_f64);
