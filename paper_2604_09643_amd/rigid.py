@@ -85,17 +85,20 @@ def finetune(grid: L.Grid, p0, samp: L.Sampling, y, template, euler6, inliers, s
     elem = torch.as_tensor(template, dtype=torch.float64, device=dev).contiguous()
     wt = torch.as_tensor(np.asarray(inliers, dtype=np.float32), device=dev).reshape(1, M).contiguous()
     yb = y.reshape(1, M, samp.K).contiguous()
-    a = torch.as_tensor(np.asarray(euler6[:3]), dtype=torch.float64, device=dev).clone().requires_grad_(True)
-    t = torch.as_tensor(np.asarray(euler6[3:]), dtype=torch.float64, device=dev).clone().requires_grad_(True)
-    opt = torch.optim.Adam([{"params": [a], "lr": lr_angle}, {"params": [t], "lr": lr_t}])
-    gpose = torch.empty((1, 12), dtype=torch.float64, device=dev)
+    # angles and translation are parts of one vector, their gradients of another, and Adam runs as one kernel per group:
+    # (four steps at 72x64x64 voxels and 64 elements 1.09 ms; 1.60 with separate tensors and its default kernels)
+    p6 = torch.as_tensor(np.asarray(euler6, dtype=np.float64)).to(dev, copy=True).reshape(1, 6)
+    a, t = p6[0, :3].detach().requires_grad_(True), p6[0, 3:].detach().requires_grad_(True)
+    opt = torch.optim.Adam([{"params": [a], "lr": lr_angle}, {"params": [t], "lr": lr_t}], fused=True)
+    poses = torch.empty((1, 12), dtype=torch.float64, device=dev)
+    gpose = torch.empty_like(poses)
+    g6 = torch.empty_like(p6)
+    a.grad, t.grad = g6[0, :3], g6[0, 3:]
     for _ in range(steps):
-        p6 = torch.cat([a.detach(), t.detach()]).reshape(1, 6).contiguous()
-        poses = L.pose_from_euler(p6, ctx=ctx)
+        L.pose_from_euler(p6, poses, ctx=ctx)
         loss = L.nc_loss_and_grad(grid, p0, elem, poses, samp, yb, weight=wt, grad_pose=gpose, ctx=ctx)
-        g6 = L.pose_grad_euler(p6, gpose, ctx=ctx)[0]
-        a.grad, t.grad = g6[:3].clone(), g6[3:].clone()
+        L.pose_grad_euler(p6, gpose, g6, ctx=ctx)
         opt.step()
         if history is not None:
             history.append(loss)
-    return torch.cat([a.detach(), t.detach()])
+    return p6[0]
