@@ -29,15 +29,14 @@ PEAK_FP32_TFLOPS = 157.3          # MI355X published FP32 vector peak
 # exponential, reported separately against the measured v_exp_f32 rate
 FLOP_PER_UPDATE = 7
 EXP_PER_UPDATE = 1
-# transcendentals the forward kernel executes per (voxel, element) pair: two exponentials of the
-# factorised window (the start of the pair's row chain and its ratio H) and one reciprocal square
-# root of the distance
-TRANS_PER_PAIR_FWD = 3
+# transcendentals the forward kernel executes per (voxel, element) pair: the reciprocal square root of
+# the distance (a pair's window is 7 polynomial moments, without exponentials)
+TRANS_PER_PAIR_FWD = 1
 # algorithmic work of the moment-form dL/dp0 adjoint: per (voxel, element) pair the distance (18
-# FLOP and one reciprocal square root), the centre sample and offset (3), Horner's rule over the 8
-# moments (14), the 1/(2d) factor and the lane sum (2) = 37 FLOP; per element and row of the moment
-# table (K + 2 JT rows, JT = floor(6 sigma / delta + 1/2)), 8 moments of 2 JT + 1 taps
-FLOP_PER_PAIR_ADJ_MOMENT = 37
+# FLOP and one reciprocal square root), the centre sample and offset (3), Horner's rule over the 7
+# moments of this kernel width (12), the 1/(2d) factor and the lane sum (2) = 35 FLOP; per element and
+# row of the moment table (K + 2 JT rows, JT = floor(6 sigma / delta + 1/2)), 8 moments of 2 JT + 1 taps
+FLOP_PER_PAIR_ADJ_MOMENT = 35
 
 
 def parse():
@@ -705,7 +704,7 @@ def main():
     ms_fwd, ms_adj = float(np.mean(t_fwd)), float(np.mean(t_adj))
     print("[bench] radiate_forward %.3f ms, radiate_adjoint(p0) %.3f ms" % (ms_fwd, ms_adj),
           file=sys.stderr, flush=True)
-    dom_name, dom_ms = ("k_forward", ms_fwd) if ms_fwd >= ms_adj else ("k_adjoint", ms_adj)
+    dom_name, dom_ms = ("k_forward_mom", ms_fwd) if ms_fwd >= ms_adj else ("k_adjoint_series", ms_adj)
     achieved = FLOP_PER_UPDATE * n_upd / (dom_ms * 1e-3) / 1e12
     fma_rate, exp_rate = ctx.probe_rates()
     pairs = w.n_voxels * w.F * w.M
@@ -745,7 +744,7 @@ def main():
                          "executed_per_s": TRANS_PER_PAIR_FWD * pairs / (ms_fwd * 1e-3),
                          "measured_exp_peak_per_s": exp_rate,
                          "frac_executed": TRANS_PER_PAIR_FWD * pairs / (ms_fwd * 1e-3) / exp_rate}},
-        "adjoint_roofline": {"kernel": "k_adjoint_mom with k_moment_table (dL/dp0, moment form)", "bound": "alu",
+        "adjoint_roofline": {"kernel": "k_adjoint_series with k_moment_series (dL/dp0, moment form)", "bound": "alu",
                              "achieved": adj_achieved, "peak": PEAK_FP32_TFLOPS, "unit": "TFLOP/s",
                              "frac": adj_achieved / PEAK_FP32_TFLOPS, "flop_per_pair": FLOP_PER_PAIR_ADJ_MOMENT,
                              "pairs_per_launch": pairs, "table_rows": table_rows,
