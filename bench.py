@@ -299,7 +299,8 @@ def serving_bench(n_requests: int, rate: float, seed: int = 0, rates=(10.0, 20.0
     t_start = time.perf_counter()
     warm, _ = requests(6, 1e6, seed + 99)
     run("batched", warm)                                   # build and capture once, untimed
-    run("unbatched", warm[:2])
+    # fresh requests: a served one's arrival is an absolute time, and would be added to the clock again
+    run("unbatched", requests(2, 1e6, seed + 98)[0])
     print("[bench] serving: executors built and warmed (%.1f s)" % (time.perf_counter() - t_start),
           file=sys.stderr, flush=True)
     points = []
