@@ -104,7 +104,7 @@ constexpr int MOM_G = 8;              // and the Gaussian's
 constexpr double FM_TOL = 2e-7;       // its largest admitted expansion error, relative to the peak
 constexpr double FM_EDGE = 0.004;     // its largest phi at the window's edge (other profiles), relative to the peak
 constexpr double AM_TOL = 2.5e-8;     // that error where the series' derivative is used (its 8 terms' grows 8-fold in rms)
-constexpr size_t AM_TABLE_MAX = (size_t)16 << 30;   // bytes of the other profiles' moment table
+constexpr size_t AM_TABLE_MAX = (size_t)16 << 30;   // bytes of the moment table (wide Gaussians: any)
 constexpr int AM_WAVES = 16;          // wavefronts of the moment-form adjoints' region workgroup, one per CU
 constexpr int AM_REFS = 3;            // references held: this chunk's, the next one's and the one after
 constexpr size_t LDS_FM_BUDGET = 80 * 1024;    // two of its workgroups per CU
@@ -3496,9 +3496,10 @@ void make_plan(ra_ctx* ctx, const ra_grid* grid, int32_t M, int32_t F, const ra_
         const bool x = mt.xkind != 0;
         plan_forward_mom(grid, samp, mt, P);
         // Up to 48 bytes of table per sample of dL/ds, where the row forms need none: beyond AM_TABLE_MAX those
-        // serve the other profiles, so that a sweep whose signals fill the memory still has room.
+        // serve the other profiles and narrow Gaussians, so that a sweep whose signals fill the memory still has
+        // room.  Wider Gaussians have always taken a table: their row form is 3 times slower.
         const size_t table = (size_t)g.E * (g.K + 2 * jout) * am_nq(MOM_MAX) * sizeof(float4);
-        const bool room = g.ktype == RA_KERNEL_GAUSSIAN || table <= AM_TABLE_MAX;
+        const bool room = table <= AM_TABLE_MAX || (g.ktype == RA_KERNEL_GAUSSIAN && delta <= 0.559 * sigma);
         P.am = room && plan_adjoint_mom(grid, samp, g, x ? 45.0 : 30.0, am_nq(mt.vol), x, P.ga1, P.am_nbuf[0]);
         P.am_pose = room && mt.pose && plan_adjoint_mom(grid, samp, g, x ? 60.0 : 43.0, am_nq(mt.pose), x, P.ga2, P.am_nbuf[1]);
         set_terms(P.ga1, mt);
