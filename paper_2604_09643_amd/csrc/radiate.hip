@@ -3383,9 +3383,17 @@ bool plan_adjoint_mom(const ra_grid* grid, const ra_sampling* samp, const Geo& b
     return found;
 }
 
+// Calls that return the sum of the elements' negative correlations: that sum is signed and may cancel to 1e-3 of its
+// terms or less, where what the two forms of the forward round differently (1e-6 of a signal) shows in its digits
+// (boxes of 36 to 82 voxels a side, 24 to 106 elements: up to 9e-5 of the sum, above 2e-5 for 4 of 150 inputs; row
+// form against itself 2e-6).  They keep the row form, so that their losses compare with recorded ones, and with edge
+// terms the adjoints' row forms, which decide the window's edge as that forward does.  Scores and gradients
+// without the sum take the moment forms.
+constexpr unsigned PLAN_ROW_FORWARD = 1u;
+
 // The context keeps the moment forms' series; without one (the batched step) the plan has the row forms only.
 void make_plan(ra_ctx* ctx, const ra_grid* grid, int32_t M, int32_t F, const ra_sampling* samp, Plan& P,
-               int sums_mode = RA_SUMS_AUTO) {
+               int sums_mode = RA_SUMS_AUTO, unsigned only = 0) {
     Geo& g = P.g;
     std::memset(&g, 0, sizeof(g));
     g.nx = grid->nx; g.ny = grid->ny; g.nz = grid->nz;
@@ -3504,6 +3512,10 @@ void make_plan(ra_ctx* ctx, const ra_grid* grid, int32_t M, int32_t F, const ra_
         P.am_pose = room && mt.pose && plan_adjoint_mom(grid, samp, g, x ? 60.0 : 43.0, am_nq(mt.pose), x, P.ga2, P.am_nbuf[1]);
         set_terms(P.ga1, mt);
         set_terms(P.ga2, mt);
+        if (only & PLAN_ROW_FORWARD) {
+            P.fm = false;
+            if (x) P.am = P.am_pose = false;
+        }
     }
     P.part_rows = P.am_pose ? std::min(P.ga2.nreg, NCU) : g.nreg;
 
@@ -3897,9 +3909,13 @@ int ra_reserve(ra_ctx* ctx, size_t bytes) {
 size_t ra_scratch_bytes(const ra_grid* grid, int32_t M, int32_t F, const ra_sampling* samp) {
     ra_ctx tmp;
     if (validate(&tmp, grid, M, F, samp) != RA_OK) return 0;
-    Plan P;
-    make_plan(&tmp, grid, M, F, samp, P, RA_SUMS_F64);      // the largest of the forward's sum modes
-    return P.total;
+    size_t most = 0;
+    for (unsigned only : {0u, PLAN_ROW_FORWARD}) {
+        Plan P;
+        make_plan(&tmp, grid, M, F, samp, P, RA_SUMS_F64, only);      // the largest of the forward's sum modes
+        most = std::max(most, P.total);
+    }
+    return most;
 }
 
 int ra_set_forward_sums(ra_ctx* ctx, int32_t mode) {
@@ -4022,7 +4038,7 @@ int nc_loss_and_grad(ra_ctx* ctx, const ra_grid* grid, const float* p0, int32_t 
     hipStream_t st = (hipStream_t)stream;
     RA_HIP(ctx, hipSetDevice(ctx->device));
     Plan P;
-    make_plan(ctx, grid, M, F, samp, P, ctx->sums_mode);
+    make_plan(ctx, grid, M, F, samp, P, ctx->sums_mode, loss ? PLAN_ROW_FORWARD : 0);
     if ((rc = ensure_scratch(ctx, P.total, st)) != RA_OK) return rc;
     if ((rc = prologue(ctx, ctx->arena, grid, P, elem, poses, st)) != RA_OK) return rc;
     float* s = at<float>(ctx, P.off_s);
