@@ -11,7 +11,8 @@
  * of Appendix A replace the Gaussian, see ra_sampling).  The Gaussian's calls take the
  * samples within floor(trunc*sigma*fs/c + 1/2) of each term's nearest sample whole: every
  * kept term is among them, and each term they add beyond the window is below psi(trunc) of
- * the kernel's peak (psi(y) = y exp(-y^2/2); 1.5e-7 at trunc = 6).  Each voxel-element pair's
+ * the kernel's peak (psi(y) = y exp(-y^2/2); 1.5e-7 at trunc = 6); the adjoints of narrow
+ * Gaussians (c/fs > 0.559 sigma) with trunc < 6 keep to the window.  Each voxel-element pair's
  * window is evaluated as a polynomial of 6 to 8 terms in the pair's offset from its nearest
  * sample, whose error is below 2e-7 of the peak (the library takes it only where that bound
  * holds, and otherwise evaluates the window sample by sample).  Main text Eq. (1)

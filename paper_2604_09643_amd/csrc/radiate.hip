@@ -104,6 +104,7 @@ constexpr int MOM_G = 8;              // and the Gaussian's
 constexpr double FM_TOL = 2e-7;       // its largest admitted expansion error, relative to the peak
 constexpr double FM_EDGE = 0.004;     // its largest phi at the window's edge (other profiles), relative to the peak
 constexpr double AM_TOL = 2.5e-8;     // that error where the series' derivative is used (its 8 terms' grows 8-fold in rms)
+constexpr double WIDE_GAUSS = 0.559;  // delta/sigma up to which Gaussian adjoints take the rows whole for any window, and a table of any size
 constexpr size_t AM_TABLE_MAX = (size_t)16 << 30;   // bytes of the moment table (wide Gaussians: any)
 constexpr int AM_WAVES = 16;          // wavefronts of the moment-form adjoints' region workgroup, one per CU
 constexpr int AM_REFS = 3;            // references held: this chunk's, the next one's and the one after
@@ -3260,6 +3261,9 @@ const MomTerms& series_terms(ra_ctx* ctx, const ra_sampling* samp, bool exact) {
     if (!t.fwd) return t;
     t.vol = kt == RA_KERNEL_GAUSSIAN ? t.fwd : kt == RA_KERNEL_POWER && t.fwd > 8 ? 12 : terms[kt][1] == 10 ? 8 : terms[kt][1];
     t.pose = kt == RA_KERNEL_POWER ? (tail[8] <= AM_TOL ? 8 : fewest(AM_TOL, 2)) : fewest(AM_TOL, 2);
+    // Short windows of narrow Gaussians: the adjoints' row forms test the window's outermost samples, whose terms
+    // are psi(trunc) of the peak (1.5e-7 from 6 sigma on, 1.6e-3 at 4)
+    if (kt == RA_KERNEL_GAUSSIAN && samp->trunc < 6.0 && dd > WIDE_GAUSS) t.vol = t.pose = 0;
     const int nm[3] = {t.fwd, t.vol, t.pose};
     MomCoef* const out[3] = {&ctx->series, &ctx->seriesv, &ctx->seriesp};
     for (int i = 0; i < 3; ++i) {
@@ -3507,8 +3511,8 @@ void make_plan(ra_ctx* ctx, const ra_grid* grid, int32_t M, int32_t F, const ra_
         // serve the other profiles and narrow Gaussians, so that a sweep whose signals fill the memory still has
         // room.  Wider Gaussians have always taken a table: their row form is 3 times slower.
         const size_t table = (size_t)g.E * (g.K + 2 * jout) * am_nq(MOM_MAX) * sizeof(float4);
-        const bool room = table <= AM_TABLE_MAX || (g.ktype == RA_KERNEL_GAUSSIAN && delta <= 0.559 * sigma);
-        P.am = room && plan_adjoint_mom(grid, samp, g, x ? 45.0 : 30.0, am_nq(mt.vol), x, P.ga1, P.am_nbuf[0]);
+        const bool room = table <= AM_TABLE_MAX || (g.ktype == RA_KERNEL_GAUSSIAN && delta <= WIDE_GAUSS * sigma);
+        P.am = room && mt.vol && plan_adjoint_mom(grid, samp, g, x ? 45.0 : 30.0, am_nq(mt.vol), x, P.ga1, P.am_nbuf[0]);
         P.am_pose = room && mt.pose && plan_adjoint_mom(grid, samp, g, x ? 60.0 : 43.0, am_nq(mt.pose), x, P.ga2, P.am_nbuf[1]);
         set_terms(P.ga1, mt);
         set_terms(P.ga2, mt);
