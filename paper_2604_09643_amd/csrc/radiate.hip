@@ -155,7 +155,7 @@ __device__ __forceinline__ DF df_sqrt(DF a) {
     float s = sqrtf(a.h);
     DF p = two_prod(s, s);
     float r = ((a.h - p.h) - p.l) + a.l;
-    return quick_two_sum(s, r / (2.0f * s));
+    return quick_two_sum(s, s == 0.0f ? 0.0f : r / (2.0f * s));   // an element may sit at the centre of a region that ends short
 }
 __device__ __forceinline__ DF df_from_double(double x) {
 #pragma clang fp contract(off)
@@ -883,8 +883,7 @@ __device__ __forceinline__ MomRef mom_make_ref(const Geo& g, const float* __rest
     r.uc0 = d.h - 2.0f * kc;
     r.n0 = d.h * d.l;
     r.kc = (int)kc;
-    // |D.o + o.o/2| < 2^e of this product (columns reach up to 4 voxels past a short region), so multiples
-    // of 2^(e - 22) below it add exactly
+    // |D.o + o.o/2| < 2^e of this product, so multiples of 2^(e - 22) below it add exactly
     const float rad = sqrtf(h2) + 4.0f * g.hs_u;
     r.magic = 1.5f * __builtin_amdgcn_ldexpf(1.0f, __builtin_amdgcn_frexp_expf(rad * (d.h + rad)) + 1);
     return r;
@@ -895,15 +894,17 @@ struct FmScale {
     float scale, inv;
 };
 
-__device__ __forceinline__ FmScale fm_scale(const Geo& g, const MomRef& m, const FmBound& bd) {
+__device__ __forceinline__ FmScale fm_scale(const Geo& g, const Region& R, const MomRef& m, const FmBound& bd) {
 #pragma clang fp contract(off)
     const float half[3] = {0.5f * (float)(g.rx - 1) * g.hs_u, 0.5f * (float)(g.ry - 1) * g.hs_u,
                            0.5f * (float)(g.rz - 1) * g.hs_u};
     const float far = m.dh + sqrtf(half[0] * half[0] + half[1] * half[1] + half[2] * half[2]);
+    const int n[3] = {R.ni, R.nj, R.nk};
     float dl2 = 0.0f, most = bd.all;
 #pragma unroll
     for (int a = 0; a < 3; ++a) {
-        const float out = fabsf(m.D[a]) - half[a];           // distance past the box along the axis
+        // distance past the region's voxels along the axis, before the first or beyond the last
+        const float out = fmaxf(m.D[a] - half[a], half[a] - (float)(n[a] - 1) * g.hs_u - m.D[a]);
         if (!(out > 0.0f)) continue;
         dl2 += out * out;
         const float gap = g.hs_u * 0.999f * out / far;       // least difference in distance of two voxels of a line
@@ -938,24 +939,28 @@ __device__ __forceinline__ int cvt_round_i32(float x) {      // floor(x + 1/2)
 }
 
 // Offsets of a region's voxels from its centre along each axis, [axis][index] (along z: of the centres of its
-// columns of FM_RZ voxels), as fm_axis takes them.
-__device__ __forceinline__ void fm_axis_table(const Geo& g, int tid, float4* axis) {
+// columns), as fm_axis takes them.  A column holds FM_RZ voxels, the last of a region that ends short those up to nk: its
+// centre is that of its own voxels, since an element may be where the missing ones would be.
+__device__ __forceinline__ void fm_axis_table(const Geo& g, int nk, int tid, float4* axis) {
     if (tid >= 3 * FM_SIDE) return;
     const int a = tid / FM_SIDE, i = tid % FM_SIDE;
     const float n = a == 0 ? (float)i - 0.5f * (float)(g.rx - 1)
                            : a == 1 ? (float)i - 0.5f * (float)(g.ry - 1)
-                                    : (float)(i * FM_RZ) + 0.5f * (float)(FM_RZ - 1) - 0.5f * (float)(g.rz - 1);
+                                    : (float)(i * FM_RZ) + 0.5f * (float)(min(FM_RZ, max(nk - i * FM_RZ, 1)) - 1) -
+                                          0.5f * (float)(g.rz - 1);
     const DF o = df_mul(DF{n, 0.0f}, DF{g.hs_u, g.hs_l});
     axis[tid] = make_float4(o.h, o.l, 0.5f * o.h * o.h, 0.0f);
 }
 
-// N of each voxel of a column about the column's centre, which is tz along z from the region's.
-__device__ __forceinline__ void fm_column_n(const Geo& g, float4 tz, float Dz, float Dzl, float (&ez)[FM_RZ]) {
+// N of each of a column's nz voxels about the column's centre, which is tz along z from the region's; the rest of the
+// FM_RZ repeat the last one (with no weight).
+__device__ __forceinline__ void fm_column_n(const Geo& g, int nz, float4 tz, float Dz, float Dzl, float (&ez)[FM_RZ]) {
 #pragma clang fp contract(off)
     const DF Dc = df_add(DF{Dz, Dzl}, DF{tz.x, tz.y});
+    const int last = min(nz, FM_RZ) - 1;
 #pragma unroll
     for (int k = 0; k < FM_RZ; ++k) {
-        const DF o = df_mul(DF{(float)k - 0.5f * (float)(FM_RZ - 1), 0.0f}, DF{g.hs_u, g.hs_l});
+        const DF o = df_mul(DF{(float)min(k, last) - 0.5f * (float)last, 0.0f}, DF{g.hs_u, g.hs_l});
         ez[k] = fmaf(o.h, Dc.l, fmaf(o.l, Dc.h, o.h * fmaf(0.5f, o.h, Dc.h)));
     }
 }
@@ -1141,7 +1146,7 @@ __device__ __forceinline__ void fm_region(const Geo& g, int reg, int c0, int cst
         reinterpret_cast<float4*>(lds)[i] = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
     if (X)
         for (int i = tid; i < rows * WAVE; i += NW * WAVE) edge[i] = 0.0f;
-    fm_axis_table(g, tid, axis);
+    fm_axis_table(g, R.nk, tid, axis);
     const FmBound bound = fm_bound<NW>(g, R, pbase, lds + fm_off_red(NM, nbin));
     const float rlo = FM_MAGIC - 2.0f * g.jclampf, rhi = FM_MAGIC + 2.0f * g.jclampf;
     const float ies = X ? 1.0f / g.es : 0.0f;
@@ -1154,7 +1159,7 @@ __device__ __forceinline__ void fm_region(const Geo& g, int reg, int c0, int cst
             if (wv < FM_REFS) {
                 const int e = (c + wv * cstep) * WAVE + lane;
                 const MomRef r = mom_make_ref(g, xe + 6 * (size_t)min(e, g.E - 1), R);
-                const FmScale q = fm_scale(g, r, bound);
+                const FmScale q = fm_scale(g, R, r, bound);
                 float* f = refs + wv * FM_FIELDS * WAVE + lane;
                 const float v[FM_FIELDS] = {r.D[0], r.D[1], r.D[2],  r.Dl[0], r.Dl[1],
                                             r.Dl[2], r.dh,  r.uc0,   r.n0,    q.scale,
@@ -1189,7 +1194,7 @@ __device__ __forceinline__ void fm_region(const Geo& g, int reg, int c0, int cst
             float zh, zl, ez[FM_RZ];
             fm_axis(tz, Dz, Dzl, magic, zh, zl);
             zl += rl[8 * WAVE];
-            fm_column_n(g, tz, Dz, Dzl, ez);
+            fm_column_n(g, nz, tz, Dz, Dzl, ez);
             int ix = -1;
             float xh = 0.0f, xl = 0.0f;
             for (int col = wv * mine; col < min((wv + 1) * mine, ncol); ++col) {
@@ -1796,7 +1801,13 @@ __device__ __forceinline__ void am_regions(const Geo& g, int reg0, int reg1, int
         }
     };
 
-    fm_axis_table(g, tid, axis);
+    // a region is one column deep: its centre at 2 FM_SIDE, that of the last region along z at 2 FM_SIDE + 1
+    fm_axis_table(g, g.rz, tid, axis);
+    __syncthreads();
+    if (tid == 0) {
+        const DF o = df_mul(DF{0.5f * (float)(g.nz - (g.nrz - 1) * g.rz - g.rz), 0.0f}, DF{g.hs_u, g.hs_l});
+        axis[2 * FM_SIDE + 1] = make_float4(o.h, o.l, 0.5f * o.h * o.h, 0.0f);
+    }
     if (wv == 0 && iters > 0) make_refs(0);
     if (wv == 1 && iters > 1) make_refs(1);
     __syncthreads();
@@ -1828,11 +1839,12 @@ __device__ __forceinline__ void am_regions(const Geo& g, int reg0, int reg1, int
             const float Dzl = rl[5 * WAVE];
             const float dh = rl[6 * WAVE], uc0 = rl[7 * WAVE], magic = rl[9 * WAVE], dh2 = dh * dh;
             const float* pbase = WANT_POSE ? p0 + (size_t)R.i0 * g.vsx + (size_t)R.j0 * g.vsy + R.k0 : nullptr;
-            const float4 tz = axis[2 * FM_SIDE];
+            const float4 tz = axis[2 * FM_SIDE + (R.nk < g.rz)];
             float zh, zl, ez[FM_RZ];
             fm_axis(tz, Dz, Dzl, magic, zh, zl);
             zl += rl[8 * WAVE];
-            fm_column_n(g, tz, Dz, Dzl, ez);
+            fm_column_n(g, R.nk, tz, Dz, Dzl, ez);
+            const float zmid = 0.5f * (float)(FM_RZ - R.nk);     // a whole column's middle from this one's, in voxels
             // a bin's table row, from the low 24 bits of rm, 0xC00000 + (centre sample offset).  Kept in vector
             // registers, so that a pair's address is one instruction without scalar operands
             constexpr unsigned STEP = NQ * WAVE * 16u;
@@ -1914,7 +1926,7 @@ __device__ __forceinline__ void am_regions(const Geo& g, int reg0, int reg1, int
                 if (WANT_POSE) {
                     Sx += (double)((Dx + ox) * c0);
                     Sy += (double)((Dy + ty.x) * c0);
-                    Sz += (double)fmaf(Dz + tz.x, c0, g.hs_u * cz);
+                    Sz += (double)fmaf(Dz + tz.x, c0, g.hs_u * fmaf(zmid, c0, cz));
                 }
             }
         }

@@ -1,0 +1,51 @@
+"""Elements on the far side of the grid along z, 10 widths or more from its voxels: where a region, or a column of
+voxels, would go on if the grid did.  Signals, dL/dp0 and element gradients against the FP64 oracle."""
+import numpy as np
+import pytest
+
+from gpu_helpers import announce, rel_l2
+from oracle import oracle as O
+
+pytestmark = pytest.mark.gpu
+
+# The power law's first element is not 4 spacings off: that is its window, 0.8 mm, so that sample 0 would lie on the edge.
+# rounding as for elements before the grid: signals and dL/dp0 2.5e-6, element gradients 1e-5; twice that for the
+# profiles with edge terms, one of which may fall either way
+TOL = {0: (2.5e-6, 1e-5), 2: (1e-5, 2e-5)}
+
+
+def far_elements(shape, h, first, last):
+    """Above voxel columns and region centres, from `first` to `last` spacings past the last voxel in steps of a half."""
+    z = shape[2] - 1 + np.arange(2 * first, 2 * last + 1) / 2.0
+    xy = [(0.5 * (shape[0] - 1), 0.5 * (shape[1] - 1)), (0.0, 0.0), (3.0, 3.0), (3.5, 3.5), (1.5, 1.5), (7.5, 3.5)]
+    return np.array([(x * h, y * h, c * h) for x, y in xy for c in z])
+
+
+@pytest.mark.parametrize("sigma,kernel,trunc,first", [(1e-4, 0, 6.0, 5.5), (6.6e-5, 0, 6.0, 3.5), (8e-5, 2, 10.0, 4.5)])
+@pytest.mark.parametrize("shape", [(8, 8, 1), (16, 9, 2), (12, 8, 9), (16, 16, 17), (9, 9, 13)])
+def test_far_side(shape, sigma, kernel, trunc, first):
+    import torch
+    from paper_2604_09643_amd import _lib as L
+    announce("far side %s sigma %g kernel %d" % (shape, sigma, kernel))
+    h, K = 2e-4, 300
+    rng = np.random.default_rng(3)
+    p0 = rng.uniform(-0.5, 1.0, shape).astype(np.float32)
+    elem = far_elements(shape, h, first, 8)
+    M = len(elem)
+    r = rng.normal(size=(1, M, K)).astype(np.float32)
+    poses = np.array([[1.0, 0, 0, 0, 1.0, 0, 0, 0, 1.0, 0, 0, 0]])
+    g, s = L.Grid(*shape, (0.0, 0.0, 0.0), h), L.Sampling(1540.0, 40e6, K, sigma, trunc, kernel, 2.0)
+    pt, et, qt, rt = (torch.tensor(a, device="cuda:0") for a in (p0, elem, poses, r))
+    ctx = L.Context(0)
+    sig = L.radiate_forward(g, pt, et, qt, s, ctx=ctx).cpu().numpy()
+    gv, gp, ge = torch.empty_like(pt), torch.empty_like(pt), torch.empty((1, M, 3), dtype=torch.float64, device="cuda:0")
+    L.radiate_adjoint(g, None, et, qt, s, rt, grad_p0=gv, ctx=ctx)
+    L.radiate_adjoint(g, pt, et, qt, s, rt, grad_p0=gp, grad_elem=ge, ctx=ctx)
+    assert ctx.status() == L.RA_OK         # 10 widths or more away
+    ctx.close()
+    og, os_ = O.Grid(*shape, np.zeros(3), h), O.Sampling(1540.0, 40e6, K, sigma, trunc, kernel, 2.0)
+    pd, rd = p0.astype(np.float64), r.astype(np.float64)
+    rp, re = O.grid_adjoint_p0(og, poses, elem, os_, rd), O.grid_adjoint_elem(og, pd, poses, elem, os_, rd)
+    assert rel_l2(sig, O.grid_forward(og, pd, poses, elem, os_)) <= TOL[kernel][0]
+    assert rel_l2(gv.cpu().numpy(), rp) <= TOL[kernel][0] and rel_l2(gp.cpu().numpy(), rp) <= TOL[kernel][0]
+    assert rel_l2(ge.cpu().numpy(), re) <= TOL[kernel][1]
