@@ -692,6 +692,7 @@ __device__ __forceinline__ void forward_region(const Geo& g, int reg, const floa
         // lanes past the last element model element 0; their rows are cleared, not flushed
         const Ref ref = make_ref(g, xe, valid ? e : 0, R);
         float* lane_rows = rows + lane + (g.kmargin - JT) * WAVE;
+        const float4 first = vtab[zl];
         // voxels four at a time, the next four loading while the current are processed
         float4 oa[4], ob[4];
         float pa[4], pb[4];
@@ -705,11 +706,13 @@ __device__ __forceinline__ void forward_region(const Geo& g, int reg, const floa
                 }
                 return;
             }
+            // a voxel that is not there (an element may be) stands at the first of its pair, or of the region
 #pragma unroll
             for (int q = 0; q < 4; ++q) {
-                o[q] = vtab[t + q + zl];
                 const int4 ix = itab[t + q];
                 const bool inside = ix.x < R.ni && ix.y < R.nj && ix.z < R.nk;
+                o[q] = vtab[t + q + zl];
+                if (!inside) o[q] = (q & 1) ? o[q - 1] : first;
                 const float v = pbase[(inside ? ix.w : 0) + zl];
                 pv[q] = inside ? v : 0.0f;
             }
@@ -940,14 +943,16 @@ __device__ __forceinline__ int cvt_round_i32(float x) {      // floor(x + 1/2)
 
 // Offsets of a region's voxels from its centre along each axis, [axis][index] (along z: of the centres of its
 // columns), as fm_axis takes them.  A column holds FM_RZ voxels, the last of a region that ends short those up to nk: its
-// centre is that of its own voxels, since an element may be where the missing ones would be.
+// centre is that of its own voxels, since an element may be where the missing ones would be.  Where regions are one
+// column deep, index 1 along z is for the grid's last ones.
 __device__ __forceinline__ void fm_axis_table(const Geo& g, int nk, int tid, float4* axis) {
     if (tid >= 3 * FM_SIDE) return;
     const int a = tid / FM_SIDE, i = tid % FM_SIDE;
+    const bool last = g.rz <= FM_RZ && i == 1;
+    const int z0 = last ? 0 : i * FM_RZ, len = last ? g.nz - (g.nrz - 1) * g.rz : min(FM_RZ, max(nk - z0, 1));
     const float n = a == 0 ? (float)i - 0.5f * (float)(g.rx - 1)
                            : a == 1 ? (float)i - 0.5f * (float)(g.ry - 1)
-                                    : (float)(i * FM_RZ) + 0.5f * (float)(min(FM_RZ, max(nk - i * FM_RZ, 1)) - 1) -
-                                          0.5f * (float)(g.rz - 1);
+                                    : (float)z0 + 0.5f * (float)(len - 1) - 0.5f * (float)(g.rz - 1);
     const DF o = df_mul(DF{n, 0.0f}, DF{g.hs_u, g.hs_l});
     axis[tid] = make_float4(o.h, o.l, 0.5f * o.h * o.h, 0.0f);
 }
@@ -1560,6 +1565,7 @@ __device__ __forceinline__ void adjoint_region(const Geo& g, int reg, const floa
             float G[4];
             float fx = 0.0f, fy = 0.0f, fz = 0.0f;     // four pairs in FP32, then into FP64
             float pv4[4];
+            int at[4] = {t, t + 1, t + 2, t + 3};
             if (WANT_POSE) {
                 if (interior) {                          // four consecutive voxels along z
                     const int off = itab[t].w;
@@ -1572,12 +1578,13 @@ __device__ __forceinline__ void adjoint_region(const Geo& g, int reg, const floa
                         const bool inside = ix.x < R.ni && ix.y < R.nj && ix.z < R.nk;
                         const float v = pbase[inside ? ix.w : 0];
                         pv4[q] = inside ? v : 0.0f;
+                        at[q] = inside ? t + q : 0;          // as in the forward
                     }
                 }
             }
 #pragma unroll
             for (int q = 0; q < 4; ++q) {
-                const float4 o = vtab[t + q];
+                const float4 o = vtab[at[q]];
                 float A, B = 0.0f, hr;             // sum_k r phi(u), sum_k r phi'(u), 1/(2d)
                 if constexpr (RS) {
                     A = __builtin_amdgcn_ldexpf(adj_rowref<JT>(cst, ref, o, lane_rows, hr), rs_exp);
@@ -1801,13 +1808,7 @@ __device__ __forceinline__ void am_regions(const Geo& g, int reg0, int reg1, int
         }
     };
 
-    // a region is one column deep: its centre at 2 FM_SIDE, that of the last region along z at 2 FM_SIDE + 1
     fm_axis_table(g, g.rz, tid, axis);
-    __syncthreads();
-    if (tid == 0) {
-        const DF o = df_mul(DF{0.5f * (float)(g.nz - (g.nrz - 1) * g.rz - g.rz), 0.0f}, DF{g.hs_u, g.hs_l});
-        axis[2 * FM_SIDE + 1] = make_float4(o.h, o.l, 0.5f * o.h * o.h, 0.0f);
-    }
     if (wv == 0 && iters > 0) make_refs(0);
     if (wv == 1 && iters > 1) make_refs(1);
     __syncthreads();

@@ -12,6 +12,7 @@ pytestmark = pytest.mark.gpu
 # rounding as for elements before the grid: signals and dL/dp0 2.5e-6, element gradients 1e-5; twice that for the
 # profiles with edge terms, one of which may fall either way
 TOL = {0: (2.5e-6, 1e-5), 2: (1e-5, 2e-5)}
+TOL_ROWS = (1e-5, 2e-5)                    # 5e-6 and 1e-5 at widths near a sample length
 
 
 def far_elements(shape, h, first, last):
@@ -21,13 +22,15 @@ def far_elements(shape, h, first, last):
     return np.array([(x * h, y * h, c * h) for x, y in xy for c in z])
 
 
-@pytest.mark.parametrize("sigma,kernel,trunc,first", [(1e-4, 0, 6.0, 5.5), (6.6e-5, 0, 6.0, 3.5), (8e-5, 2, 10.0, 4.5)])
+@pytest.mark.parametrize("sigma,kernel,trunc,first", [(1e-4, 0, 6.0, 5.5), (6.6e-5, 0, 6.0, 3.5), (8e-5, 2, 10.0, 4.5),
+                                                        (3.6e-5, 0, 6.0, 2)])      # the last in row form
 @pytest.mark.parametrize("shape", [(8, 8, 1), (16, 9, 2), (12, 8, 9), (16, 16, 17), (9, 9, 13)])
 def test_far_side(shape, sigma, kernel, trunc, first):
     import torch
     from paper_2604_09643_amd import _lib as L
     announce("far side %s sigma %g kernel %d" % (shape, sigma, kernel))
     h, K = 2e-4, 300
+    tol = TOL_ROWS if sigma == 3.6e-5 else TOL[kernel]
     rng = np.random.default_rng(3)
     p0 = rng.uniform(-0.5, 1.0, shape).astype(np.float32)
     elem = far_elements(shape, h, first, 8)
@@ -46,6 +49,6 @@ def test_far_side(shape, sigma, kernel, trunc, first):
     og, os_ = O.Grid(*shape, np.zeros(3), h), O.Sampling(1540.0, 40e6, K, sigma, trunc, kernel, 2.0)
     pd, rd = p0.astype(np.float64), r.astype(np.float64)
     rp, re = O.grid_adjoint_p0(og, poses, elem, os_, rd), O.grid_adjoint_elem(og, pd, poses, elem, os_, rd)
-    assert rel_l2(sig, O.grid_forward(og, pd, poses, elem, os_)) <= TOL[kernel][0]
-    assert rel_l2(gv.cpu().numpy(), rp) <= TOL[kernel][0] and rel_l2(gp.cpu().numpy(), rp) <= TOL[kernel][0]
-    assert rel_l2(ge.cpu().numpy(), re) <= TOL[kernel][1]
+    assert rel_l2(sig, O.grid_forward(og, pd, poses, elem, os_)) <= tol[0]
+    assert rel_l2(gv.cpu().numpy(), rp) <= tol[0] and rel_l2(gp.cpu().numpy(), rp) <= tol[0]
+    assert rel_l2(ge.cpu().numpy(), re) <= tol[1]
