@@ -47,6 +47,11 @@
  *             (or order the streams yourself).  Two streams that run calls of
  *             the same context concurrently race on its scratch; give each
  *             stream its own context instead.
+ *   Sums      a region's terms add in 32-bit fixed point in the polynomial forms, in a unit set by
+ *             a bound on the region's largest bin (2^31 units).  Where a line of voxels in 16 stays
+ *             below 2^-14 of that bound the region's voxels are summed in classes of size, each
+ *             in its own unit, so that a voxel keeps its digits beside one that is many orders
+ *             larger: a term is rounded to at most 2^-17 of the largest on its line.
  *   Errors    every int-returning call returns one of the RA_* codes below;
  *             ra_last_error() holds a message for the last failing call.
  *             Arguments are validated before any work is enqueued.  Bulk

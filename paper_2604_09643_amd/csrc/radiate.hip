@@ -99,6 +99,7 @@ constexpr int FM_REFS = 2;            // element chunks whose references it comp
 constexpr int FM_FIELDS = 13;         // floats of a reference
 constexpr int FM_RZ = 8;              // voxels of a column it unrolls
 constexpr int FM_SIDE = 16;           // its largest region side
+constexpr float FM_FAINT = 0x1p-14f;  // largest |p0| of a line over the bound of its region's bins below which it is faint
 constexpr int MOM_MAX = 12;           // largest number of moments
 constexpr int MOM_G = 8;              // and the Gaussian's
 constexpr double FM_TOL = 2e-7;       // its largest admitted expansion error, relative to the peak
@@ -846,7 +847,7 @@ constexpr int fm_dlen(int jt) { return 2 * jt + 1 + FM_PAD + 16; }
 constexpr size_t fm_off_ref(int nm, int nbin) { return (size_t)(nbin + 1) * fm_stride(nm); }
 constexpr size_t fm_off_axis(int nm, int nbin) { return fm_off_ref(nm, nbin) + FM_REFS * FM_FIELDS * WAVE; }
 constexpr size_t fm_off_red(int nm, int nbin) { return fm_off_axis(nm, nbin) + 3 * FM_SIDE * 4; }
-constexpr size_t fm_off_dt(int nm, int nbin) { return fm_off_red(nm, nbin) + 4 * FM_WAVES_BIG; }
+constexpr size_t fm_off_dt(int nm, int nbin) { return fm_off_red(nm, nbin) + 4 * FM_WAVES_BIG + 4; }
 constexpr size_t fm_off_edge(int nm, int nbin, int jt) { return fm_off_dt(nm, nbin) + (nm * fm_dlen(jt) + 63) / 64 * 64; }
 constexpr size_t fm_lds(int nm, int nbin, int jt, bool edge) {       // with edge sums, [row][lane]
     return (fm_off_edge(nm, nbin, jt) + (edge ? (size_t)(nbin + 2 * jt) * WAVE : 0)) * sizeof(float);
@@ -855,7 +856,7 @@ constexpr size_t fm_lds(int nm, int nbin, int jt, bool edge) {       // with edg
 // What bounds the sums of a region's bins: sum |p0|, and per axis the sum over the lines along it of the
 // largest |p0| in each (NaN if any p0 is not finite).
 struct FmBound {
-    float all, line[3];
+    float all, line[3], low;               // low: see fm_bound
 };
 
 // Reference of a (region, element) pair in units: D = centre - x_e in double-float, dh = |D| rounded,
@@ -962,11 +963,16 @@ __device__ __forceinline__ void fm_axis_table(const Geo& g, int nk, int tid, flo
 __device__ __forceinline__ void fm_column_n(const Geo& g, int nz, float4 tz, float Dz, float Dzl, float (&ez)[FM_RZ]) {
 #pragma clang fp contract(off)
     const DF Dc = df_add(DF{Dz, Dzl}, DF{tz.x, tz.y});
-    const int last = min(nz, FM_RZ) - 1;
+    auto at = [&](float k) {
+        const DF o = df_mul(DF{k, 0.0f}, DF{g.hs_u, g.hs_l});
+        return fmaf(o.h, Dc.l, fmaf(o.l, Dc.h, o.h * fmaf(0.5f, o.h, Dc.h)));
+    };
+    if (nz >= FM_RZ) {                                       // with constant offsets, which leave the loops over chunks
 #pragma unroll
-    for (int k = 0; k < FM_RZ; ++k) {
-        const DF o = df_mul(DF{(float)min(k, last) - 0.5f * (float)last, 0.0f}, DF{g.hs_u, g.hs_l});
-        ez[k] = fmaf(o.h, Dc.l, fmaf(o.l, Dc.h, o.h * fmaf(0.5f, o.h, Dc.h)));
+        for (int k = 0; k < FM_RZ; ++k) ez[k] = at((float)k - 0.5f * (float)(FM_RZ - 1));
+    } else {
+#pragma unroll
+        for (int k = 0; k < FM_RZ; ++k) ez[k] = at((float)min(k, nz - 1) - 0.5f * (float)(nz - 1));
     }
 }
 
@@ -1092,40 +1098,65 @@ __device__ __forceinline__ void fm_column(const Geo& g, const EdgeCoef& xc, unsi
     }
 }
 
-// Sum |p0| and the line bounds of a region by the whole workgroup (`red`: LDS, 4 floats a wavefront).
+// A value that the whole wavefront has, in a scalar register.
+__device__ __forceinline__ float to_scalar(float x) {
+    return __int_as_float(__builtin_amdgcn_readfirstlane(__float_as_int(x)));
+}
+
+// Sum |p0| and the line bounds of a region's voxels with |p0| below top by the whole workgroup (`red`: LDS, 4 floats a
+// wavefront and 3), and from where on its voxels make a class of their own (FmBound's `low`, 0: they are taken together).
+// One unit for all sums of a region suits voxels of like size.  A line is faint if its largest |p0| is below FM_FAINT
+// of what bounds the region's bins, so that the unit would exceed 2^-17 of it; where one line in 16 along any axis is,
+// the voxels from FM_FAINT of the bound on are summed first and the rest after them, in a unit of their own.  One voxel
+// of 1e4 over a background of 0.01: the samples that it does not reach are off by 2.5e-4 of themselves in one unit.
 template <int NW>
-__device__ __forceinline__ FmBound fm_bound(const Geo& g, const Region& R, const float* __restrict__ pbase, float* red) {
+__device__ __forceinline__ FmBound fm_bound(const Geo& g, const Region& R, const float* __restrict__ pbase, float top,
+                                            float* red) {
     const int tid = threadIdx.x, lane = tid & (WAVE - 1), wv = tid / WAVE;
     const int n[3] = {R.ni, R.nj, R.nk};
     const long long st[3] = {g.vsx, g.vsy, 1};
     float b[4] = {0.0f, 0.0f, 0.0f, 0.0f};
+    float most[3] = {0.0f, 0.0f, 0.0f};                      // of this thread's line: at most FM_SIDE^2 of them along an axis
+    static_assert(NW * WAVE >= FM_SIDE * FM_SIDE, "a thread per line");
 #pragma unroll
     for (int a = 0; a < 3; ++a) {
         const int p = a == 0 ? 1 : 0, q = a == 2 ? 1 : 2;    // the other two axes
-        for (int l = tid; l < n[p] * n[q]; l += NW * WAVE) {
-            const float* line = pbase + (size_t)(l / n[q]) * st[p] + (size_t)(l % n[q]) * st[q];
-            float top = 0.0f, sum = 0.0f;
+        if (tid < n[p] * n[q]) {
+            const float* line = pbase + (size_t)(tid / n[q]) * st[p] + (size_t)(tid % n[q]) * st[q];
+            float sum = 0.0f;
             for (int i = 0; i < n[a]; ++i) {
-                const float v = fabsf(line[(size_t)i * st[a]]);
-                top = fmaxf(top, v);
+                float v = fabsf(line[(size_t)i * st[a]]);
+                v = v >= top ? 0.0f : v;                     // with top NaN all stay, and NaN does
+                most[a] = fmaxf(most[a], v);
                 sum += v;
             }
-            b[a] += top;
-            if (a == 2) b[3] += sum;
+            b[a] = most[a];
+            if (a == 2) b[3] = sum;
         }
     }
+    int* few = reinterpret_cast<int*>(red + 4 * FM_WAVES_BIG);   // per axis: 16 times the faint lines, less the lines with any voxel
+    if (tid < 3) few[tid] = 0;
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
         b[i] = wave_sum_to_63(b[i]);
         if (lane == WAVE - 1) red[4 * wv + i] = b[i];
     }
     __syncthreads();
-    FmBound r{0.0f, {0.0f, 0.0f, 0.0f}};
-    for (int w = 0; w < NW; ++w) {
+    float t[4] = {0.0f, 0.0f, 0.0f, 0.0f};
+    for (int w = 0; w < NW; ++w)
 #pragma unroll
-        for (int i = 0; i < 3; ++i) r.line[i] += red[4 * w + i];
-        r.all += red[4 * w + 3];
+        for (int i = 0; i < 4; ++i) t[i] += red[4 * w + i];
+    FmBound r{to_scalar(t[3]), {to_scalar(t[0]), to_scalar(t[1]), to_scalar(t[2])}, 0.0f};
+    const bool finite = r.all - r.all == 0.0f;
+    const float low = FM_FAINT * fminf(fminf(r.line[0], r.line[1]), fminf(r.line[2], r.all));
+#pragma unroll
+    for (int a = 0; a < 3; ++a) {
+        const int faint = __popcll(__ballot(most[a] > 0.0f && most[a] < low)), any = __popcll(__ballot(most[a] > 0.0f));
+        if (lane == 0 && any) __hip_atomic_fetch_add(few + a, 16 * faint - any, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
     }
+    __syncthreads();
+    if (finite && max(few[0], max(few[1], few[2])) > 0) r.low = low;
+    r.low = to_scalar(r.low);
     return r;
 }
 
@@ -1152,152 +1183,171 @@ __device__ __forceinline__ void fm_region(const Geo& g, int reg, int c0, int cst
     if (X)
         for (int i = tid; i < rows * WAVE; i += NW * WAVE) edge[i] = 0.0f;
     fm_axis_table(g, R.nk, tid, axis);
-    const FmBound bound = fm_bound<NW>(g, R, pbase, lds + fm_off_red(NM, nbin));
     const float rlo = FM_MAGIC - 2.0f * g.jclampf, rhi = FM_MAGIC + 2.0f * g.jclampf;
     const float ies = X ? 1.0f / g.es : 0.0f;
 
-    int slot = FM_REFS;
-    for (int c = c0; c < nchunk; c += cstep, ++slot) {
-        if (slot == FM_REFS) {                               // references of the next FM_REFS chunks
-            slot = 0;
-            __syncthreads();
-            if (wv < FM_REFS) {
-                const int e = (c + wv * cstep) * WAVE + lane;
-                const MomRef r = mom_make_ref(g, xe + 6 * (size_t)min(e, g.E - 1), R);
-                const FmScale q = fm_scale(g, R, r, bound);
-                float* f = refs + wv * FM_FIELDS * WAVE + lane;
-                const float v[FM_FIELDS] = {r.D[0], r.D[1], r.D[2],  r.Dl[0], r.Dl[1],
-                                            r.Dl[2], r.dh,  r.uc0,   r.n0,    q.scale,
-                                            r.magic, q.inv, __int_as_float(r.kc - g.jclamp - jt)};
+    // classes of voxels, the largest first (see fm_bound): those from low on and below top (NaN: no limit)
+    float top = __builtin_nanf("");
+    for (bool more = true; more;) {
+        const FmBound bound = fm_bound<NW>(g, R, pbase, top, lds + fm_off_red(NM, nbin));
+        const float low = bound.low;
+        const bool part = low > 0.0f || top == top;
+        int slot = FM_REFS;
+        for (int c = c0; c < nchunk; c += cstep, ++slot) {
+            if (slot == FM_REFS) {                               // references of the next FM_REFS chunks
+                slot = 0;
+                if (c != c0) __syncthreads();                    // the last ones have been read
+                if (wv < FM_REFS) {
+                    const int e = (c + wv * cstep) * WAVE + lane;
+                    const MomRef r = mom_make_ref(g, xe + 6 * (size_t)min(e, g.E - 1), R);
+                    const FmScale q = fm_scale(g, R, r, bound);
+                    float* f = refs + wv * FM_FIELDS * WAVE + lane;
+                    const float v[FM_FIELDS] = {r.D[0], r.D[1], r.D[2],  r.Dl[0], r.Dl[1],
+                                                r.Dl[2], r.dh,  r.uc0,   r.n0,    q.scale,
+                                                r.magic, q.inv, __int_as_float(r.kc - g.jclamp - jt)};
 #pragma unroll
-                for (int i = 0; i < FM_FIELDS; ++i) f[i * WAVE] = v[i];
+                    for (int i = 0; i < FM_FIELDS; ++i) f[i * WAVE] = v[i];
+                }
+                __syncthreads();
+            }
+            const float* rf = refs + slot * FM_FIELDS * WAVE;
+            const float* rl = rf + lane;
+            const float dh = rl[6 * WAVE], scale = rl[9 * WAVE];
+            const int kb = __float_as_int(rl[12 * WAVE]);
+            const bool valid = c * WAVE + lane < g.E;
+            const bool finite = dh < 1e15f;
+            // nothing to add: every window of the chunk misses the record, or the region is all zero
+            const bool hit = valid && (!finite || (kb + rows > 0 && kb < K && bound.all != 0.0f));
+            if (!__any(hit)) continue;
+            const bool fixed = !__any(valid && scale == 0.0f);
+            const float Dx = rl[0], Dy = rl[WAVE], Dz = rl[2 * WAVE], Dxl = rl[3 * WAVE], Dyl = rl[4 * WAVE];
+            const float Dzl = rl[5 * WAVE], uc0 = rl[7 * WAVE], magic = rl[10 * WAVE], dh2 = dh * dh;
+            unsigned off0 = (unsigned)lane * 4u + (unsigned)g.jclamp * (STR * 4u) - 0xC00000u * (STR * 4u);
+            unsigned str = STR * 4u;
+            asm volatile("" : "+v"(off0), "+v"(str));            // in vector registers: scalar operands halve the issue rate
+            // row of a bin's sample kc - jt; FM_MAGIC << 8 is 0xC0000000
+            unsigned eoff = (unsigned)(fm_off_edge(NM, nbin, jt) + lane + g.jclamp * WAVE) * 4u - 0xC0000000u;
+            asm volatile("" : "+v"(eoff));
+            const EdgeCoef xc = edge_coef(g, g.es);
+            for (int z0 = 0; z0 < R.nk; z0 += FM_RZ) {
+                const int nz = R.nk - z0;
+                const float4 tz = axis[2 * FM_SIDE + z0 / FM_RZ];
+                float zh, zl, ez[FM_RZ];
+                fm_axis(tz, Dz, Dzl, magic, zh, zl);
+                zl += rl[8 * WAVE];
+                fm_column_n(g, nz, tz, Dz, Dzl, ez);
+                int ix = -1;
+                float xh = 0.0f, xl = 0.0f;
+                for (int col = wv * mine; col < min((wv + 1) * mine, ncol); ++col) {
+                    const int i = col / R.nj, j = col - i * R.nj;
+                    const float* pc = pbase + (size_t)i * g.vsx + (size_t)j * g.vsy + z0;
+                    float pv[FM_RZ];
+                    if (nz >= FM_RZ) {
+#pragma unroll
+                        for (int k = 0; k < FM_RZ; ++k) pv[k] = pc[k];
+                    } else {
+#pragma unroll
+                        for (int k = 0; k < FM_RZ; ++k) pv[k] = k < nz ? pc[min(k, nz - 1)] : 0.0f;
+                    }
+                    if (part) {                              // the column's voxels of this class, if any (kept in scalar registers)
+                        bool any = false;
+#pragma unroll
+                        for (int k = 0; k < FM_RZ; ++k) {
+                            const float v = fabsf(pv[k]);
+                            const bool in = v >= low && !(v >= top);
+                            pv[k] = __int_as_float(__builtin_amdgcn_readfirstlane(__float_as_int(in ? pv[k] : 0.0f)));
+                            any = any || in;
+                        }
+                        if (!__any(any)) continue;
+                    }
+                    if (i != ix) {                               // the wavefront's columns run along y
+                        ix = i;
+                        fm_axis(axis[i], Dx, Dxl, magic, xh, xl);
+                        xh += zh;
+                        xl += zl;
+                    }
+                    float yh, yl;
+                    fm_axis(axis[FM_SIDE + j], Dy, Dyl, magic, yh, yl);
+                    const FmCol cl = fm_col(xh + yh, xl + yl, dh, dh2, uc0);
+                    if (fixed)
+                        fm_column<NM, true, X>(g, xc, eoff, pv, ez, cl, scale, rlo, rhi, off0, str, reinterpret_cast<char*>(lds));
+                    else
+                        fm_column<NM, false, X>(g, xc, eoff, pv, ez, cl, 1.0f, rlo, rhi, off0, str, reinterpret_cast<char*>(lds));
+                }
             }
             __syncthreads();
-        }
-        const float* rf = refs + slot * FM_FIELDS * WAVE;
-        const float* rl = rf + lane;
-        const float dh = rl[6 * WAVE], scale = rl[9 * WAVE];
-        const int kb = __float_as_int(rl[12 * WAVE]);
-        const bool valid = c * WAVE + lane < g.E;
-        const bool finite = dh < 1e15f;
-        // nothing to add: every window of the chunk misses the record, or the region is all zero
-        const bool hit = valid && (!finite || (kb + rows > 0 && kb < K && bound.all != 0.0f));
-        if (!__any(hit)) continue;
-        const bool fixed = !__any(valid && scale == 0.0f);
-        const float Dx = rl[0], Dy = rl[WAVE], Dz = rl[2 * WAVE], Dxl = rl[3 * WAVE], Dyl = rl[4 * WAVE];
-        const float Dzl = rl[5 * WAVE], uc0 = rl[7 * WAVE], magic = rl[10 * WAVE], dh2 = dh * dh;
-        unsigned off0 = (unsigned)lane * 4u + (unsigned)g.jclamp * (STR * 4u) - 0xC00000u * (STR * 4u);
-        unsigned str = STR * 4u;
-        asm volatile("" : "+v"(off0), "+v"(str));            // in vector registers: scalar operands halve the issue rate
-        // row of a bin's sample kc - jt; FM_MAGIC << 8 is 0xC0000000
-        unsigned eoff = (unsigned)(fm_off_edge(NM, nbin, jt) + lane + g.jclamp * WAVE) * 4u - 0xC0000000u;
-        asm volatile("" : "+v"(eoff));
-        const EdgeCoef xc = edge_coef(g, g.es);
-        for (int z0 = 0; z0 < R.nk; z0 += FM_RZ) {
-            const int nz = R.nk - z0;
-            const float4 tz = axis[2 * FM_SIDE + z0 / FM_RZ];
-            float zh, zl, ez[FM_RZ];
-            fm_axis(tz, Dz, Dzl, magic, zh, zl);
-            zl += rl[8 * WAVE];
-            fm_column_n(g, nz, tz, Dz, Dzl, ez);
-            int ix = -1;
-            float xh = 0.0f, xl = 0.0f;
-            for (int col = wv * mine; col < min((wv + 1) * mine, ncol); ++col) {
-                const int i = col / R.nj, j = col - i * R.nj;
-                const float* pc = pbase + (size_t)i * g.vsx + (size_t)j * g.vsy + z0;
-                float pv[FM_RZ];
-                if (nz >= FM_RZ) {
+            if (fixed) {
+                // [16 rows x 16 elements] tiles: wavefront w takes elements 16 (w & 3).. and row tiles w / 4,
+                // w / 4 + NW / 4, .., two at a time (they share the D operand)
+                const int eg = wv & 3, li = lane & 15, lk = lane >> 4;
+                const int nq = (2 * jt + 16 + 3) / 4;
+                const int* acc = reinterpret_cast<const int*>(lds) + 16 * eg + li;
+                const float* db = dt + 2 * jt + FM_PAD + li - lk;          // D_n(jt + li - lk - 4 q)
+                const int dl = fm_dlen(jt);
+                const int e0 = 16 * eg + 4 * lk;
+                const vf4 inv = *reinterpret_cast<const vf4*>(rf + 11 * WAVE + e0);
+                const vf4 kbe = *reinterpret_cast<const vf4*>(rf + 12 * WAVE + e0);
+                auto add_rows = [&](vf4 v, int r0) {
 #pragma unroll
-                    for (int k = 0; k < FM_RZ; ++k) pv[k] = pc[k];
-                } else {
+                    for (int i = 0; i < 4; ++i) {
+                        const int e = c * WAVE + e0 + i, k = __float_as_int(kbe[i]) + r0 + li;
+                        float x = v[i] * inv[i];
+                        if (X && r0 + li < rows)
+                            x = fmaf((float)reinterpret_cast<const int*>(edge)[(r0 + li) * WAVE + e0 + i], inv[i] * ies, x);
+                        if (e < g.E && x != 0.0f && r0 + li < rows && k >= 0 && k < K)
+                            atomicAdd(s + (size_t)e * K + k, (SumT)x);
+                    }
+                };
+                for (int r0 = 16 * (wv >> 2); r0 < rows; r0 += 8 * NW) {
+                    const int r1 = r0 + 4 * NW;
+                    vf4 s0 = {0.0f, 0.0f, 0.0f, 0.0f}, s1 = {0.0f, 0.0f, 0.0f, 0.0f};
+                    const int b0 = r0 - 2 * jt + lk;
+                    // bins that do not exist read the zero bin
+                    auto bin = [&](int b) { return acc + (b >= 0 && b < nbin ? b : nbin) * STR; };
+                    if (r1 < rows) {
+                        for (int q = 0; q < nq; ++q) {
+                            const int* a0 = bin(b0 + 4 * q);
+                            const int* a1 = bin(b0 + 4 * q + 4 * NW);
 #pragma unroll
-                    for (int k = 0; k < FM_RZ; ++k) pv[k] = k < nz ? pc[min(k, nz - 1)] : 0.0f;
-                }
-                if (i != ix) {                               // the wavefront's columns run along y
-                    ix = i;
-                    fm_axis(axis[i], Dx, Dxl, magic, xh, xl);
-                    xh += zh;
-                    xl += zl;
-                }
-                float yh, yl;
-                fm_axis(axis[FM_SIDE + j], Dy, Dyl, magic, yh, yl);
-                const FmCol cl = fm_col(xh + yh, xl + yl, dh, dh2, uc0);
-                if (fixed)
-                    fm_column<NM, true, X>(g, xc, eoff, pv, ez, cl, scale, rlo, rhi, off0, str, reinterpret_cast<char*>(lds));
-                else
-                    fm_column<NM, false, X>(g, xc, eoff, pv, ez, cl, 1.0f, rlo, rhi, off0, str, reinterpret_cast<char*>(lds));
-            }
-        }
-        __syncthreads();
-        if (fixed) {
-            // [16 rows x 16 elements] tiles: wavefront w takes elements 16 (w & 3).. and row tiles w / 4,
-            // w / 4 + NW / 4, .., two at a time (they share the D operand)
-            const int eg = wv & 3, li = lane & 15, lk = lane >> 4;
-            const int nq = (2 * jt + 16 + 3) / 4;
-            const int* acc = reinterpret_cast<const int*>(lds) + 16 * eg + li;
-            const float* db = dt + 2 * jt + FM_PAD + li - lk;          // D_n(jt + li - lk - 4 q)
-            const int dl = fm_dlen(jt);
-            const int e0 = 16 * eg + 4 * lk;
-            const vf4 inv = *reinterpret_cast<const vf4*>(rf + 11 * WAVE + e0);
-            const vf4 kbe = *reinterpret_cast<const vf4*>(rf + 12 * WAVE + e0);
-            auto add_rows = [&](vf4 v, int r0) {
+                            for (int n = 0; n < NM; ++n) {
+                                const float bv = db[n * dl - 4 * q];
+                                s0 = __builtin_amdgcn_mfma_f32_16x16x4f32((float)a0[n * WAVE], bv, s0, 0, 0, 0);
+                                s1 = __builtin_amdgcn_mfma_f32_16x16x4f32((float)a1[n * WAVE], bv, s1, 0, 0, 0);
+                            }
+                        }
+                        add_rows(s1, r1);
+                    } else {
+                        for (int q = 0; q < nq; ++q) {
+                            const int* a0 = bin(b0 + 4 * q);
 #pragma unroll
-                for (int i = 0; i < 4; ++i) {
-                    const int e = c * WAVE + e0 + i, k = __float_as_int(kbe[i]) + r0 + li;
-                    float x = v[i] * inv[i];
-                    if (X && r0 + li < rows)
-                        x = fmaf((float)reinterpret_cast<const int*>(edge)[(r0 + li) * WAVE + e0 + i], inv[i] * ies, x);
-                    if (e < g.E && x != 0.0f && r0 + li < rows && k >= 0 && k < K)
-                        atomicAdd(s + (size_t)e * K + k, (SumT)x);
-                }
-            };
-            for (int r0 = 16 * (wv >> 2); r0 < rows; r0 += 8 * NW) {
-                const int r1 = r0 + 4 * NW;
-                vf4 s0 = {0.0f, 0.0f, 0.0f, 0.0f}, s1 = {0.0f, 0.0f, 0.0f, 0.0f};
-                const int b0 = r0 - 2 * jt + lk;
-                // bins that do not exist read the zero bin
-                auto bin = [&](int b) { return acc + (b >= 0 && b < nbin ? b : nbin) * STR; };
-                if (r1 < rows) {
-                    for (int q = 0; q < nq; ++q) {
-                        const int* a0 = bin(b0 + 4 * q);
-                        const int* a1 = bin(b0 + 4 * q + 4 * NW);
-#pragma unroll
-                        for (int n = 0; n < NM; ++n) {
-                            const float bv = db[n * dl - 4 * q];
-                            s0 = __builtin_amdgcn_mfma_f32_16x16x4f32((float)a0[n * WAVE], bv, s0, 0, 0, 0);
-                            s1 = __builtin_amdgcn_mfma_f32_16x16x4f32((float)a1[n * WAVE], bv, s1, 0, 0, 0);
+                            for (int n = 0; n < NM; ++n)
+                                s0 = __builtin_amdgcn_mfma_f32_16x16x4f32((float)a0[n * WAVE], db[n * dl - 4 * q], s0, 0, 0, 0);
                         }
                     }
-                    add_rows(s1, r1);
-                } else {
-                    for (int q = 0; q < nq; ++q) {
-                        const int* a0 = bin(b0 + 4 * q);
+                    add_rows(s0, r0);
+                }
+            } else {
+                // FP32 sums: plain sums over the window rows, lane = element
+                const float* acc = lds + lane;
+                for (int r = wv; r < rows; r += NW) {
+                    float v = X ? edge[r * WAVE + lane] * ies : 0.0f;
+                    for (int b = max(r - 2 * jt, 0); b <= min(r, nbin - 1); ++b)
 #pragma unroll
                         for (int n = 0; n < NM; ++n)
-                            s0 = __builtin_amdgcn_mfma_f32_16x16x4f32((float)a0[n * WAVE], db[n * dl - 4 * q], s0, 0, 0, 0);
-                    }
+                            v = fmaf(acc[b * STR + n * WAVE], dt[n * fm_dlen(jt) + FM_PAD + r - b], v);
+                    const int k = kb + r;
+                    if (valid && v != 0.0f && k >= 0 && k < K) atomicAdd(s + (size_t)(c * WAVE + lane) * K + k, (SumT)v);
                 }
-                add_rows(s0, r0);
             }
-        } else {
-            // FP32 sums: plain sums over the window rows, lane = element
-            const float* acc = lds + lane;
-            for (int r = wv; r < rows; r += NW) {
-                float v = X ? edge[r * WAVE + lane] * ies : 0.0f;
-                for (int b = max(r - 2 * jt, 0); b <= min(r, nbin - 1); ++b)
-#pragma unroll
-                    for (int n = 0; n < NM; ++n)
-                        v = fmaf(acc[b * STR + n * WAVE], dt[n * fm_dlen(jt) + FM_PAD + r - b], v);
-                const int k = kb + r;
-                if (valid && v != 0.0f && k >= 0 && k < K) atomicAdd(s + (size_t)(c * WAVE + lane) * K + k, (SumT)v);
-            }
-        }
-        __syncthreads();
-        for (int i = tid; i < nbin * STR / 4; i += NW * WAVE)
-            reinterpret_cast<float4*>(lds)[i] = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
-        if (X)
-            for (int i = tid; i < rows * WAVE; i += NW * WAVE) edge[i] = 0.0f;
-        __syncthreads();
+            __syncthreads();
+            for (int i = tid; i < nbin * STR / 4; i += NW * WAVE)
+                reinterpret_cast<float4*>(lds)[i] = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
+            if (X)
+                for (int i = tid; i < rows * WAVE; i += NW * WAVE) edge[i] = 0.0f;
+            __syncthreads();
+        }        __syncthreads();                                     // the bound has been read
+        more = low > 0.0f;
+        top = low;
     }
 }
 
