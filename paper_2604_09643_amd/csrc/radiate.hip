@@ -1001,6 +1001,50 @@ __device__ __forceinline__ FmCol fm_col(float bh, float bl, float dh, float dh2,
     return c;
 }
 
+// The same for the profiles with edge terms, from the column's and the element's own positions in FP64, so that it depends
+// on nothing of the region: the forward and the adjoints, on regions of different sizes, then find the same t of a
+// pair to the last bit and put an outermost sample in or out alike (from each region's centre, a pair within
+// rounding of the edge fell in on one side and out on the other: <A p, r> and <p, A^T r> apart by 1e-3 of |A p| where
+// all pairs are at the edge).  c: the column's centre from the element, in units.
+struct FmElem {
+    double x, y, z, h;                     // grid origin from the element, spacing; units
+};
+
+__device__ __forceinline__ FmElem fm_elem(const Geo& g, const float* __restrict__ x) {
+#pragma clang fp contract(off)
+    const double u = (double)g.unit_h + (double)g.unit_l;
+    double o[3];
+#pragma unroll
+    for (int a = 0; a < 3; ++a)
+        o[a] = (((double)g.org_h[a] + (double)g.org_l[a]) - ((double)x[a] + (double)x[3 + a])) * u;
+    return {o[0], o[1], o[2], ((double)g.sp_h + (double)g.sp_l) * u};
+}
+
+__device__ __forceinline__ FmCol fm_col_f64(double cx2z2, double cy, int kc) {
+#pragma clang fp contract(off)
+    const double S = fma(cy, cy, cx2z2);
+    const double y0 = __builtin_amdgcn_rsq(S);
+    double d = S * y0, hf = 0.5 * y0;
+    const double r = fma(-hf, d, 0.5);
+    d = fma(d, r, d);
+    hf = fma(hf, r, hf);
+    d = S > 0.0 ? fma(fma(-d, d, S), hf, d) : S;             // 0, and NaN as it is
+    const double k = __builtin_rint(0.5 * d);
+    FmCol c;
+    c.dc = (float)d;
+    c.uc = (float)fma(-2.0, k, d);
+    c.magic = FM_MAGIC + 2.0f * (float)(k - (double)kc);
+    return c;
+}
+
+__device__ __forceinline__ double fm_square_add(double c, double s) { return fma(c, c, s); }
+
+// N of a column's voxels about its centre, cz along z from the element.
+__device__ __forceinline__ void fm_column_n(const Geo& g, int nz, double cz, float (&ez)[FM_RZ]) {
+    const float h = (float)cz;
+    fm_column_n(g, nz, make_float4(0.0f, 0.0f, 0.0f, 0.0f), h, (float)(cz - (double)h), ez);
+}
+
 // A voxel of the column: rs = 1/d, t, and FM_MAGIC plus its nearest sample's offset from kc (kept in
 // [lo, hi] whatever the inputs).
 struct FmPair {
@@ -1229,13 +1273,22 @@ __device__ __forceinline__ void fm_region(const Geo& g, int reg, int c0, int cst
             unsigned eoff = (unsigned)(fm_off_edge(NM, nbin, jt) + lane + g.jclamp * WAVE) * 4u - 0xC0000000u;
             asm volatile("" : "+v"(eoff));
             const EdgeCoef xc = edge_coef(g, g.es);
+            FmElem fe{};
+            if (X) fe = fm_elem(g, xe + 6 * (size_t)min(c * WAVE + lane, g.E - 1));
             for (int z0 = 0; z0 < R.nk; z0 += FM_RZ) {
                 const int nz = R.nk - z0;
                 const float4 tz = axis[2 * FM_SIDE + z0 / FM_RZ];
                 float zh, zl, ez[FM_RZ];
-                fm_axis(tz, Dz, Dzl, magic, zh, zl);
-                zl += rl[8 * WAVE];
-                fm_column_n(g, nz, tz, Dz, Dzl, ez);
+                double cz2 = 0.0, cx2 = 0.0;
+                if (X) {
+                    const double cz = fma((double)(R.k0 + z0) + 0.5 * (double)(min(nz, FM_RZ) - 1), fe.h, fe.z);
+                    cz2 = cz * cz;
+                    fm_column_n(g, nz, cz, ez);
+                } else {
+                    fm_axis(tz, Dz, Dzl, magic, zh, zl);
+                    zl += rl[8 * WAVE];
+                    fm_column_n(g, nz, tz, Dz, Dzl, ez);
+                }
                 int ix = -1;
                 float xh = 0.0f, xl = 0.0f;
                 for (int col = wv * mine; col < min((wv + 1) * mine, ncol); ++col) {
@@ -1260,15 +1313,22 @@ __device__ __forceinline__ void fm_region(const Geo& g, int reg, int c0, int cst
                         }
                         if (!__any(any)) continue;
                     }
-                    if (i != ix) {                               // the wavefront's columns run along y
+                    FmCol cl;
+                    if (X) {
+                        if (i != ix) cx2 = fm_square_add(fma((double)(R.i0 + i), fe.h, fe.x), cz2);
                         ix = i;
-                        fm_axis(axis[i], Dx, Dxl, magic, xh, xl);
-                        xh += zh;
-                        xl += zl;
+                        cl = fm_col_f64(cx2, fma((double)(R.j0 + j), fe.h, fe.y), kb + g.jclamp + jt);
+                    } else {
+                        if (i != ix) {                           // the wavefront's columns run along y
+                            ix = i;
+                            fm_axis(axis[i], Dx, Dxl, magic, xh, xl);
+                            xh += zh;
+                            xl += zl;
+                        }
+                        float yh, yl;
+                        fm_axis(axis[FM_SIDE + j], Dy, Dyl, magic, yh, yl);
+                        cl = fm_col(xh + yh, xl + yl, dh, dh2, uc0);
                     }
-                    float yh, yl;
-                    fm_axis(axis[FM_SIDE + j], Dy, Dyl, magic, yh, yl);
-                    const FmCol cl = fm_col(xh + yh, xl + yl, dh, dh2, uc0);
                     if (fixed)
                         fm_column<NM, true, X>(g, xc, eoff, pv, ez, cl, scale, rlo, rhi, off0, str, reinterpret_cast<char*>(lds));
                     else
@@ -1892,9 +1952,18 @@ __device__ __forceinline__ void am_regions(const Geo& g, int reg0, int reg1, int
             const float* pbase = WANT_POSE ? p0 + (size_t)R.i0 * g.vsx + (size_t)R.j0 * g.vsy + R.k0 : nullptr;
             const float4 tz = axis[2 * FM_SIDE + (R.nk < g.rz)];
             float zh, zl, ez[FM_RZ];
-            fm_axis(tz, Dz, Dzl, magic, zh, zl);
-            zl += rl[8 * WAVE];
-            fm_column_n(g, R.nk, tz, Dz, Dzl, ez);
+            FmElem fe{};
+            double cz2 = 0.0, cx2 = 0.0;
+            if (X) {                                         // as the forward, to the last bit
+                fe = fm_elem(g, xe + 6 * (size_t)min(c * WAVE + lane, g.E - 1));
+                const double cz = fma((double)R.k0 + 0.5 * (double)(R.nk - 1), fe.h, fe.z);
+                cz2 = cz * cz;
+                fm_column_n(g, R.nk, cz, ez);
+            } else {
+                fm_axis(tz, Dz, Dzl, magic, zh, zl);
+                zl += rl[8 * WAVE];
+                fm_column_n(g, R.nk, tz, Dz, Dzl, ez);
+            }
             const float zmid = 0.5f * (float)(FM_RZ - R.nk);     // a whole column's middle from this one's, in voxels
             // a bin's table row, from the low 24 bits of rm, 0xC00000 + (centre sample offset).  Kept in vector
             // registers, so that a pair's address is one instruction without scalar operands
@@ -1912,18 +1981,27 @@ __device__ __forceinline__ void am_regions(const Geo& g, int reg0, int reg1, int
                 const int col = wv * CPW + cc;
                 if (col >= ncol) continue;
                 const int i = col / R.nj, j = col - i * R.nj;
+                const float4 ty = axis[FM_SIDE + j];
+                FmCol cl;
                 if (i != ix) {                               // a wavefront's columns run along y
-                    ix = i;
                     const float4 tx = axis[i];
                     ox = tx.x;
-                    fm_axis(tx, Dx, Dxl, magic, xh, xl);
-                    xh += zh;
-                    xl += zl;
+                    if (X) {
+                        cx2 = fm_square_add(fma((double)(R.i0 + i), fe.h, fe.x), cz2);
+                    } else {
+                        fm_axis(tx, Dx, Dxl, magic, xh, xl);
+                        xh += zh;
+                        xl += zl;
+                    }
+                    ix = i;
                 }
-                const float4 ty = axis[FM_SIDE + j];
-                float yh, yl;
-                fm_axis(ty, Dy, Dyl, magic, yh, yl);
-                const FmCol cl = fm_col(xh + yh, xl + yl, dh, dh2, uc0);
+                if (X) {
+                    cl = fm_col_f64(cx2, fma((double)(R.j0 + j), fe.h, fe.y), __float_as_int(rl[10 * WAVE]));
+                } else {
+                    float yh, yl;
+                    fm_axis(ty, Dy, Dyl, magic, yh, yl);
+                    cl = fm_col(xh + yh, xl + yl, dh, dh2, uc0);
+                }
                 const float dc2 = cl.dc * cl.dc, hdc = 0.5f * cl.dc;
                 float pv[FM_RZ];
                 if (WANT_POSE) {
@@ -3579,6 +3657,8 @@ void make_plan(ra_ctx* ctx, const ra_grid* grid, int32_t M, int32_t F, const ra_
         P.am_pose = room && mt.pose && plan_adjoint_mom(grid, samp, g, x ? 60.0 : 43.0, am_nq(mt.pose), x, P.ga2, P.am_nbuf[1]);
         set_terms(P.ga1, mt);
         set_terms(P.ga2, mt);
+        // with edge terms the forward and the dL/dp0 adjoint take the same form, so that they decide the edges alike
+        if (x && !(P.fm && P.am)) P.fm = P.am = P.am_pose = false;
         if (only & PLAN_ROW_FORWARD) {
             P.fm = false;
             if (x) P.am = P.am_pose = false;
