@@ -1836,7 +1836,7 @@ __global__ __launch_bounds__(MT_ROWS) void k_moment_series(int E, int K, int jt,
 // over its chunks' elements of every voxel it visits in a register, and the 64 lanes meet once, after the
 // last chunk.  With WANT_POSE the sum runs together with its derivative in t, P and P':
 //   dL/dx_e = - sum_v p0 (2 / delta) / d^2 (P' - P / d) (D + o), d and o in units;
-// the terms of a column are FP32, columns add in FP64, the wavefronts' sums of a chunk meet in LDS (in the
+// the terms of four voxels add in FP32, those sums in FP64, the wavefronts' sums of a chunk meet in LDS (in the
 // window just used) in wavefront order, and a workgroup adds its regions into one row of partials in their
 // order (or each into its own row, row_step apart), so no result depends on timing.
 // Bounds: VALU.  About 19 instructions per pair for dL/dp0 and 36 per column of 8 pairs, 34 per pair with
@@ -2014,7 +2014,7 @@ __device__ __forceinline__ void am_regions(const Geo& g, int reg0, int reg1, int
                         for (int k = 0; k < FM_RZ; ++k) pv[k] = k < R.nk ? pc[min(k, R.nk - 1)] : 0.0f;
                     }
                 }
-                float c0 = 0.0f, cz = 0.0f;
+                float c0[2] = {0.0f, 0.0f}, cz[2] = {0.0f, 0.0f};         // of four voxels each
 #pragma unroll
                 for (int k = 0; k < FM_RZ; ++k) {
                     const FmPair p = fm_pair(cl, dc2, hdc, ez[k], rlo, rhi);
@@ -2048,14 +2048,15 @@ __device__ __forceinline__ void am_regions(const Geo& g, int reg0, int reg1, int
                     if (WANT_POSE) {
                         const float w = (pv[k] * p.rs) * p.rs;
                         const float f = w * fmaf(-h, p.rs, dd);
-                        c0 += f;
-                        cz = fmaf(f, (float)k - 0.5f * (float)(FM_RZ - 1), cz);
+                        c0[k / 4] += f;
+                        cz[k / 4] = fmaf(f, (float)k - 0.5f * (float)(FM_RZ - 1), cz[k / 4]);
                     }
                 }
                 if (WANT_POSE) {
-                    Sx += (double)((Dx + ox) * c0);
-                    Sy += (double)((Dy + ty.x) * c0);
-                    Sz += (double)fmaf(Dz + tz.x, c0, g.hs_u * fmaf(zmid, c0, cz));
+                    const double C = (double)c0[0] + (double)c0[1];
+                    Sx = fma((double)(Dx + ox), C, Sx);
+                    Sy = fma((double)(Dy + ty.x), C, Sy);
+                    Sz = fma((double)fmaf(zmid, g.hs_u, Dz + tz.x), C, fma((double)g.hs_u, (double)cz[0] + (double)cz[1], Sz));
                 }
             }
         }
