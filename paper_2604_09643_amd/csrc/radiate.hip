@@ -693,7 +693,6 @@ __device__ __forceinline__ void forward_region(const Geo& g, int reg, const floa
         // lanes past the last element model element 0; their rows are cleared, not flushed
         const Ref ref = make_ref(g, xe, valid ? e : 0, R);
         float* lane_rows = rows + lane + (g.kmargin - JT) * WAVE;
-        const float4 first = vtab[zl];
         // voxels four at a time, the next four loading while the current are processed
         float4 oa[4], ob[4];
         float pa[4], pb[4];
@@ -708,6 +707,7 @@ __device__ __forceinline__ void forward_region(const Geo& g, int reg, const floa
                 return;
             }
             // a voxel that is not there (an element may be) stands at the first of its pair, or of the region
+            const float4 first = vtab[zl];
 #pragma unroll
             for (int q = 0; q < 4; ++q) {
                 const int4 ix = itab[t + q];
