@@ -152,7 +152,10 @@ int ra_status(ra_ctx* ctx, void* stream);
 /* Grow the context's device scratch to at least `bytes`.  Calls allocate scratch
  * on demand outside stream capture; under capture they return RA_ENOMEM instead,
  * so reserve first when capturing into a HIP graph.  ra_scratch_bytes() reports
- * what any call with the given sizes needs (whatever ra_set_forward_sums chose). */
+ * what any call with the given sizes needs (whatever ra_set_forward_sums chose).
+ * radiate_forward and ra_count_updates run with less (radiate_forward_static's limit
+ * states how much); calls with an adjoint that find no room for their moment table (up to
+ * 48 bytes per sample of dL/ds) take the row forms, which need none and are slower. */
 int ra_reserve(ra_ctx* ctx, size_t bytes);
 size_t ra_scratch_bytes(const ra_grid* grid, int32_t M, int32_t F, const ra_sampling* samp);
 

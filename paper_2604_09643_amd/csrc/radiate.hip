@@ -3232,8 +3232,8 @@ struct Plan {
     size_t lds_adj, lds_adj0, lds_fwd;
     // scratch layout (byte offsets)
     size_t off_xe, off_vtab, off_itab, off_vtab_a, off_itab_a, off_vtab_f, off_itab_f, off_part, off_ge, off_s,
-        off_partial, off_count, off_nc, off_ncw, off_nct, off_s64,
-        off_xe64, off_q, total;
+        off_partial, off_nc, off_ncw, off_nct, off_s64, off_q, total;
+    size_t kept;        // bytes a forward-only call reserves beyond what it needs: the adjoints' but for tables the row forms do without
 };
 
 size_t align_up(size_t x) { return (x + 255) & ~(size_t)255; }
@@ -3536,6 +3536,7 @@ bool plan_adjoint_mom(const ra_grid* grid, const ra_sampling* samp, const Geo& b
 // terms the adjoints' row forms, which decide the window's edge as that forward does.  Scores and gradients
 // without the sum take the moment forms.
 constexpr unsigned PLAN_ROW_FORWARD = 1u;
+constexpr unsigned PLAN_NO_TABLE = 2u;     // adjoints without a moment table (see plan_call)
 
 // The context keeps the moment forms' series; without one (the batched step) the plan has the row forms only.
 void make_plan(ra_ctx* ctx, const ra_grid* grid, int32_t M, int32_t F, const ra_sampling* samp, Plan& P,
@@ -3653,7 +3654,8 @@ void make_plan(ra_ctx* ctx, const ra_grid* grid, int32_t M, int32_t F, const ra_
         // serve the other profiles and narrow Gaussians, so that a sweep whose signals fill the memory still has
         // room.  Wider Gaussians have always taken a table: their row form is 3 times slower.
         const size_t table = (size_t)g.E * (g.K + 2 * jout) * am_nq(MOM_MAX) * sizeof(float4);
-        const bool room = table <= AM_TABLE_MAX || (g.ktype == RA_KERNEL_GAUSSIAN && delta <= WIDE_GAUSS * sigma);
+        const bool room = !(only & PLAN_NO_TABLE) &&
+                          (table <= AM_TABLE_MAX || (g.ktype == RA_KERNEL_GAUSSIAN && delta <= WIDE_GAUSS * sigma));
         P.am = room && mt.vol && plan_adjoint_mom(grid, samp, g, x ? 45.0 : 30.0, am_nq(mt.vol), x, P.ga1, P.am_nbuf[0]);
         P.am_pose = room && mt.pose && plan_adjoint_mom(grid, samp, g, x ? 60.0 : 43.0, am_nq(mt.pose), x, P.ga2, P.am_nbuf[1]);
         set_terms(P.ga1, mt);
@@ -3679,15 +3681,15 @@ void make_plan(ra_ctx* ctx, const ra_grid* grid, int32_t M, int32_t F, const ra_
     P.off_ge = o; o = align_up(o + (size_t)g.E * 3 * sizeof(double));
     P.off_s = o; o = align_up(o + (size_t)g.E * g.K * sizeof(float));
     P.off_partial = o; o = align_up(o + RESID_BLOCKS * sizeof(float));
-    P.off_count = o; o = align_up(o + sizeof(unsigned long long));
     P.off_nc = o; o = align_up(o + (size_t)g.E * sizeof(double));
     P.off_ncw = o; o = align_up(o + (size_t)g.E * sizeof(double));
     P.off_nct = o; o = align_up(o + sizeof(double));
     P.off_s64 = o; o = align_up(o + (P.f64_sums ? (size_t)g.E * g.K * sizeof(double) : 0));
-    P.off_xe64 = o; o = align_up(o + (size_t)g.E * 3 * sizeof(double));
     const int nq = std::max(P.am ? am_nq(mt.vol) : 0, P.am_pose ? am_nq(mt.pose) : 0);
     P.off_q = o; o = align_up(o + ((size_t)g.E * (g.K + 2 * jout) + 1) * nq * sizeof(float4));
     P.total = o;
+    const bool own = g.ktype == RA_KERNEL_GAUSSIAN && delta <= WIDE_GAUSS * sigma;
+    P.kept = own || nq == 0 ? o : P.off_q + align_up((size_t)g.nreg * g.E * 3 * sizeof(double));
 }
 
 int ensure_scratch(ra_ctx* ctx, size_t bytes, hipStream_t stream) {
@@ -3706,6 +3708,18 @@ int ensure_scratch(ra_ctx* ctx, size_t bytes, hipStream_t stream) {
     }
     ctx->arena_bytes = bytes;
     return RA_OK;
+}
+
+// Plan of a call with an adjoint, and its scratch.  Where there is no room for the moment table (up to 48 bytes per
+// sample of dL/ds), the row forms, which need none, take the call.
+int plan_call(ra_ctx* ctx, const ra_grid* grid, int32_t M, int32_t F, const ra_sampling* samp, Plan& P, hipStream_t stream,
+              unsigned only = 0) {
+    make_plan(ctx, grid, M, F, samp, P, ctx->sums_mode, only);
+    int rc = ensure_scratch(ctx, P.total, stream);
+    if (rc != RA_ENOMEM || !(P.am || P.am_pose)) return rc;
+    make_plan(ctx, grid, M, F, samp, P, ctx->sums_mode, only | PLAN_NO_TABLE);
+    if ((rc = ensure_scratch(ctx, P.total, stream)) == RA_OK) ctx->err.clear();
+    return rc;
 }
 
 // Allow a kernel the full LDS of a CU, once per kernel (so not again under stream capture).
@@ -4085,7 +4099,10 @@ int radiate_forward(ra_ctx* ctx, const ra_grid* grid, const float* p0, int32_t M
     RA_HIP(ctx, hipSetDevice(ctx->device));
     Plan P;
     make_plan(ctx, grid, M, F, samp, P, ctx->sums_mode);
-    if ((rc = ensure_scratch(ctx, P.total, st)) != RA_OK) return rc;
+    // a later call with an adjoint may be captured, and finds its scratch; but a forward that fits runs
+    rc = ensure_scratch(ctx, std::min(P.total, P.kept), st);
+    if (rc == RA_ENOMEM && (rc = ensure_scratch(ctx, forward_layout(P), st)) == RA_OK) ctx->err.clear();
+    if (rc != RA_OK) return rc;
     if ((rc = prologue(ctx, ctx->arena, grid, P, elem, poses, st, true)) != RA_OK) return rc;
     return launch_forward(ctx, ctx->arena, P, p0, s, st);
 }
@@ -4122,8 +4139,7 @@ int radiate_adjoint(ra_ctx* ctx, const ra_grid* grid, const float* p0, int32_t M
     hipStream_t st = (hipStream_t)stream;
     RA_HIP(ctx, hipSetDevice(ctx->device));
     Plan P;
-    make_plan(ctx, grid, M, F, samp, P, ctx->sums_mode);
-    if ((rc = ensure_scratch(ctx, P.total, st)) != RA_OK) return rc;
+    if ((rc = plan_call(ctx, grid, M, F, samp, P, st)) != RA_OK) return rc;
     if ((rc = prologue(ctx, ctx->arena, grid, P, elem, poses, st)) != RA_OK) return rc;
     return adjoint_body(ctx, P, p0, elem, r, grad_p0, grad_pose, grad_elem, flags, st);
 }
@@ -4143,8 +4159,7 @@ int loss_and_grad(ra_ctx* ctx, const ra_grid* grid, const float* p0, int32_t M, 
     hipStream_t st = (hipStream_t)stream;
     RA_HIP(ctx, hipSetDevice(ctx->device));
     Plan P;
-    make_plan(ctx, grid, M, F, samp, P, ctx->sums_mode);
-    if ((rc = ensure_scratch(ctx, P.total, st)) != RA_OK) return rc;
+    if ((rc = plan_call(ctx, grid, M, F, samp, P, st)) != RA_OK) return rc;
     if ((rc = prologue(ctx, ctx->arena, grid, P, elem, poses, st)) != RA_OK) return rc;
     float* s = at<float>(ctx, P.off_s);
     const size_t n = (size_t)P.g.E * P.g.K;
@@ -4186,8 +4201,7 @@ int nc_loss_and_grad(ra_ctx* ctx, const ra_grid* grid, const float* p0, int32_t 
     hipStream_t st = (hipStream_t)stream;
     RA_HIP(ctx, hipSetDevice(ctx->device));
     Plan P;
-    make_plan(ctx, grid, M, F, samp, P, ctx->sums_mode, loss ? PLAN_ROW_FORWARD : 0);
-    if ((rc = ensure_scratch(ctx, P.total, st)) != RA_OK) return rc;
+    if ((rc = plan_call(ctx, grid, M, F, samp, P, st, loss ? PLAN_ROW_FORWARD : 0)) != RA_OK) return rc;
     if ((rc = prologue(ctx, ctx->arena, grid, P, elem, poses, st)) != RA_OK) return rc;
     float* s = at<float>(ctx, P.off_s);
     if ((rc = launch_forward(ctx, ctx->arena, P, p0, s, st)) != RA_OK) return rc;
@@ -4311,17 +4325,16 @@ int ra_count_updates(ra_ctx* ctx, const ra_grid* grid, int32_t M, const double* 
     if (!elem || !poses || !count) return fail(ctx, RA_EINVAL, "elem, poses and count are required");
     hipStream_t st = (hipStream_t)stream;
     RA_HIP(ctx, hipSetDevice(ctx->device));
-    Plan P;
-    make_plan(ctx, grid, M, F, samp, P, ctx->sums_mode);
-    if ((rc = ensure_scratch(ctx, P.total, st)) != RA_OK) return rc;
-    const Geo& g = P.g;
-    double* xe64 = at<double>(ctx, P.off_xe64);
-    unsigned long long* d_count = at<unsigned long long>(ctx, P.off_count);
-    hipLaunchKernelGGL(k_elements_f64, dim3((g.E + 255) / 256), dim3(256), 0, st, g.M, g.E, elem, poses, xe64);
+    const int E = M * F;
+    const size_t off_count = align_up((size_t)E * 3 * sizeof(double));
+    if ((rc = ensure_scratch(ctx, off_count + sizeof(unsigned long long), st)) != RA_OK) return rc;
+    double* xe64 = at<double>(ctx, 0);
+    unsigned long long* d_count = at<unsigned long long>(ctx, off_count);
+    hipLaunchKernelGGL(k_elements_f64, dim3((E + 255) / 256), dim3(256), 0, st, M, E, elem, poses, xe64);
     hipLaunchKernelGGL(k_fill, dim3(1), dim3(64), 0, st, reinterpret_cast<float*>(d_count), (size_t)2, 0.0f);
-    long long nvox = (long long)g.nx * g.ny * g.nz;
-    hipLaunchKernelGGL(k_count, dim3((unsigned)((nvox + 255) / 256)), dim3(256), 0, st, g.nx, g.ny, g.nz,
-                       grid->origin[0], grid->origin[1], grid->origin[2], grid->spacing, g.E, xe64, samp->c,
+    long long nvox = (long long)grid->nx * grid->ny * grid->nz;
+    hipLaunchKernelGGL(k_count, dim3((unsigned)((nvox + 255) / 256)), dim3(256), 0, st, grid->nx, grid->ny, grid->nz,
+                       grid->origin[0], grid->origin[1], grid->origin[2], grid->spacing, E, xe64, samp->c,
                        samp->fs, samp->K, samp->trunc * samp->sigma, d_count);
     RA_HIP(ctx, hipGetLastError());
     RA_HIP(ctx, hipMemcpyAsync(ctx->h_count, d_count, sizeof(unsigned long long), hipMemcpyDeviceToHost, st));
