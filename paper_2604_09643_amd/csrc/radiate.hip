@@ -3140,17 +3140,23 @@ struct MomTerms {
     int xkind;
 };
 
+struct MomSeries {
+    double key[4] = {0.0, 0.0, 0.0, 0.0};  // profile, delta / width, window, nu
+    MomTerms terms{};
+    MomCoef fwd, vol, pose;                // with the terms of the forward, of dL/dp0 alone and of the element gradients
+};
+
 struct ra_ctx {
     int device = 0;
     int* d_status = nullptr;
     char* arena = nullptr;                  // the context's scratch (grown by ensure_scratch)
     size_t arena_bytes = 0;
     char* static_scratch = nullptr;         // this device's static array (radiate_forward_static)
-    // series of the moment-form forward for the sampling of the last call (its key: profile, window, nu)
-    MomCoef series, seriesv, seriesp;       // with the terms of the forward, of dL/dp0 alone and of the element gradients
-    double series_key[4] = {0.0, 0.0, 0.0, 0.0};
-    double series_tail[MOM_MAX + 1];
-    MomTerms terms;
+    // the moment forms' series for the last few samplings used, and that of the current call (20 to 30 us of host time to make
+    // one, against calls of 20 us on: a program may go through several widths or profiles in turn)
+    MomSeries series[8];
+    int series_oldest = 0;
+    const MomSeries* now = nullptr;
     unsigned long long* h_count = nullptr;  // pinned
     double* h_f64 = nullptr;                // pinned, one value
     double* d_f64 = nullptr;                // device, one value
@@ -3312,10 +3318,15 @@ constexpr int MOM_NODES = 24;
 
 void mom_series(const ra_sampling* samp, double dd, int j0, int j1, double peak, double cheb[MOM_MAX][JMAX + 1],
                 double tail[MOM_MAX + 1]) {
-    const double pi = 3.14159265358979323846;
-    double cs[MOM_NODES][MOM_NODES];
-    for (int k = 0; k < MOM_NODES; ++k)
-        for (int i = 0; i < MOM_NODES; ++i) cs[k][i] = std::cos(pi * k * (i + 0.5) / MOM_NODES);
+    struct Nodes {
+        double c[MOM_NODES][MOM_NODES];
+        Nodes() {
+            for (int k = 0; k < MOM_NODES; ++k)
+                for (int i = 0; i < MOM_NODES; ++i) c[k][i] = std::cos(3.14159265358979323846 * k * (i + 0.5) / MOM_NODES);
+        }
+    };
+    static const Nodes nodes;
+    const double(&cs)[MOM_NODES][MOM_NODES] = nodes.c;
     for (int n = 0; n <= MOM_MAX; ++n) tail[n] = 0.0;
     for (int j = j0; j <= j1; ++j) {
         double f[MOM_NODES];
@@ -3346,7 +3357,7 @@ void mom_monomials(const double cheb[MOM_MAX][JMAX + 1], int nm, int j, float* o
     }
 }
 
-// The moment forms' series for this sampling, kept in the context until the sampling changes.  Their numbers of
+// The moment forms' series for this sampling, kept in the context (its last eight).  Their numbers of
 // terms are the fewest of those compiled whose cut series is within FM_TOL (AM_TOL where the derivative is used too):
 //   Gaussian     6 up to delta/sigma 0.41, 7 up to 0.64, 8 up to 1.05 (the row form's own rounding is about 4e-7); 8 with
 //                derivatives, up to 0.75.  The window's rows are taken whole, as the Gaussian's row forms do for
@@ -3359,25 +3370,31 @@ void mom_monomials(const double cheb[MOM_MAX][JMAX + 1], int nm, int j, float* o
 //                put an edge sample in on one side and out on the other, which the row forms, on shared
 //                regions, avoid (single results then moved by 1.4e-3 at an edge value of 0.0135).  The uniform
 //                sphere keeps those always; a power law with nu = 2 passes from 9.1 widths on, the exponential from 8.7.
-const MomTerms& series_terms(ra_ctx* ctx, const ra_sampling* samp, bool exact) {
+const MomSeries& series_of(ra_ctx* ctx, const ra_sampling* samp, bool exact) {
     const double delta = samp->c / samp->fs, dd = delta / samp->sigma, jw = samp->trunc * samp->sigma / delta;
     const double key[4] = {(double)samp->kernel + (exact ? 0.5 : 0.0), dd, samp->trunc, samp->nu};
-    if (std::memcmp(key, ctx->series_key, sizeof(key)) == 0) return ctx->terms;
-    std::memcpy(ctx->series_key, key, sizeof(key));
-    MomTerms& t = ctx->terms;
+    for (const MomSeries& m : ctx->series)
+        if (std::memcmp(key, m.key, sizeof(key)) == 0) return *(ctx->now = &m);
+    constexpr int kept = sizeof(ctx->series) / sizeof(ctx->series[0]);
+    MomSeries& m = ctx->series[ctx->series_oldest];
+    ctx->series_oldest = (ctx->series_oldest + 1) % kept;
+    ctx->now = &m;
+    std::memcpy(m.key, key, sizeof(key));
+    MomTerms& t = m.terms;
     t = MomTerms{};
     const int jo = (int)std::floor(jw + 0.5), kt = samp->kernel;
-    if (jo < 1 || jo > JMAX || kt == RA_KERNEL_UNIFORM || (kt == RA_KERNEL_GAUSSIAN && !(exact || samp->trunc >= 6.0))) return t;
-    double peak = 0.0;
-    for (int i = 1; i <= 1024; ++i) peak = std::max(peak, profile(samp, dd, jw * i / 1024.0));
+    if (jo < 1 || jo > JMAX || kt == RA_KERNEL_UNIFORM || (kt == RA_KERNEL_GAUSSIAN && !(exact || samp->trunc >= 6.0))) return m;
+    // phi's peak: at the width (power law: width / sqrt(2 nu - 1)), or the window's edge before it
+    const double top = std::min(jw, (kt == RA_KERNEL_POWER ? 1.0 / std::sqrt(2.0 * samp->nu - 1.0) : 1.0) / dd);
+    const double peak = profile(samp, dd, top);
     double cheb[MOM_MAX][JMAX + 1] = {}, ce[MOM_MAX][JMAX + 1] = {}, te[MOM_MAX + 1];
     const double edge = 2.0 * (jo - jw);                   // kc + jo is in the window for t >= edge
     const int j0 = kt == RA_KERNEL_EXPONENTIAL ? 1 : 0, j1 = kt == RA_KERNEL_GAUSSIAN || edge <= 0.0 ? jo : jo - 1;
-    double* tail = ctx->series_tail;
+    double tail[MOM_MAX + 1];
     mom_series(samp, dd, j0, j1, peak, cheb, tail);
     if (kt != RA_KERNEL_GAUSSIAN) {
         mom_series(samp, dd, jo, jo, peak, ce, te);
-        if (!(te[4] <= FM_TOL) || profile(samp, dd, jw) > FM_EDGE * peak) return t;
+        if (!(te[4] <= FM_TOL) || profile(samp, dd, jw) > FM_EDGE * peak) return m;
         t.xkind = kt == RA_KERNEL_EXPONENTIAL ? 2 : 1;
         mom_monomials(ce, 4, jo, t.ev);
         t.thr = (float)edge;
@@ -3400,19 +3417,19 @@ const MomTerms& series_terms(ra_ctx* ctx, const ra_sampling* samp, bool exact) {
         return 0;
     };
     t.fwd = fewest(FM_TOL, 0);
-    if (!t.fwd) return t;
+    if (!t.fwd) return m;
     t.vol = kt == RA_KERNEL_GAUSSIAN ? t.fwd : kt == RA_KERNEL_POWER && t.fwd > 8 ? 12 : terms[kt][1] == 10 ? 8 : terms[kt][1];
     t.pose = kt == RA_KERNEL_POWER ? (tail[8] <= AM_TOL ? 8 : fewest(AM_TOL, 2)) : fewest(AM_TOL, 2);
     // Short windows of narrow Gaussians: the adjoints' row forms test the window's outermost samples, whose terms
     // are psi(trunc) of the peak (1.5e-7 from 6 sigma on, 1.6e-3 at 4)
     if (kt == RA_KERNEL_GAUSSIAN && samp->trunc < 6.0 && dd > WIDE_GAUSS) t.vol = t.pose = 0;
     const int nm[3] = {t.fwd, t.vol, t.pose};
-    MomCoef* const out[3] = {&ctx->series, &ctx->seriesv, &ctx->seriesp};
+    MomCoef* const out[3] = {&m.fwd, &m.vol, &m.pose};
     for (int i = 0; i < 3; ++i) {
         std::memset(out[i], 0, sizeof(MomCoef));
         for (int j = j0; nm[i] && j <= j1; ++j) mom_monomials(cheb, nm[i], j, out[i]->d + j * MOM_MAX);
     }
-    return t;
+    return m;
 }
 
 // Moment forms: lengths in units of delta / 2.
@@ -3644,7 +3661,7 @@ void make_plan(ra_ctx* ctx, const ra_grid* grid, int32_t M, int32_t F, const ra_
     P.f64_sums = sums_mode == RA_SUMS_F64 || (sums_mode == RA_SUMS_AUTO && P.gf.nreg > FWD_F32_MAX_REGIONS);
 
     static const MomTerms none{};
-    const MomTerms& mt = ctx ? series_terms(ctx, samp, P.exact) : none;
+    const MomTerms& mt = ctx ? series_of(ctx, samp, P.exact).terms : none;
     P.terms = mt;
     P.fm = P.am = P.am_pose = false;
     if (mt.fwd) {
@@ -3828,7 +3845,7 @@ int launch_forward_mom(ra_ctx* ctx, char* base, const Plan& P, const float* p0, 
         auto kern = k_forward_mom<NM, NW, X, float>;
         RA_HIP(ctx, allow_full_lds(kern));
         hipLaunchKernelGGL(k_fill, dim3(1024), dim3(256), 0, stream, s, n, 0.0f);
-        hipLaunchKernelGGL(kern, grid, block, P.lds_fm, stream, P.gm, ctx->series, P.fm_slices, p0, xe, s);
+        hipLaunchKernelGGL(kern, grid, block, P.lds_fm, stream, P.gm, ctx->now->fwd, P.fm_slices, p0, xe, s);
         RA_HIP(ctx, hipGetLastError());
         return RA_OK;
     }
@@ -3836,7 +3853,7 @@ int launch_forward_mom(ra_ctx* ctx, char* base, const Plan& P, const float* p0, 
     RA_HIP(ctx, allow_full_lds(kern));
     double* s64 = at<double>(base, P.off_s64);
     hipLaunchKernelGGL(k_fill_f64, dim3(1024), dim3(256), 0, stream, s64, n);
-    hipLaunchKernelGGL(kern, grid, block, P.lds_fm, stream, P.gm, ctx->series, P.fm_slices, p0, xe, s64);
+    hipLaunchKernelGGL(kern, grid, block, P.lds_fm, stream, P.gm, ctx->now->fwd, P.fm_slices, p0, xe, s64);
     hipLaunchKernelGGL(k_to_f32, dim3(1024), dim3(256), 0, stream, s64, n, s);
     RA_HIP(ctx, hipGetLastError());
     return RA_OK;
@@ -3945,7 +3962,7 @@ int launch_adjoint_series(ra_ctx* ctx, const Plan& P, const float* p0, const flo
     const int nm = pose ? P.terms.pose : P.terms.vol;
     auto table = am_nq(nm) == 2 ? k_moment_series<2> : k_moment_series<3>;
     hipLaunchKernelGGL(table, dim3((unsigned)P.g.E * per), dim3(MT_ROWS), 0, stream, P.g.E, K, jt,
-                       pose ? ctx->seriesp : ctx->seriesv, r, at<float4>(ctx, P.off_q));
+                       pose ? ctx->now->pose : ctx->now->vol, r, at<float4>(ctx, P.off_q));
 #define RA_CASE(n, x)                                                                                    \
     if (nm == n && P.terms.xkind == x && pose)                                                           \
         return gp0 ? launch_adjoint_series_c<n, true, true, x>(ctx, P, p0, r, gp0, acc, stream)          \
@@ -4419,13 +4436,13 @@ int ra_batch_describe(ra_ctx* ctx, const ra_grid* box, int64_t stride_x, int64_t
     g.jt = P.jt;
     g.nbin = 2 * g.jclamp + 1;
     set_units(g, box, delta);
-    const MomTerms mt = P.exact ? series_terms(ctx, samp, true) : MomTerms{};
+    const MomTerms mt = P.exact ? series_of(ctx, samp, true).terms : MomTerms{};
     bg.nm = mt.fwd;
     const bool moment = mt.fwd && mt.pose && g.rz <= FM_RZ && g.nbin <= BATCH_BINS_MAX &&
                         fm_lds(bg.nm, g.nbin, g.jt, false) <= 160 * 1024 && am_lds(g.nbin, 2, 0, 1) <= 160 * 1024;
     if (moment) {
-        bg.series = ctx->series;
-        bg.series8 = ctx->seriesp;
+        bg.series = ctx->now->fwd;
+        bg.series8 = ctx->now->pose;
     }
     std::memcpy(geo, &bg, sizeof(BatchGeo));
     info->nreg = g.nreg;
