@@ -1863,6 +1863,9 @@ __device__ __forceinline__ void am_regions(const Geo& g, int reg0, int reg1, int
                                            const float* __restrict__ r, float* __restrict__ grad_p0, int accumulate,
                                            double* __restrict__ pose_part, size_t row_step, float* lds) {
     constexpr int NQ = am_nq(NM);
+    // With edge terms (compiled for 4 columns a wavefront alone) the columns go round the wavefronts, so that regions of 16
+    // or 32 columns occupy all of them too (exponential, 40^3 voxels of 0.3 mm, 256 elements: 352 us with 4 of 16 at work)
+    constexpr bool STRIDED = X != 0;
     const int tid = threadIdx.x, lane = tid & (WAVE - 1);
     const int wv = __builtin_amdgcn_readfirstlane(tid / WAVE);
     const int nbin = g.nbin, jt = g.jt, kq = g.K + 2 * jt;
@@ -1978,7 +1981,7 @@ __device__ __forceinline__ void am_regions(const Geo& g, int reg0, int reg1, int
             float xh = 0.0f, xl = 0.0f, ox = 0.0f;
 #pragma unroll
             for (int cc = 0; cc < CPW; ++cc) {
-                const int col = wv * CPW + cc;
+                const int col = STRIDED ? cc * AM_WAVES + wv : wv * CPW + cc;
                 if (col >= ncol) continue;
                 const int i = col / R.nj, j = col - i * R.nj;
                 const float4 ty = axis[FM_SIDE + j];
@@ -2087,7 +2090,8 @@ __device__ __forceinline__ void am_regions(const Geo& g, int reg0, int reg1, int
 #pragma unroll
             for (int i = 0; i < CPW * FM_RZ; i += 4) {
                 const float v = wave_sum4_rows(acc[i], acc[i + 1], acc[i + 2], acc[i + 3], lane);
-                if ((lane & 15) >= 12) part[(lane >> 4) * NV + wv * CPW * FM_RZ + i + vsel] = v;
+                const int at = STRIDED ? (i / FM_RZ * AM_WAVES + wv) * FM_RZ + i % FM_RZ : wv * CPW * FM_RZ + i;
+                if ((lane & 15) >= 12) part[(lane >> 4) * NV + at + vsel] = v;
                 acc[i] = acc[i + 1] = acc[i + 2] = acc[i + 3] = 0.0f;
             }
             __syncthreads();
@@ -3450,12 +3454,24 @@ void set_terms(Geo& g, const MomTerms& t) {
     g.kx = t.kx;
 }
 
+// Estimated cycles of the Gaussian's row-form forward: its wavefronts take 57 cycles per voxel and window row (32 where voxels
+// go in pairs), a third of that hidden behind the atomics of other workgroups, of which the chip does 108 a cycle; and 20 us
+// of start-up.  Within 25 % of what 30 calls took (spacings 0.05 to 1.2 mm, widths 0.06 to 0.15 mm, 64 and 256 elements).
+double row_forward_cost(const Geo& g, int jt, int pair_d) {
+    const double rows = 2.0 * jt + 1 + pair_d, chunks = (g.E + WAVE - 1) / WAVE;
+    const double work = std::ceil(g.nreg / 512.0) * std::ceil(chunks / WAVES) * g.nvpad * rows * (pair_d ? 32.0 : 57.0);
+    return 48000.0 + 0.7 * work + (double)g.nreg * g.E * g.L / 108.0;
+}
+
 // The moment-form forward of a call, with nm terms: on which regions.
 // Those that make the estimated time least.  Per pair and wavefront a CU spends about 34 cycles on the
 // adds; per region and chunk the expansion takes row tiles x quads x NM matrix instructions of 32 cycles
 // on each SIMD (measured: 1.45 times that, with the operand conversions and the atomics), and barriers and
 // clearing about 2500 cycles where one workgroup has the CU, 800 where two share it.  Large grids take
-// 16x16x16; a box of 32^3 voxels seen by one chunk takes small ones, which fill the chip.
+// 16x16x16; a box of 32^3 voxels seen by one chunk takes small ones, which fill the chip.  Coarse spacings leave regions of
+// few voxels, for each of which a window is expanded: there the Gaussian's row form is the faster one, and is taken where
+// its estimate is below 1.1 times this one's with 17 us a workgroup for references, bounds and clearing (sigma 0.1 mm, 40^3
+// voxels, 256 elements: 69 us against 150 in rows at 0.25 mm, 354 against 366 at 0.46, 1263 against 375 at 0.5).
 void plan_forward_mom(const ra_grid* grid, const ra_sampling* samp, const MomTerms& mt, Plan& P) {
     P.fm = false;
     const int nm = mt.fwd;
@@ -3465,7 +3481,7 @@ void plan_forward_mom(const ra_grid* grid, const ra_sampling* samp, const MomTer
     static const int cand[][3] = {{16, 16, 16}, {16, 16, 8}, {8, 16, 8}, {8, 8, 16}, {8, 8, 8}, {4, 8, 8},
                                   {4, 4, 8},    {2, 4, 8},   {2, 2, 8},  {1, 2, 8},  {1, 1, 8}};
     const int nchunk = (P.g.E + WAVE - 1) / WAVE;
-    double best = 0.0;
+    double best = 0.0, start = 0.0;
     for (const auto& cd : cand) {
         Geo g = P.g;
         // as many regions along x and y as the candidate's size gives, of even size
@@ -3496,31 +3512,47 @@ void plan_forward_mom(const ra_grid* grid, const ra_sampling* samp, const MomTer
         const double cost = (full + last) * per_cu * per_wg * each;
         if (P.fm && cost >= best) continue;
         best = cost;
+        start = (full + last) * 40000.0;
         P.fm = true;
         P.gm = g;
         P.fm_slices = slices;
         P.lds_fm = lds;
     }
+    if (samp->kernel == RA_KERNEL_GAUSSIAN && best + start > 0.9 * row_forward_cost(P.gf, P.jt, P.pair_d)) P.fm = false;
     if (!P.fm) return;
     set_units(P.gm, grid, delta);
     set_terms(P.gm, mt);
 }
 
-// The moment-form adjoint's regions: columns of 8 voxels, up to 64 of them, those that make the estimated
+// Estimated cycles of the Gaussian's row-form adjoints: 46 per voxel and window row of a wavefront and 600 per row staged, and
+// 20 us of start-up; `slots` workgroups run at once.
+double row_adjoint_cost(const Geo& g, int jt, double slots) {
+    const double chunks = (g.E + WAVE - 1) / WAVE;
+    return 48000.0 + std::ceil(g.nreg / slots) * std::ceil(chunks / WAVES) * (g.nvpad * (2.0 * jt + 1) * 46.0 + g.L * 600.0);
+}
+
+// The moment-form adjoint's regions: columns of up to 8 voxels, up to 64 of them, those that make the estimated
 // time least (`pair`: CU cycles per pair and wavefront, 30 for dL/dp0, 44 with the element gradients).  Two
 // table windows in LDS let a chunk's loads run behind the previous chunk's voxels; where the spacing is so
-// coarse that only one fits, the loads (about 41 cycles per bin, and their latency) add to the time.
-bool plan_adjoint_mom(const ra_grid* grid, const ra_sampling* samp, const Geo& base, double pair, int nq, bool edge, Geo& out,
-                      int& nbuf) {
-    static const int cand[][2] = {{8, 8}, {4, 8}, {4, 4}, {2, 4}, {2, 2}, {1, 2}, {1, 1}};
+// coarse that only one fits, the loads (about 41 cycles per bin, and their latency) add to the time.  Columns of 4 and 2
+// voxels cost what one of 8 does, and are for spacings where the table window of 8 would not fit (40^3 voxels of 0.42 mm,
+// 256 elements: the row form took 528 us, these 107).  `rows`: the row form's estimate; it keeps the call where 1.5 times
+// this one's and 15 us exceed it, as with narrow Gaussians (19 rows) at coarse spacings: sigma 0.06 mm at 0.42 mm, element
+// gradients 107 us in rows and 132 in moments, at 0.3 mm 103 and 76.
+bool plan_adjoint_mom(const ra_grid* grid, const ra_sampling* samp, const Geo& base, double pair, int nq, bool edge, double rows,
+                      Geo& out, int& nbuf) {
+    // with edge terms whole columns only, which are the forward's
+    static const int cand[][3] = {{8, 8, 8}, {4, 8, 8}, {4, 4, 8}, {2, 4, 8}, {2, 2, 8}, {1, 2, 8}, {1, 1, 8}, {8, 8, 4}, {4, 8, 4},
+                                  {4, 4, 4}, {2, 4, 4}, {2, 2, 4}, {4, 4, 2}, {2, 4, 2}, {2, 2, 2}, {1, 2, 2}, {1, 1, 2}, {1, 1, 1}};
     const double delta = samp->c / samp->fs;
     const int nchunk = (base.E + WAVE - 1) / WAVE;
     double best = 0.0;
     bool found = false;
     for (const auto& cd : cand) {
+        if (edge && cd[2] < FM_RZ) break;
         Geo g = base;
-        g.nrx = (g.nx + cd[0] - 1) / cd[0]; g.nry = (g.ny + cd[1] - 1) / cd[1]; g.nrz = (g.nz + FM_RZ - 1) / FM_RZ;
-        g.rx = (g.nx + g.nrx - 1) / g.nrx; g.ry = (g.ny + g.nry - 1) / g.nry; g.rz = std::min(FM_RZ, g.nz);
+        g.nrx = (g.nx + cd[0] - 1) / cd[0]; g.nry = (g.ny + cd[1] - 1) / cd[1]; g.nrz = (g.nz + cd[2] - 1) / cd[2];
+        g.rx = (g.nx + g.nrx - 1) / g.nrx; g.ry = (g.ny + g.nry - 1) / g.nry; g.rz = std::min(cd[2], g.nz);
         g.nrx = (g.nx + g.rx - 1) / g.rx; g.nry = (g.ny + g.ry - 1) / g.ry;
         g.nreg = g.nrx * g.nry * g.nrz;
         const double rad = 0.5 * grid->spacing * std::sqrt((double)(g.rx - 1) * (g.rx - 1) + (double)(g.ry - 1) * (g.ry - 1) +
@@ -3542,6 +3574,7 @@ bool plan_adjoint_mom(const ra_grid* grid, const ra_sampling* samp, const Geo& b
         out = g;
         nbuf = nb;
     }
+    if (1.5 * best + 36000.0 > rows) found = false;
     if (found) set_units(out, grid, delta);
     return found;
 }
@@ -3673,8 +3706,11 @@ void make_plan(ra_ctx* ctx, const ra_grid* grid, int32_t M, int32_t F, const ra_
         const size_t table = (size_t)g.E * (g.K + 2 * jout) * am_nq(MOM_MAX) * sizeof(float4);
         const bool room = !(only & PLAN_NO_TABLE) &&
                           (table <= AM_TABLE_MAX || (g.ktype == RA_KERNEL_GAUSSIAN && delta <= WIDE_GAUSS * sigma));
-        P.am = room && mt.vol && plan_adjoint_mom(grid, samp, g, x ? 45.0 : 30.0, am_nq(mt.vol), x, P.ga1, P.am_nbuf[0]);
-        P.am_pose = room && mt.pose && plan_adjoint_mom(grid, samp, g, x ? 60.0 : 43.0, am_nq(mt.pose), x, P.ga2, P.am_nbuf[1]);
+        const double any = INFINITY;
+        P.am = room && mt.vol && plan_adjoint_mom(grid, samp, g, x ? 45.0 : 30.0, am_nq(mt.vol), x,
+                                                  x ? any : row_adjoint_cost(P.ga, P.jt, 768.0), P.ga1, P.am_nbuf[0]);
+        P.am_pose = room && mt.pose && plan_adjoint_mom(grid, samp, g, x ? 60.0 : 43.0, am_nq(mt.pose), x,
+                                                        x ? any : row_adjoint_cost(g, P.jt, 512.0), P.ga2, P.am_nbuf[1]);
         set_terms(P.ga1, mt);
         set_terms(P.ga2, mt);
         // with edge terms the forward and the dL/dp0 adjoint take the same form, so that they decide the edges alike
