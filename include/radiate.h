@@ -115,9 +115,11 @@ typedef struct {
  *   RA_KERNEL_EXPONENTIAL  exp(-x/w)
  *   RA_KERNEL_POWER        (1 + x^2/w^2)^(-nu), nu > 1/2
  *   RA_KERNEL_UNIFORM      1 inside the window (a uniform sphere of radius w: trunc = 1)
- * The other profiles take voxels one at a time: the exponential factorises per leg of the
- * window, the power law and the uniform sphere evaluate every sample.  They are not
- * supported by the batched serving step (RA_ENOTSUP).  RA_EINVAL for an unknown kernel or,
+ * The exponential and the power law take the polynomial form where they have fallen to 0.4 %
+ * of their peak at the window's edge (from 8.7 widths on, and 9.1 with nu = 2); nearer, the
+ * exponential factorises per leg of the window and the power law evaluates every sample, as
+ * the uniform sphere always does.  The three are not supported by the batched serving step
+ * (RA_ENOTSUP).  RA_EINVAL for an unknown kernel or,
  * with RA_KERNEL_POWER, nu <= 1/2 or not finite. */
 enum { RA_KERNEL_GAUSSIAN = 0, RA_KERNEL_EXPONENTIAL = 1, RA_KERNEL_POWER = 2, RA_KERNEL_UNIFORM = 3 };
 typedef struct {
@@ -240,7 +242,10 @@ int loss_and_grad(ra_ctx* ctx, const ra_grid* grid, const float* p0,
  *   y          float[F][M][K]   measured signals
  *   weight     float[F][M] or NULL (all 1): per-element weights w_e (an inlier mask)
  *   loss       HOST double* or NULL.  Non-NULL: the call waits for the stream and stores L
- *              (per-element FP64 values summed in a fixed order on the device).
+ *              (per-element FP64 values summed in a fixed order on the device).  L is a signed
+ *              sum and may nearly cancel, where it shows the signals' rounding (1e-7 of sum
+ *              |w_e L_e|); calls that return it run the forward sample by sample, others in
+ *              the faster polynomial form.
  *   loss_elem  double[F][M] or NULL: the unweighted L_e (e.g. to rank candidate positions)
  *   s_out      float[F][M][K] or NULL: the forward signals
  * Row statistics are taken in FP64 over the FP32 signals. */
@@ -263,10 +268,10 @@ int nc_loss_and_grad(ra_ctx* ctx, const ra_grid* grid, const float* p0,
  *   loss    HOST double* or NULL: scale * TGV (FP64 sum; the call waits for the stream)
  *   grad_u  float[nx][ny][nz] or NULL; grad_w float[3][nx][ny][nz] or NULL
  *   flags   RA_ACCUMULATE adds scale * gradient into grad_u / grad_w
- * One pass: each voxel re-evaluates its neighbours' normalised fields from u and w, so HBM
- * sees only the inputs read and the gradients written.
- * Scratch: ra_tgv_scratch_bytes(nx, ny, nz) (one FP64 partial of the value per 64 x 4 voxels of
- * a plane), taken as in the other calls.
+ * One pass: each voxel's normalised fields are computed once and handed to its neighbours on
+ * the chip, so HBM sees only the inputs read and the gradients written.
+ * Scratch: ra_tgv_scratch_bytes(nx, ny, nz) (one FP64 partial of the value per tile), taken as
+ * in the other calls.
  * Errors: RA_EINVAL for non-positive dimensions, missing u or w, alpha < 0, eps < 1e-18 (eps^2
  * must be a normal FP32 number). */
 size_t ra_tgv_scratch_bytes(int32_t nx, int32_t ny, int32_t nz);
@@ -350,7 +355,8 @@ typedef struct {
     int32_t rx, ry, rz;     /* region size                                                    */
     int32_t moment;         /* 1: the batch may take the moment forms (a pair's window as a
                                polynomial in its offset from its nearest sample, as the
-                               single calls do); equal for requests that may share a batch    */
+                               single calls do); 2: in the adjoints only (regions of few
+                               voxels); equal for requests that may share a batch             */
     int32_t nbin;           /* centre samples per region and element (moment form)           */
     int64_t q_bytes;        /* bytes of the request's moment table (0 without the form)      */
 } ra_batch_info;
@@ -372,14 +378,14 @@ typedef struct {
     int32_t pair_d;               /* from ra_batch_describe (equal for all requests)        */
     int32_t lmax, nvpad;          /* maxima over the batch                                  */
     int32_t grid_blocks;          /* workgroups per launch; 0 = 1024                        */
-    int32_t moment;               /* 1: forward and adjoints in moment form (every request has
-                                     ra_batch_info.moment set and a q buffer); 0: row form.
+    int32_t moment;               /* 1: forward and adjoints in moment form, 2: the adjoints only (every
+                                     request has this ra_batch_info.moment and a q buffer); 0: row form.
                                      RA_EINVAL for the moment form without coef, without the
                                      exact window, or with nbin outside 1..40 or beyond the LDS */
     int32_t nbin;                 /* ra_batch_info.nbin (moment form; equal for all requests:
                                      a request whose window needs more bins is skipped)     */
-    float* coef;                  /* moment form: float[8 (2 jt + 1)] device scratch (jt <= 40,
-                                     so 648 floats always suffice)                          */
+    float* coef;                  /* required with the moment form, and not used any more: its
+                                     coefficients travel in the descriptors                 */
 } ra_batch;
 
 /* Size of one request descriptor. */

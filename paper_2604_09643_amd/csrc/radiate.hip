@@ -2744,9 +2744,10 @@ __global__ __launch_bounds__(256) void k_probe_exp(float* __restrict__ out, int 
 // ==========================================================================================
 constexpr int BATCH_THREADS = 256;
 
-// A request's descriptor: its geometry and the moment forms' series (nm terms for the forward, 8 for the adjoints).
+// A request's descriptor: its geometry and the moment forms' series (nm terms for the forward, 8 for the adjoints).  The
+// adjoints take a region of 16 voxels along z as two of 8, those of ga.
 struct BatchGeo {
-    Geo g;
+    Geo g, ga;
     int nm;
     MomCoef series, series8;
 };
@@ -2871,29 +2872,33 @@ __global__ __launch_bounds__(BATCH_THREADS) void k_batch_begin(const BatchGeo* _
     }
 }
 
-// lds_bytes: this launch's LDS; a request that needs more (a descriptor from another batch layout) is skipped.
 template <int NM>
-__device__ __forceinline__ void batch_forward_item(const BatchGeo& bg, const ra_batch_request& rq, int reg, float* lds) {
+__device__ __forceinline__ void batch_forward_item(const BatchGeo& bg, const ra_batch_request& rq, int reg, bool same, float* lds) {
     const int dl = fm_dlen(bg.g.jt);
     float* dt = lds + fm_off_dt(NM, bg.g.nbin);
-    for (int i = threadIdx.x; i < NM * dl; i += FM_WAVES * WAVE)
-        dt[i] = mom_coef(bg.series, i / dl, i % dl - FM_PAD - bg.g.jt, bg.g.jt);
+    if (!same)                                               // the last item's table, if it was of the same request, is in place
+        for (int i = threadIdx.x; i < NM * dl; i += FM_WAVES * WAVE)
+            dt[i] = mom_coef(bg.series, i / dl, i % dl - FM_PAD - bg.g.jt, bg.g.jt);
     fm_region<NM, FM_WAVES, 0, float>(bg.g, reg, 0, 1, rq.p0, rq.xe, rq.s, lds);
     __syncthreads();                                         // the LDS is free for the next item
 }
 
+// lds_bytes: this launch's LDS; a request that needs more (a descriptor from another batch layout) is skipped.
 __global__ __launch_bounds__(FM_WAVES * WAVE) __attribute__((amdgpu_waves_per_eu(4))) void k_forward_mom_batch(
     const BatchGeo* __restrict__ geos, const ra_batch_request* __restrict__ reqs, const int2* __restrict__ items,
     const int* __restrict__ counts, int lds_bytes) {
     extern __shared__ float lds[];
     const int n = counts[0];
+    int last = -1;
     for (int it = blockIdx.x; it < n; it += gridDim.x) {
         const int2 w = items[it];
         const BatchGeo& bg = geos[w.x];
+        const bool same = w.x == last;
         if ((int)fm_lds(bg.nm, bg.g.nbin, bg.g.jt, false) > lds_bytes) continue;      // uniform per workgroup
-        if (bg.nm == 6) batch_forward_item<6>(bg, reqs[w.x], w.y, lds);
-        else if (bg.nm == 7) batch_forward_item<7>(bg, reqs[w.x], w.y, lds);
-        else batch_forward_item<8>(bg, reqs[w.x], w.y, lds);
+        if (bg.nm == 6) batch_forward_item<6>(bg, reqs[w.x], w.y, same, lds);
+        else if (bg.nm == 7) batch_forward_item<7>(bg, reqs[w.x], w.y, same, lds);
+        else batch_forward_item<8>(bg, reqs[w.x], w.y, same, lds);
+        last = w.x;
     }
 }
 
@@ -2970,6 +2975,15 @@ template <int CPW, bool WANT_P0, bool WANT_POSE>
 __device__ __forceinline__ void batch_adjoint_run(const BatchGeo& bg, const ra_batch_request& rq, int reg, int cnt, int nbuf,
                                                   float* lds) {
     const size_t row = (size_t)bg.g.E * 3;
+    if (bg.g.rz > FM_RZ) {                                   // a region's halves add into one row of partials
+        for (int i = 0; i < cnt; ++i, ++reg) {
+            const int c = 2 * (reg % bg.g.nrz), half = reg / bg.g.nrz * bg.ga.nrz + c;
+            am_regions<MOM_G, CPW, WANT_P0, WANT_POSE, 0>(bg.ga, half, half + min(2, bg.ga.nrz - c), nbuf, rq.p0, rq.xe,
+                                                          reinterpret_cast<const float4*>(rq.q), nullptr, rq.grad_p0, 0,
+                                                          WANT_POSE ? rq.pose_part + reg * row : nullptr, 0, lds);
+        }
+        return;
+    }
     am_regions<MOM_G, CPW, WANT_P0, WANT_POSE, 0>(bg.g, reg, reg + cnt, nbuf, rq.p0, rq.xe,
                                                    reinterpret_cast<const float4*>(rq.q), nullptr, rq.grad_p0, 0,
                                                    WANT_POSE ? rq.pose_part + reg * row : nullptr, row, lds);
@@ -3002,13 +3016,15 @@ __global__ __launch_bounds__(AM_WAVES * WAVE) __attribute__((amdgpu_waves_per_eu
         const BatchGeo& bg = geos[x];
         i += cnt;
         if (bg.g.nbin > nbin) continue;                      // the LDS windows hold nbin bins
-        const bool wide = bg.g.rx * bg.g.ry > 2 * AM_WAVES;
+        const int cols = bg.g.rx * bg.g.ry;
         if (pose) {
-            if (wide) batch_adjoint_run<4, false, true>(bg, reqs[x], reg, cnt, nbuf, lds);
-            else batch_adjoint_run<2, false, true>(bg, reqs[x], reg, cnt, nbuf, lds);
+            if (cols > 2 * AM_WAVES) batch_adjoint_run<4, false, true>(bg, reqs[x], reg, cnt, nbuf, lds);
+            else if (cols > AM_WAVES) batch_adjoint_run<2, false, true>(bg, reqs[x], reg, cnt, nbuf, lds);
+            else batch_adjoint_run<1, false, true>(bg, reqs[x], reg, cnt, nbuf, lds);
         } else {
-            if (wide) batch_adjoint_run<4, true, false>(bg, reqs[x], reg, cnt, nbuf, lds);
-            else batch_adjoint_run<2, true, false>(bg, reqs[x], reg, cnt, nbuf, lds);
+            if (cols > 2 * AM_WAVES) batch_adjoint_run<4, true, false>(bg, reqs[x], reg, cnt, nbuf, lds);
+            else if (cols > AM_WAVES) batch_adjoint_run<2, true, false>(bg, reqs[x], reg, cnt, nbuf, lds);
+            else batch_adjoint_run<1, true, false>(bg, reqs[x], reg, cnt, nbuf, lds);
         }
     }
 }
@@ -4472,24 +4488,36 @@ int ra_batch_describe(ra_ctx* ctx, const ra_grid* box, int64_t stride_x, int64_t
     g.jt = P.jt;
     g.nbin = 2 * g.jclamp + 1;
     set_units(g, box, delta);
+    bg.ga = g;
+    if (g.rz > FM_RZ) {
+        bg.ga.rz = FM_RZ;
+        bg.ga.nrz = (g.nz + FM_RZ - 1) / FM_RZ;
+        bg.ga.nreg = g.nrx * g.nry * bg.ga.nrz;
+    }
     const MomTerms mt = P.exact ? series_of(ctx, samp, true).terms : MomTerms{};
     bg.nm = mt.fwd;
-    const bool moment = mt.fwd && mt.pose && g.rz <= FM_RZ && g.nbin <= BATCH_BINS_MAX &&
-                        fm_lds(bg.nm, g.nbin, g.jt, false) <= 160 * 1024 && am_lds(g.nbin, 2, 0, 1) <= 160 * 1024;
+    const size_t lds = fm_lds(bg.nm, g.nbin, g.jt, false);
+    const bool moment = mt.fwd && mt.pose && g.nbin <= BATCH_BINS_MAX && lds <= 160 * 1024 && am_lds(g.nbin, 2, 0, 1) <= 160 * 1024;
     if (moment) {
         bg.series = ctx->now->fwd;
         bg.series8 = ctx->now->pose;
     }
+    // Regions of few voxels (coarse spacings) keep the row form in the forward: per region and chunk, CU cycles of the adds and
+    // the expansion (see plan_forward_mom) against those of the rows and their atomics (see row_forward_cost).  2x2x4 voxels
+    // of 0.4 mm: 26.3 ms a step of six requests of 96^3 voxels and 128 elements in moments, 17.3 in rows.
+    const double mom = g.rx * g.ry * ((g.rz + FM_RZ - 1) / FM_RZ * FM_RZ) * 34.0 +
+                       ((g.nbin + 2 * g.jt + 15) / 16) * ((2 * g.jt + 19) / 4) * bg.nm * 32.0 * 1.45 + (lds <= LDS_FM_BUDGET ? 800.0 : 2500.0);
+    const double rows = g.nvpad * (2 * g.jt + 1 + pd) * 0.7 * (pd ? 32.0 : 57.0) / 8.0 + g.L * 152.0;
     std::memcpy(geo, &bg, sizeof(BatchGeo));
     info->nreg = g.nreg;
     info->jt = P.jt;
     info->exact = P.exact ? 1 : 0;
     info->pair_d = pd;
     // rows of LDS of 1 KiB: the row form's samples, or what the moment-form forward needs
-    info->lmax = moment ? std::max(g.L, (int)((fm_lds(bg.nm, g.nbin, g.jt, false) + 1023) / 1024)) : g.L;
+    info->moment = moment ? (mom <= 1.1 * rows ? 1 : 2) : 0;
+    info->lmax = info->moment == 1 ? std::max(g.L, (int)((lds + 1023) / 1024)) : g.L;
     info->nvpad = g.nvpad;
     info->rx = g.rx; info->ry = g.ry; info->rz = g.rz;
-    info->moment = moment ? 1 : 0;
     info->nbin = g.nbin;
     // the table with its zero row, then one loss per element
     info->q_bytes = moment ? (((int64_t)M * (samp->K + 2 * P.jt) + 1) * MOM_G + M) * (int64_t)sizeof(float) : 0;
@@ -4526,6 +4554,18 @@ int batch_finish(ra_ctx* ctx, const ra_batch* b, uint32_t flags, hipStream_t st)
     return RA_OK;
 }
 
+// Residuals with losses and tables, both kinds of adjoint in one launch, and what follows them.
+int batch_adjoints_mom(ra_ctx* ctx, const ra_batch* b, uint32_t flags, hipStream_t st) {
+    const BatchGeo* geos = (const BatchGeo*)b->geos;
+    const int grid = b->grid_blocks > 0 ? b->grid_blocks : 1024;
+    const int nbuf = am_lds(b->nbin, 2, 0, 2) <= 160 * 1024 ? 2 : 1;
+    RA_HIP(ctx, allow_full_lds(k_adjoint_series_batch));
+    hipLaunchKernelGGL(k_batch_series, dim3(grid), dim3(MT_ROWS), 0, st, geos, b->reqs, (const int2*)b->items_elem, b->counts);
+    hipLaunchKernelGGL(k_adjoint_series_batch, dim3(std::min(grid, NCU)), dim3(AM_WAVES * WAVE), am_lds(b->nbin, 2, 0, nbuf), st,
+                       geos, b->reqs, (const int2*)b->items_pose, (const int2*)b->items_vol, b->counts, b->nbin, nbuf);
+    return batch_finish(ctx, b, flags, st);
+}
+
 template <int JT, bool EXACT, int D>
 int batch_step_t(ra_ctx* ctx, const ra_batch* b, uint32_t flags, hipStream_t st) {
     const BatchGeo* geos = (const BatchGeo*)b->geos;
@@ -4547,6 +4587,7 @@ int batch_step_t(ra_ctx* ctx, const ra_batch* b, uint32_t flags, hipStream_t st)
     hipLaunchKernelGGL(k_batch_elements, dim3(64), dim3(256), 0, st, b->reqs, ielem, b->counts);
     hipLaunchKernelGGL(k_batch_zero, dim3(grid), dim3(256), 0, st, geos, b->reqs, b->counts);
     hipLaunchKernelGGL(kf, dim3(grid), dim3(BLOCK), lds_f, st, geos, b->reqs, vtab, itab, ifwd, b->counts, b->lmax);
+    if (b->moment) return batch_adjoints_mom(ctx, b, flags, st);
     hipLaunchKernelGGL(k_batch_residual, dim3(grid), dim3(BATCH_THREADS), 0, st, geos, b->reqs, b->counts);
     hipLaunchKernelGGL(kp, dim3(grid), dim3(BLOCK), lds_a, st, geos, b->reqs, vtab, itab, ipose, b->counts, 1,
                        b->lmax);
@@ -4555,23 +4596,16 @@ int batch_step_t(ra_ctx* ctx, const ra_batch* b, uint32_t flags, hipStream_t st)
     return batch_finish(ctx, b, flags, st);
 }
 
-// The moment form: positions and cleared signals, the forward, residuals with losses and tables, both kinds of
-// adjoint in one launch.
+// The moment form: positions and cleared signals, the forward, then the adjoints.
 int batch_step_mom(ra_ctx* ctx, const ra_batch* b, uint32_t flags, hipStream_t st) {
     const BatchGeo* geos = (const BatchGeo*)b->geos;
-    const int2* ielem = (const int2*)b->items_elem;
     const int grid = b->grid_blocks > 0 ? b->grid_blocks : 1024;
     const size_t lds_f = (size_t)b->lmax * 1024;
-    const int nbuf = am_lds(b->nbin, 2, 0, 2) <= 160 * 1024 ? 2 : 1;
     RA_HIP(ctx, allow_full_lds(k_forward_mom_batch));
-    RA_HIP(ctx, allow_full_lds(k_adjoint_series_batch));
-    hipLaunchKernelGGL(k_batch_begin, dim3(grid), dim3(BATCH_THREADS), 0, st, geos, b->reqs, ielem, b->counts);
+    hipLaunchKernelGGL(k_batch_begin, dim3(grid), dim3(BATCH_THREADS), 0, st, geos, b->reqs, (const int2*)b->items_elem, b->counts);
     hipLaunchKernelGGL(k_forward_mom_batch, dim3(grid), dim3(FM_WAVES * WAVE), lds_f, st, geos, b->reqs,
                        (const int2*)b->items_fwd, b->counts, (int)lds_f);
-    hipLaunchKernelGGL(k_batch_series, dim3(grid), dim3(MT_ROWS), 0, st, geos, b->reqs, ielem, b->counts);
-    hipLaunchKernelGGL(k_adjoint_series_batch, dim3(std::min(grid, NCU)), dim3(AM_WAVES * WAVE), am_lds(b->nbin, 2, 0, nbuf), st,
-                       geos, b->reqs, (const int2*)b->items_pose, (const int2*)b->items_vol, b->counts, b->nbin, nbuf);
-    return batch_finish(ctx, b, flags, st);
+    return batch_adjoints_mom(ctx, b, flags, st);
 }
 
 }  // namespace
@@ -4599,7 +4633,7 @@ extern "C" int ra_batch_step(ra_ctx* ctx, const ra_batch* b, uint32_t flags, voi
     hipStream_t st = (hipStream_t)stream;
     if (b->pair_d != 0 && (b->pair_d != PAIR_D || !ex))
         return fail(ctx, RA_EINVAL, "pair_d must be the value ra_batch_describe reported");
-    if (b->moment) return batch_step_mom(ctx, b, flags, st);
+    if (b->moment && b->moment != 2) return batch_step_mom(ctx, b, flags, st);
 #define RA_CASE(n)                                                                                      \
     if (ex && b->jt == n)                                                                               \
         return b->pair_d ? batch_step_t<n, true, PAIR_D>(ctx, b, flags, st)                             \
