@@ -13,6 +13,7 @@ HERE = os.path.dirname(os.path.abspath(__file__))
 ROOT = os.path.dirname(HERE)
 SRC = os.path.join(HERE, "csrc", "radiate.hip")
 HDR = os.path.join(ROOT, "include", "radiate.h")
+SERIES = os.path.join(HERE, "csrc", "moment_series.h")
 LIB = os.path.join(HERE, "libradiate.so")
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 
@@ -47,7 +48,7 @@ def is_stale() -> bool:
     if not os.path.exists(LIB):
         return True
     t = os.path.getmtime(LIB)
-    return any(os.path.getmtime(p) > t for p in (SRC, HDR))
+    return any(os.path.getmtime(p) > t for p in (SRC, HDR, SERIES))
 
 
 if __name__ == "__main__":

@@ -24,21 +24,20 @@
 //     and Gamma_j = exp(-j^2 delta^2/2s^2) a per-call table.  So each sample
 //     costs one multiply of a running power of H plus one or two FMAs, with
 //     no transcendental; two or three exponentials are evaluated per pair.
-//   * Forward with the Gaussian: every pair adds NM polynomial moments of its offset
-//     from its centre sample into fixed-point sums in LDS, which a region's workgroup expands into
-//     signal rows and adds to the signals with global atomics (k_forward_mom).
-//   * Forward otherwise (other profiles, coarse sampling): every lane owns a private
+//   * Forward in moment form (Gaussian, exponential, power law): every pair adds NM polynomial
+//     moments of its offset from its centre sample into fixed-point sums in LDS, which a region's
+//     workgroup expands into signal rows and adds to the signals with global atomics (k_forward_mom).
+//   * Forward otherwise (uniform sphere, short windows, coarse sampling or spacing): every lane owns a private
 //     row of signal samples in LDS (layout [sample][lane], bank = lane, no conflicts) and updates it by
 //     read-modify-write; two z-neighbouring voxels share one pass over the rows (the Gaussian's rows
 //     about each voxel's centre sample are taken whole).  At the end of each region the rows are added
 //     into the signals with global atomics (transposed, so each atomic instruction covers consecutive
 //     samples of one element).
 //   * Sums of the regions' rows: FP32 up to 4096 row-form regions, FP64 sums beyond.
-//   * Adjoints with the Gaussian: a table of dL/ds's local expansions per sample, built once per
+//   * Adjoints in moment form: a table of dL/ds's local expansions per sample, built once per
 //     call, two LDS reads and a Horner sum per pair, with its derivative for the element gradients
 //     (am_regions).
-//   * Adjoints otherwise (other profiles, or where the expansion's bound
-//     fails): each lane stages its element's dL/ds window in the same
+//   * Adjoints otherwise: each lane stages its element's dL/ds window in the same
 //     private-row layout and gathers.  dL/dp0 of a voxel is summed across the
 //     64 lanes with DPP and across the four wavefronts in LDS.  It is written
 //     once, with no atomics.  The element gradient is accumulated per lane in
@@ -48,7 +47,7 @@
 //   * The other source profiles of Appendix A (exponential, power law, uniform
 //     sphere) swap the pair functions; the exponential factorises per leg.
 //   * Around the model: the Stage 2/4 negative-correlation loss (FP64 row
-//     statistics), the TGV regulariser (one LDS-tiled pass), the axis-angle and
+//     statistics), the TGV regulariser (one marching pass), the axis-angle and
 //     Euler-angle pose maps, and the batched serving step.
 #include <hip/hip_runtime.h>
 
@@ -61,6 +60,7 @@
 #include <set>
 #include <string>
 
+#include "moment_series.h"
 #include "radiate.h"
 
 // Scratch of radiate_forward_static, for callers that cannot allocate: one copy per device
@@ -75,7 +75,6 @@ namespace {
 constexpr int WAVE = 64;
 constexpr int WAVES = 4;              // wavefronts per region workgroup
 constexpr int BLOCK = WAVE * WAVES;
-constexpr int JMAX = 40;              // largest supported window half-width in samples
 constexpr int GEN_STEP = 8;           // spacing of the generic window bounds (8, 16, ..., 40)
 #ifdef RA_FAST_BUILD
 constexpr int EXP_STEP = 8;           // spacing of the exponential profile's window bounds
@@ -100,12 +99,6 @@ constexpr int FM_FIELDS = 13;         // floats of a reference
 constexpr int FM_RZ = 8;              // voxels of a column it unrolls
 constexpr int FM_SIDE = 16;           // its largest region side
 constexpr float FM_FAINT = 0x1p-14f;  // largest |p0| of a line over the bound of its region's bins below which it is faint
-constexpr int MOM_MAX = 12;           // largest number of moments
-constexpr int MOM_G = 8;              // and the Gaussian's
-constexpr double FM_TOL = 2e-7;       // its largest admitted expansion error, relative to the peak
-constexpr double FM_EDGE = 0.004;     // its largest phi at the window's edge (other profiles), relative to the peak
-constexpr double AM_TOL = 2.5e-8;     // that error where the series' derivative is used (its 8 terms' grows 8-fold in rms)
-constexpr double WIDE_GAUSS = 0.559;  // delta/sigma up to which Gaussian adjoints take the rows whole for any window, and a table of any size
 constexpr size_t AM_TABLE_MAX = (size_t)16 << 30;   // bytes of the moment table (wide Gaussians: any)
 constexpr int AM_WAVES = 16;          // wavefronts of the moment-form adjoints' region workgroup, one per CU
 constexpr int AM_REFS = 3;            // references held: this chunk's, the next one's and the one after
@@ -808,7 +801,8 @@ __global__ __launch_bounds__(BLOCK) void k_forward(Geo g, const float* __restric
 // region's box.  The best of the three axes, or sum |p0| / d_low, becomes 2^31 units: for 16^3 equal
 // voxels a term is rounded to 1.2e-7 of itself, as one FP32 addition would.  Regions whose p0 is not
 // finite, and elements inside or within half a voxel of the region's box, or not finite, take FP32 sums
-// by ds_add_f32 instead (slow, and the values then propagate as they would in FP32).
+// by ds_add_f32 instead (slow, and the values then propagate as they would in FP32).  A region whose
+// voxels differ by many orders of magnitude is summed in classes of size (fm_bound).
 //
 // The expansion into rows is a banded Toeplitz product, [rows x 64] = D [rows x (bins NM)] M: FP32
 // matrix instructions (16 rows x 16 elements x 4 bins each), whose result has consecutive samples
@@ -817,7 +811,8 @@ __global__ __launch_bounds__(BLOCK) void k_forward(Geo g, const float* __restric
 // Distances.  A region is up to 1.3 mm in radius, 67 units, where FP32 rounds u = d - c t to 4e-6 units;
 // so each column of 8 voxels first takes its own distance and nearest sample, with D.o split into a
 // part that adds exactly and the rest, and its voxels count from there: rms error of t 0.9e-6 over
-// 16^3 voxels, against 1.4e-6 in the row form over 8x8x16.
+// 16^3 voxels, against 1.4e-6 in the row form over 8x8x16.  With edge terms the column's distance is
+// FP64 and the same in every region (fm_col_f64).
 //
 // Bounds: 24 VALU instructions (one at a quarter of the rate) and NM ds_add_u32 (33 LDS cycles at NM = 7)
 // per pair and wavefront plus about 40 per column, against 104 VALU and 58 LDS cycles per pair in the
@@ -825,10 +820,6 @@ __global__ __launch_bounds__(BLOCK) void k_forward(Geo g, const float* __restric
 // about 8 ms of 9.9, the row form 26.9.  The FP32 matrix instructions share the VALU's time, so the
 // expansion adds to that: 5.7 ms with 8x8x8 regions, two workgroups to a CU; hence the largest regions
 // that the LDS holds, one workgroup of 16 wavefronts to a CU.
-struct MomCoef {
-    float d[(JMAX + 1) * MOM_MAX];     // D_n(j) / delta at j * MOM_MAX + n, j >= 0; D_n(-j) = (-1)^(n+1) D_n(j)
-};
-
 __device__ __forceinline__ float mom_coef(const MomCoef& m, int n, int j, int jt) {
     const int a = j < 0 ? -j : j;
     if (a > jt) return 0.0f;
@@ -1066,8 +1057,6 @@ __device__ __forceinline__ FmPair fm_pair(const FmCol& c, float dc2, float hdc, 
     return p;
 }
 
-// The adds of one column of FM_RZ voxels (p0 values pv, zero past the grid); ez: N of each voxel about
-// the column's centre.  INT: fixed-point sums.
 // What a pair adds beyond its polynomial, at one of the window's outermost samples kc +- jt, each of which is in
 // the window for |u| <= T w only.  If the window reaches less than half a sample past kc + jt - 1/2 .. (thr > 0, the
 // polynomial holds |j| < jt), that is the sample on t's side, for |t| >= thr; otherwise the polynomial holds |j| <= jt and
@@ -1101,9 +1090,12 @@ __device__ __forceinline__ Edge edge_phi(const EdgeCoef& c, float t) {
     return e;
 }
 
+// The adds of one column of FM_RZ voxels (p0 values pv, zero past the grid); ez: N of each voxel about
+// the column's centre.  INT: fixed-point sums.
 template <int NM, bool INT, int X>
-__device__ __forceinline__ void fm_column(const Geo& g, const EdgeCoef& xc, unsigned eoff, const float (&pv)[FM_RZ], const float (&ez)[FM_RZ], const FmCol& c, float scale,
-                                          float lo, float hi, unsigned off0, unsigned str, char* sums) {
+__device__ __forceinline__ void fm_column(const Geo& g, const EdgeCoef& xc, unsigned eoff, const float (&pv)[FM_RZ],
+                                          const float (&ez)[FM_RZ], const FmCol& c, float scale, float lo, float hi,
+                                          unsigned off0, unsigned str, char* sums) {
     const float dc2 = c.dc * c.dc, hdc = 0.5f * c.dc;
 #pragma unroll
     for (int k = 0; k < FM_RZ; ++k) {
@@ -3152,20 +3144,6 @@ __global__ __launch_bounds__(BLOCK) void k_batch_volume_apply(const BatchGeo* __
 // ==============================================================================================
 // host side
 // ==============================================================================================
-// Terms of the moment forms' series (0: the form cannot be taken).
-struct MomTerms {
-    int fwd, vol, pose;
-    float thr, ev[4], es, kx;      // Geo's of the same names
-    unsigned flip;
-    int xkind;
-};
-
-struct MomSeries {
-    double key[4] = {0.0, 0.0, 0.0, 0.0};  // profile, delta / width, window, nu
-    MomTerms terms{};
-    MomCoef fwd, vol, pose;                // with the terms of the forward, of dL/dp0 alone and of the element gradients
-};
-
 struct ra_ctx {
     int device = 0;
     int* d_status = nullptr;
@@ -3321,134 +3299,17 @@ size_t set_regions(Geo& g, const ra_grid* grid, double delta, int jt, bool with_
     return lds;
 }
 
-// phi(x delta) / delta of a source profile, x in samples, dd = delta / w.
-double profile(const ra_sampling* samp, double dd, double x) {
-    const double y = std::fabs(x) * dd;
-    switch (samp->kernel) {
-        case RA_KERNEL_EXPONENTIAL: return x * std::exp(-y);
-        case RA_KERNEL_POWER: return x * std::pow(1.0 + y * y, -samp->nu);
-        case RA_KERNEL_UNIFORM: return x;
-        default: return x * std::exp(-0.5 * y * y);
-    }
-}
-
-// Chebyshev coefficients in t of phi((t/2 - j) delta) / delta for j = j0..j1, from MOM_NODES nodes; tail[n] bounds
-// what is cut after n terms, relative to `peak`.
-constexpr int MOM_NODES = 24;
-
-void mom_series(const ra_sampling* samp, double dd, int j0, int j1, double peak, double cheb[MOM_MAX][JMAX + 1],
-                double tail[MOM_MAX + 1]) {
-    struct Nodes {
-        double c[MOM_NODES][MOM_NODES];
-        Nodes() {
-            for (int k = 0; k < MOM_NODES; ++k)
-                for (int i = 0; i < MOM_NODES; ++i) c[k][i] = std::cos(3.14159265358979323846 * k * (i + 0.5) / MOM_NODES);
-        }
-    };
-    static const Nodes nodes;
-    const double(&cs)[MOM_NODES][MOM_NODES] = nodes.c;
-    for (int n = 0; n <= MOM_MAX; ++n) tail[n] = 0.0;
-    for (int j = j0; j <= j1; ++j) {
-        double f[MOM_NODES];
-        for (int i = 0; i < MOM_NODES; ++i) f[i] = profile(samp, dd, 0.5 * cs[1][i] - j);
-        double rest = 0.0;
-        for (int k = MOM_NODES - 1; k >= 0; --k) {
-            double c = 0.0;
-            for (int i = 0; i < MOM_NODES; ++i) c += f[i] * cs[k][i];
-            c *= (k ? 2.0 : 1.0) / MOM_NODES;
-            if (k < MOM_MAX) cheb[k][j] = c;
-            rest += std::fabs(c);
-            if (k <= MOM_MAX) tail[k] = std::max(tail[k], rest / peak);
-        }
-    }
-}
-
-// The sum of the first nm Chebyshev terms of sample j as a polynomial in t.
-void mom_monomials(const double cheb[MOM_MAX][JMAX + 1], int nm, int j, float* out) {
-    double T[MOM_MAX][MOM_MAX] = {};                       // T[k][n]: coefficient of t^n in T_k
-    T[0][0] = 1.0;
-    T[1][1] = 1.0;
-    for (int k = 2; k < nm; ++k)
-        for (int n = 0; n < nm; ++n) T[k][n] = (n ? 2.0 * T[k - 1][n - 1] : 0.0) - T[k - 2][n];
-    for (int n = 0; n < nm; ++n) {
-        double v = 0.0;
-        for (int k = n; k < nm; ++k) v += cheb[k][j] * T[k][n];
-        out[n] = (float)v;
-    }
-}
-
-// The moment forms' series for this sampling, kept in the context (its last eight).  Their numbers of
-// terms are the fewest of those compiled whose cut series is within FM_TOL (AM_TOL where the derivative is used too):
-//   Gaussian     6 up to delta/sigma 0.41, 7 up to 0.64, 8 up to 1.05 (the row form's own rounding is about 4e-7); 8 with
-//                derivatives, up to 0.75.  The window's rows are taken whole, as the Gaussian's row forms do for
-//                the half-widths of RA_EXACT_LIST; for longer windows those test each term, so the form is taken
-//                there only from 6 sigma on, where the terms in question are below 1.5e-7 of the peak.
-//   the others   6 or 8 for the exponential (without the centre sample, which is added by itself), 8 to 12 for the
-//                power law.  A sample that is in the window for some offsets only is added by itself too, by its
-//                first four terms.  Only where phi has fallen to FM_EDGE of its peak at the window's edge: the
-//                forward and the adjoint take different regions, so that their rounding of a pair's offset can
-//                put an edge sample in on one side and out on the other, which the row forms, on shared
-//                regions, avoid (single results then moved by 1.4e-3 at an edge value of 0.0135).  The uniform
-//                sphere keeps those always; a power law with nu = 2 passes from 9.1 widths on, the exponential from 8.7.
+// This sampling's series, kept in the context with those of the last seven others.
 const MomSeries& series_of(ra_ctx* ctx, const ra_sampling* samp, bool exact) {
-    const double delta = samp->c / samp->fs, dd = delta / samp->sigma, jw = samp->trunc * samp->sigma / delta;
-    const double key[4] = {(double)samp->kernel + (exact ? 0.5 : 0.0), dd, samp->trunc, samp->nu};
+    const double key[4] = {(double)samp->kernel + (exact ? 0.5 : 0.0), samp->c / samp->fs / samp->sigma, samp->trunc, samp->nu};
     for (const MomSeries& m : ctx->series)
         if (std::memcmp(key, m.key, sizeof(key)) == 0) return *(ctx->now = &m);
     constexpr int kept = sizeof(ctx->series) / sizeof(ctx->series[0]);
     MomSeries& m = ctx->series[ctx->series_oldest];
     ctx->series_oldest = (ctx->series_oldest + 1) % kept;
     ctx->now = &m;
+    make_series(samp, exact, m);
     std::memcpy(m.key, key, sizeof(key));
-    MomTerms& t = m.terms;
-    t = MomTerms{};
-    const int jo = (int)std::floor(jw + 0.5), kt = samp->kernel;
-    if (jo < 1 || jo > JMAX || kt == RA_KERNEL_UNIFORM || (kt == RA_KERNEL_GAUSSIAN && !(exact || samp->trunc >= 6.0))) return m;
-    // phi's peak: at the width (power law: width / sqrt(2 nu - 1)), or the window's edge before it
-    const double top = std::min(jw, (kt == RA_KERNEL_POWER ? 1.0 / std::sqrt(2.0 * samp->nu - 1.0) : 1.0) / dd);
-    const double peak = profile(samp, dd, top);
-    double cheb[MOM_MAX][JMAX + 1] = {}, ce[MOM_MAX][JMAX + 1] = {}, te[MOM_MAX + 1];
-    const double edge = 2.0 * (jo - jw);                   // kc + jo is in the window for t >= edge
-    const int j0 = kt == RA_KERNEL_EXPONENTIAL ? 1 : 0, j1 = kt == RA_KERNEL_GAUSSIAN || edge <= 0.0 ? jo : jo - 1;
-    double tail[MOM_MAX + 1];
-    mom_series(samp, dd, j0, j1, peak, cheb, tail);
-    if (kt != RA_KERNEL_GAUSSIAN) {
-        mom_series(samp, dd, jo, jo, peak, ce, te);
-        if (!(te[4] <= FM_TOL) || profile(samp, dd, jw) > FM_EDGE * peak) return m;
-        t.xkind = kt == RA_KERNEL_EXPONENTIAL ? 2 : 1;
-        mom_monomials(ce, 4, jo, t.ev);
-        t.thr = (float)edge;
-        if (edge <= 0.0) {                                 // take back phi at kc - jo for t > -edge: F(|t|) = E(-|t|)
-            t.thr = std::nextafterf((float)-edge, 2.0f);
-            t.flip = 0x80000000u;
-            t.ev[1] = -t.ev[1];
-            t.ev[3] = -t.ev[3];
-        }
-        // |phi| / delta of the single samples: three of them meet in a row at most (centre, kc + jt, kc - jt)
-        double top = 0.0;
-        for (int i = -1; i <= 1; ++i) top = std::max(top, std::fabs(profile(samp, dd, 0.5 * i - jo)));
-        t.es = (float)(1.0 / (0.5 + 2.0 * std::max(top, peak)));
-        t.kx = (float)(-0.5 * dd * 1.4426950408889634);
-    }
-    static const int terms[3][3] = {{6, 7, 8}, {6, 8, 8}, {8, 10, 12}};      // by profile
-    auto fewest = [&](double tol, int from) {
-        for (int i = from; i < 3; ++i)
-            if (tail[terms[kt][i]] <= tol) return terms[kt][i];
-        return 0;
-    };
-    t.fwd = fewest(FM_TOL, 0);
-    if (!t.fwd) return m;
-    t.vol = kt == RA_KERNEL_GAUSSIAN ? t.fwd : kt == RA_KERNEL_POWER && t.fwd > 8 ? 12 : terms[kt][1] == 10 ? 8 : terms[kt][1];
-    t.pose = kt == RA_KERNEL_POWER ? (tail[8] <= AM_TOL ? 8 : fewest(AM_TOL, 2)) : fewest(AM_TOL, 2);
-    // Short windows of narrow Gaussians: the adjoints' row forms test the window's outermost samples, whose terms
-    // are psi(trunc) of the peak (1.5e-7 from 6 sigma on, 1.6e-3 at 4)
-    if (kt == RA_KERNEL_GAUSSIAN && samp->trunc < 6.0 && dd > WIDE_GAUSS) t.vol = t.pose = 0;
-    const int nm[3] = {t.fwd, t.vol, t.pose};
-    MomCoef* const out[3] = {&m.fwd, &m.vol, &m.pose};
-    for (int i = 0; i < 3; ++i) {
-        std::memset(out[i], 0, sizeof(MomCoef));
-        for (int j = j0; nm[i] && j <= j1; ++j) mom_monomials(cheb, nm[i], j, out[i]->d + j * MOM_MAX);
-    }
     return m;
 }
 
