@@ -739,6 +739,9 @@ def main():
                      "frac": achieved / PEAK_FP32_TFLOPS, "traffic": traffic_from_profile(dom_name),
                      "kernel": dom_name, "timed": "radiate_forward call (HIP events on its stream)",
                      "flop_per_update": FLOP_PER_UPDATE, "updates_per_launch": n_upd,
+                     "note": "achieved counts 7 FLOP per in-window update of the direct form; the moment form adds a "
+                             "few polynomial terms per (voxel, element) pair instead of visiting its 25 updates one "
+                             "by one, so achieved and frac compare runs and are no utilisation",
                      "measured_fp32_fma_peak_tflops": 2 * fma_rate / 1e12,
                      "transcendental": {
                          "algorithmic_exp_per_s": EXP_PER_UPDATE * n_upd / (ms_fwd * 1e-3),
