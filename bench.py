@@ -67,8 +67,10 @@ def parse():
 
 
 def source_hash() -> str:
-    p = os.path.join(ROOT, "paper_2604_09643_amd", "csrc", "radiate.hip")
-    return hashlib.sha256(open(p, "rb").read()).hexdigest()[:16]
+    h = hashlib.sha256()
+    for name in ("radiate.hip", "moment_series.h"):
+        h.update(open(os.path.join(ROOT, "paper_2604_09643_amd", "csrc", name), "rb").read())
+    return h.hexdigest()[:16]
 
 
 def traffic_from_profile(kernel: str):

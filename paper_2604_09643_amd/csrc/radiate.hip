@@ -3150,7 +3150,7 @@ struct ra_ctx {
     char* arena = nullptr;                  // the context's scratch (grown by ensure_scratch)
     size_t arena_bytes = 0;
     char* static_scratch = nullptr;         // this device's static array (radiate_forward_static)
-    // the moment forms' series for the last few samplings used, and that of the current call (20 to 30 us of host time to make
+    // the moment forms' series for the last few samplings used, and that of the current call (10 to 22 us of host time to make
     // one, against calls of 20 us on: a program may go through several widths or profiles in turn)
     MomSeries series[8];
     int series_oldest = 0;
